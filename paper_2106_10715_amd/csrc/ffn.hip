@@ -5,7 +5,7 @@
 //     H  = act(Xp W_gate[e]) * (Xp W_in[e])        "up"   grouped GEMM, epilogue fused
 //     Yp = H W_out[e]                               "down" grouped GEMM
 //
-// bf16 path: 32x32x16 bf16 MFMA, fp32 accumulate.  One block = up to 256 rows of one expert x 4 waves;
+// bf16 path: 16x16x32 bf16 MFMA, fp32 accumulate.  One block = up to 256 rows of one expert x 4 waves;
 // every wave owns its own output columns for all rows, so a weight fragment is needed by exactly
 // one wave: weights go HBM -> registers directly in pre-packed fragment order (no LDS, fully
 // coalesced 1 KiB reads), only the activation tile is shared through LDS (padded rows,
@@ -21,9 +21,9 @@ namespace moe {
 namespace {
 
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
-typedef float f32x16 __attribute__((ext_vector_type(16)));
+typedef float f32x4 __attribute__((ext_vector_type(4)));
 
-constexpr int kKC = 64;                 // reduction elements staged per pipeline step (4 MFMA k-steps)
+constexpr int kKC = 64;                 // reduction elements staged per pipeline step (2 MFMA k-steps)
 // Rows of a tile when the up-projection gathers its rows itself: a thread then holds one source offset per
 // 32-row block, which the registers allow up to seven blocks (eight accumulator blocks leave no room).
 constexpr int kGatherTileM = 224;
@@ -167,13 +167,14 @@ __global__ __launch_bounds__(256) void pack_bf16_kernel(const uint16_t* __restri
 // weights of step c+1.  The wait names those registers as read-write operands so that no use of them
 // can be moved above it.
 
-constexpr int kKS = kKC / 16;           // MFMA k-steps per pipeline step
+constexpr int kKS = kKC / 32;           // MFMA k-steps per pipeline step
+constexpr uint32_t kStepBytes = (kKC / 16) * 2048;   // bytes of a wave's weight stream one pipeline step spans
 constexpr int kLdsRow = 9;              // uint4 per activation row in LDS: 128 B of data + 16 B pad (conflict-free)
 
 typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 
 template <int NF>
-struct BFrags { u32x4 v[kKS][NF]; };    // one pipeline step of one wave: 4 k-steps x NF fragments
+struct BFrags { u32x4 v[kKS][2 * NF]; };    // one pipeline step of one wave: 2 k-steps x NF column units x 2 halves of 16 columns
 template <int MBS>
 struct ARegs { u32x4 v[MBS]; };         // this thread's share of one activation tile step
 
@@ -198,20 +199,24 @@ __device__ inline void ld_pinned_stream(u32x4& dst, uint32_t voff, const void* s
         asm volatile("global_load_dwordx4 %0, %1, %2 offset:%3 nt" : "=v"(dst) : "v"(voff), "s"(sbase), "n"(IMM) : "memory");
 }
 
-// The two fragments of one (column unit, k-step) are adjacent in the packed block:
-// [k-step][2][64 lanes] x 16 bytes (2 KiB per k-step); a wave with NF = 1 reads one of the two.
-// voff = byte offset of this lane inside its wave's stream at the first k-step of the pipeline step.
+// A packed fragment holds 16 reduction rows x 32 columns; the two fragments of one (column unit, 16 rows) are adjacent,
+// [16-row step][2][64 slots] x 16 bytes (2 KiB per step); a wave with NF = 1 reads one of the two.  The 16x16x32
+// instruction wants, in lane 16 g + c, column c and the reduction elements 8 g .. 8 g + 7 of 32: those lie in 16-row step
+// g / 2, slot 32 (g % 2) + c (+ 16 for the upper half of the columns).  So a lane's offset inside the 4 KiB of a k-step is
+// the constant below, and one load covers four runs of 256 bytes, whole cache lines, the other half of the columns the rest.
+__device__ inline uint32_t weight_lane_offset(int lane) { return ((lane >> 5) << 11) + (((lane >> 4) & 1) << 9) + ((lane & 15) << 4); }
+// voff = weight_lane_offset + byte offset of the pipeline step in the wave's stream.
 template <bool KEEP, int NF>
 __device__ inline void load_b(BFrags<NF>& b, uint32_t voff, const void* wave_base) {
-    ld_pinned_stream<0, KEEP>(b.v[0][0], voff, wave_base);
-    if (NF == 2) ld_pinned_stream<1024, KEEP>(b.v[0][NF - 1], voff, wave_base);
-    ld_pinned_stream<2048, KEEP>(b.v[1][0], voff, wave_base);
-    if (NF == 2) ld_pinned_stream<3072, KEEP>(b.v[1][NF - 1], voff, wave_base);
     const uint32_t voff2 = voff + 4096;
-    ld_pinned_stream<0, KEEP>(b.v[2][0], voff2, wave_base);
-    if (NF == 2) ld_pinned_stream<1024, KEEP>(b.v[2][NF - 1], voff2, wave_base);
-    ld_pinned_stream<2048, KEEP>(b.v[3][0], voff2, wave_base);
-    if (NF == 2) ld_pinned_stream<3072, KEEP>(b.v[3][NF - 1], voff2, wave_base);
+    ld_pinned_stream<0, KEEP>(b.v[0][0], voff, wave_base);
+    ld_pinned_stream<256, KEEP>(b.v[0][1], voff, wave_base);
+    if (NF == 2) ld_pinned_stream<1024, KEEP>(b.v[0][2 * NF - 2], voff, wave_base);
+    if (NF == 2) ld_pinned_stream<1280, KEEP>(b.v[0][2 * NF - 1], voff, wave_base);
+    ld_pinned_stream<0, KEEP>(b.v[1][0], voff2, wave_base);
+    ld_pinned_stream<256, KEEP>(b.v[1][1], voff2, wave_base);
+    if (NF == 2) ld_pinned_stream<1024, KEEP>(b.v[1][2 * NF - 2], voff2, wave_base);
+    if (NF == 2) ld_pinned_stream<1280, KEEP>(b.v[1][2 * NF - 1], voff2, wave_base);
 }
 
 // Wait until at most N_YOUNGER loads are outstanding; the registers named become usable afterwards.
@@ -223,7 +228,7 @@ __device__ inline void wait_loads(ARegs<MBS>& a, BFrags<NF>& b) {
 #pragma unroll
     for (int ks = 0; ks < kKS; ++ks)
 #pragma unroll
-        for (int j = 0; j < NF; ++j) asm volatile("" : "+v"(b.v[ks][j]));
+        for (int j = 0; j < 2 * NF; ++j) asm volatile("" : "+v"(b.v[ks][j]));
 }
 // The activation tile lives in LDS row-major, one padded row of kLdsRow uint4 per tile row.
 // Staging: thread t moves, for i < MBS, the 16-byte piece (row i*32 + t/8, piece t%8): eight
@@ -235,38 +240,41 @@ __device__ inline void store_a(const ARegs<MBS>& a, uint4* lds_buf, unsigned tid
     for (int mb = 0; mb < MBS; ++mb) p[mb * 32 * kLdsRow] = a.v[mb];
 }
 
-// The MFMAs of a pipeline step are issued in units: unit u = (k-step u / H, row-block group u % H),
-// H = 1 or 2 groups of at most 4 row blocks.  The A fragments of unit u+1 are read from LDS while the
-// MFMAs of unit u run; two register buffers of G fragments alternate.
-// Fragment (mb, ks) of lane l = row mb*32 + l%32, 8 elements at k = 16 ks + 8 (l / 32).
+// The MFMAs of a pipeline step are issued in units: unit u = (k-step u / H, row group u % H), H = 2 or 4 groups of
+// at most 4 blocks of 16 rows.  The A fragments of unit u+1 are read from LDS while the MFMAs of unit u run; two
+// register buffers of G fragments alternate.
+// Fragment (rb, ks) of lane l = row rb*16 + l%16, 8 elements at k = 32 ks + 8 (l / 16).
+// Why 16x16x32 and not 32x32x16, in whose operand order the weights are packed: experts with many rows are bound by the
+// power the matrix pipes draw, and the narrow instruction spends less per multiplication (a loop of nothing but MFMAs on
+// normally distributed operands: 1.97-2.03 PFLOP/s against 1.77-1.82).  Measured, whole layer, 32x32x16 -> 16x16x32:
+// 65536 tokens 13.96 -> 13.36 ms, 16384 tokens x 2 skewed over 64 experts 7.70 -> 7.47 ms, 2048 tokens on 8 experts
+// 575 -> 560 us, 4096 tokens on 32 experts 1367 -> 1346 us, 512 tokens unchanged.
 template <int MBS>
 struct Units {
-    static constexpr int H = MBS > 4 ? 2 : 1;
-    static constexpr int G = (MBS + H - 1) / H;
+    static constexpr int RB = 2 * MBS;
+    static constexpr int H = MBS > 4 ? 4 : 2;
+    static constexpr int G = (RB + H - 1) / H;
     static constexpr int U = kKS * H;
+    static constexpr int first(int u) { return (u % H) * RB / H; }               // first 16-row block of unit u
+    static constexpr int count(int u) { return (u % H + 1) * RB / H - first(u); }   // and how many it has
 };
 
 template <int MBS, int UNIT>
 __device__ inline void read_unit(uint4 (&af)[Units<MBS>::G], const uint4* lds_buf, int lane) {
-    constexpr int ks = UNIT / Units<MBS>::H, mb0 = (UNIT % Units<MBS>::H) * Units<MBS>::G;
-    const uint4* rp = lds_buf + (lane & 31) * kLdsRow + (lane >> 5) + 2 * ks;
+    constexpr int ks = UNIT / Units<MBS>::H, rb0 = Units<MBS>::first(UNIT);
+    const uint4* rp = lds_buf + (lane & 15) * kLdsRow + (lane >> 4) + 4 * ks;
 #pragma unroll
-    for (int i = 0; i < Units<MBS>::G; ++i)
-        if (mb0 + i < MBS) af[i] = rp[(mb0 + i) * 32 * kLdsRow];
+    for (int i = 0; i < Units<MBS>::count(UNIT); ++i) af[i] = rp[(rb0 + i) * 16 * kLdsRow];
 }
 
 template <int NF, int MBS, int UNIT>
-__device__ inline void mma_unit(f32x16 (&acc)[MBS][NF], const uint4 (&af)[Units<MBS>::G], const BFrags<NF>& b) {
-    constexpr int ks = UNIT / Units<MBS>::H, mb0 = (UNIT % Units<MBS>::H) * Units<MBS>::G;
+__device__ inline void mma_unit(f32x4 (&acc)[2 * MBS][2 * NF], const uint4 (&af)[Units<MBS>::G], const BFrags<NF>& b) {
+    constexpr int ks = UNIT / Units<MBS>::H, rb0 = Units<MBS>::first(UNIT);
 #pragma unroll
-    for (int i = 0; i < Units<MBS>::G; ++i) {
-        if (mb0 + i < MBS) {
+    for (int i = 0; i < Units<MBS>::count(UNIT); ++i)
 #pragma unroll
-            for (int j = 0; j < NF; ++j)
-                acc[mb0 + i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(as_bf16x8(b.v[ks][j]), as_bf16x8(af[i]),
-                                                                          acc[mb0 + i][j], 0, 0, 0);
-        }
-    }
+        for (int j = 0; j < 2 * NF; ++j)
+            acc[rb0 + i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(as_bf16x8(b.v[ks][j]), as_bf16x8(af[i]), acc[rb0 + i][j], 0, 0, 0);
 }
 
 template <int LO, int HI, class F>
@@ -310,22 +318,17 @@ constexpr int younger_at_write(int w, int MBS, int nb, int U) {
     return (MBS + nb - issued_before(w, MBS, nb, U) - 1) + issued_before(unit_of_write(w, MBS, U), MBS, nb, U);
 }
 
-template <int MBS>
-constexpr int unit_rows(int u) {
-    const int left = MBS - (u % Units<MBS>::H) * Units<MBS>::G;
-    return left > Units<MBS>::G ? Units<MBS>::G : (left < 0 ? 0 : left);
-}
 // fragment I of unit UNIT, from the activation tile in lds_buf
 template <int MBS, int UNIT, int I>
 __device__ inline void read_frag(uint4 (&af)[Units<MBS>::G], const uint4* lds_buf, int lane) {
-    constexpr int ks = UNIT / Units<MBS>::H, mb = (UNIT % Units<MBS>::H) * Units<MBS>::G + I;
-    af[I] = lds_buf[(lane & 31) * kLdsRow + (lane >> 5) + 2 * ks + mb * 32 * kLdsRow];
+    constexpr int ks = UNIT / Units<MBS>::H, rb = Units<MBS>::first(UNIT) + I;
+    af[I] = lds_buf[(lane & 15) * kLdsRow + (lane >> 4) + 4 * ks + rb * 16 * kLdsRow];
 }
-// MFMA M of unit UNIT: row block M / NF of the unit, weight fragment M % NF
+// MFMA M of unit UNIT: 16-row block M / (2 NF) of the unit, weight fragment M % (2 NF)
 template <int NF, int MBS, int UNIT, int M>
-__device__ inline void mma_one(f32x16 (&acc)[MBS][NF], const uint4 (&af)[Units<MBS>::G], const BFrags<NF>& b) {
-    constexpr int ks = UNIT / Units<MBS>::H, i = M / NF, j = M % NF, mb = (UNIT % Units<MBS>::H) * Units<MBS>::G + i;
-    acc[mb][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(as_bf16x8(b.v[ks][j]), as_bf16x8(af[i]), acc[mb][j], 0, 0, 0);
+__device__ inline void mma_one(f32x4 (&acc)[2 * MBS][2 * NF], const uint4 (&af)[Units<MBS>::G], const BFrags<NF>& b) {
+    constexpr int ks = UNIT / Units<MBS>::H, i = M / (2 * NF), j = M % (2 * NF), rb = Units<MBS>::first(UNIT) + i;
+    acc[rb][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(as_bf16x8(b.v[ks][j]), as_bf16x8(af[i]), acc[rb][j], 0, 0, 0);
 }
 // Row block mb of the staged activations has landed once at most N_YOUNGER loads are outstanding; it goes
 // into the LDS tile (thread t holds the 16-byte piece t%8 of row mb*32 + t/8).
@@ -351,21 +354,22 @@ __device__ inline void stage_block(u32x4& v, uint4* lds_buf, unsigned tid, int m
 // from nxt under the remaining MFMAs.  nxt may be written from the start of the step: its last readers
 // passed the barrier of the step before.
 template <int NF, int MBS, class IssueA, class IssueB>
-__device__ inline void run_step(f32x16 (&acc)[MBS][NF], uint4 (&af)[2][Units<MBS>::G], const uint4* cur, uint4* nxt,
+__device__ inline void run_step(f32x4 (&acc)[2 * MBS][2 * NF], uint4 (&af)[2][Units<MBS>::G], const uint4* cur, uint4* nxt,
                                 const BFrags<NF>& b, ARegs<MBS>& a_next, BFrags<NF>& b_next, int lane, unsigned tid,
                                 IssueA issue_a, IssueB issue_b) {
-    constexpr int U = Units<MBS>::U, kB = kKS * NF;
+    constexpr int U = Units<MBS>::U, kB = kKS * 2 * NF;
     static_for<0, U>([&](auto uc) {
         constexpr int UU = decltype(uc)::value;
         constexpr bool kLast = UU + 1 == U;
-        constexpr int M = unit_rows<MBS>(UU) * NF;                 // MFMAs of this unit
+        constexpr int M = Units<MBS>::count(UU) * 2 * NF;          // MFMAs of this unit
         constexpr int NU = kLast ? 0 : UU + 1;                     // the unit whose fragments are fetched meanwhile
-        constexpr int nR = unit_rows<MBS>(NU);
+        constexpr int nR = Units<MBS>::count(NU);
         constexpr int w0 = kLast ? MBS : writes_upto(UU - 1, MBS, U), nW = (kLast ? MBS : writes_upto(UU, MBS, U)) - w0;
         constexpr int nA = UU < MBS ? 1 : 0;
         constexpr int b0 = loads_upto(UU - 1, kB, U), nB = loads_upto(UU, kB, U) - b0;
         constexpr int nOther = nR + nW + nA + nB;
-        constexpr int kFirst = kLast && M > 1 ? 1 : 0;             // other instruction s follows MFMA kFirst + s
+        constexpr int kFirst = !kLast ? 0 : M > 4 ? 3 : 1;         // other instruction s follows MFMA kFirst + kEvery s
+        constexpr int kEvery = M - kFirst >= 2 * nOther ? 2 : 1;
         auto other = [&](auto sc) {
             constexpr int s = decltype(sc)::value;
             if constexpr (s < nR) {
@@ -377,7 +381,7 @@ __device__ inline void run_step(f32x16 (&acc)[MBS][NF], uint4 (&af)[2][Units<MBS
 #pragma unroll
                     for (int ks = 0; ks < kKS; ++ks)
 #pragma unroll
-                        for (int j = 0; j < NF; ++j) asm volatile("" : "+v"(b_next.v[ks][j]));
+                        for (int j = 0; j < 2 * NF; ++j) asm volatile("" : "+v"(b_next.v[ks][j]));
                 }
             } else if constexpr (s < nR + nW + nA) {
                 issue_a(std::integral_constant<int, UU + 0 * s>{});     // (made dependent on s: only instantiated when taken)
@@ -390,8 +394,8 @@ __device__ inline void run_step(f32x16 (&acc)[MBS][NF], uint4 (&af)[2][Units<MBS
             mma_one<NF, MBS, UU, m>(acc, af[UU & 1], b);
             if constexpr (kLast && m == kFirst) __syncthreads();
             if constexpr (m >= kFirst) {
-                constexpr int lo = m - kFirst;
-                constexpr int hi = m == M - 1 ? nOther : (lo + 1 < nOther ? lo + 1 : nOther);
+                constexpr int before = (m - kFirst + kEvery - 1) / kEvery, lo = before < nOther ? before : nOther;
+                constexpr int upto = (m - kFirst) / kEvery + 1, hi = m == M - 1 || upto > nOther ? nOther : upto;
                 static_for<lo, hi>(other);
             }
         });
@@ -401,7 +405,7 @@ __device__ inline void run_step(f32x16 (&acc)[MBS][NF], uint4 (&af)[2][Units<MBS
 // A step without any overlap, for the few steps that do not fill a group of the unrolled pipeline:
 // fetch, wait, stage, compute.  Uses LDS buffer 0 and the registers passed in; nothing stays in flight.
 template <int NF, int MBS>
-__device__ inline void slow_step(f32x16 (&acc)[MBS][NF], uint4 (&af)[2][Units<MBS>::G], uint4* buf, ARegs<MBS>& a,
+__device__ inline void slow_step(f32x4 (&acc)[2 * MBS][2 * NF], uint4 (&af)[2][Units<MBS>::G], uint4* buf, ARegs<MBS>& a,
                                  BFrags<NF>& b, int lane, unsigned tid) {
     wait_loads<0>(a, b);
     __syncthreads();                            // nobody reads buf any more
@@ -550,15 +554,15 @@ __device__ inline void ffn_tile(uint4 (&lds)[2][kTileM * kLdsRow], const uint16_
         }
     }
 
-    f32x16 acc[MBS][NF];
+    f32x4 acc[2 * MBS][2 * NF];
     // cleared in place, in the accumulation registers: a zero constant would be parked in 16 registers for all
     // tile heights and copied from there
 #pragma unroll
-    for (int mb = 0; mb < MBS; ++mb)
+    for (int rb = 0; rb < 2 * MBS; ++rb)
 #pragma unroll
-        for (int j = 0; j < NF; ++j)
+        for (int j = 0; j < 2 * NF; ++j)
 #pragma unroll
-            for (int v = 0; v < 16; ++v) asm volatile("v_accvgpr_write_b32 %0, 0" : "=a"(acc[mb][j][v]));
+            for (int v = 0; v < 4; ++v) asm volatile("v_accvgpr_write_b32 %0, 0" : "=a"(acc[rb][j][v]));
 
     // Pipeline depth: activations 2 steps ahead (two register sets), weights 3 steps ahead (ring of 4).
     // Step c issues A(c+2) and B(c+3), spread over its MFMA units (after unit u the activation load of row
@@ -568,7 +572,7 @@ __device__ inline void ffn_tile(uint4 (&lds)[2][kTileM * kLdsRow], const uint16_
     // Everything older, B(c+1) included, has then landed.
     constexpr int AD = 2;
     constexpr int R = AD + 2;                   // weight ring; register indices repeat with period R
-    constexpr int kB = kKS * NF;                // loads of one weight step
+    constexpr int kB = kKS * 2 * NF;            // loads of one weight step
     constexpr int kU = Units<MBS>::U;
     static_assert(MBS <= kU, "one activation load per unit");
     ARegs<MBS> areg[AD];
@@ -588,9 +592,9 @@ __device__ inline void ffn_tile(uint4 (&lds)[2][kTileM * kLdsRow], const uint16_
         }
     };
     auto fetch_b = [&](BFrags<NF>& dst, int chunk) {
-        load_b<KEEP>(dst, static_cast<uint32_t>(chunk) * (kKS * 2048) + lane * 16, wave_base);
+        load_b<KEEP>(dst, static_cast<uint32_t>(chunk) * kStepBytes + weight_lane_offset(lane), wave_base);
     };
-    const uint32_t lane_off = lane * 16;
+    const uint32_t lane_off = weight_lane_offset(lane);
     // Blocks that share a weight stream or an activation tile start their sweep over the reduction
     // dimension at the same step (and wrap around), other blocks at other steps, so that concurrent
     // waves do not all walk their weight streams, which lie a power of two apart, in lockstep.  The
@@ -634,12 +638,12 @@ __device__ inline void ffn_tile(uint4 (&lds)[2][kTileM * kLdsRow], const uint16_
             else                                                                                           \
                 ld_pinned<0>(areg[((I) + AD) % AD].v[mb], a_last_c, a_base);                               \
         };                                                                                                 \
-        const uint32_t voff = static_cast<uint32_t>(at(min(ci + AD + 1, last))) * (kKS * 2048) +           \
+        const uint32_t voff = static_cast<uint32_t>(at(min(ci + AD + 1, last))) * kStepBytes +             \
                               (ci + AD + 1 > last ? 0u : lane_off);                                        \
         auto issue_b = [&](auto ic) {                                                                      \
-            constexpr int i = decltype(ic)::value, ks = i / NF, j = i % NF;                                \
-            ld_pinned_stream<(ks & 1) * 2048 + j * 1024, KEEP>(ring[((I) + AD + 1) % R].v[ks][j],          \
-                                                         voff + (ks >> 1) * 4096, wave_base);              \
+            constexpr int i = decltype(ic)::value, ks = i / (2 * NF), j = i % (2 * NF);                    \
+            ld_pinned_stream<(j >> 1) * 1024 + (j & 1) * 256, KEEP>(ring[((I) + AD + 1) % R].v[ks][j],     \
+                                                                    voff + ks * 4096, wave_base);          \
         };                                                                                                 \
         run_step(acc, af, lds[ci & 1], lds[(ci + 1) & 1], ring[(I) % R], areg[((I) + 1) % AD],             \
                  ring[((I) + 1) % R], lane, tid, issue_a, issue_b);                                        \
@@ -666,7 +670,7 @@ __device__ inline void ffn_tile(uint4 (&lds)[2][kTileM * kLdsRow], const uint16_
 #pragma unroll
         for (int ks = 0; ks < kKS; ++ks)
 #pragma unroll
-            for (int j = 0; j < NF; ++j) asm volatile("" : : "v"(ring[r].v[ks][j]));
+            for (int j = 0; j < 2 * NF; ++j) asm volatile("" : : "v"(ring[r].v[ks][j]));
 #pragma unroll
     for (int i = 0; i < AD; ++i)
 #pragma unroll
@@ -680,7 +684,7 @@ __device__ inline void ffn_tile(uint4 (&lds)[2][kTileM * kLdsRow], const uint16_
     // few microseconds before the block turns to it, so the balance of the queues is what it was.
     unsigned taken = 0u;
     if (tid == 0) taken = take_first(Q);
-    constexpr int kWarm = kKS * (GATED ? 2 : NF);       // 16-byte pieces per lane of one pipeline step of this wave's stream
+    constexpr int kWarm = 2 * kKS * (GATED ? 2 : NF);       // 16-byte pieces per lane of one pipeline step of this wave's stream
     u32x4 warm[kWarm];
 #pragma unroll
     for (int i = 0; i < kWarm; ++i) warm[i] = u32x4{0u, 0u, 0u, 0u};
@@ -699,7 +703,7 @@ __device__ inline void ffn_tile(uint4 (&lds)[2][kTileM * kLdsRow], const uint16_
     char* tile = reinterpret_cast<char*>(&lds[0][0]);
     static_assert(kRowsPerPass * kTileRowBytes <= static_cast<int>(sizeof(lds)), "epilogue tile must fit the LDS buffers");
     const int wave = wave_s;
-    const int row_in = (tid & 31), col_in = 4 * ((tid & 63) >> 5);
+    const int row_in = (tid & 15), col_in = 4 * ((tid & 63) >> 4);
     // the first step of this wave's weight stream in the block's next item (plain loads: they stay in the L2)
     auto warm_next = [&]() {
         const int nq = __builtin_amdgcn_readfirstlane(*sh_q);
@@ -711,7 +715,7 @@ __device__ inline void ffn_tile(uint4 (&lds)[2][kTileM * kLdsRow], const uint16_
         // (addressed as global memory, so that the loads return in order with the other global loads and the stores
         // that follow wait for their own operands only)
         typedef const __attribute__((address_space(1))) u32x4 global_u32x4;
-        global_u32x4* src = (global_u32x4*)(nw + static_cast<size_t>(nkey % static_cast<unsigned>(chunks)) * (kKS * 2048)) + (tid & 63);
+        global_u32x4* src = (global_u32x4*)(nw + static_cast<size_t>(nkey % static_cast<unsigned>(chunks)) * kStepBytes) + (tid & 63);
 #pragma unroll
         for (int i = 0; i < kWarm; ++i) warm[i] = src[(GATED || NF == 2) ? i * 64 : i * 128];
     };
@@ -722,25 +726,22 @@ __device__ inline void ffn_tile(uint4 (&lds)[2][kTileM * kLdsRow], const uint16_
         // independent evaluations of a fragment can overlap
         auto fill = [&](auto exact) {
 #pragma unroll
-            for (int mb = p0 / 32; mb < MBS && mb < (p0 + kRowsPerPass) / 32; ++mb) {
-                char* trow = tile + (mb * 32 + row_in - p0) * kTileRowBytes + (wave * W + col_in) * 2;
+            for (int rb = p0 / 16; rb < 2 * MBS && rb < (p0 + kRowsPerPass) / 16; ++rb) {
+                char* trow = tile + (rb * 16 + row_in - p0) * kTileRowBytes + (wave * W + col_in) * 2;
 #pragma unroll
-                for (int j = 0; j < (GATED ? 1 : NF); ++j) {
+                for (int j = 0; j < (GATED ? 2 : 2 * NF); ++j) {        // 16 columns each
+                    float h[4];
 #pragma unroll
-                    for (int g = 0; g < 4; ++g) {
-                        float h[4];
-#pragma unroll
-                        for (int i = 0; i < 4; ++i) {
-                            if constexpr (GATED)
-                                h[i] = act_fn_bf16(acc[mb][0][4 * g + i], decltype(exact)::value ? 0 : 1) * acc[mb][NF - 1][4 * g + i];
-                            else
-                                h[i] = acc[mb][j][4 * g + i];
-                        }
-                        typedef __bf16 bf16x4 __attribute__((ext_vector_type(4)));
-                        const bf16x4 packed = {static_cast<__bf16>(h[0]), static_cast<__bf16>(h[1]), static_cast<__bf16>(h[2]),
-                                               static_cast<__bf16>(h[3])};
-                        *reinterpret_cast<uint2*>(trow + (32 * j + 8 * g) * 2) = __builtin_bit_cast(uint2, packed);
+                    for (int i = 0; i < 4; ++i) {
+                        if constexpr (GATED)
+                            h[i] = act_fn_bf16(acc[rb][j][i], decltype(exact)::value ? 0 : 1) * acc[rb][2 * NF - 2 + j][i];
+                        else
+                            h[i] = acc[rb][j][i];
                     }
+                    typedef __bf16 bf16x4 __attribute__((ext_vector_type(4)));
+                    const bf16x4 packed = {static_cast<__bf16>(h[0]), static_cast<__bf16>(h[1]), static_cast<__bf16>(h[2]),
+                                           static_cast<__bf16>(h[3])};
+                    *reinterpret_cast<uint2*>(trow + 32 * j) = __builtin_bit_cast(uint2, packed);
                 }
             }
         };
