@@ -11,7 +11,7 @@ HERE = os.path.dirname(os.path.abspath(__file__))
 ROOT = os.path.dirname(HERE)
 CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "libmoe355.so")
-SOURCES = ["api.hip", "route.hip", "permute.hip", "ffn.hip", "combine.hip", "schedule.hip"]
+SOURCES = ["api.hip", "route.hip", "permute.hip", "ffn.hip", "ffn_f32.hip", "combine.hip", "schedule.hip"]
 FLAGS = ["-O3", "-std=c++17", "--offload-arch=gfx950", "-fPIC", "-Wall", "-Wno-unused-function",
          "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
          "-I", os.path.join(ROOT, "include"), "-I", CSRC]

@@ -343,14 +343,14 @@ int layer_forward(const moe_cfg* cfg, const void* x, const void* W_g, const floa
     // hashing gate): the combine step would only move row inv[t] of the batched results to row t.  The
     // down-projection then stores its rows at their tokens' places itself (perm[r] is the token of batched
     // row r) and the combine kernel is not run; the bytes written are the same ones.
-    const bool direct = c.dtype == MOE_BF16 && c.k == 1 && (c.renorm == 1 || c.gate == MOE_GATE_HASH);
+    const bool direct = c.k == 1 && (c.renorm == 1 || c.gate == MOE_GATE_HASH);
     void* ffn_out = direct ? y : static_cast<void*>(base + L.Yp);
     const int32_t* row_map = direct ? perm : nullptr;
     // With few rows per expert (the layer is then bound by streaming the weights, and every microsecond beside the
     // expert kernels counts) the up-projection reads its rows from x through the permutation itself: the batched
     // copy Xp is neither written nor read.  Row tiles are then slightly lower, which costs experts with many rows
-    // an extra pass over their weights, hence the bound on the mean.
-    const bool gather_rows = c.dtype == MOE_BF16 && A / c.E <= 160;
+    // an extra pass over their weights, hence the bound on the mean.  (The fp32 kernel looks its rows up at no such cost.)
+    const bool gather_rows = c.dtype == MOE_F32 || A / c.E <= 160;
     const int32_t* gather = gather_rows ? perm : nullptr;
     const void* ffn_in = gather_rows ? x : static_cast<const void*>(base + L.Xp);
 

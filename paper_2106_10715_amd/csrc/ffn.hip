@@ -11,7 +11,7 @@
 // coalesced 1 KiB reads), only the activation tile is shared through LDS (padded rows,
 // conflict-free 16-byte reads and writes).  With few rows per expert the layer is bound by streaming the
 // weights once from HBM, which is what this layout is built for.
-// fp32 path: plain LDS-tiled FMA kernel (small-shape correctness vehicle).
+// fp32 path: ffn_f32.hip.
 #include "common.h"
 #include "ffn_plan.h"
 
@@ -53,56 +53,6 @@ __device__ inline float act_fn_bf16(float z, int act) {
     float relu;                                  // one instruction: fmaxf would first quiet a signalling NaN, and a NaN comes through ac anyway
     asm("v_max_f32 %0, 0, %1" : "=v"(relu) : "v"(z));
     return fmaf(-ac, __builtin_amdgcn_exp2f(p), relu);
-}
-
-// Which (expert, row tile) a block works on: tile slot `slot` counted over the experts
-// [e_first, e_first + e_count) in order, at most tile_m rows per tile.  Returns false when the slot is past
-// the last tile (uniform for the block).  Must be called by all threads of the block.
-__device__ inline bool find_tile(const int32_t* __restrict__ offsets, int e_first, int e_count, int tile_m, int slot,
-                                 int total_rows, int& e_out, int& row_begin, int& rows) {
-    // segment of expert e, clamped so that whatever the offsets hold no tile reaches outside the rows there are
-    auto seg_lo = [&](int e) { return min(max(offsets[e], 0), total_rows); };
-    auto seg_hi = [&](int e) { return min(max(offsets[e + 1], seg_lo(e)), total_rows); };
-    __shared__ int sh_e, sh_mt;
-    if (threadIdx.x < 64) {
-        const int lane = threadIdx.x;
-        int tl[4], sum = 0;
-#pragma unroll
-        for (int q = 0; q < 4; ++q) {
-            const int e = lane * 4 + q;
-            const int cnt = e < e_count ? seg_hi(e_first + e) - seg_lo(e_first + e) : 0;
-            tl[q] = (cnt + tile_m - 1) / tile_m;
-            sum += tl[q];
-        }
-        int incl = sum;
-#pragma unroll
-        for (int off = 1; off < 64; off <<= 1) {
-            const int v = __shfl_up(incl, off);
-            if (lane >= off) incl += v;
-        }
-        const int target = slot;
-        int run = incl - sum;
-        if (target >= run && target < incl) {
-#pragma unroll
-            for (int q = 0; q < 4; ++q) {
-                if (target >= run && target < run + tl[q]) { sh_e = lane * 4 + q; sh_mt = target - run; }
-                run += tl[q];
-            }
-        }
-        const int total = __shfl(incl, 63);
-        if (lane == 0 && target >= total) sh_e = -1;
-    }
-    __syncthreads();
-    if (sh_e < 0) return false;
-    e_out = e_first + sh_e;
-    // the expert's rows are split evenly over its tiles (in multiples of 32 rows), not into full tiles
-    // and a small remainder: equal tiles finish together and none is nearly empty
-    const int lo = seg_lo(e_out), hi = seg_hi(e_out), n = hi - lo;
-    const int tiles = (n + tile_m - 1) / tile_m;
-    const int per_tile = min(tile_m, ((n + tiles - 1) / tiles + 31) & ~31);
-    row_begin = lo + sh_mt * per_tile;
-    rows = min(per_tile, hi - row_begin);
-    return true;
 }
 
 // ------------------------------------------------------------------------------------------ packing
@@ -896,70 +846,6 @@ __global__ __launch_bounds__(256) void ffn_mfma_kernel(const uint16_t* __restric
     }
 }
 
-// ------------------------------------------------------------------------------------------ fp32 FMA
-
-constexpr int kF32Tile = 64;
-
-template <bool GATED>
-__global__ __launch_bounds__(256) void ffn_f32_kernel(const float* __restrict__ A, const int32_t* __restrict__ offsets,
-                                                      int e_first, int e_count, const float* __restrict__ W,
-                                                      size_t expert_stride_elems, size_t off_b0, size_t off_b1,
-                                                      float* __restrict__ C, int K, int N, int act, int total_rows) {
-    __shared__ float As[16][kF32Tile + 4];
-    __shared__ float B0s[16][kF32Tile + 4];
-    __shared__ float B1s[GATED ? 16 : 1][kF32Tile + 4];
-    int e, row_begin, rows;
-    if (!find_tile(offsets, e_first, e_count, kF32Tile, blockIdx.y, total_rows, e, row_begin, rows)) return;
-    const float* B0 = W + static_cast<size_t>(e - e_first) * expert_stride_elems + off_b0;
-    const float* B1 = W + static_cast<size_t>(e - e_first) * expert_stride_elems + off_b1;
-    const int tx = threadIdx.x & 15, ty = threadIdx.x >> 4;
-    const int n0 = blockIdx.x * kF32Tile;
-    float acc0[4][4], acc1[4][4];
-#pragma unroll
-    for (int i = 0; i < 4; ++i)
-#pragma unroll
-        for (int j = 0; j < 4; ++j) { acc0[i][j] = 0.f; acc1[i][j] = 0.f; }
-    for (int k0 = 0; k0 < K; k0 += 16) {
-#pragma unroll
-        for (int i = 0; i < 4; ++i) {
-            const int id = threadIdx.x + i * 256;
-            const int r = id >> 4, kk = id & 15;
-            As[kk][r] = r < rows ? A[static_cast<size_t>(row_begin + r) * K + k0 + kk] : 0.f;
-            const int kb = id >> 6, cc = id & 63;
-            B0s[kb][cc] = B0[static_cast<size_t>(k0 + kb) * N + n0 + cc];
-            if (GATED) B1s[kb][cc] = B1[static_cast<size_t>(k0 + kb) * N + n0 + cc];
-        }
-        __syncthreads();
-#pragma unroll
-        for (int kk = 0; kk < 16; ++kk) {
-            float a[4], p[4], q[4];
-#pragma unroll
-            for (int i = 0; i < 4; ++i) a[i] = As[kk][ty * 4 + i];
-#pragma unroll
-            for (int j = 0; j < 4; ++j) { p[j] = B0s[kk][tx * 4 + j]; q[j] = GATED ? B1s[kk][tx * 4 + j] : 0.f; }
-#pragma unroll
-            for (int i = 0; i < 4; ++i)
-#pragma unroll
-                for (int j = 0; j < 4; ++j) {
-                    acc0[i][j] = fmaf(a[i], p[j], acc0[i][j]);
-                    if (GATED) acc1[i][j] = fmaf(a[i], q[j], acc1[i][j]);
-                }
-        }
-        __syncthreads();
-    }
-#pragma unroll
-    for (int i = 0; i < 4; ++i) {
-        const int r = ty * 4 + i;
-        if (r < rows) {
-#pragma unroll
-            for (int j = 0; j < 4; ++j) {
-                const float v = GATED ? act_fn(acc0[i][j], act) * acc1[i][j] : acc0[i][j];
-                C[static_cast<size_t>(row_begin + r) * N + n0 + tx * 4 + j] = v;
-            }
-        }
-    }
-}
-
 __global__ __launch_bounds__(256) void copy_vec_kernel(const uint4* __restrict__ src, uint4* __restrict__ dst, size_t n) {
     const size_t i = static_cast<size_t>(blockIdx.x) * 256 + threadIdx.x;
     if (i < n) dst[i] = src[i];
@@ -1016,7 +902,6 @@ int launch_expert_ffn(const moe_cfg& c, const void* Xp, const int32_t* offsets, 
                       const int32_t* gather) {
     if (max_rows <= 0 || e_count <= 0) return MOE_OK;
     const size_t df = static_cast<size_t>(c.d) * c.f;
-    if (gather != nullptr && c.dtype != MOE_BF16) return fail(MOE_ERR_UNSUPPORTED, "gathered rows are a bf16 path");
     if (c.dtype == MOE_BF16) {
         // Work items: 8 queues x (groups of row tiles per queue) x (chunks of column groups) x 32; the
         // resident blocks take them until the queues are empty.
@@ -1096,20 +981,9 @@ int launch_expert_ffn(const moe_cfg& c, const void* Xp, const int32_t* offsets, 
         MOE_LAUNCH_CHECK("ffn_mfma_kernel<down>");
         return MOE_OK;
     }
-    const long slots = max_rows / kF32Tile + e_count;
-    if (slots > 65535) return fail(MOE_ERR_UNSUPPORTED, "too many row tiles for one launch (%ld)", slots);
-    const size_t stride = expert_stride_bytes / 4;
-    const float* Wf = static_cast<const float*>(W);
-    hipLaunchKernelGGL(ffn_f32_kernel<true>, dim3(c.f / kF32Tile, static_cast<unsigned>(slots)), dim3(256), 0, s,
-                       static_cast<const float*>(Xp), offsets, e_first, e_count, Wf, stride, size_t(0), df,
-                       static_cast<float*>(H), c.d, c.f, c.act, c.T * c.k);
-    MOE_LAUNCH_CHECK("ffn_f32_kernel<up>");
-    if (between != nullptr) MOE_HIP_CHECK(hipEventRecord(between, s));
-    hipLaunchKernelGGL(ffn_f32_kernel<false>, dim3(c.d / kF32Tile, static_cast<unsigned>(slots)), dim3(256), 0, s,
-                       static_cast<const float*>(H), offsets, e_first, e_count, Wf, stride, 2 * df, 2 * df,
-                       static_cast<float*>(Yp), c.f, c.d, c.act, c.T * c.k);
-    MOE_LAUNCH_CHECK("ffn_f32_kernel<down>");
-    return MOE_OK;
+    return launch_expert_ffn_f32(c, static_cast<const float*>(Xp), offsets, e_first, e_count, static_cast<const float*>(W),
+                                 expert_stride_bytes / 4, max_rows, static_cast<float*>(H), static_cast<float*>(Yp), s, between,
+                                 row_map, gather);
 }
 
 }  // namespace moe

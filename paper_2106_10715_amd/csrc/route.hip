@@ -17,7 +17,6 @@ namespace moe {
 namespace {
 
 constexpr int kWaves = 4;      // waves per block
-constexpr int kTPW = 4;        // tokens per wave, share every W_g load
 constexpr int kBK = 32;        // terms of one blocked partial sum
 constexpr int kNE = 4;         // experts per lane at most (E <= 256, 64 lanes)
 constexpr int kSel = 9;        // k + 1 <= 9 ranks are looked at
@@ -139,15 +138,80 @@ __device__ __attribute__((always_inline)) inline void rank_gaps(const double (&s
     }
 }
 
-template <typename XT>
+// ---- wave-wide reductions in the lanes' own registers: an inclusive scan by row shifts, then row
+// broadcasts, leaves the total in lane 63 (a dozen vector instructions; a butterfly of lane exchanges goes
+// through the LDS permute unit six times, some hundred cycles each, and the selection is a chain of them).
+template <int CTRL, int ROW_MASK>
+__device__ inline unsigned dpp_from(unsigned identity, unsigned v) {
+    return static_cast<unsigned>(__builtin_amdgcn_update_dpp(static_cast<int>(identity), static_cast<int>(v), CTRL, ROW_MASK, 0xf, false));
+}
+__device__ inline unsigned wave_max_u32(unsigned v) {
+    v = max(v, dpp_from<0x111, 0xf>(0u, v));      // row_shr:1
+    v = max(v, dpp_from<0x112, 0xf>(0u, v));      // row_shr:2
+    v = max(v, dpp_from<0x114, 0xf>(0u, v));      // row_shr:4
+    v = max(v, dpp_from<0x118, 0xf>(0u, v));      // row_shr:8: lane 15 of every row of 16 holds the row's maximum
+    v = max(v, dpp_from<0x142, 0xa>(0u, v));      // row_bcast:15 into rows 1 and 3
+    v = max(v, dpp_from<0x143, 0xc>(0u, v));      // row_bcast:31 into rows 2 and 3: lane 63 holds the wave's
+    return static_cast<unsigned>(__builtin_amdgcn_readlane(static_cast<int>(v), 63));
+}
+__device__ inline unsigned wave_min_u32(unsigned v) { return ~wave_max_u32(~v); }
+__device__ inline float wave_sum_f32(float x) {
+    auto step = [](float v, unsigned got) { return v + __uint_as_float(got); };
+    x = step(x, dpp_from<0x111, 0xf>(0u, __float_as_uint(x)));
+    x = step(x, dpp_from<0x112, 0xf>(0u, __float_as_uint(x)));
+    x = step(x, dpp_from<0x114, 0xf>(0u, __float_as_uint(x)));
+    x = step(x, dpp_from<0x118, 0xf>(0u, __float_as_uint(x)));
+    x = step(x, dpp_from<0x142, 0xa>(0u, __float_as_uint(x)));
+    x = step(x, dpp_from<0x143, 0xc>(0u, __float_as_uint(x)));
+    return __uint_as_float(static_cast<unsigned>(__builtin_amdgcn_readlane(static_cast<int>(__float_as_uint(x)), 63)));
+}
+// fp32 values as unsigned keys of the same order (finite values; -0 must have been turned into +0)
+__device__ inline unsigned order_key(float v) {
+    const unsigned u = __float_as_uint(v);
+    return (u & 0x80000000u) ? ~u : (u | 0x80000000u);
+}
+__device__ inline float from_order_key(unsigned key) {
+    return __uint_as_float((key & 0x80000000u) ? (key & 0x7fffffffu) : ~key);
+}
+
+// The kk largest of the wave's fp32 logits, rank by rank: the largest key of the wave, then the lowest expert that has
+// it.  Lane `eg` holds experts eg + 64 i (i < NE) when `owner`; every lane receives the same result.
+template <int NE>
+__device__ __attribute__((always_inline)) inline void rank_f32(const float (&fv)[NE], int eg, bool owner, int E, int kk,
+                                                               double (&sv)[kSel], int (&se)[kSel]) {
+    unsigned key[NE], taken = 0;
+#pragma unroll
+    for (int i = 0; i < NE; ++i) key[i] = owner && eg + 64 * i < E ? order_key(fv[i]) : 0u;
+#pragma unroll
+    for (int r = 0; r < kSel; ++r) {
+        if (r < kk) {
+            unsigned bk = 0u, be = 0xffffffffu;
+#pragma unroll
+            for (int i = 0; i < NE; ++i)
+                if (owner && eg + 64 * i < E && !((taken >> i) & 1u) && key[i] > bk) { bk = key[i]; be = static_cast<unsigned>(eg + 64 * i); }
+            const unsigned top = wave_max_u32(bk);
+            const unsigned who = wave_min_u32(bk == top ? be : 0xffffffffu);
+            sv[r] = static_cast<double>(from_order_key(top));
+            se[r] = static_cast<int>(who);
+            if ((who & 63u) == static_cast<unsigned>(eg)) taken |= 1u << (who >> 6);
+        }
+    }
+}
+
+// TPW: tokens per wave (they share the W_g loads); NE: experts per lane at most.  The kernel is bound by the latency of
+// its loads: kUnroll terms are requested at a time (one memory latency for all of them), and a batch too short to give
+// every compute unit several waves is handled one token per wave.
+template <typename XT, int TPW, int NE>
 __global__ __launch_bounds__(kWaves * 64) void route_kernel(const XT* __restrict__ x, const XT* __restrict__ Wg,
                                                             const float* __restrict__ bias,
                                                             int32_t* __restrict__ idx, float* __restrict__ w,
                                                             int T, int d, int E, int k, int renorm, int hash) {
     // hash: E is the number of sign bits (columns of the projection), one expert id per token, weight 1
+    constexpr int kUnroll = TPW * NE == 1 ? 32 : NE == 1 ? 16 : 8;
+    static_assert(kBK % kUnroll == 0, "a partial sum is a whole number of load batches");
     const int lane = threadIdx.x & 63;
     const int wave = threadIdx.x >> 6;
-    const int t0 = (blockIdx.x * kWaves + wave) * kTPW;
+    const int t0 = (blockIdx.x * kWaves + wave) * TPW;
     if (t0 >= T) return;                       // whole wave leaves; the kernel has no block-wide barrier
 
     int EP = 1;                                // lanes that hold distinct experts (power of two, <= 64)
@@ -157,90 +221,97 @@ __global__ __launch_bounds__(kWaves * 64) void route_kernel(const XT* __restrict
     const int ks = lane / EP;
     const bool owner = ks == 0;
 
-    size_t xrow[kTPW];
+    size_t xrow[TPW];
 #pragma unroll
-    for (int tt = 0; tt < kTPW; ++tt) xrow[tt] = static_cast<size_t>(min(t0 + tt, T - 1)) * d;
+    for (int tt = 0; tt < TPW; ++tt) xrow[tt] = static_cast<size_t>(min(t0 + tt, T - 1)) * d;
 
-    float tot[kTPW][kNE], wsq[kNE], xsq[kTPW];
+    float tot[TPW][NE], wsq[NE], xsq[TPW];
 #pragma unroll
-    for (int i = 0; i < kNE; ++i) {
+    for (int i = 0; i < NE; ++i) {
         wsq[i] = 0.f;
 #pragma unroll
-        for (int tt = 0; tt < kTPW; ++tt) tot[tt][i] = 0.f;
+        for (int tt = 0; tt < TPW; ++tt) tot[tt][i] = 0.f;
     }
 #pragma unroll
-    for (int tt = 0; tt < kTPW; ++tt) xsq[tt] = 0.f;
+    for (int tt = 0; tt < TPW; ++tt) xsq[tt] = 0.f;
 
     // Blocked summation: partial sums of kBK terms are added into the running total, so a logit goes
     // through at most kBK + ceil(d / (KS kBK)) + log2(KS) + 1 roundings instead of d.
     const int span = KS * kBK;
     for (int kb = 0; kb < d; kb += span) {
-        float part[kTPW][kNE];
+        float part[TPW][NE];
 #pragma unroll
-        for (int i = 0; i < kNE; ++i)
+        for (int i = 0; i < NE; ++i)
 #pragma unroll
-            for (int tt = 0; tt < kTPW; ++tt) part[tt][i] = 0.f;
-        for (int ii = 0; ii < kBK; ++ii) {
-            const int kk = kb + ii * KS + ks;
-            if (kk < d) {
-                float xv[kTPW], wv[kNE];
+            for (int tt = 0; tt < TPW; ++tt) part[tt][i] = 0.f;
+        for (int ii = 0; ii < kBK && kb + ii * KS < d; ii += kUnroll) {
+            // d is a multiple of 64 and so of KS: a term is past the end for all lanes or for none.  Such terms are
+            // read from the start of the row and the column and enter as zeros.
+            float xv[kUnroll][TPW], wv[kUnroll][NE];
 #pragma unroll
-                for (int tt = 0; tt < kTPW; ++tt) xv[tt] = ldf(x, xrow[tt] + kk);
+            for (int u = 0; u < kUnroll; ++u) {
+                const bool in = kb + (ii + u) * KS < d;
+                const int kk = (in ? kb + (ii + u) * KS : 0) + ks;
 #pragma unroll
-                for (int i = 0; i < kNE; ++i) {
+                for (int tt = 0; tt < TPW; ++tt) xv[u][tt] = in ? ldf(x, xrow[tt] + kk) : 0.f;
+#pragma unroll
+                for (int i = 0; i < NE; ++i) {
                     const int ei = eg + 64 * i;
-                    wv[i] = ei < E ? ldf(Wg, static_cast<size_t>(kk) * E + ei) : 0.f;
+                    const float v = ldf(Wg, static_cast<size_t>(kk) * E + min(ei, E - 1));
+                    wv[u][i] = in && ei < E ? v : 0.f;
+                }
+            }
+#pragma unroll
+            for (int u = 0; u < kUnroll; ++u) {
+#pragma unroll
+                for (int tt = 0; tt < TPW; ++tt) {
+                    xsq[tt] = fmaf(xv[u][tt], xv[u][tt], xsq[tt]);
+#pragma unroll
+                    for (int i = 0; i < NE; ++i) part[tt][i] = fmaf(xv[u][tt], wv[u][i], part[tt][i]);
                 }
 #pragma unroll
-                for (int tt = 0; tt < kTPW; ++tt) {
-                    xsq[tt] = fmaf(xv[tt], xv[tt], xsq[tt]);
-#pragma unroll
-                    for (int i = 0; i < kNE; ++i) part[tt][i] = fmaf(xv[tt], wv[i], part[tt][i]);
-                }
-#pragma unroll
-                for (int i = 0; i < kNE; ++i) wsq[i] = fmaf(wv[i], wv[i], wsq[i]);
+                for (int i = 0; i < NE; ++i) wsq[i] = fmaf(wv[u][i], wv[u][i], wsq[i]);
             }
         }
 #pragma unroll
-        for (int i = 0; i < kNE; ++i)
+        for (int i = 0; i < NE; ++i)
 #pragma unroll
-            for (int tt = 0; tt < kTPW; ++tt) tot[tt][i] += part[tt][i];
+            for (int tt = 0; tt < TPW; ++tt) tot[tt][i] += part[tt][i];
     }
     int log2ks = 0;
     for (int off = EP; off < 64; off <<= 1) {
         ++log2ks;
 #pragma unroll
-        for (int i = 0; i < kNE; ++i) {
+        for (int i = 0; i < NE; ++i) {
             wsq[i] += __shfl_xor(wsq[i], off);
 #pragma unroll
-            for (int tt = 0; tt < kTPW; ++tt) tot[tt][i] += __shfl_xor(tot[tt][i], off);
+            for (int tt = 0; tt < TPW; ++tt) tot[tt][i] += __shfl_xor(tot[tt][i], off);
         }
 #pragma unroll
-        for (int tt = 0; tt < kTPW; ++tt) xsq[tt] += __shfl_xor(xsq[tt], off);
+        for (int tt = 0; tt < TPW; ++tt) xsq[tt] += __shfl_xor(xsq[tt], off);
     }
     // largest column norm of W_g among this wave's experts (all lanes end with the wave maximum)
     float wn2 = 0.f;
 #pragma unroll
-    for (int i = 0; i < kNE; ++i) wn2 = fmaxf(wn2, wsq[i]);
-#pragma unroll
-    for (int off = 32; off >= 1; off >>= 1) wn2 = fmaxf(wn2, __shfl_xor(wn2, off));
+    for (int i = 0; i < NE; ++i) wn2 = fmaxf(wn2, wsq[i]);
+    wn2 = __uint_as_float(wave_max_u32(__float_as_uint(wn2)));      // sums of squares: not negative, ordered like their bits
     const float n_round = static_cast<float>(kBK + (d + span - 1) / span + log2ks + 2);
 
     float bl[kNE];
 #pragma unroll
     for (int i = 0; i < kNE; ++i) {
         const int ei = eg + 64 * i;
-        bl[i] = (bias != nullptr && ei < E) ? bias[ei] : 0.f;
+        bl[i] = (i < NE && bias != nullptr && ei < E) ? bias[ei] : 0.f;
     }
 
     const int kk_sel = min(k + 1, E);
 #pragma unroll
-    for (int tt = 0; tt < kTPW; ++tt) {
+    for (int tt = 0; tt < TPW; ++tt) {
         const int t = t0 + tt;
         if (t >= T) continue;
         double lv[kNE], ll[kNE];                // logits as pairs (value, low part); the low part is 0 for fp32 logits
 #pragma unroll
-        for (int i = 0; i < kNE; ++i) { lv[i] = static_cast<double>(tot[tt][i] + bl[i]); ll[i] = 0.0; }
+        for (int i = 0; i < kNE; ++i) { lv[i] = i < NE ? static_cast<double>(tot[tt][i < NE ? i : 0] + bl[i]) : 0.0; ll[i] = 0.0; }
         double sv[kSel];
         int se[kSel];
         int code = 0;
@@ -248,7 +319,10 @@ __global__ __launch_bounds__(kWaves * 64) void route_kernel(const XT* __restrict
         if (hash) {
             sign_bits(lv, ll, eg, owner, E, code, gap, vmax);
         } else {
-            wave_topk(lv, ll, eg, owner, E, kk_sel, sv, se);
+            float fv[NE];
+#pragma unroll
+            for (int i = 0; i < NE; ++i) fv[i] = (tot[tt][i] + bl[i]) + 0.0f;      // a -0 becomes +0: equal logits must compare equal
+            rank_f32<NE>(fv, eg, owner, E, kk_sel, sv, se);
             rank_gaps(sv, kk_sel, gap, vmax);
         }
         // |computed - exact| <= n_round u |x_t| |W_g col| + u |logit| for every logit that matters
@@ -257,25 +331,25 @@ __global__ __launch_bounds__(kWaves * 64) void route_kernel(const XT* __restrict
                              (static_cast<double>(n_round) * sqrt(static_cast<double>(xsq[tt]) * static_cast<double>(wn2)) + vmax);
         if (gap <= 2.0 * delta) {
             // too close to call in fp32: exact products, sums in twice the fp64 precision
-            double acc[kNE], low[kNE];
+            double acc[NE], low[NE];
 #pragma unroll
-            for (int i = 0; i < kNE; ++i) { acc[i] = 0.0; low[i] = 0.0; }
+            for (int i = 0; i < NE; ++i) { acc[i] = 0.0; low[i] = 0.0; }
             for (int kk = ks; kk < d; kk += KS) {
                 const double xv = static_cast<double>(ldf(x, xrow[tt] + kk));
 #pragma unroll
-                for (int i = 0; i < kNE; ++i) {
+                for (int i = 0; i < NE; ++i) {
                     const int ei = eg + 64 * i;
                     if (ei < E) dd_add_product(acc[i], low[i], xv, static_cast<double>(ldf(Wg, static_cast<size_t>(kk) * E + ei)));
                 }
             }
             for (int off = EP; off < 64; off <<= 1)
 #pragma unroll
-                for (int i = 0; i < kNE; ++i) {
+                for (int i = 0; i < NE; ++i) {
                     const double oh = __shfl_xor(acc[i], off), ol = __shfl_xor(low[i], off);
                     dd_add(acc[i], low[i], oh, ol);
                 }
 #pragma unroll
-            for (int i = 0; i < kNE; ++i) {
+            for (int i = 0; i < NE; ++i) {
                 dd_add(acc[i], low[i], static_cast<double>(bl[i]), 0.0);
                 dd_normalise(acc[i], low[i]);
                 lv[i] = acc[i];
@@ -346,42 +420,6 @@ __global__ __launch_bounds__(256) void gate_prep_kernel(const uint16_t* __restri
             part[static_cast<size_t>(S) * NB * 32 + col] = ((sq[0][col_in] + sq[1][col_in]) + sq[2][col_in]) + sq[3][col_in];
         __syncthreads();
     }
-}
-
-// ---- wave-wide reductions in the lanes' own registers: an inclusive scan by row shifts, then row
-// broadcasts, leaves the total in lane 63 (a dozen vector instructions; a butterfly of lane exchanges goes
-// through the LDS permute unit six times, some hundred cycles each, and the selection is a chain of them).
-template <int CTRL, int ROW_MASK>
-__device__ inline unsigned dpp_from(unsigned identity, unsigned v) {
-    return static_cast<unsigned>(__builtin_amdgcn_update_dpp(static_cast<int>(identity), static_cast<int>(v), CTRL, ROW_MASK, 0xf, false));
-}
-__device__ inline unsigned wave_max_u32(unsigned v) {
-    v = max(v, dpp_from<0x111, 0xf>(0u, v));      // row_shr:1
-    v = max(v, dpp_from<0x112, 0xf>(0u, v));      // row_shr:2
-    v = max(v, dpp_from<0x114, 0xf>(0u, v));      // row_shr:4
-    v = max(v, dpp_from<0x118, 0xf>(0u, v));      // row_shr:8: lane 15 of every row of 16 holds the row's maximum
-    v = max(v, dpp_from<0x142, 0xa>(0u, v));      // row_bcast:15 into rows 1 and 3
-    v = max(v, dpp_from<0x143, 0xc>(0u, v));      // row_bcast:31 into rows 2 and 3: lane 63 holds the wave's
-    return static_cast<unsigned>(__builtin_amdgcn_readlane(static_cast<int>(v), 63));
-}
-__device__ inline unsigned wave_min_u32(unsigned v) { return ~wave_max_u32(~v); }
-__device__ inline float wave_sum_f32(float x) {
-    auto step = [](float v, unsigned got) { return v + __uint_as_float(got); };
-    x = step(x, dpp_from<0x111, 0xf>(0u, __float_as_uint(x)));
-    x = step(x, dpp_from<0x112, 0xf>(0u, __float_as_uint(x)));
-    x = step(x, dpp_from<0x114, 0xf>(0u, __float_as_uint(x)));
-    x = step(x, dpp_from<0x118, 0xf>(0u, __float_as_uint(x)));
-    x = step(x, dpp_from<0x142, 0xa>(0u, __float_as_uint(x)));
-    x = step(x, dpp_from<0x143, 0xc>(0u, __float_as_uint(x)));
-    return __uint_as_float(static_cast<unsigned>(__builtin_amdgcn_readlane(static_cast<int>(__float_as_uint(x)), 63)));
-}
-// fp32 values as unsigned keys of the same order (finite values; -0 must have been turned into +0)
-__device__ inline unsigned order_key(float v) {
-    const unsigned u = __float_as_uint(v);
-    return (u & 0x80000000u) ? ~u : (u | 0x80000000u);
-}
-__device__ inline float from_order_key(unsigned key) {
-    return __uint_as_float((key & 0x80000000u) ? (key & 0x7fffffffu) : ~key);
 }
 
 // Value of column `col` of the projection of token t from exact products, by one wave, from the packed fragments:
@@ -594,9 +632,8 @@ __global__ __launch_bounds__(kGateWaves * 64, (TOK == 32 && NB == 1) ? 4 : 2) vo
     for (int tt = wave; tt < TOK; tt += kGateWaves) {
         const int t = t0 + tt;
         if (t >= T) { if (lane == 0) flagged[tt] = 0; continue; }
-        // this lane's logits, fp32 (a -0 becomes +0: equal logits must compare equal) and as ordered keys
+        // this lane's logits, fp32 (a -0 becomes +0: equal logits must compare equal)
         float fv[NE];
-        unsigned key[NE];
 #pragma unroll
         for (int i = 0; i < NE; ++i) {
             const int ei = eg + 64 * i;
@@ -607,7 +644,6 @@ __global__ __launch_bounds__(kGateWaves * 64, (TOK == 32 && NB == 1) ? 4 : 2) vo
                 for (int pw = 1; pw < kParts; ++pw) sum += tile_at(pw, tt, ec);
             }
             fv[i] = ei < E ? (sum + bl[i]) + 0.0f : 0.f;
-            key[i] = ei < E ? order_key(fv[i]) : 0u;
         }
         double lv[kNE], ll[kNE];                 // (value, low part); entries from NE on belong to no expert and are never looked at
 #pragma unroll
@@ -619,22 +655,7 @@ __global__ __launch_bounds__(kGateWaves * 64, (TOK == 32 && NB == 1) ? 4 : 2) vo
         if (hash) {
             sign_bits(lv, ll, eg, true, E, code, gap, vmax);
         } else {
-            // rank by rank: the largest key of the wave, then the lowest expert that has it
-            unsigned taken = 0;
-#pragma unroll
-            for (int r = 0; r < kSel; ++r) {
-                if (r < kk_sel) {
-                    unsigned bk = 0u, be = 0xffffffffu;
-#pragma unroll
-                    for (int i = 0; i < NE; ++i)
-                        if (eg + 64 * i < E && !((taken >> i) & 1u) && key[i] > bk) { bk = key[i]; be = static_cast<unsigned>(eg + 64 * i); }
-                    const unsigned top = wave_max_u32(bk);
-                    const unsigned who = wave_min_u32(bk == top ? be : 0xffffffffu);
-                    sv[r] = static_cast<double>(from_order_key(top));
-                    se[r] = static_cast<int>(who);
-                    if ((who & 63u) == static_cast<unsigned>(eg)) taken |= 1u << (who >> 6);
-                }
-            }
+            rank_f32<NE>(fv, eg, true, E, kk_sel, sv, se);
             rank_gaps(sv, kk_sel, gap, vmax);
         }
         float xn2f = xsq_w[0][tt];
@@ -889,10 +910,19 @@ int launch_route(const moe_cfg& c, const void* x, const void* Wg, const float* b
         MOE_LAUNCH_CHECK("route_mfma_kernel");
         return MOE_OK;
     }
-    const int per_block = kWaves * kTPW;
+    // one token per wave up to 16 waves per compute unit, then four
+    const int tpw = c.T <= 4096 ? 1 : 4;
+    const int per_block = kWaves * tpw;
     dim3 grid((c.T + per_block - 1) / per_block), block(kWaves * 64);
-    hipLaunchKernelGGL(route_kernel<float>, grid, block, 0, s, static_cast<const float*>(x),
-                       static_cast<const float*>(Wg), bias, idx, w, c.T, c.d, cols, c.k, c.renorm, hash);
+#define MOE_ROUTE_F32(TPW, NE)                                                                                        \
+    hipLaunchKernelGGL((route_kernel<float, TPW, NE>), grid, block, 0, s, static_cast<const float*>(x),               \
+                       static_cast<const float*>(Wg), bias, idx, w, c.T, c.d, cols, c.k, c.renorm, hash)
+    if (tpw == 1) {
+        if (cols <= 64) MOE_ROUTE_F32(1, 1); else MOE_ROUTE_F32(1, kNE);
+    } else {
+        if (cols <= 64) MOE_ROUTE_F32(4, 1); else MOE_ROUTE_F32(4, kNE);
+    }
+#undef MOE_ROUTE_F32
     MOE_LAUNCH_CHECK("route_kernel");
     return MOE_OK;
 }

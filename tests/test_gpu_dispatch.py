@@ -1,0 +1,62 @@
+"""GPU parity at the edges of the size rules that choose between kernel shapes, against the CPU oracle."""
+import numpy as np
+import pytest
+import torch
+
+import paper_2106_10715_amd as M
+from oracle import moe_oracle as O
+from paper_2106_10715_amd import harness as H
+from test_gpu_stages import TOL, gpu_route, make_inputs, rel_l2, run_ffn
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("d,f", [(64, 64),       # both products in 32 x 32 tiles with the reduction split over the waves
+                                 (128, 4096),    # up-projection in 64 x 64 tiles
+                                 (4096, 64)])    # down-projection in 64 x 64 tiles
+def test_f32_expert_ffn_tile_shapes(d, f):
+    counts = [0, 1, 31, 32, 33, 64, 65, 130]
+    got, ref, offsets = run_ffn(sum(counts), d, f, len(counts), 1, "f32", counts, 0, seed=d + 3 * f)
+    for e in range(len(counts)):
+        lo, hi = offsets[e], offsets[e + 1]
+        if hi > lo:
+            # two chained fp32 sums of at most 4096 terms: rounding errors of 2^-24 add up like a random walk, 2^-24 * 64 = 4e-6
+            assert rel_l2(got[lo:hi], ref[lo:hi]) <= 4e-6, f"expert {e}"
+
+
+@pytest.mark.parametrize("T,d,E,k", [(4096, 64, 5, 2), (4097, 64, 5, 2), (4098, 128, 70, 3), (33, 192, 65, 2)])
+def test_f32_gate_tokens_per_wave(T, d, E, k):
+    x, Wg, b = make_inputs(T + E, T, d, E, "f32", bias=True)
+    idx, w = gpu_route(M.MoeCfg.make(T, d, 64, E, k, "f32"), x, Wg, b, "f32")
+    r = O.route(x, Wg, k, b, 1)
+    assert np.array_equal(idx, r.idx)
+    assert rel_l2(w, r.w) <= 1e-5
+
+
+def test_f32_layer_without_copy_and_combine():
+    """One expert per token: the layer reads its rows from x and writes them to y itself; the four calls give the same bytes."""
+    rng = np.random.default_rng(5)
+    T, d, f, E = 333, 128, 192, 5
+    cfg = M.MoeCfg.make(T, d, f, E, 1, "f32")
+    x, Wg, _ = make_inputs(9, T, d, E, "f32")
+    ex = [tuple(rng.standard_normal(s).astype(np.float32) * 0.05 for s in ((d, f), (d, f), (f, d))) for _ in range(E)]
+    packed = torch.empty((E, M.moe_expert_bytes(cfg)), dtype=torch.uint8, device="cuda")
+    for e in range(E):
+        M.moe_pack_weights(cfg, *(H.to_device(m, "f32") for m in ex[e]), packed[e])
+    dx, dW = H.to_device(x, "f32"), H.to_device(Wg, "f32")
+    ws = torch.empty(M.moe_workspace_bytes(cfg), dtype=torch.uint8, device="cuda")
+    y = torch.full((T, d), float("nan"), device="cuda")
+    M.moe_layer_forward(cfg, dx, dW, None, packed, None, y, ws)
+
+    def ints(*n):
+        return torch.empty(n, dtype=torch.int32, device="cuda")
+    idx, w, counts, offsets, perm, inv = ints(T, 1), torch.empty((T, 1), device="cuda"), ints(E), ints(E + 1), ints(T), ints(T)
+    Xp, Yp, y4 = torch.empty_like(dx), torch.empty_like(dx), torch.empty_like(dx)
+    M.moe_route(cfg, dx, dW, None, idx, w, ws)
+    M.moe_permute(cfg, dx, idx, counts, offsets, perm, inv, Xp, ws)
+    M.moe_expert_ffn(cfg, Xp, offsets, packed, Yp, ws)
+    M.moe_combine(cfg, Yp, inv, w, y4)
+    torch.cuda.synchronize()
+    assert torch.equal(y, y4)
+    ref = O.layer_forward(x, Wg, lambda e: ex[e], E, 1, None, 1)[0]
+    assert rel_l2(H.to_f64(y), ref) <= TOL["f32"]
