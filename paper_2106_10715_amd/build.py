@@ -12,6 +12,9 @@ ROOT = os.path.dirname(HERE)
 CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "libmoe355.so")
 SOURCES = ["api.hip", "route.hip", "permute.hip", "ffn.hip", "ffn_f32.hip", "combine.hip", "schedule.hip"]
+# ffn.hip is compiled in parts, side by side: each of its large kernels is an object of its own.
+PARTS = {"ffn.hip": 5}
+UNITS = [(src, part) for src in SOURCES for part in range(PARTS.get(src, 1))]
 FLAGS = ["-O3", "-std=c++17", "--offload-arch=gfx950", "-fPIC", "-Wall", "-Wno-unused-function",
          "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
          "-I", os.path.join(ROOT, "include"), "-I", CSRC]
@@ -187,21 +190,33 @@ def check_prologue_in_flight(asm: str, kernel_pattern: str, what: str = "assembl
     return checked
 
 
-def _compile(src: str) -> str:
-    obj = os.path.join(HERE, "_build", src.replace(".hip", ".o"))
-    cmd = [_hipcc(), *FLAGS, *EXTRA.get(src, []), "-c", os.path.join(CSRC, src), "-o", obj]
+def _flags(src: str, part: int) -> list:
+    return [*FLAGS, *EXTRA.get(src, []), *([f"-DFFN_PART={part}"] if src in PARTS else [])]
+
+
+def _built(src: str, part: int, suffix: str) -> str:
+    return os.path.join(HERE, "_build", src.replace(".hip", f"_{part}{suffix}" if src in PARTS else suffix))
+
+
+def _check(src: str, part: int) -> None:
+    """Compiles the unit to assembly and refuses what the checks above refuse (ffn.hip's part 0 holds no pipelined loop)."""
+    asm = _built(src, part, ".s")
+    ra = subprocess.run([_hipcc(), *_flags(src, part), "-S", "--cuda-device-only", os.path.join(CSRC, src), "-o", asm],
+                        capture_output=True, text=True)
+    if ra.returncode != 0:
+        raise RuntimeError(f"hipcc -S failed on {src}:\n{ra.stderr}")
+    text = open(asm).read()
+    check_no_spill(text, NO_SPILL[src], src)
+    loops = check_loads_in_flight(text, NO_SPILL[src], src), check_prologue_in_flight(text, NO_SPILL[src], src)
+    if part > 0 and 0 in loops:
+        raise RuntimeError(f"{src}: no pipelined loop found to verify (markers missing?)")
+
+
+def _compile(src: str, part: int) -> str:
+    obj = _built(src, part, ".o")
+    cmd = [_hipcc(), *_flags(src, part), "-c", os.path.join(CSRC, src), "-o", obj]
     r = subprocess.run(cmd, capture_output=True, text=True)
     noise = "is not a recognized feature for this target"
-    if r.returncode == 0 and src in NO_SPILL:
-        asm = os.path.join(HERE, "_build", src.replace(".hip", ".s"))
-        ra = subprocess.run([_hipcc(), *FLAGS, *EXTRA.get(src, []), "-S", "--cuda-device-only",
-                             os.path.join(CSRC, src), "-o", asm], capture_output=True, text=True)
-        if ra.returncode != 0:
-            raise RuntimeError(f"hipcc -S failed on {src}:\n{ra.stderr}")
-        text = open(asm).read()
-        check_no_spill(text, NO_SPILL[src], src)
-        if check_loads_in_flight(text, NO_SPILL[src], src) == 0 or check_prologue_in_flight(text, NO_SPILL[src], src) == 0:
-            raise RuntimeError(f"{src}: no pipelined loop found to verify (markers missing?)")
     err = "\n".join(l for l in r.stderr.splitlines() if noise not in l)
     if r.returncode != 0:
         raise RuntimeError(f"hipcc failed on {src}:\n{err}")
@@ -212,8 +227,11 @@ def _compile(src: str) -> str:
 
 def build(verbose: bool = False) -> str:
     os.makedirs(os.path.join(HERE, "_build"), exist_ok=True)
-    with ThreadPoolExecutor(max_workers=min(8, len(SOURCES))) as pool:
-        objs = list(pool.map(_compile, SOURCES))
+    with ThreadPoolExecutor(max_workers=8) as pool:
+        checks = [pool.submit(_check, src, part) for src, part in UNITS if src in NO_SPILL]
+        objs = list(pool.map(lambda u: _compile(*u), UNITS))
+        for c in checks:
+            c.result()
     cmd = [_hipcc(), "--offload-arch=gfx950", "-shared", "-fPIC", "-o", LIB, *objs]
     r = subprocess.run(cmd, capture_output=True, text=True)
     if r.returncode != 0:

@@ -13,17 +13,38 @@
 // weights once from HBM, which is what this layout is built for.
 // fp32 path: ffn_f32.hip.
 #include "common.h"
+#include "ffn_few.h"
 #include "ffn_plan.h"
 
 #include <type_traits>
 
+// This file is compiled in five parts side by side (FFN_PART 0..4; a kernel holds the tile code for eight heights in two
+// load flavours and takes minutes): the four instantiations of ffn_mfma_kernel, and everything else.
+#ifndef FFN_PART
+#error "compile with -DFFN_PART=0..4"
+#endif
+
 namespace moe {
+
+// One launch of ffn_mfma_kernel (arguments as there).
+struct FfnLaunch {
+    const void* A; int32_t* plan; int counter_base, e_first;
+    const void* W; size_t expert_stride_bytes, block_offset_bytes;
+    void* C; int K, N, act, y_chunks, y_shift, mt_shift;
+    const int32_t *row_map, *gather;
+    int gather_k, h_rows, list, max_tiles;
+    unsigned grid;
+};
+void launch_ffn_up(const FfnLaunch& a, hipStream_t s);
+void launch_ffn_up_gather(const FfnLaunch& a, hipStream_t s);
+void launch_ffn_down(const FfnLaunch& a, hipStream_t s);
+void launch_ffn_down_narrow(const FfnLaunch& a, hipStream_t s);
+
 namespace {
 
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 typedef float f32x4 __attribute__((ext_vector_type(4)));
 
-constexpr int kKC = 64;                 // reduction elements staged per pipeline step (2 MFMA k-steps)
 // Rows of a tile when the up-projection gathers its rows itself: a thread then holds one source offset per
 // 32-row block, which the registers allow up to seven blocks (eight accumulator blocks leave no room).
 constexpr int kGatherTileM = 224;
@@ -55,6 +76,7 @@ __device__ inline float act_fn_bf16(float z, int act) {
     return fmaf(-ac, __builtin_amdgcn_exp2f(p), relu);
 }
 
+#if FFN_PART == 0
 // ------------------------------------------------------------------------------------------ packing
 
 // One thread per 16-byte lane slot of a fragment: element 8 l + j of fragment (n, s) is
@@ -99,6 +121,35 @@ __global__ __launch_bounds__(256) void pack_bf16_kernel(const uint16_t* __restri
     packed[F * 64 + l] = o;
 }
 
+__global__ __launch_bounds__(256) void copy_vec_kernel(const uint4* __restrict__ src, uint4* __restrict__ dst, size_t n) {
+    const size_t i = static_cast<size_t>(blockIdx.x) * 256 + threadIdx.x;
+    if (i < n) dst[i] = src[i];
+}
+
+// The work list of a launch is written by ffn_plan_block (ffn_plan.h): here as a kernel of its own.
+__global__ __launch_bounds__(256) void ffn_plan_kernel(const int32_t* __restrict__ offsets, int e_first, int e_count,
+                                                       int tile_m_up, int tile_m_down, int32_t* __restrict__ plan, int total_rows,
+                                                       int max_tiles) {
+    __shared__ int scratch[4][256];
+    ffn_plan_block(offsets, e_first, e_count, tile_m_up, plan, total_rows, max_tiles, scratch, 0);
+    if (tile_m_down != tile_m_up) {             // else the down kernel reads the up kernel's list
+        __syncthreads();
+        ffn_plan_block(offsets, e_first, e_count, tile_m_down, plan, total_rows, max_tiles, scratch, 1);
+    }
+}
+
+template <bool GATED, int CB>
+__global__ __launch_bounds__(kFewWaves * 64, 3) void ffn_few_kernel(const uint16_t* __restrict__ A, const int32_t* __restrict__ plan,
+                                                                  int e_first, const char* __restrict__ W, size_t expert_stride_bytes,
+                                                                  size_t block_offset_bytes, uint16_t* __restrict__ C, int K, int N,
+                                                                  int act, const int32_t* __restrict__ row_map,
+                                                                  const int32_t* __restrict__ gather, int gather_k, int h_rows) {
+    __shared__ __align__(16) float lds[kFewWaves * (GATED ? 4 : CB) * 16 * 20];
+    ffn_few_block<GATED, CB>(lds, A, plan, e_first, W, expert_stride_bytes, block_offset_bytes, C, K, N, row_map, gather, gather_k,
+                                 h_rows, [act](float z) { return act_fn_bf16(z, act); });
+}
+
+#else   // FFN_PART 1..4
 // ------------------------------------------------------------------------------------------ bf16 MFMA
 //
 // Software pipeline of one block (4 waves, up to 256 rows of one expert, 64 reduction elements per
@@ -117,6 +168,7 @@ __global__ __launch_bounds__(256) void pack_bf16_kernel(const uint16_t* __restri
 // weights of step c+1.  The wait names those registers as read-write operands so that no use of them
 // can be moved above it.
 
+constexpr int kKC = 64;                 // reduction elements staged per pipeline step (2 MFMA k-steps)
 constexpr int kKS = kKC / 32;           // MFMA k-steps per pipeline step
 constexpr uint32_t kStepBytes = (kKC / 16) * 2048;   // bytes of a wave's weight stream one pipeline step spans
 constexpr int kLdsRow = 9;              // uint4 per activation row in LDS: 128 B of data + 16 B pad (conflict-free)
@@ -382,10 +434,10 @@ __device__ inline unsigned thread_id(int wave) {
 // ---- work items.  A launch's items are positions of 8 queues (one per XCD; see ffn_mfma_kernel); everything a
 // block needs to take one and to find out what it means, all of it uniform (scalar registers):
 struct ItemQueue {
-    unsigned* counters;            // next position of each queue
+    unsigned* counters;            // positions taken of each queue beyond the first ones (see first_positions)
     unsigned total_q, home;        // positions per queue; this block's own queue
     const int4* tile_list;         // (expert, first row, rows, row tiles of the expert) per row tile
-    int tiles, y_chunks, mt_shift;
+    int tiles, y_chunks, y_shift, mt_shift;
     const char* W;                 // packed weights of expert e_first (+ block_offset_bytes: the up or the down block)
     size_t expert_stride_bytes, block_offset_bytes;
     int e_first;
@@ -396,12 +448,12 @@ struct Item {
 };
 
 __device__ inline Item decode_item(const ItemQueue& Q, unsigned q, unsigned xcd, int units) {
-    const unsigned ny = 32u >> Q.mt_shift;     // column groups per run of 32; 1 << mt_shift row tiles
-    const unsigned yg = q & (ny - 1u), mt = (q / ny) & ((1u << Q.mt_shift) - 1u), rest = q >> 5;
+    // a run: 1 << mt_shift row tiles x 1 << y_shift column groups
+    const unsigned yg = q & ((1u << Q.y_shift) - 1u), mt = (q >> Q.y_shift) & ((1u << Q.mt_shift) - 1u), rest = q >> (Q.y_shift + Q.mt_shift);
     const unsigned y_chunk = rest % static_cast<unsigned>(Q.y_chunks), tile_group = rest / static_cast<unsigned>(Q.y_chunks);
     const int slot = static_cast<int>((((tile_group << 3) + xcd) << Q.mt_shift) + mt);
     Item it;
-    it.block_y = static_cast<int>(y_chunk * ny + yg);
+    it.block_y = static_cast<int>((y_chunk << Q.y_shift) + yg);
     it.real = slot < Q.tiles && it.block_y * 4 < units;
     it.e = it.row_begin = it.rows = it.tiles_of_expert = 0;
     if (it.real) {
@@ -440,19 +492,35 @@ __device__ inline const void* wave_stream(const ItemQueue& Q, int e, int block_y
     return reinterpret_cast<const void*>((static_cast<uintptr_t>(wb_hi) << 32) | static_cast<uintptr_t>(wb_lo));
 }
 
+// The first positions of a queue belong to the blocks that call it home, in order, without asking: a block starts on
+// position blockIdx / 8.  The counters count what is taken after those.
+#ifdef V_ATOM
+__device__ inline unsigned first_positions(unsigned x) { return 0u; }
+#else
+__device__ inline unsigned first_positions(unsigned x) { return (gridDim.x + 7u - x) >> 3; }
+#endif
 // Thread 0 takes the next position: first from the block's own queue, and when that is empty from the others.
-// The first attempt is split from the rest so that its answer can arrive under other work.
-__device__ inline unsigned take_first(const ItemQueue& Q) { return atomicAdd(&Q.counters[Q.home], 1u); }
+// The first attempt is split from the rest so that its answer can arrive under other work.  Before it asks another queue
+// it looks at all counters at once (they only grow, so an old value costs a vain attempt and nothing else): at the end of a
+// launch every block finds every queue empty, and seven questions one after the other take some 10 us.
+__device__ inline unsigned take_first(const ItemQueue& Q) { return first_positions(Q.home) + atomicAdd(&Q.counters[Q.home], 1u); }
 __device__ inline void take_finish(const ItemQueue& Q, unsigned v, int* sh_q, int* sh_x) {
     int got = -1;
     unsigned x = Q.home;
     if (v < Q.total_q) {
         got = static_cast<int>(v);
     } else {
+        unsigned seen[8];
+#pragma unroll
+        for (unsigned i = 1; i < 8u; ++i)
+            seen[i] = __hip_atomic_load(&Q.counters[(Q.home + i) & 7u], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+#pragma unroll
         for (unsigned i = 1; i < 8u; ++i) {
-            x = (Q.home + i) & 7u;
-            const unsigned w = atomicAdd(&Q.counters[x], 1u);
-            if (w < Q.total_q) { got = static_cast<int>(w); break; }
+            const unsigned y = (Q.home + i) & 7u, first = first_positions(y);
+            if (got < 0 && first + seen[i] < Q.total_q) {
+                const unsigned w = first + atomicAdd(&Q.counters[y], 1u);
+                if (w < Q.total_q) { got = static_cast<int>(w); x = y; }
+            }
         }
     }
     *sh_q = got;
@@ -746,19 +814,7 @@ __device__ inline void ffn_tile(uint4 (&lds)[2][kTileM * kLdsRow], const uint16_
     for (int i = 0; i < kWarm; ++i) asm volatile("" : : "v"(warm[i]));
 }
 
-// The work list of a launch is written by ffn_plan_block (ffn_plan.h): here as a kernel of its own.
 constexpr int kKeepFromTiles = 2;       // row tiles of an expert from which its weights are worth keeping in the L2
-
-__global__ __launch_bounds__(256) void ffn_plan_kernel(const int32_t* __restrict__ offsets, int e_first, int e_count,
-                                                       int tile_m_up, int tile_m_down, int32_t* __restrict__ plan, int total_rows,
-                                                       int max_tiles) {
-    __shared__ int scratch[4][256];
-    ffn_plan_block(offsets, e_first, e_count, tile_m_up, plan, total_rows, max_tiles, scratch, 0);
-    if (tile_m_down != tile_m_up) {             // else the down kernel reads the up kernel's list
-        __syncthreads();
-        ffn_plan_block(offsets, e_first, e_count, tile_m_down, plan, total_rows, max_tiles, scratch, 1);
-    }
-}
 
 // C[rows of one expert tile, N] = A[rows, K] * B_e, B_e in packed fragment order.
 // A work item is one row tile (up to 256 rows of one expert; only the 32-row blocks that hold rows are
@@ -771,8 +827,8 @@ __global__ __launch_bounds__(256) void ffn_plan_kernel(const int32_t* __restrict
 //
 // One block per compute unit stays resident and takes work items from 8 queues, one per XCD (blocks go
 // round-robin to the XCDs, each with its own L2, so blockIdx % 8 names the XCD): position q of a
-// queue decodes into 32-item runs of 2^mt_shift neighbouring row tiles x 32 / 2^mt_shift neighbouring
-// column groups.  Tiles of one expert then share its weight stream, and the column groups of a tile
+// queue decodes into runs of 2^mt_shift neighbouring row tiles x 2^y_shift neighbouring column groups (32 items, or
+// fewer where that leaves no position without an item).  Tiles of one expert then share its weight stream, and the column groups of a tile
 // share its activation tile, in that XCD's L2; groups of tiles are dealt to the queues in turn.  A
 // block whose own queue is empty helps with the others.
 // GATHER (up-projection only): A is the token array x and the rows of a tile are looked up through `gather`
@@ -783,7 +839,7 @@ __global__ __launch_bounds__(256) void ffn_mfma_kernel(const uint16_t* __restric
                                                        int counter_base, int e_first, const char* __restrict__ W,
                                                        size_t expert_stride_bytes, size_t block_offset_bytes,
                                                        uint16_t* __restrict__ C, int K, int N, int act, int y_chunks,
-                                                       int mt_shift, const int32_t* __restrict__ row_map,
+                                                       int y_shift, int mt_shift, const int32_t* __restrict__ row_map,
                                                        const int32_t* __restrict__ gather, int gather_k, int h_rows,
                                                        int list, int max_tiles) {
     __shared__ uint4 lds[2][kTileM * kLdsRow];     // 2 x 36 KiB activation tiles, padded rows
@@ -791,9 +847,10 @@ __global__ __launch_bounds__(256) void ffn_mfma_kernel(const uint16_t* __restric
     ItemQueue Q;
     Q.tiles = plan[16 + list];
     Q.y_chunks = y_chunks;
+    Q.y_shift = y_shift;
     Q.mt_shift = mt_shift;
     const unsigned per_group = 8u << mt_shift;
-    Q.total_q = (static_cast<unsigned>(Q.tiles) + per_group - 1u) / per_group * static_cast<unsigned>(y_chunks) * 32u;
+    Q.total_q = ((static_cast<unsigned>(Q.tiles) + per_group - 1u) / per_group * static_cast<unsigned>(y_chunks)) << (mt_shift + y_shift);
     Q.tile_list = reinterpret_cast<const int4*>(plan + kPlanHeader + 4 * list * max_tiles);
     Q.counters = reinterpret_cast<unsigned*>(plan) + counter_base;
     Q.home = blockIdx.x & 7u;
@@ -802,13 +859,18 @@ __global__ __launch_bounds__(256) void ffn_mfma_kernel(const uint16_t* __restric
     Q.block_offset_bytes = block_offset_bytes;
     Q.e_first = e_first;
     const int wave = __builtin_amdgcn_readfirstlane(static_cast<int>(threadIdx.x >> 6));
-    // an item taken with nothing to do meanwhile: the first one, and the one after a padding position
+    // an item taken with nothing to do meanwhile: the one after a padding position
     auto take_now = [&]() {
         __syncthreads();                           // everybody has read the previous position
         if (thread_id(wave) == 0) take_finish(Q, take_first(Q), &sh_q, &sh_x);
         __syncthreads();
     };
+#ifdef V_ATOM
     take_now();
+#else
+    if (thread_id(wave) == 0) take_finish(Q, blockIdx.x >> 3, &sh_q, &sh_x);      // the block's own first position
+    __syncthreads();
+#endif
     for (;;) {
         if (sh_q < 0) return;                      // every queue is empty (uniform for the block)
         // The tile code below is compiled for eight tile heights; values that do not change from item to
@@ -846,13 +908,26 @@ __global__ __launch_bounds__(256) void ffn_mfma_kernel(const uint16_t* __restric
     }
 }
 
-__global__ __launch_bounds__(256) void copy_vec_kernel(const uint4* __restrict__ src, uint4* __restrict__ dst, size_t n) {
-    const size_t i = static_cast<size_t>(blockIdx.x) * 256 + threadIdx.x;
-    if (i < n) dst[i] = src[i];
+template <bool GATED, int NF, bool GATHER>
+void launch_mfma(const FfnLaunch& a, hipStream_t s) {
+    hipLaunchKernelGGL((ffn_mfma_kernel<GATED, NF, GATHER>), dim3(a.grid), dim3(256), 0, s, static_cast<const uint16_t*>(a.A), a.plan,
+                       a.counter_base, a.e_first, static_cast<const char*>(a.W), a.expert_stride_bytes, a.block_offset_bytes,
+                       static_cast<uint16_t*>(a.C), a.K, a.N, a.act, a.y_chunks, a.y_shift, a.mt_shift, a.row_map, a.gather, a.gather_k,
+                       a.h_rows, a.list, a.max_tiles);
 }
+#endif  // FFN_PART
 
 }  // namespace
 
+#if FFN_PART == 1
+void launch_ffn_up(const FfnLaunch& a, hipStream_t s) { launch_mfma<true, 2, false>(a, s); }
+#elif FFN_PART == 2
+void launch_ffn_up_gather(const FfnLaunch& a, hipStream_t s) { launch_mfma<true, 2, true>(a, s); }
+#elif FFN_PART == 3
+void launch_ffn_down(const FfnLaunch& a, hipStream_t s) { launch_mfma<false, 2, false>(a, s); }
+#elif FFN_PART == 4
+void launch_ffn_down_narrow(const FfnLaunch& a, hipStream_t s) { launch_mfma<false, 1, false>(a, s); }
+#else
 constexpr int kMinTileM = 64;           // lowest row tile a launch is ever cut into
 size_t ffn_plan_tiles(const moe_cfg& c) { return static_cast<size_t>(c.T) * c.k / kMinTileM + c.E; }   // room for the lowest tiles
 int ffn_tile_rows(bool gather) { return gather ? kGatherTileM : kTileM; }
@@ -872,6 +947,18 @@ int ffn_down_tile_rows(const moe_cfg& c, int e_count, long max_rows, int tile_m_
     long tm = ((mean_rows * 5 / 4 + per_expert - 1) / per_expert + 31) / 32 * 32;
     tm = tm < kMinTileM ? kMinTileM : tm;
     return tm < tile_m_up ? static_cast<int>(tm) : tile_m_up;
+}
+
+// Whether a layer's experts run on the kernels for few rows (ffn_few.h), by the layer's own sizes, so that a launch over one
+// expert sums like a launch over all.  The large kernel needs work items (an expert's tile x 256 columns in the
+// down-projection) for the compute units; the fewer it has, the more rows per expert the other one may be given.
+// Large kernel / few rows, layer us, d 4096 f 10240: 32 experts 40 rows in all 900 / 849, 64 rows 1084 / 1074, 128 rows
+// 1239 / 1245; 64 experts 128 rows 2073 / 2046; 16 experts 64 rows 599 / 588, 128 rows 636 / 634, 256 rows 641 / 659;
+// 8 experts 64 rows 353 / 332, 128 rows 345 / 341, 192 rows 347 / 359.  Smaller layers: d 1024 f 2048 8 experts 256 rows
+// 55 / 47, 512 rows 60 / 67; d 512 f 1024 33 experts 1000 rows 61 / 56; d 2048 f 4096 16 experts 400 rows 157 / 173.
+bool few_rows(const moe_cfg& c, int n_cu) {
+    const long rows = static_cast<long>(c.T) * c.k, items = static_cast<long>(c.E) * ((c.d / 64 + 3) / 4);
+    return rows <= (2 * items < n_cu ? 32L : items <= n_cu ? 8L : 2L) * c.E;
 }
 
 int launch_pack(const moe_cfg& c, const void* Win, const void* Wgate, const void* Wout, void* packed, hipStream_t s) {
@@ -929,15 +1016,22 @@ int launch_expert_ffn(const moe_cfg& c, const void* Xp, const int32_t* offsets, 
             return by_rows < by_tiles ? by_rows : by_tiles;
         };
         const int mt_shift = shift_for(slots), mt_shift_down = shift_for(slots_down);
-        auto items_for = [&](long n_slots, int shift, int col_groups, int& y_chunks) {
+        // positions of all queues.  Runs hold 32 items; narrower ones are taken where they leave fewer positions without an
+        // item (80 column groups: five runs of 16 and not three of 32).
+        auto items_for = [&](long n_slots, int shift, int col_groups, int& y_shift, int& y_chunks) {
             const long tile_groups = (n_slots + (8L << shift) - 1) / (8L << shift);   // per queue
-            const int ny = 32 >> shift;
-            y_chunks = (col_groups + ny - 1) / ny;
-            return tile_groups * y_chunks * 32 * 8;
+            y_shift = 5 - shift;
+            auto padded = [&](int ys) { return (col_groups + (1 << ys) - 1) >> ys << ys; };
+#ifdef V_RUN
+            if (0)
+#endif
+            for (int ys = y_shift - 1; ys >= 0; --ys)
+                if (padded(ys) < padded(y_shift)) y_shift = ys;
+            y_chunks = padded(y_shift) >> y_shift;
+            return ((tile_groups * 8) << (shift + y_shift)) * y_chunks;
         };
         const int max_tiles = static_cast<int>(ffn_plan_tiles(c));
         const int down_list = tile_m_down != tile_m ? 1 : 0;       // equal heights: one list serves both kernels
-        auto grid_for = [&](long items) { return dim3(static_cast<unsigned>(items < n_cu ? items : n_cu)); };
         if (!plan_ready) {          // else the kernel that batched the tokens has written the work list as well
             hipLaunchKernelGGL(ffn_plan_kernel, dim3(1), dim3(256), 0, s, offsets, e_first, e_count, tile_m, tile_m_down, plan,
                                c.T * c.k, max_tiles);
@@ -945,20 +1039,37 @@ int launch_expert_ffn(const moe_cfg& c, const void* Xp, const int32_t* offsets, 
         }
         if (before_up != nullptr) MOE_HIP_CHECK(hipEventRecord(before_up, s));
         const size_t down_off = 2 * df * 2;
-        dim3 block(256);
-        int yc = 0;
-        long items = items_for(slots, mt_shift, (c.f / 32 + 3) / 4, yc);
+        if (few_rows(c, n_cu)) {
+            const unsigned n_tiles = static_cast<unsigned>(max_rows < slots ? max_rows : slots);
+            const dim3 few_block(kFewWaves * 64);
+#define MOE_FFN_FEW(CB)                                                                                               \
+    {                                                                                                                 \
+        hipLaunchKernelGGL((ffn_few_kernel<true, 2>), dim3(c.f / 32, n_tiles), few_block, 0, s,                   \
+                           static_cast<const uint16_t*>(Xp), plan, e_first, static_cast<const char*>(W),              \
+                           expert_stride_bytes, size_t(0), static_cast<uint16_t*>(H), c.d, c.f, c.act,                \
+                           static_cast<const int32_t*>(nullptr), gather, c.k, c.T * c.k);                             \
+        MOE_LAUNCH_CHECK("ffn_few_kernel<up>");                                                                       \
+        if (between != nullptr) MOE_HIP_CHECK(hipEventRecord(between, s));                                            \
+        hipLaunchKernelGGL((ffn_few_kernel<false, CB>), dim3(c.d / (16 * CB), n_tiles), few_block, 0, s,  \
+                           static_cast<const uint16_t*>(H), plan, e_first, static_cast<const char*>(W),               \
+                           expert_stride_bytes, down_off, static_cast<uint16_t*>(Yp), c.f, c.d, c.act, row_map,       \
+                           static_cast<const int32_t*>(nullptr), 1, c.T * c.k);                                       \
+        MOE_LAUNCH_CHECK("ffn_few_kernel<down>");                                                                     \
+    }
+            // the down-projection in units of 16 columns (twice the blocks) for one 16-row block at most; with two, a unit
+            // would read twice the activations its weights have (32 tokens: 787 us in units of 16 columns, 767 of 32)
+            if (c.T * c.k <= 16) MOE_FFN_FEW(1) else MOE_FFN_FEW(2)
+#undef MOE_FFN_FEW
+            return MOE_OK;
+        }
+        FfnLaunch up{Xp, plan, 0, e_first, W, expert_stride_bytes, 0, H, c.d, c.f, c.act, 0, 0, mt_shift, nullptr, gather,
+                     gather != nullptr ? c.k : 1, c.T * c.k, 0, max_tiles, 0};
+        long items = items_for(slots, mt_shift, (c.f / 32 + 3) / 4, up.y_shift, up.y_chunks);
         if (items > 0x7fffffffL) return fail(MOE_ERR_UNSUPPORTED, "too many work items for one launch (%ld)", items);
+        up.grid = static_cast<unsigned>(items < n_cu ? items : n_cu);
         // (with `gather`, Xp is the token array and the kernel looks its rows up itself)
-        if (gather != nullptr)
-            hipLaunchKernelGGL((ffn_mfma_kernel<true, 2, true>), grid_for(items), block, 0, s, static_cast<const uint16_t*>(Xp), plan, 0,
-                               e_first, static_cast<const char*>(W), expert_stride_bytes, size_t(0), static_cast<uint16_t*>(H),
-                               c.d, c.f, c.act, yc, mt_shift, static_cast<const int32_t*>(nullptr), gather, c.k, c.T * c.k, 0, max_tiles);
-        else
-            hipLaunchKernelGGL((ffn_mfma_kernel<true, 2>), grid_for(items), block, 0, s, static_cast<const uint16_t*>(Xp), plan, 0,
-                               e_first, static_cast<const char*>(W), expert_stride_bytes, size_t(0), static_cast<uint16_t*>(H),
-                               c.d, c.f, c.act, yc, mt_shift, static_cast<const int32_t*>(nullptr),
-                               static_cast<const int32_t*>(nullptr), 1, c.T * c.k, 0, max_tiles);
+        if (gather != nullptr) launch_ffn_up_gather(up, s);
+        else launch_ffn_up(up, s);
         MOE_LAUNCH_CHECK("ffn_mfma_kernel<up>");
         if (between != nullptr) MOE_HIP_CHECK(hipEventRecord(between, s));
         // down-projection: narrow (32-column) units when wide ones would leave compute units idle
@@ -968,16 +1079,13 @@ int launch_expert_ffn(const moe_cfg& c, const void* Xp, const int32_t* offsets, 
         // second LDS read per MFMA costs more than the idle compute units do; measured on 8 experts: 128 rows per
         // expert 0.148 ms narrow against 0.177 ms wide, 256 rows 0.274 against 0.239)
         const bool narrow = tiles_hint * ((c.d / 64 + 3) / 4) < 2 * 256 && mean_rows <= 224;
-        items = items_for(slots_down, mt_shift_down, ((narrow ? c.d / 32 : c.d / 64) + 3) / 4, yc);
+        FfnLaunch down{H, plan, 8, e_first, W, expert_stride_bytes, down_off, Yp, c.f, c.d, c.act, 0, 0, mt_shift_down, row_map, nullptr,
+                       1, c.T * c.k, down_list, max_tiles, 0};
+        items = items_for(slots_down, mt_shift_down, ((narrow ? c.d / 32 : c.d / 64) + 3) / 4, down.y_shift, down.y_chunks);
         if (items > 0x7fffffffL) return fail(MOE_ERR_UNSUPPORTED, "too many work items for one launch (%ld)", items);
-        if (narrow)
-            hipLaunchKernelGGL((ffn_mfma_kernel<false, 1>), grid_for(items), block, 0, s, static_cast<const uint16_t*>(H), plan, 8,
-                               e_first, static_cast<const char*>(W), expert_stride_bytes, down_off, static_cast<uint16_t*>(Yp),
-                               c.f, c.d, c.act, yc, mt_shift_down, row_map, static_cast<const int32_t*>(nullptr), 1, c.T * c.k, down_list, max_tiles);
-        else
-            hipLaunchKernelGGL((ffn_mfma_kernel<false, 2>), grid_for(items), block, 0, s, static_cast<const uint16_t*>(H), plan, 8,
-                               e_first, static_cast<const char*>(W), expert_stride_bytes, down_off, static_cast<uint16_t*>(Yp),
-                               c.f, c.d, c.act, yc, mt_shift_down, row_map, static_cast<const int32_t*>(nullptr), 1, c.T * c.k, down_list, max_tiles);
+        down.grid = static_cast<unsigned>(items < n_cu ? items : n_cu);
+        if (narrow) launch_ffn_down_narrow(down, s);
+        else launch_ffn_down(down, s);
         MOE_LAUNCH_CHECK("ffn_mfma_kernel<down>");
         return MOE_OK;
     }
@@ -985,5 +1093,7 @@ int launch_expert_ffn(const moe_cfg& c, const void* Xp, const int32_t* offsets, 
                                  expert_stride_bytes / 4, max_rows, static_cast<float*>(H), static_cast<float*>(Yp), s, between,
                                  row_map, gather);
 }
+
+#endif  // FFN_PART
 
 }  // namespace moe
