@@ -494,11 +494,7 @@ __device__ inline const void* wave_stream(const ItemQueue& Q, int e, int block_y
 
 // The first positions of a queue belong to the blocks that call it home, in order, without asking: a block starts on
 // position blockIdx / 8.  The counters count what is taken after those.
-#ifdef V_ATOM
-__device__ inline unsigned first_positions(unsigned x) { return 0u; }
-#else
 __device__ inline unsigned first_positions(unsigned x) { return (gridDim.x + 7u - x) >> 3; }
-#endif
 // Thread 0 takes the next position: first from the block's own queue, and when that is empty from the others.
 // The first attempt is split from the rest so that its answer can arrive under other work.  Before it asks another queue
 // it looks at all counters at once (they only grow, so an old value costs a vain attempt and nothing else): at the end of a
@@ -865,12 +861,8 @@ __global__ __launch_bounds__(256) void ffn_mfma_kernel(const uint16_t* __restric
         if (thread_id(wave) == 0) take_finish(Q, take_first(Q), &sh_q, &sh_x);
         __syncthreads();
     };
-#ifdef V_ATOM
-    take_now();
-#else
     if (thread_id(wave) == 0) take_finish(Q, blockIdx.x >> 3, &sh_q, &sh_x);      // the block's own first position
     __syncthreads();
-#endif
     for (;;) {
         if (sh_q < 0) return;                      // every queue is empty (uniform for the block)
         // The tile code below is compiled for eight tile heights; values that do not change from item to
@@ -1022,9 +1014,6 @@ int launch_expert_ffn(const moe_cfg& c, const void* Xp, const int32_t* offsets, 
             const long tile_groups = (n_slots + (8L << shift) - 1) / (8L << shift);   // per queue
             y_shift = 5 - shift;
             auto padded = [&](int ys) { return (col_groups + (1 << ys) - 1) >> ys << ys; };
-#ifdef V_RUN
-            if (0)
-#endif
             for (int ys = y_shift - 1; ys >= 0; --ys)
                 if (padded(ys) < padded(y_shift)) y_shift = ys;
             y_chunks = padded(y_shift) >> y_shift;

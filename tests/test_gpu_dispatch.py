@@ -60,3 +60,34 @@ def test_f32_layer_without_copy_and_combine():
     assert torch.equal(y, y4)
     ref = O.layer_forward(x, Wg, lambda e: ex[e], E, 1, None, 1)[0]
     assert rel_l2(H.to_f64(y), ref) <= TOL["f32"]
+
+
+@pytest.mark.parametrize("counts", [[1], [0, 16, 0], [17, 0], [5, 0, 9, 18], [32], [0, 15, 17], [33], [1] * 32, [28, 5]],
+                         ids=lambda c: "x".join(map(str, c[:4])) + f"-{sum(c)}")
+@pytest.mark.parametrize("d,f", [(64, 64), (192, 704), (1024, 576)])
+def test_few_rows_expert_ffn(counts, d, f):
+    """Up to 32 rows in all run on kernels of their own (16 or 32 rows per expert); 33 rows and more do not."""
+    got, ref, offsets = run_ffn(sum(counts), d, f, len(counts), 1, "bf16", counts, d % 128 // 64, seed=sum(counts) + d)
+    for e in range(len(counts)):
+        lo, hi = offsets[e], offsets[e + 1]
+        if hi > lo:
+            assert rel_l2(got[lo:hi], ref[lo:hi]) <= TOL["bf16"], f"expert {e}"
+
+
+@pytest.mark.parametrize("T,k", [(1, 1), (7, 2), (30, 1), (21, 3)])
+def test_few_rows_streamed_equals_resident(T, k):
+    import moe_workloads as W
+    wl = W.Workload("few", T=T, d=256, f=384, E=6, k=k, dtype="bf16", seed=50 + T)
+    L = H.build_layer(wl, host_copy=True)
+    M.moe_layer_forward(L.cfg, L.x, L.Wg, L.bias, L.packed, None, L.y, L.ws)
+    torch.cuda.synchronize()
+    want = L.y.clone()
+    ref = O.layer_forward(W.gen_x(wl), W.gen_gate(wl)[0], lambda e: W.gen_expert(wl, e), wl.E, k, None, wl.renorm)[0]
+    assert rel_l2(H.to_f64(want), ref) <= TOL["bf16"]
+    ctx = M.StreamCtx(L.cfg, L.host_packed, torch.empty((2, M.moe_expert_bytes(L.cfg)), dtype=torch.uint8, device="cuda"), 2)
+    for _ in range(2):
+        L.y.fill_(float("nan"))
+        M.moe_layer_forward(L.cfg, L.x, L.Wg, L.bias, None, ctx, L.y, L.ws)
+        torch.cuda.synchronize()
+        assert torch.equal(L.y, want)
+    ctx.close()
