@@ -185,8 +185,7 @@ int moe_combine(const moe_cfg* cfg, const void* Yp, const int32_t* inv, const fl
  *   call fails half-way, the context forgets what its slots hold (nothing is taken for resident that may
  *   not have been copied).
  *   Results are bitwise identical in both modes.
- *   Resident calls consist of kernel launches only and can be recorded into a HIP graph; with more than 32
- *   experts, run one call outside the capture first (the gate kernel raises its LDS limit once per device).
+ *   Resident calls consist of kernel launches only and can be recorded into a HIP graph.
  */
 int moe_layer_forward(const moe_cfg* cfg, const void* x, const void* W_g, const float* gate_bias,
                       const void* W_packed, moe_stream_ctx* sctx, void* y, void* ws, void* stream);

@@ -10,7 +10,6 @@
 // columns whose exact projections tie do tie.
 #include "common.h"
 
-#include <atomic>
 #include <type_traits>
 
 namespace moe {
@@ -164,6 +163,21 @@ __device__ inline float wave_sum_f32(float x) {
     x = step(x, dpp_from<0x142, 0xa>(0u, __float_as_uint(x)));
     x = step(x, dpp_from<0x143, 0xc>(0u, __float_as_uint(x)));
     return __uint_as_float(static_cast<unsigned>(__builtin_amdgcn_readlane(static_cast<int>(__float_as_uint(x)), 63)));
+}
+// The same over a row of 16 lanes, by rotations inside the row: every lane of the row gets the result.
+__device__ inline unsigned row_max_u32(unsigned v) {
+    v = max(v, dpp_from<0x128, 0xf>(0u, v));      // row_ror:8
+    v = max(v, dpp_from<0x124, 0xf>(0u, v));
+    v = max(v, dpp_from<0x122, 0xf>(0u, v));
+    return max(v, dpp_from<0x121, 0xf>(0u, v));
+}
+__device__ inline unsigned row_min_u32(unsigned v) { return ~row_max_u32(~v); }
+__device__ inline float row_sum_f32(float x) {
+    auto step = [](float v, unsigned got) { return v + __uint_as_float(got); };
+    x = step(x, dpp_from<0x128, 0xf>(0u, __float_as_uint(x)));
+    x = step(x, dpp_from<0x124, 0xf>(0u, __float_as_uint(x)));
+    x = step(x, dpp_from<0x122, 0xf>(0u, __float_as_uint(x)));
+    return step(x, dpp_from<0x121, 0xf>(0u, __float_as_uint(x)));
 }
 // fp32 values as unsigned keys of the same order (finite values; -0 must have been turned into +0)
 __device__ inline unsigned order_key(float v) {
@@ -369,25 +383,25 @@ __global__ __launch_bounds__(kWaves * 64) void route_kernel(const XT* __restrict
 
 // ------------------------------------------------------------------------------------------ bf16: MFMA gate
 //
-// logits tile = 32 tokens x E on 32x32x16 bf16 MFMAs.  The eight waves of a block split the reduction
+// logits tile = 32 tokens (64, 16) x E on 16x16x32 bf16 MFMAs.  The eight waves of a block split the reduction
 // dimension (wave w takes the 64-element groups S = w, w+8, ...), the partial tiles are added in wave
 // order through LDS.  W_g is first rewritten (gate_prep_kernel) into MFMA fragment order so that its
 // fragments are plain 1 KiB coalesced reads, and so that a lane's four fragments of a group use 64
 // contiguous bytes of its token row: fragment (nb, S, q), lane l, element j holds
 //     W_g[64 S + 32 (l / 32) + 8 q + j, 32 nb + l % 32]            (0 beyond E).
 //
-// Error bound of an MFMA logit (measured behaviour of the instruction: the addends of one
-// instruction -- accumulator and products -- are aligned to the largest of them and cut to fp32
-// precision, so one instruction loses at most 17 units in the last place of its largest addend, which
-// is at most the sum of |products|): |error| <= (17 n + 8) 2^-24 |x_t| |W_g column| with n the MFMAs a
-// wave chains per logit.  Tokens whose k+1 best logits are not separated by twice that are
+// Error bound of an MFMA logit (measured behaviour of the instruction: the addends -- accumulator and products -- are
+// aligned to the largest of them and cut to fp32 precision, so one 16x16x32 instruction, 33 addends, loses at most
+// 34 x 2^-24 of its largest addend, which is at most the sum of |products|; 34.0 is the largest loss over 10^8 random
+// instructions, with all addends of one sign, whose sum is then some thirty times the largest): |error| <= (17 n + 8) 2^-24
+// |x_t| |W_g column| with n = two per instruction a wave chains per logit.  Tokens whose k+1 best logits are not separated
+// by twice that are
 // re-evaluated in fp64 by the whole block.
 
-constexpr int kGateTokens = 32;
 constexpr int kGateWaves = 8;    // waves of a gate block; they split the reduction dimension
 
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
-typedef float f32x16 __attribute__((ext_vector_type(16)));
+typedef float f32x4 __attribute__((ext_vector_type(4)));
 
 // Block b packs the 64-row group S = b of W_g for every 32-expert block and writes the sums of squares
 // of those 64 rows per expert column: part[b][E_pad].
@@ -423,10 +437,8 @@ __global__ __launch_bounds__(256) void gate_prep_kernel(const uint16_t* __restri
 }
 
 // Value of column `col` of the projection of token t from exact products, by one wave, from the packed fragments:
-// lane j takes the 8-row pieces j, j + 64, ... of the column.  PAIR = false: plain fp64 sums (error at most about
-// d 2^-53 |x_t| |column|), lo = 0.  PAIR = true: sums in twice that precision, the pair (hi, lo) not yet normalised;
-// only needed when fp64 leaves candidates closer than its own error.  Every lane gets the sum.
-template <bool PAIR>
+// lane j takes the 8-row pieces j, j + 64, ... of the column; sums in twice the fp64 precision, the pair (hi, lo) not yet
+// normalised.  Every lane gets the sum.
 __device__ __attribute__((always_inline)) inline void exact_column_dot(const uint16_t* __restrict__ x, const uint4* __restrict__ pack, size_t t,
                                                            int col, int nS, int d, int lane, double& hi, double& lo) {
     const int nb = col >> 5, cin = col & 31;
@@ -441,321 +453,529 @@ __device__ __attribute__((always_inline)) inline void exact_column_dot(const uin
         for (int i = 0; i < 4; ++i) {
             const double x0 = static_cast<double>(__uint_as_float(xu[i] << 16)), w0 = static_cast<double>(__uint_as_float(wu[i] << 16));
             const double x1 = static_cast<double>(__uint_as_float(xu[i] & 0xffff0000u)), w1 = static_cast<double>(__uint_as_float(wu[i] & 0xffff0000u));
-            if constexpr (PAIR) {
-                dd_add_product(sum, low, x0, w0);
-                dd_add_product(sum, low, x1, w1);
-            } else {
-                sum = fma(x0, w0, sum);
-                sum = fma(x1, w1, sum);
-            }
+            dd_add_product(sum, low, x0, w0);
+            dd_add_product(sum, low, x1, w1);
         }
     }
 #pragma unroll
     for (int off = 32; off >= 1; off >>= 1) {
-        const double oh = __shfl_xor(sum, off);
-        if constexpr (PAIR) {
-            const double ol = __shfl_xor(low, off);
-            dd_add(sum, low, oh, ol);
-        } else {
-            sum += oh;
-        }
+        const double oh = __shfl_xor(sum, off), ol = __shfl_xor(low, off);
+        dd_add(sum, low, oh, ol);
     }
     hi = sum;
     lo = low;
 }
 
+// Column of the n-th set bit of the masks (bit l of mask i: column l + 64 i).
+template <int NE>
+__device__ inline int nth_column(const unsigned long long (&mask)[NE], int n) {
+    int col = 0;
+    bool found = false;
+#pragma unroll
+    for (int i = 0; i < NE; ++i) {
+        const int here = __popcll(mask[i]);
+        if (!found && n < here) {
+            unsigned long long m = mask[i];
+            for (int skip = n; skip > 0; --skip) m &= m - 1ull;
+            col = __ffsll(static_cast<long long>(m)) - 1 + 64 * i;
+            found = true;
+        }
+        n -= here;
+    }
+    return col;
+}
+
 constexpr int kMaxCand = 12;     // columns of one token that are re-evaluated one by one; more than that: all columns
 
+constexpr int gate_row(int columns) { return columns + 4; }      // floats per tile row: the four lane groups of a tile write hit different banks
 template <int NB>
 constexpr int gate_parts() { return NB <= 4 ? kGateWaves : 1; }      // one partial tile per wave while they fit the LDS
-template <int NB>
-constexpr size_t gate_tile_bytes() { return static_cast<size_t>(gate_parts<NB>()) * kGateTokens * (NB * 32 + 1) * sizeof(float); }
-
-// TOK: tokens a block really has (32, 16 or 8).  The MFMA tile always has 32 token rows; with fewer tokens
-// the rows repeat them (the same addresses, so no more bytes are read) and only the first TOK are ranked.
-// A short batch gets more, smaller blocks this way: a block's time is mostly its own loads through one
-// compute unit plus a selection that is a latency chain per token, and 128 blocks leave half the chip idle.
+constexpr int gate_rows(int tok) { return tok > 32 ? tok : 32; }     // token rows of a tile
+// TOK: tokens of a block (64, 32, 16 or 8; with 8, the 16 rows of a matrix tile repeat them).  A short batch gets more,
+// smaller blocks: a block's time is mostly its own loads through one compute unit, and 128 blocks leave half the chip idle.
+// A long one gets fewer, larger ones: every block reads the whole gate from the L2, beside its own tokens.
 template <int NB, int TOK>
-__global__ __launch_bounds__(kGateWaves * 64, (TOK == 32 && NB == 1) ? 4 : 2) void route_mfma_kernel(const uint16_t* __restrict__ x,
+__global__ __launch_bounds__(kGateWaves * 64, 2) void route_mfma_kernel(const uint16_t* __restrict__ x,
                                                          const uint4* __restrict__ pack, const float* __restrict__ part,
                                                          const float* __restrict__ bias, int32_t* __restrict__ idx,
                                                          float* __restrict__ w, int T, int d, int E, int k, int renorm,
                                                          int hash) {
     // hash: E is the number of sign bits (columns of the projection), one expert id per token, weight 1
     constexpr int EP = NB * 32;
-    constexpr int kParts = gate_parts<NB>();
-    extern __shared__ float part_tile[];                   // [kParts][kGateTokens][EP + 1]: partial logit tiles
-    __shared__ float xsq_w[kGateWaves][kGateTokens];
-    __shared__ float wn2_sh;
-    __shared__ int flagged[kGateTokens];
+    constexpr int kParts = gate_parts<NB>(), kRows = gate_rows(TOK);
+    __shared__ float part_tile[kParts * kRows * gate_row(EP)];     // [kParts][kRows][gate_row(EP)]: partial logit tiles
+    __shared__ float xsq_w[kGateWaves][kRows];
+    __shared__ float colpart[kGateWaves * 64];             // partial column sums of squares (up to 512 columns' worth)
+    __shared__ unsigned long long many_sh;                     // those of them with more columns in reach than are evaluated one by one
+    __shared__ unsigned long long close_sh;                     // tokens fp32 cannot decide, one bit each
+    __shared__ double reach_sh[kRows];                     // and from which logit on (hash: up to which magnitude) their columns matter
     __shared__ double resc[kGateWaves][EP], resc_lo[kGateWaves][EP];    // re-evaluated logits per wave: value and low part
-    auto tile_at = [&](int p, int tok, int e) -> float& { return part_tile[(p * kGateTokens + tok) * (EP + 1) + e]; };
+    auto tile_at = [&](int p, int tok, int e) -> float& { return part_tile[(p * kRows + tok) * gate_row(EP) + e]; };
 
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(static_cast<int>(threadIdx.x >> 6));
     const int t0 = blockIdx.x * TOK;
     const int nS = d / 64;
 
-    // A wave's groups S = wave, wave + 8, ... are taken kAhead at a time: the token pieces of all of them are
-    // requested first (they come from HBM: one latency instead of one per group; the first batch is
-    // requested before the column norms below are worked out), the gate fragments, which every block re-reads
-    // from the L2, one or two groups ahead of the MFMAs that use them (as many as the registers of two waves
-    // per SIMD hold for this number of expert blocks).
-    // Long batches (full 32-token blocks, several per compute unit) prefetch less and stay within the registers
-    // of two resident blocks per compute unit, which overlap each other's phases.
-    constexpr bool kTwoBlocks = TOK == 32 && NB == 1;
-    constexpr int kAhead = kTwoBlocks ? 2 : NB <= 2 ? 4 : NB <= 4 ? 2 : 1;
-    constexpr int kRing = (NB <= 1 && !kTwoBlocks) ? 3 : 2;
-    const int row = min(t0 + (lane & (TOK - 1)), T - 1);
-    const uint4* xrow = reinterpret_cast<const uint4*>(x + static_cast<size_t>(row) * d + 32 * (lane >> 5));
-    uint4 xv[kAhead][4];
-    auto fetch_x = [&](int S0) {
+    // ---- column norms of W_g, for the error bound: thread (g, c) adds the per-group sums S = g, g + G, ... of column c; the
+    // partial sums are added up where they are used, after the barrier that publishes the logits.  The first kNorm
+    // are requested before everything else and added once the loads below are on their way.
+    constexpr int G = EP >= kGateWaves * 64 ? 1 : kGateWaves * 64 / EP, kNorm = 8;
+    const int norm_c = static_cast<int>(threadIdx.x) % EP, norm_g = static_cast<int>(threadIdx.x) / EP;
+    float norm[kNorm];                     // (threads past the last whole group of columns, EP = 96 and others, hold unused sums)
 #pragma unroll
-        for (int p = 0; p < kAhead; ++p) {
-            const int S = S0 + p * kGateWaves < nS ? S0 + p * kGateWaves : 0;      // past the end: group 0, unused
-#pragma unroll
-            for (int q = 0; q < 4; ++q) xv[p][q] = xrow[S * 8 + q];                // 64 contiguous bytes of the token row
-        }
-    };
-    fetch_x(wave);
-
-    // ---- largest column norm of W_g: fixed-order sum of the per-group parts, then the block maximum.
-    // Thread (g, c) adds the parts S = g, g + G, ... of column c; thread c adds the G partial sums in order.
-    {
-        float* colpart = part_tile;                        // kGateWaves * 64 floats, free until the tiles are written
-        constexpr int G = EP >= kGateWaves * 64 ? 1 : kGateWaves * 64 / EP;
-        float best = 0.f;
-        for (int c0 = 0; c0 < EP; c0 += kGateWaves * 64) {          // one round unless EP exceeds the block
-            const int c = c0 + static_cast<int>(threadIdx.x) % EP, g = static_cast<int>(threadIdx.x) / EP;
-            float ssum = 0.f;
-            if (c < EP && g < G)
-                for (int S = g; S < nS; S += G) ssum += part[static_cast<size_t>(S) * EP + c];
-            colpart[threadIdx.x] = ssum;
-            __syncthreads();
-            if (g == 0 && c < EP) {
-                float tot = 0.f;
-                for (int gg = 0; gg < G; ++gg) tot += colpart[gg * EP + (c - c0)];
-                best = fmaxf(best, tot);
-            }
-            __syncthreads();
-        }
-        best = __uint_as_float(wave_max_u32(__float_as_uint(best)));   // sums of squares: not negative, ordered like their bits
-        if (lane == 0) xsq_w[wave][0] = best;
-        __syncthreads();
-        if (threadIdx.x == 0) {
-            float m = xsq_w[0][0];
-            for (int wv = 1; wv < kGateWaves; ++wv) m = fmaxf(m, xsq_w[wv][0]);
-            wn2_sh = m;
-        }
-        __syncthreads();
+    for (int i = 0; i < kNorm; ++i) {
+        const int S = norm_g + i * G;
+        norm[i] = part[static_cast<size_t>(S < nS ? S : 0) * EP + norm_c];
     }
+    asm volatile("" : : : "memory");
 
-    // ---- MFMA partial tiles
-    f32x16 acc[NB];
+    // A wave's groups of 64 reduction elements are S = wave, wave + 8, ...  Products on 16x16x32: in k-step m of a group, lane
+    // 16 g + c holds elements 64 S + 32 m + 8 g + j of token row c (and of column c), so that a load of token pieces covers 64
+    // contiguous bytes of 16 rows (one lane per 16 bytes of 32 rows, as 32x32x16 wants it, takes the address unit twice as
+    // long: 40 cycles per load, which bounded the kernel); the gate fragment holds those elements at slot 32 m + 16 cb + c of its part g.
+    constexpr int RB = TOK > 16 ? TOK / 16 : 1;                  // 16-row blocks; 8 tokens: every row twice
+    const int c15 = lane & 15, g4 = lane >> 4;
+    uint32_t x_lane[RB];                                   // byte offsets from x (T d 2 < 2^32)
 #pragma unroll
-    for (int nb = 0; nb < NB; ++nb)
+    for (int rb = 0; rb < RB; ++rb)
+        x_lane[rb] = static_cast<uint32_t>(min(t0 + ((16 * rb + c15) & (TOK - 1)), T - 1)) * static_cast<uint32_t>(d) * 2u + 16u * g4;
+    const uint32_t w_lane = 1024u * g4 + 16u * c15;
+    auto x_piece = [&](int S, int m, int rb) __attribute__((always_inline)) {
+        return *reinterpret_cast<const uint4*>(reinterpret_cast<const char*>(x) + static_cast<size_t>(S) * 128 + 64 * m + x_lane[rb]);
+    };
+    auto w_piece = [&](int S, int nb, int m, int cb) __attribute__((always_inline)) {
+        return *reinterpret_cast<const uint4*>(reinterpret_cast<const char*>(pack) + (static_cast<size_t>(nb) * nS + S) * 4096 + 512 * m + 256 * cb + w_lane);
+    };
+    struct XGroup { uint4 v[2][RB]; };
+    struct WGroup { uint4 v[NB][2][2]; };
+    f32x4 acc[RB][NB][2];
+    float xs[RB];
 #pragma unroll
-        for (int v = 0; v < 16; ++v) acc[nb][v] = 0.f;
-    float xs = 0.f;
-    for (int S0 = wave; S0 < nS; S0 += kGateWaves * kAhead) {
-        if (S0 != wave) fetch_x(S0);
-        uint4 wv[kRing][NB][4];
-        auto fetch_w = [&](int p, uint4 (&dst)[NB][4]) {
-            const int S = S0 + p * kGateWaves < nS ? S0 + p * kGateWaves : S0;
+    for (int rb = 0; rb < RB; ++rb) {
+        xs[rb] = 0.f;
 #pragma unroll
-            for (int nb = 0; nb < NB; ++nb) {
-                const uint4* bp = pack + ((static_cast<size_t>(nb) * nS + S) * 4) * 64 + lane;
+        for (int nb = 0; nb < NB; ++nb) acc[rb][nb][0] = acc[rb][nb][1] = f32x4{0.f, 0.f, 0.f, 0.f};
+    }
+    auto multiply = [&](const XGroup& xg, const WGroup& wg) __attribute__((always_inline)) {
 #pragma unroll
-                for (int q = 0; q < 4; ++q) dst[nb][q] = bp[q * 64];
-            }
-        };
+        for (int m = 0; m < 2; ++m)
 #pragma unroll
-        for (int p = 0; p + 1 < kRing; ++p) fetch_w(p, wv[p]);
+            for (int rb = 0; rb < RB; ++rb) {
+                const uint4 piece = xg.v[m][rb];
+                const uint32_t u[4] = {piece.x, piece.y, piece.z, piece.w};
 #pragma unroll
-        for (int p = 0; p < kAhead; ++p) {
-            if (p + kRing - 1 < kAhead) fetch_w(p + kRing - 1, wv[(p + kRing - 1) % kRing]);
-            if (S0 + p * kGateWaves < nS) {                                        // uniform for the wave
-#pragma unroll
-                for (int q = 0; q < 4; ++q) {
-                    const uint32_t u[4] = {xv[p][q].x, xv[p][q].y, xv[p][q].z, xv[p][q].w};
-#pragma unroll
-                    for (int i = 0; i < 4; ++i) {
-                        const float lo = __uint_as_float(u[i] << 16), hi = __uint_as_float(u[i] & 0xffff0000u);
-                        xs = fmaf(lo, lo, xs);
-                        xs = fmaf(hi, hi, xs);
-                    }
+                for (int i = 0; i < 4; ++i) {
+                    const float lo = __uint_as_float(u[i] << 16), hi = __uint_as_float(u[i] & 0xffff0000u);
+                    xs[rb] = fmaf(lo, lo, xs[rb]);
+                    xs[rb] = fmaf(hi, hi, xs[rb]);
                 }
 #pragma unroll
                 for (int nb = 0; nb < NB; ++nb)
 #pragma unroll
-                    for (int q = 0; q < 4; ++q)
-                        acc[nb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, xv[p][q]),
-                                                                           __builtin_bit_cast(bf16x8, wv[p % kRing][nb][q]), acc[nb], 0, 0, 0);
+                    for (int cb = 0; cb < 2; ++cb)
+                        acc[rb][nb][cb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, piece),
+                                                                                  __builtin_bit_cast(bf16x8, wg.v[nb][m][cb]), acc[rb][nb][cb], 0, 0, 0);
             }
-        }
-    }
-    xs += __shfl_xor(xs, 32);
-    if (lane < 32) xsq_w[wave][lane] = xs;
-    // The partial tiles are added in wave order, ((w0 + w1) + w2) + ...: by the lane that reads a logit when
-    // every wave has a tile of its own, else wave after wave into one tile.
-    if (kParts == kGateWaves) {
+    };
+    auto load_x = [&](int S, XGroup& dst) __attribute__((always_inline)) {
+#pragma unroll
+        for (int rb = 0; rb < RB; ++rb)
+#pragma unroll
+            for (int m = 0; m < 2; ++m) dst.v[m][rb] = x_piece(S, m, rb);
+    };
+    auto load_w = [&](int S, WGroup& dst) __attribute__((always_inline)) {
 #pragma unroll
         for (int nb = 0; nb < NB; ++nb)
 #pragma unroll
-            for (int v = 0; v < 16; ++v)
-                tile_at(wave, 8 * (v >> 2) + 4 * (lane >> 5) + (v & 3), 32 * nb + (lane & 31)) = acc[nb][v];
+            for (int m = 0; m < 2; ++m)
+#pragma unroll
+                for (int cb = 0; cb < 2; ++cb) dst.v[nb][m][cb] = w_piece(S, nb, m, cb);
+    };
+    auto norms_to_lds = [&]() __attribute__((always_inline)) {
+        float ssum = 0.f;
+#pragma unroll
+        for (int i = 0; i < kNorm; ++i) ssum += norm_g + i * G < nS ? norm[i] : 0.f;
+        for (int S = norm_g + kNorm * G; S < nS; S += G) ssum += part[static_cast<size_t>(S) * EP + norm_c];
+        colpart[threadIdx.x] = ssum;
+        if (threadIdx.x == 0) close_sh = many_sh = 0ull;
+    };
+
+    // ---- MFMA partial tiles
+    if constexpr (NB <= 2) {
+        // The token pieces come from HBM: a ring of kXDepth groups is requested ahead, for as many groups as the registers
+        // hold (at d_model 4096 a wave has eight).  The gate fragments, which every block re-reads from the L2, are requested
+        // kWRing - 1 groups ahead, the first ones before the token pieces (loads return in order).
+        constexpr int kXDepth = TOK == 64 ? 2 : TOK == 32 && NB == 2 ? 4 : 8, kWRing = 2;
+        const int n_mine = (nS - wave + kGateWaves - 1) / kGateWaves;      // this wave's groups (0 when d is short)
+        XGroup xv[kXDepth];
+        WGroup wv[kWRing];
+        const int phase = n_mine > 0 ? static_cast<int>((blockIdx.x >> 3) % static_cast<unsigned>(n_mine)) : 0;
+        auto group_of = [&](int i) {
+            const int r = i + phase < n_mine ? i + phase : i + phase - n_mine;
+            return i < n_mine ? wave + r * kGateWaves : 0;                 // past the end: group 0, unused
+        };
+        // (a fence after every batch of loads: the compiler would move them down to their use)
+        auto fetch_x = [&](int i, XGroup& dst) __attribute__((always_inline)) {
+            load_x(group_of(i), dst);
+            asm volatile("" : : : "memory");
+        };
+        auto fetch_w = [&](int i, WGroup& dst) __attribute__((always_inline)) {
+            load_w(group_of(i), dst);
+            asm volatile("" : : : "memory");
+        };
+#pragma unroll
+        for (int p = 0; p + 1 < kWRing; ++p) fetch_w(p, wv[p]);
+        fetch_x(0, xv[0]);
+        if (TOK >= 32 || n_mine > 1) {               // (short batches: nothing to request ahead when d is short)
+#pragma unroll
+            for (int p = 1; p < kXDepth; ++p) fetch_x(p, xv[p]);
+        }
+        norms_to_lds();
+        for (int i0 = 0; i0 < n_mine; i0 += kXDepth) {
+            auto groups = [&](auto more) __attribute__((always_inline)) {  // more: the ring is refilled behind the groups used
+#pragma unroll
+                for (int p = 0; p < kXDepth; ++p) {
+                    const int i = i0 + p;
+                    if ((p + kWRing - 1 < kXDepth && (TOK >= 32 || n_mine > 1)) || decltype(more)::value) fetch_w(i + kWRing - 1, wv[(p + kWRing - 1) % kWRing]);
+                    if (i < n_mine) multiply(xv[p], wv[p % kWRing]);       // uniform for the wave
+                    if (decltype(more)::value) fetch_x(i + kXDepth, xv[p]);
+                }
+            };
+            if (i0 + kXDepth < n_mine) groups(std::true_type{});
+            else groups(std::false_type{});
+        }
+    } else {
+        // more expert blocks: as many groups of token pieces at a time and gate fragments ahead as the registers hold
+        constexpr int kAhead = NB <= 4 ? 2 : 1;
+        norms_to_lds();
+        for (int S0 = wave; S0 < nS; S0 += kGateWaves * kAhead) {
+            XGroup xv[kAhead];
+            WGroup wv[2];
+            auto group_of = [&](int p) { return S0 + p * kGateWaves < nS ? S0 + p * kGateWaves : S0; };
+#pragma unroll
+            for (int p = 0; p < kAhead; ++p) load_x(group_of(p), xv[p]);
+            load_w(S0, wv[0]);
+#pragma unroll
+            for (int p = 0; p < kAhead; ++p) {
+                if (p + 1 < kAhead) load_w(group_of(p + 1), wv[(p + 1) % 2]);
+                if (S0 + p * kGateWaves < nS) multiply(xv[p], wv[p % 2]);  // uniform for the wave
+            }
+        }
+    }
+#pragma unroll
+    for (int rb = 0; rb < RB; ++rb) {
+        xs[rb] += __shfl_xor(xs[rb], 16);
+        xs[rb] += __shfl_xor(xs[rb], 32);
+        if (lane < 16) xsq_w[wave][16 * rb + lane] = xs[rb];
+    }
+    // accumulator v of lane 16 g + c: token 4 g + v of its row block, column c of its half block
+    // The partial tiles are added in wave order: by the lane that reads a logit when every wave has a tile of its own,
+    // else wave after wave into one tile.
+    auto each_value = [&](auto&& put) __attribute__((always_inline)) {
+#pragma unroll
+        for (int rb = 0; rb < RB; ++rb)
+#pragma unroll
+            for (int nb = 0; nb < NB; ++nb)
+#pragma unroll
+                for (int cb = 0; cb < 2; ++cb)
+#pragma unroll
+                    for (int v = 0; v < 4; ++v) put(16 * rb + 4 * g4 + v, 32 * nb + 16 * cb + c15, acc[rb][nb][cb][v]);
+    };
+    if (kParts == kGateWaves) {
+        each_value([&](int tok, int col, float v) { tile_at(wave, tok, col) = v; });
         __syncthreads();
     } else {
         for (int turn = 0; turn < kGateWaves; ++turn) {
-            if (wave == turn) {
-#pragma unroll
-                for (int nb = 0; nb < NB; ++nb)
-#pragma unroll
-                    for (int v = 0; v < 16; ++v) {
-                        float& at = tile_at(0, 8 * (v >> 2) + 4 * (lane >> 5) + (v & 3), 32 * nb + (lane & 31));
-                        at = turn == 0 ? acc[nb][v] : at + acc[nb][v];
-                    }
-            }
+            if (wave == turn)
+                each_value([&](int tok, int col, float v) {
+                    float& at = tile_at(0, tok, col);
+                    at = turn == 0 ? v : at + v;
+                });
             __syncthreads();
         }
     }
 
-    // ---- selection: wave w ranks tokens w, w + 8, ...
-    const int n_chain = ((nS + kGateWaves - 1) / kGateWaves) * 4;                               // MFMAs a wave chains per logit
+    // ---- selection
+    // largest column norm: every wave adds up the partial sums for itself
+    float wn2_f = 0.f;
+    for (int c = lane; c < EP; c += 64) {
+        float tot = 0.f;
+#pragma unroll
+        for (int g = 0; g < G; ++g) tot += colpart[g * EP + c];
+        wn2_f = fmaxf(wn2_f, tot);
+    }
+    wn2_f = __uint_as_float(wave_max_u32(__float_as_uint(wn2_f)));         // sums of squares: not negative, ordered like their bits
+    const int n_chain = ((nS + kGateWaves - 1) / kGateWaves) * 4;                               // 16-row steps a wave chains per logit
     const double gamma = 1.0625 * 5.9604644775390625e-8 * static_cast<double>(17 * n_chain + 8);
     constexpr int NE = (NB + 1) / 2;         // experts a lane holds: eg, eg + 64, ... (kNE at most)
     const int eg = lane;
     const int kk_sel = min(k + 1, E);
+    const double wn2 = static_cast<double>(wn2_f);
+    // logit of (token, column): the partial tiles added in wave order, ((w0 + w1) + w2) + ..., and the bias
+    auto logit = [&](int tt, int e) __attribute__((always_inline)) {
+        float sum = tile_at(0, tt, e);
+        if (kParts > 1) {
+#pragma unroll
+            for (int pw = 1; pw < kParts; ++pw) sum += tile_at(pw, tt, e);
+        }
+        return sum;
+    };
+    auto token_norm2 = [&](int tt) __attribute__((always_inline)) {
+        float v = xsq_w[0][tt];
+#pragma unroll
+        for (int wv = 1; wv < kGateWaves; ++wv) v += xsq_w[wv][tt];
+        return static_cast<double>(v);
+    };
+    // Sixteen lanes (one row of the cross-lane moves) per token, lane j of the row holds columns j, j + 16, ...: a wave ranks
+    // four tokens at once, a block 32.  The selection is a latency chain per rank (largest key
+    // of the row, then the lowest column that has it); one token per wave after the other, it took longer than the products.
+    for (int first = wave * 4; first < TOK; first += 4 * kGateWaves) {
+        constexpr int NL = EP / 16;
+        const int j0 = lane & 15, tt = first + (lane >> 4), t = t0 + tt;
+        const bool real = t < T;
+        const int tr = real ? t : T - 1;             // past the end: as the last token, nothing is written
+        float fv[NL];
+        unsigned key[NL];
+#pragma unroll
+        for (int i = 0; i < NL; ++i) {
+            const int c = j0 + 16 * i, cc = c < E ? c : 0;                 // columns past the end read column 0 and drop it
+            fv[i] = (logit(tt, cc) + (bias != nullptr && c < E ? bias[cc] : 0.f)) + 0.0f;   // a -0 becomes +0: equal logits must compare equal
+            key[i] = c < E ? order_key(fv[i]) : 0u;
+        }
+        double gap, vmax, reach_from = 0.0;
+        if (hash) {
+            unsigned set = 0u, least = 0x7f800000u, most = 0u;
+#pragma unroll
+            for (int i = 0; i < NL; ++i)
+                if (j0 + 16 * i < E) {
+                    const unsigned mag = __float_as_uint(fabsf(fv[i]));
+                    set |= fv[i] > 0.f ? 1u << (j0 + 16 * i) : 0u;
+                    least = min(least, mag);
+                    most = max(most, mag);
+                }
+            set |= dpp_from<0x128, 0xf>(0u, set);
+            set |= dpp_from<0x124, 0xf>(0u, set);
+            set |= dpp_from<0x122, 0xf>(0u, set);
+            set |= dpp_from<0x121, 0xf>(0u, set);
+            gap = static_cast<double>(__uint_as_float(row_min_u32(least)));
+            vmax = static_cast<double>(__uint_as_float(row_max_u32(most)));
+            if (real && j0 == 0) { idx[tr] = static_cast<int>(set); w[tr] = 1.f; }
+        } else {
+            double sv[kSel];
+            int se[kSel];
+            unsigned taken = 0;
+#pragma unroll
+            for (int r = 0; r < kSel; ++r) {
+                if (r < kk_sel) {
+                    unsigned bk = 0u, be = 0xffffffffu;
+#pragma unroll
+                    for (int i = 0; i < NL; ++i)
+                        if (!((taken >> i) & 1u) && key[i] > bk) { bk = key[i]; be = static_cast<unsigned>(j0 + 16 * i); }
+                    const unsigned top = row_max_u32(bk);
+                    const unsigned who = row_min_u32(bk == top ? be : 0xffffffffu);
+                    sv[r] = static_cast<double>(from_order_key(top));
+                    se[r] = static_cast<int>(who);
+                    if ((who & 15u) == static_cast<unsigned>(j0)) taken |= 1u << (who >> 4);
+                }
+            }
+            rank_gaps(sv, kk_sel, gap, vmax);
+#pragma unroll
+            for (int r = 0; r < kSel; ++r)
+                if (r + 1 == kk_sel) reach_from = sv[r];
+            float wj[kSel], denom = 0.f;
+#pragma unroll
+            for (int r = 0; r < kSel; ++r)
+                if (r < k) wj[r] = expf(static_cast<float>(sv[r] - sv[0]));
+            if (renorm) {
+#pragma unroll
+                for (int r = 0; r < kSel; ++r)
+                    if (r < k) denom += wj[r];
+            } else {
+                float part_sum = 0.f;
+#pragma unroll
+                for (int i = 0; i < NL; ++i)
+                    if (j0 + 16 * i < E) part_sum += expf(static_cast<float>(static_cast<double>(fv[i]) - sv[0]));
+                denom = row_sum_f32(part_sum);
+            }
+            if (real && j0 == 0) {
+#pragma unroll
+                for (int r = 0; r < kSel; ++r)
+                    if (r < k) {
+                        idx[static_cast<size_t>(tr) * k + r] = se[r];
+                        w[static_cast<size_t>(tr) * k + r] = wj[r] / denom;
+                    }
+            }
+        }
+        // Too close to call in fp32 (the answer is written above all the same, and again below).  Which columns can exact
+        // arithmetic still change it for?  Top-k: every logit within 2 delta of the (k+1)-th best, or above it (anything
+        // lower stays below all of those even with both errors against it).  Sign bits: every projection within 2 delta
+        // of zero.  Usually two or three columns; the others keep their fp32 values, which cannot reach the selected ones.
+        const double delta = gamma * sqrt(token_norm2(tt) * wn2) + 1.0625 * 5.9604644775390625e-8 * vmax;
+        if (real && j0 == 0 && gap <= 2.0 * delta) {
+            reach_sh[tt] = hash ? 2.0 * delta : reach_from - 2.0 * delta;
+            atomicOr(&close_sh, 1ull << tt);
+        }
+    }
     float bl[kNE];
 #pragma unroll
     for (int i = 0; i < kNE; ++i) bl[i] = i >= NE ? 0.f : (bias != nullptr && eg + 64 * i < E) ? bias[eg + 64 * i] : 0.f;
-    const double wn2 = static_cast<double>(wn2_sh);
-    for (int tt = wave; tt < TOK; tt += kGateWaves) {
-        const int t = t0 + tt;
-        if (t >= T) { if (lane == 0) flagged[tt] = 0; continue; }
-        // this lane's logits, fp32 (a -0 becomes +0: equal logits must compare equal)
-        float fv[NE];
-#pragma unroll
-        for (int i = 0; i < NE; ++i) {
-            const int ei = eg + 64 * i;
-            const int ec = ei < E ? ei : 0;                 // lanes without an expert read column 0 and drop it
-            float sum = tile_at(0, tt, ec);
-            if (kParts > 1) {
-#pragma unroll
-                for (int pw = 1; pw < kParts; ++pw) sum += tile_at(pw, tt, ec);
-            }
-            fv[i] = ei < E ? (sum + bl[i]) + 0.0f : 0.f;
-        }
-        double lv[kNE], ll[kNE];                 // (value, low part); entries from NE on belong to no expert and are never looked at
-#pragma unroll
-        for (int i = 0; i < kNE; ++i) { lv[i] = i < NE ? static_cast<double>(fv[i < NE ? i : 0]) : 0.0; ll[i] = 0.0; }
-        double sv[kSel];
-        int se[kSel];
-        int code = 0;
-        double gap, vmax;
-        if (hash) {
-            sign_bits(lv, ll, eg, true, E, code, gap, vmax);
-        } else {
-            rank_f32<NE>(fv, eg, true, E, kk_sel, sv, se);
-            rank_gaps(sv, kk_sel, gap, vmax);
-        }
-        float xn2f = xsq_w[0][tt];
-        for (int wv = 1; wv < kGateWaves; ++wv) xn2f += xsq_w[wv][tt];
-        const double xn2 = static_cast<double>(xn2f);
-        const double delta = gamma * sqrt(xn2 * wn2) + 1.0625 * 5.9604644775390625e-8 * vmax;
-        const bool close = gap <= 2.0 * delta;
-        if (!close) {
-            if (lane == 0) flagged[tt] = 0;
-            if (hash) {
-                if (lane == 0) { idx[t] = code; w[t] = 1.f; }
-            } else {
-                float wj[kSel];
-                float denom = 0.f;
-#pragma unroll
-                for (int r = 0; r < kSel; ++r)
-                    if (r < k) wj[r] = expf(static_cast<float>(sv[r] - sv[0]));
-                if (renorm) {
-#pragma unroll
-                    for (int r = 0; r < kSel; ++r)
-                        if (r < k) denom += wj[r];
-                } else {
-                    float part_sum = 0.f;
-#pragma unroll
-                    for (int i = 0; i < NE; ++i)
-                        if (eg + 64 * i < E) part_sum += expf(static_cast<float>(lv[i] - sv[0]));
-                    denom = wave_sum_f32(part_sum);
-                }
-                if (lane == 0) {
-#pragma unroll
-                    for (int r = 0; r < kSel; ++r)
-                        if (r < k) {
-                            idx[static_cast<size_t>(t) * k + r] = se[r];
-                            w[static_cast<size_t>(t) * k + r] = wj[r] / denom;
-                        }
-                }
-            }
-            continue;
-        }
-        // Too close to call in fp32.  Which columns can exact arithmetic still change the answer for?
-        // Top-k: every logit within 2 delta of the (k+1)-th best, or above it (anything lower stays below
-        // all of those even with both errors against it).  Sign bits: every projection within 2 delta of
-        // zero.  Usually two or three columns: each is one exact dot product by this wave; the other
-        // columns keep their fp32 values, which cannot reach the selected ones.
-        const double reach = hash ? 2.0 * delta : sv[kk_sel - 1] - 2.0 * delta;
-        unsigned long long in_reach[NE];
+    __syncthreads();
+
+    // ---- the tokens fp32 cannot decide, by the whole block: one of them in a block would otherwise keep a single wave busy for
+    // longer than all the rest of the kernel takes
+    auto uniform64 = [](unsigned long long v) {
+        const unsigned lo = static_cast<unsigned>(__builtin_amdgcn_readfirstlane(static_cast<int>(v)));
+        const unsigned hi = static_cast<unsigned>(__builtin_amdgcn_readfirstlane(static_cast<int>(v >> 32)));
+        return static_cast<unsigned long long>(hi) << 32 | lo;
+    };
+    unsigned long long todo = uniform64(close_sh);
+    // Up to kSets tokens at a time: all waves compute their share of the sums of every one, then wave i finishes token i.
+    constexpr int kSets = NB == 1 ? 4 : 8;           // sets of 16 sums per wave in the two arrays of re-evaluated logits
+    auto sums_at = [&](int n, int wv, int c) -> double& {
+        constexpr int kHalf = kSets / 2;
+        return n < kHalf ? resc[wv][16 * n + c] : resc_lo[wv][16 * (n - kHalf) + c];
+    };
+    // this lane's logits of token tt, fp32 (a -0 becomes +0: equal logits must compare equal), and which columns are in reach
+    auto look = [&](int tt, double (&lv)[kNE], double (&ll)[kNE], unsigned long long (&in_reach)[NE]) __attribute__((always_inline)) {
+        const double reach = reach_sh[tt];
         int count = 0;
 #pragma unroll
+        for (int i = 0; i < kNE; ++i) { lv[i] = 0.0; ll[i] = 0.0; }        // (value, low part); from NE on: no expert, never looked at
+#pragma unroll
         for (int i = 0; i < NE; ++i) {
-            in_reach[i] = __ballot(eg + 64 * i < E && (hash ? fabs(lv[i]) <= reach : lv[i] >= reach));
+            const int ei = eg + 64 * i, ec = ei < E ? ei : 0;              // lanes without an expert read column 0 and drop it
+            lv[i] = ei < E ? static_cast<double>((logit(tt, ec) + bl[i]) + 0.0f) : 0.0;
+            in_reach[i] = __ballot(ei < E && (hash ? fabs(lv[i]) <= reach : lv[i] >= reach));
             count += __popcll(in_reach[i]);
         }
-        if (lane == 0) flagged[tt] = count > kMaxCand ? 1 : 0;
-        if (count > kMaxCand) continue;                                  // all columns, by the whole block, below
-        // the columns in reach from exact products: in fp64 first, and once more in twice that precision if that
-        // still leaves the decision inside the rounding error (in practice: exact ties)
-        auto evaluate = [&](auto pair) __attribute__((always_inline)) {
+        return count;
+    };
+    while (todo != 0ull) {                           // the same in every wave
+        unsigned long long batch = 0ull;
+        for (int n = 0; n < kSets && todo != 0ull; ++n) {
+            const int tt = __ffsll(static_cast<long long>(todo)) - 1, t = t0 + tt;
+            todo &= todo - 1ull;
+            batch |= 1ull << tt;
+            double lv[kNE], ll[kNE];
+            unsigned long long in_reach[NE];
+            const int count = look(tt, lv, ll, in_reach);
+            if (count > kMaxCand) continue;
+            // The columns in reach from exact products in fp64, an eighth of the reduction per wave (at d_model 4096 one
+            // 8-row piece per lane), the waves' sums added in wave order by the wave that finishes the token.
+            for (int c0 = 0; c0 < count; c0 += 4) {
+                int col[4];
 #pragma unroll
-            for (int i = 0; i < NE; ++i) {
-                unsigned long long m = in_reach[i];
-                while (m != 0ull) {                                      // uniform for the wave
-                    const int l = __ffsll(static_cast<long long>(m)) - 1;
-                    m &= m - 1ull;
-                    double hi, lo;
-                    exact_column_dot<decltype(pair)::value>(x, pack, static_cast<size_t>(t), l + 64 * i, nS, d, lane, hi, lo);
-                    if (eg == l) {
+                for (int c = 0; c < 4; ++c) col[c] = nth_column<NE>(in_reach, min(c0 + c, count - 1));
+                double sum[4] = {0.0, 0.0, 0.0, 0.0};
+                for (int j0 = wave * 64; j0 < nS * 8; j0 += kGateWaves * 64) {
+                    const int j = min(j0 + lane, nS * 8 - 1);
+                    const bool in = j0 + lane < nS * 8;
+                    const int S = j >> 3, q = (j & 7) >> 1, h = j & 1;           // rows 64 S + 32 h + 8 q .. + 8
+                    const uint4 xq = reinterpret_cast<const uint4*>(x + static_cast<size_t>(t) * d)[S * 8 + h * 4 + q];
+                    const uint32_t xu[4] = {xq.x, xq.y, xq.z, xq.w};
+                    uint4 wq[4];
+#pragma unroll
+                    for (int c = 0; c < 4; ++c)
+                        wq[c] = pack[((static_cast<size_t>(col[c] >> 5) * nS + S) * 4 + q) * 64 + h * 32 + (col[c] & 31)];
+#pragma unroll
+                    for (int c = 0; c < 4; ++c) {
+                        const uint32_t wu[4] = {wq[c].x, wq[c].y, wq[c].z, wq[c].w};
+                        double part_sum = 0.0;
+#pragma unroll
+                        for (int i = 0; i < 4; ++i) {
+                            part_sum = fma(static_cast<double>(__uint_as_float(xu[i] << 16)), static_cast<double>(__uint_as_float(wu[i] << 16)), part_sum);
+                            part_sum = fma(static_cast<double>(__uint_as_float(xu[i] & 0xffff0000u)),
+                                           static_cast<double>(__uint_as_float(wu[i] & 0xffff0000u)), part_sum);
+                        }
+                        sum[c] += in ? part_sum : 0.0;
+                    }
+                }
+#pragma unroll
+                for (int off = 32; off >= 1; off >>= 1)
+#pragma unroll
+                    for (int c = 0; c < 4; ++c) sum[c] += __shfl_xor(sum[c], off);
+                if (lane == 0) {
+#pragma unroll
+                    for (int c = 0; c < 4; ++c)
+                        if (c0 + c < count) sums_at(n, wave, c0 + c) = sum[c];
+                }
+            }
+        }
+        __syncthreads();
+        if (wave < __popcll(batch)) {
+            unsigned long long mine = batch;
+            for (int skip = wave; skip > 0; --skip) mine &= mine - 1ull;
+            const int tt = __ffsll(static_cast<long long>(mine)) - 1, t = t0 + tt;
+            const double xn2 = token_norm2(tt);
+            double lv[kNE], ll[kNE];
+            unsigned long long in_reach[NE];
+            if (look(tt, lv, ll, in_reach) > kMaxCand) {
+                if (lane == 0) atomicOr(&many_sh, 1ull << tt);
+            } else {
+                int before_mine = 0;
+    #pragma unroll
+                for (int i = 0; i < NE; ++i) {
+                    if ((in_reach[i] >> lane) & 1ull) {
+                        const int c = before_mine + __popcll(in_reach[i] & ((1ull << lane) - 1ull));
+                        double hi = 0.0, lo = 0.0;
+                        for (int wv = 0; wv < kGateWaves; ++wv) hi += sums_at(wave, wv, c);
                         dd_add(hi, lo, static_cast<double>(bl[i]), 0.0);
                         dd_normalise(hi, lo);
                         lv[i] = hi;
-                        ll[i] = decltype(pair)::value ? lo : 0.0;
                     }
+                    before_mine += __popcll(in_reach[i]);
+                }
+                double sv[kSel];
+                int se[kSel];
+                int code = 0;
+                double gap, vmax;
+                auto decide = [&]() __attribute__((always_inline)) {
+                    if (hash) {
+                        sign_bits(lv, ll, eg, true, E, code, gap, vmax);
+                    } else {
+                        wave_topk(lv, ll, eg, true, E, kk_sel, sv, se);
+                        rank_gaps(sv, kk_sel, gap, vmax);
+                    }
+                };
+                decide();
+                // and once more in twice that precision if that still leaves the decision inside the rounding error (in
+                // practice: exact ties)
+                const double delta64 = 1.0625 * 1.1102230246251565e-16 * (static_cast<double>(d + 8) * sqrt(xn2 * wn2) + 2.0 * vmax);
+                if (gap <= 2.0 * delta64) {
+    #pragma unroll
+                    for (int i = 0; i < NE; ++i) {
+                        unsigned long long m = in_reach[i];
+                        while (m != 0ull) {                                    // uniform for the wave
+                            const int l = __ffsll(static_cast<long long>(m)) - 1;
+                            m &= m - 1ull;
+                            double hi, lo;
+                            exact_column_dot(x, pack, static_cast<size_t>(t), l + 64 * i, nS, d, lane, hi, lo);
+                            if (eg == l) {
+                                dd_add(hi, lo, static_cast<double>(bl[i]), 0.0);
+                                dd_normalise(hi, lo);
+                                lv[i] = hi;
+                                ll[i] = lo;
+                            }
+                        }
+                    }
+                    decide();
+                }
+                if (hash) {
+                    if (lane == 0) { idx[t] = code; w[t] = 1.f; }
+                } else {
+                    emit_token(lv, sv, se, eg, true, E, k, renorm, lane, idx + static_cast<size_t>(t) * k, w + static_cast<size_t>(t) * k);
                 }
             }
-            if (hash) {
-                sign_bits(lv, ll, eg, true, E, code, gap, vmax);
-            } else {
-                wave_topk(lv, ll, eg, true, E, kk_sel, sv, se);
-                rank_gaps(sv, kk_sel, gap, vmax);
-            }
-        };
-        evaluate(std::false_type{});
-        const double delta64 = 1.0625 * 1.1102230246251565e-16 * (static_cast<double>(d + 8) * sqrt(xn2 * wn2) + 2.0 * vmax);
-        if (gap <= 2.0 * delta64) evaluate(std::true_type{});
-        if (hash) {
-            if (lane == 0) { idx[t] = code; w[t] = 1.f; }
-        } else {
-            emit_token(lv, sv, se, eg, true, E, k, renorm, lane, idx + static_cast<size_t>(t) * k, w + static_cast<size_t>(t) * k);
         }
+        __syncthreads();
     }
-    __syncthreads();
-
-    // ---- tokens with more columns in reach than that: all columns in fp64, by the whole block, from the
-    // same packed fragments and with the same split as the MFMA pass: wave w takes the groups
-    // S = w, w+8, ..., lane (c, h) the 32 rows 64 S + 32 h .. of column c of every expert block; the two
-    // halves are added by a lane exchange, the waves in wave order.
-    unsigned long long todo = __ballot(lane < TOK && flagged[lane & (TOK - 1)] != 0);   // the same in every wave
-    while (todo != 0ull) {
-        const int tt = __ffsll(static_cast<long long>(todo)) - 1;
-        todo &= todo - 1ull;
-        const int t = t0 + tt;
+    unsigned long long many = uniform64(many_sh);
+    while (many != 0ull) {                           // the same in every wave
+        const int tt = __ffsll(static_cast<long long>(many)) - 1, t = t0 + tt;
+        many &= many - 1ull;
+        // More than kMaxCand columns in reach: all columns in fp64 pairs, from the same packed fragments and with the same split as
+        // the MFMA pass: wave w takes the groups S = w, w+8, ..., lane (c, h) the 32 rows 64 S + 32 h .. of column c of
+        // every expert block; the two halves are added by a lane exchange, the waves in wave order.
         const uint4* xr = reinterpret_cast<const uint4*>(x + static_cast<size_t>(t) * d + 32 * (lane >> 5));
         double a64[NB], l64[NB];
 #pragma unroll
@@ -878,27 +1098,17 @@ int launch_route(const moe_cfg& c, const void* x, const void* Wg, const float* b
         if (int rc = device_info(&dev, &info)) return rc;
         const int n_cu = info->compute_units;
         // as many tokens per block as still give every compute unit a block
-        const int tok = (c.T + 31) / 32 >= n_cu ? 32 : (c.T + 15) / 16 >= n_cu ? 16 : 8;
+        const int tok = NB == 1 && (c.T + 63) / 64 >= n_cu ? 64 : (c.T + 31) / 32 >= n_cu ? 32 : (c.T + 15) / 16 >= n_cu ? 16 : 8;
         dim3 grid((c.T + tok - 1) / tok), block(kGateWaves * 64);
 #define MOE_ROUTE_LAUNCH(N, TK)                                                                                       \
-    {                                                                                                                 \
-        /* the tiles of more than 32 experts exceed the default LDS limit of a launch: raised once per device and   \
-           kernel (a bit per device; two threads that both find it clear both raise it, which is harmless) */       \
-        static std::atomic<uint64_t> raised{0};                                                                       \
-        const uint64_t bit = uint64_t(1) << (dev & 63);                                                               \
-        if (gate_tile_bytes<N>() > 48 * 1024 && (dev >= 64 || !(raised.load(std::memory_order_acquire) & bit))) {     \
-            MOE_HIP_CHECK(hipFuncSetAttribute(reinterpret_cast<const void*>(&route_mfma_kernel<N, TK>),               \
-                                              hipFuncAttributeMaxDynamicSharedMemorySize,                             \
-                                              static_cast<int>(gate_tile_bytes<N>())));                               \
-            if (dev < 64) raised.fetch_or(bit, std::memory_order_release);                                            \
-        }                                                                                                             \
-        hipLaunchKernelGGL((route_mfma_kernel<N, TK>), grid, block, gate_tile_bytes<N>(), s,                          \
-                           static_cast<const uint16_t*>(x), pack, part, bias, idx, w, c.T, c.d, cols, c.k, c.renorm,  \
-                           hash);                                                                                     \
-    }
+    hipLaunchKernelGGL((route_mfma_kernel<N, TK>), grid, block, 0, s, static_cast<const uint16_t*>(x), pack, part, bias, idx,  \
+                       w, c.T, c.d, cols, c.k, c.renorm, hash)
 #define MOE_ROUTE_CASE(N)                                                                                             \
     case N:                                                                                                           \
-        if (tok == 32) MOE_ROUTE_LAUNCH(N, 32) else if (tok == 16) MOE_ROUTE_LAUNCH(N, 16) else MOE_ROUTE_LAUNCH(N, 8) \
+        if (tok == 64) MOE_ROUTE_LAUNCH(1, 64);                                                                       \
+        else if (tok == 32) MOE_ROUTE_LAUNCH(N, 32);                                                                  \
+        else if (tok == 16) MOE_ROUTE_LAUNCH(N, 16);                                                                  \
+        else MOE_ROUTE_LAUNCH(N, 8);                                                                                  \
         break;
         switch (NB) {
             MOE_ROUTE_CASE(1) MOE_ROUTE_CASE(2) MOE_ROUTE_CASE(3) MOE_ROUTE_CASE(4)

@@ -91,3 +91,25 @@ def test_few_rows_streamed_equals_resident(T, k):
         torch.cuda.synchronize()
         assert torch.equal(L.y, want)
     ctx.close()
+
+
+@pytest.mark.parametrize("T", [16320, 16321, 16449])      # 32 tokens per block, 64 with one in the last block, and a few more
+@pytest.mark.parametrize("d,E,k,bias", [(64, 7, 2, True), (192, 45, 3, False)])
+def test_gate_block_sizes(T, d, E, k, bias):
+    x, Wg, b = make_inputs(T + E, T, d, E, "bf16", bias=bias)
+    idx, w = gpu_route(M.MoeCfg.make(T, d, 64, E, k, "bf16"), x, Wg, b, "bf16")
+    r = O.route(x, Wg, k, b, 1)
+    assert np.array_equal(idx, r.idx)
+    assert rel_l2(w, r.w) <= 1e-5
+
+
+@pytest.mark.parametrize("T,E,k,renorm", [(70, 40, 3, 0), (40, 20, 1, 1)])
+def test_gate_many_close_tokens_in_one_block(T, E, k, renorm):
+    """Equal columns, and more of them than are evaluated one by one: every token of a block goes through the exact branches."""
+    x, Wg, _ = make_inputs(T, T, 256, E, "bf16")
+    Wg[:, 1::2] = Wg[:, 0::2]                       # pairs tie exactly
+    Wg[:, E // 2:] = Wg[:, :1]                      # and half of the columns are one and the same
+    idx, w = gpu_route(M.MoeCfg.make(T, 256, 64, E, k, "bf16", renorm), x, Wg, None, "bf16")
+    r = O.route(x, Wg, k, None, renorm)
+    assert np.array_equal(idx, r.idx)
+    assert rel_l2(w, r.w) <= 1e-5
