@@ -6,8 +6,6 @@
 namespace moe {
 namespace {
 
-constexpr int kMaxK = 8;
-
 __device__ inline float bf16_lo(uint32_t u) { return __uint_as_float(u << 16); }
 __device__ inline float bf16_hi(uint32_t u) { return __uint_as_float(u & 0xffff0000u); }
 __device__ inline uint32_t pack_bf16(float lo, float hi) {
@@ -16,47 +14,68 @@ __device__ inline uint32_t pack_bf16(float lo, float hi) {
     return a | (static_cast<uint32_t>(b) << 16);
 }
 
-template <bool BF16>
+// Bound by HBM (every row is read once, hence non-temporally); a thread's pieces of all K rows are requested before the
+// first is used, two positions of the row at a time.
+template <bool BF16, int K>
 __global__ __launch_bounds__(256) void combine_kernel(const uint4* __restrict__ Yp, const int32_t* __restrict__ inv,
-                                                      const float* __restrict__ w, uint4* __restrict__ y, int k,
+                                                      const float* __restrict__ w, uint4* __restrict__ y,
                                                       int vec_per_row, int n_rows) {
+    typedef unsigned int u4v __attribute__((ext_vector_type(4)));
+    constexpr int U = K <= 4 ? 2 : 1;
     const int t = blockIdx.x;
-    int rows[kMaxK];
-    float wt[kMaxK];
+    const u4v* rows[K];
+    float wt[K];
 #pragma unroll
-    for (int j = 0; j < kMaxK; ++j) {
-        rows[j] = j < k ? min(max(inv[static_cast<size_t>(t) * k + j], 0), n_rows - 1) : 0;   // never outside Yp
-        wt[j] = j < k ? w[static_cast<size_t>(t) * k + j] : 0.f;
+    for (int j = 0; j < K; ++j) {
+        const int row = min(max(inv[static_cast<size_t>(t) * K + j], 0), n_rows - 1);   // never outside Yp
+        rows[j] = reinterpret_cast<const u4v*>(Yp) + static_cast<size_t>(row) * vec_per_row;
+        wt[j] = w[static_cast<size_t>(t) * K + j];
     }
-    for (int v = threadIdx.x; v < vec_per_row; v += 256) {
-        float acc[8];
+    for (int v0 = threadIdx.x; v0 < vec_per_row; v0 += 256 * U) {
+        u4v u[U][K];
 #pragma unroll
-        for (int i = 0; i < 8; ++i) acc[i] = 0.f;
+        for (int i = 0; i < U; ++i) {
+            const int v = min(v0 + 256 * i, vec_per_row - 1);
 #pragma unroll
-        for (int j = 0; j < kMaxK; ++j) {
-            if (j < k) {
-                const uint4 u = Yp[static_cast<size_t>(rows[j]) * vec_per_row + v];
-                if (BF16) {
-                    acc[0] = fmaf(wt[j], bf16_lo(u.x), acc[0]); acc[1] = fmaf(wt[j], bf16_hi(u.x), acc[1]);
-                    acc[2] = fmaf(wt[j], bf16_lo(u.y), acc[2]); acc[3] = fmaf(wt[j], bf16_hi(u.y), acc[3]);
-                    acc[4] = fmaf(wt[j], bf16_lo(u.z), acc[4]); acc[5] = fmaf(wt[j], bf16_hi(u.z), acc[5]);
-                    acc[6] = fmaf(wt[j], bf16_lo(u.w), acc[6]); acc[7] = fmaf(wt[j], bf16_hi(u.w), acc[7]);
-                } else {
-                    acc[0] = fmaf(wt[j], __uint_as_float(u.x), acc[0]); acc[1] = fmaf(wt[j], __uint_as_float(u.y), acc[1]);
-                    acc[2] = fmaf(wt[j], __uint_as_float(u.z), acc[2]); acc[3] = fmaf(wt[j], __uint_as_float(u.w), acc[3]);
+            for (int j = 0; j < K; ++j) u[i][j] = __builtin_nontemporal_load(rows[j] + v);
+        }
+#pragma unroll
+        for (int i = 0; i < U; ++i) {
+            float acc[8];
+#pragma unroll
+            for (int c = 0; c < 8; ++c) acc[c] = 0.f;
+#pragma unroll
+            for (int j = 0; j < K; ++j)
+#pragma unroll
+                for (int c = 0; c < 4; ++c) {
+                    if (BF16) {
+                        acc[2 * c] = fmaf(wt[j], bf16_lo(u[i][j][c]), acc[2 * c]);
+                        acc[2 * c + 1] = fmaf(wt[j], bf16_hi(u[i][j][c]), acc[2 * c + 1]);
+                    } else {
+                        acc[c] = fmaf(wt[j], __uint_as_float(u[i][j][c]), acc[c]);
+                    }
                 }
+            uint4 o;
+            if (BF16) {
+                o.x = pack_bf16(acc[0], acc[1]); o.y = pack_bf16(acc[2], acc[3]);
+                o.z = pack_bf16(acc[4], acc[5]); o.w = pack_bf16(acc[6], acc[7]);
+            } else {
+                o.x = __float_as_uint(acc[0]); o.y = __float_as_uint(acc[1]);
+                o.z = __float_as_uint(acc[2]); o.w = __float_as_uint(acc[3]);
             }
+            if (v0 + 256 * i < vec_per_row) y[static_cast<size_t>(t) * vec_per_row + v0 + 256 * i] = o;
         }
-        uint4 o;
-        if (BF16) {
-            o.x = pack_bf16(acc[0], acc[1]); o.y = pack_bf16(acc[2], acc[3]);
-            o.z = pack_bf16(acc[4], acc[5]); o.w = pack_bf16(acc[6], acc[7]);
-        } else {
-            o.x = __float_as_uint(acc[0]); o.y = __float_as_uint(acc[1]);
-            o.z = __float_as_uint(acc[2]); o.w = __float_as_uint(acc[3]);
-        }
-        y[static_cast<size_t>(t) * vec_per_row + v] = o;
     }
+}
+
+template <bool BF16>
+void launch_for_k(const moe_cfg& c, const uint4* Yp, const int32_t* inv, const float* w, uint4* y, int vec_per_row, hipStream_t s) {
+#define MOE_COMBINE(K) \
+    case K: hipLaunchKernelGGL((combine_kernel<BF16, K>), dim3(c.T), dim3(256), 0, s, Yp, inv, w, y, vec_per_row, c.T * c.k); break;
+    switch (c.k) {
+        MOE_COMBINE(1) MOE_COMBINE(2) MOE_COMBINE(3) MOE_COMBINE(4) MOE_COMBINE(5) MOE_COMBINE(6) MOE_COMBINE(7) MOE_COMBINE(8)
+    }
+#undef MOE_COMBINE
 }
 
 }  // namespace
@@ -65,11 +84,9 @@ int launch_combine(const moe_cfg& c, const void* Yp, const int32_t* inv, const f
     if (c.T == 0) return MOE_OK;
     const int vec_per_row = static_cast<int>(c.d * elem_size(c) / 16);
     if (c.dtype == MOE_BF16)
-        hipLaunchKernelGGL(combine_kernel<true>, dim3(c.T), dim3(256), 0, s, static_cast<const uint4*>(Yp), inv, w,
-                           static_cast<uint4*>(y), c.k, vec_per_row, c.T * c.k);
+        launch_for_k<true>(c, static_cast<const uint4*>(Yp), inv, w, static_cast<uint4*>(y), vec_per_row, s);
     else
-        hipLaunchKernelGGL(combine_kernel<false>, dim3(c.T), dim3(256), 0, s, static_cast<const uint4*>(Yp), inv, w,
-                           static_cast<uint4*>(y), c.k, vec_per_row, c.T * c.k);
+        launch_for_k<false>(c, static_cast<const uint4*>(Yp), inv, w, static_cast<uint4*>(y), vec_per_row, s);
     MOE_LAUNCH_CHECK("combine_kernel");
     return MOE_OK;
 }

@@ -1,6 +1,6 @@
 // Batching of assignments by expert (CPM-2 Section 6.2: tokens are routed and batched to their
 // experts before computation): a deterministic, stable counting sort of a = t*k + j by expert id,
-// followed by the row gather Xp[row] = x[perm[row] / k].
+// followed by the row copy Xp[row] = x[perm[row] / k].
 //
 //   1. chunk_hist_kernel : LDS histogram of each chunk of kPermChunk assignments
 //   2. scan_kernel       : counts, offsets and, per chunk, the first row of every expert
@@ -220,19 +220,27 @@ __global__ __launch_bounds__(kSmallWaves * 64) void permute_small_kernel(const i
     }
 }
 
-// One block per destination row; 16-byte vectors, coalesced on both sides.
-__global__ __launch_bounds__(256) void gather_rows_kernel(const uint4* __restrict__ x, const int32_t* __restrict__ perm,
+// One block per token: its row is read once and written to the batched rows of its k assignments (16-byte vectors, whole
+// rows, coalesced on both sides).  Bound by HBM; a thread requests four pieces before it stores the first.
+__global__ __launch_bounds__(256) void gather_rows_kernel(const uint4* __restrict__ x, const int32_t* __restrict__ inv,
                                                           int k, int vec_per_row, uint4* __restrict__ Xp) {
-    const int row = blockIdx.x;
-    const int t = perm[row] / k;
-    const uint4* src = x + static_cast<size_t>(t) * vec_per_row;
-    uint4* dst = Xp + static_cast<size_t>(row) * vec_per_row;
     // stored non-temporal: the rows are next read by the expert kernels, which want the L2 for themselves
     // (left there as dirty lines, the batch costs the up-projection 2.5 % at 128 tokens per expert)
     typedef unsigned int u4v __attribute__((ext_vector_type(4)));
-    for (int v = threadIdx.x; v < vec_per_row; v += 256) {
-        const uint4 piece = src[v];
-        __builtin_nontemporal_store(u4v{piece.x, piece.y, piece.z, piece.w}, reinterpret_cast<u4v*>(dst + v));
+    constexpr int U = 4;
+    const size_t t = blockIdx.x;
+    const u4v* src = reinterpret_cast<const u4v*>(x) + t * vec_per_row;
+    u4v* dst = reinterpret_cast<u4v*>(Xp);
+    for (int v0 = threadIdx.x; v0 < vec_per_row; v0 += 256 * U) {
+        u4v piece[U];
+#pragma unroll
+        for (int i = 0; i < U; ++i) piece[i] = __builtin_nontemporal_load(src + min(v0 + 256 * i, vec_per_row - 1));
+        for (int j = 0; j < k; ++j) {
+            const size_t row = inv[t * k + j];
+#pragma unroll
+            for (int i = 0; i < U; ++i)
+                if (v0 + 256 * i < vec_per_row) __builtin_nontemporal_store(piece[i], dst + row * vec_per_row + v0 + 256 * i);
+        }
     }
 }
 
@@ -262,7 +270,7 @@ int launch_permute(const moe_cfg& c, const void* x, const int32_t* idx, int32_t*
     if (chunks > 0) {
         if (Xp != nullptr) {
             const int vec_per_row = static_cast<int>(c.d * elem_size(c) / 16);
-            hipLaunchKernelGGL(gather_rows_kernel, dim3(A), dim3(256), 0, s, static_cast<const uint4*>(x), perm, c.k,
+            hipLaunchKernelGGL(gather_rows_kernel, dim3(c.T), dim3(256), 0, s, static_cast<const uint4*>(x), inv, c.k,
                                vec_per_row, static_cast<uint4*>(Xp));
             MOE_LAUNCH_CHECK("gather_rows_kernel");
         }
