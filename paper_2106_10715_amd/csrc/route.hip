@@ -385,9 +385,8 @@ __global__ __launch_bounds__(kWaves * 64) void route_kernel(const XT* __restrict
 //
 // logits tile = 32 tokens (64, 16) x E on 16x16x32 bf16 MFMAs.  The eight waves of a block split the reduction
 // dimension (wave w takes the 64-element groups S = w, w+8, ...), the partial tiles are added in wave
-// order through LDS.  W_g is first rewritten (gate_prep_kernel) into MFMA fragment order so that its
-// fragments are plain 1 KiB coalesced reads, and so that a lane's four fragments of a group use 64
-// contiguous bytes of its token row: fragment (nb, S, q), lane l, element j holds
+// order through LDS.  W_g is first rewritten (gate_prep_kernel) into fragments whose 16-byte pieces are
+// operand pieces: fragment (nb, S, q), slot l, element j holds
 //     W_g[64 S + 32 (l / 32) + 8 q + j, 32 nb + l % 32]            (0 beyond E).
 //
 // Error bound of an MFMA logit (measured behaviour of the instruction: the addends -- accumulator and products -- are
