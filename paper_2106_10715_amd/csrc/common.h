@@ -96,13 +96,13 @@ int launch_expert_ffn(const moe_cfg& c, const void* Xp, const int32_t* offsets, 
                       hipStream_t s, hipEvent_t between = nullptr, hipEvent_t before_up = nullptr,
                       const int32_t* row_map = nullptr, bool plan_ready = false, const int32_t* gather = nullptr);
 // gather: Xp is then the token array x[T, d] itself and batched row r is its row gather[r] / k (gather = the
-// perm written by the batching step), so the batched copy of the activations need not exist; bf16 row tiles are then
-// ffn_tile_rows(true) rows high instead of ffn_tile_rows(false), and a work list written elsewhere (plan_ready) must
-// have been cut to that height.
+// perm written by the batching step), so the batched copy of the activations need not exist.  A bf16 work list written elsewhere (plan_ready) must
+// have been cut to tiles of ffn_tile_rows(c, gather != NULL, n_cu) rows.
 int launch_expert_ffn_f32(const moe_cfg& c, const float* Xp, const int32_t* offsets, int e_first, int e_count, const float* W,
                           size_t expert_stride_elems, long max_rows, float* H, float* Yp, hipStream_t s, hipEvent_t between,
                           const int32_t* row_map, const int32_t* gather);
-int ffn_tile_rows(bool gather);
+// Rows of a bf16 row tile of the up-projection (and of the down-projection, unless ffn_down_tile_rows says less).
+int ffn_tile_rows(const moe_cfg& c, bool gather, int n_cu);
 // Height of the down-projection's row tiles for a launch over e_count experts with at most max_rows rows in all (the two
 // kernels have a tile list each); n_cu: compute units of the device.
 int ffn_down_tile_rows(const moe_cfg& c, int e_count, long max_rows, int tile_m_up, int n_cu);

@@ -138,15 +138,13 @@ __global__ __launch_bounds__(256) void ffn_plan_kernel(const int32_t* __restrict
     }
 }
 
-template <bool GATED, int CB>
-__global__ __launch_bounds__(kFewWaves * 64, 3) void ffn_few_kernel(const uint16_t* __restrict__ A, const int32_t* __restrict__ plan,
-                                                                  int e_first, const char* __restrict__ W, size_t expert_stride_bytes,
-                                                                  size_t block_offset_bytes, uint16_t* __restrict__ C, int K, int N,
-                                                                  int act, const int32_t* __restrict__ row_map,
-                                                                  const int32_t* __restrict__ gather, int gather_k, int h_rows) {
-    __shared__ __align__(16) float lds[kFewWaves * (GATED ? 4 : CB) * 16 * 20];
-    ffn_few_block<GATED, CB>(lds, A, plan, e_first, W, expert_stride_bytes, block_offset_bytes, C, K, N, row_map, gather, gather_k,
-                                 h_rows, [act](float z) { return act_fn_bf16(z, act); });
+template <bool GATED, bool SMALL>
+__global__ __launch_bounds__(64, few_waves_per_simd(SMALL)) void ffn_few_kernel(
+    const uint16_t* A, const int32_t* __restrict__ plan, int e_first, const char* W, size_t expert_stride_bytes, size_t block_offset_bytes,
+    uint16_t* __restrict__ C, int K, int N, int act, const int32_t* __restrict__ row_map, const int32_t* __restrict__ gather,
+    int gather_k, int h_rows) {
+    ffn_few_block<GATED, SMALL>(A, plan, e_first, W, expert_stride_bytes, block_offset_bytes, C, K, N, row_map, gather, gather_k, h_rows,
+                                [act](float z) { return act_fn_bf16(z, act); });
 }
 
 #else   // FFN_PART 1..4
@@ -487,8 +485,7 @@ __device__ inline const void* wave_stream(const ItemQueue& Q, int e, int block_y
     const uintptr_t wbi = reinterpret_cast<uintptr_t>(wb);
     const uint32_t wb_lo = static_cast<uint32_t>(__builtin_amdgcn_readfirstlane(static_cast<int>(static_cast<uint32_t>(wbi))));
     const uint32_t wb_hi = static_cast<uint32_t>(__builtin_amdgcn_readfirstlane(static_cast<int>(static_cast<uint32_t>(wbi >> 32))));
-    const unsigned col_chunk = static_cast<unsigned>(block_y) >> ((GATED || NF == 2) ? 3 : 4);   // same for both unit widths
-    key = static_cast<unsigned>(e) * 37u + col_chunk;
+    key = sweep_key(e, static_cast<unsigned>(block_y) >> ((GATED || NF == 2) ? 3 : 4));   // 128 or 256 columns per group
     return reinterpret_cast<const void*>((static_cast<uintptr_t>(wb_hi) << 32) | static_cast<uintptr_t>(wb_lo));
 }
 
@@ -921,8 +918,25 @@ void launch_ffn_down(const FfnLaunch& a, hipStream_t s) { launch_mfma<false, 2, 
 void launch_ffn_down_narrow(const FfnLaunch& a, hipStream_t s) { launch_mfma<false, 1, false>(a, s); }
 #else
 constexpr int kMinTileM = 64;           // lowest row tile a launch is ever cut into
+static_assert(kFewTileM >= kMinTileM, "the work list has room for the tiles");
 size_t ffn_plan_tiles(const moe_cfg& c) { return static_cast<size_t>(c.T) * c.k / kMinTileM + c.E; }   // room for the lowest tiles
-int ffn_tile_rows(bool gather) { return gather ? kGatherTileM : kTileM; }
+// Whether a layer's experts run on the kernels for few rows (ffn_few.h; the same bits either way).  The large kernel needs work
+// items (an expert's tile x 256 columns in the down-projection) for the compute units; the fewer it has, the more rows per
+// expert the other one may be given.
+// Large kernel / few rows, layer us, d 4096 f 10240: 32 experts 40 rows in all 904 / 871, 64 rows 1029 / 1032, 128 rows
+// 1195 / 1196, 256 rows 1197 / 1216; 64 experts 128 rows 1979 / 1962; 16 experts 64 rows 636 / 634, 128 rows 640 / 641,
+// 192 rows 621 / 633; 8 experts 64 rows 334 / 320, 128 rows 337 / 334, 192 rows 341 / 364; 4 experts 128 rows 242 / 238,
+// 192 rows 243 / 295.  Smaller layers: d 1024 f 2048 8 experts 256 rows 54 / 47, 512 rows 63 / 78; d 512 f 1024 33 experts
+// 1056 rows 55 / 54, 1500 rows 54 / 58; d 768 f 3072 33 experts 256 rows 119 / 113, 500 rows 121 / 120, 1056 rows 133 / 145;
+// d 2048 f 4096 16 experts 128 rows 155 / 143, 400 rows 162 / 181.  All rows on one of the experts (the FFN alone): 64 rows of
+// 32 experts 180 / 110, 128 rows of 16 185 / 150, 128 rows of 64 212 / 149; d 1024 f 2048 256 rows of 8 64 / 27; d 512 f 1024
+// 1056 rows of 33 38 / 31.
+bool few_rows(const moe_cfg& c, int n_cu) {
+    const long rows = static_cast<long>(c.T) * c.k, items = static_cast<long>(c.E) * ((c.d / 64 + 3) / 4);
+    return rows <= (3 * items < n_cu ? 32L : items <= n_cu ? 8L : 2L) * c.E;
+}
+
+int ffn_tile_rows(const moe_cfg& c, bool gather, int n_cu) { return few_rows(c, n_cu) ? kFewTileM : gather ? kGatherTileM : kTileM; }
 size_t ffn_plan_bytes(const moe_cfg& c) { return (kPlanHeader + 2 * 4 * ffn_plan_tiles(c)) * sizeof(int32_t); }
 
 // Height of the down-projection's row tiles.  Its work items are (row tile x 256 output columns): with few experts of
@@ -939,18 +953,6 @@ int ffn_down_tile_rows(const moe_cfg& c, int e_count, long max_rows, int tile_m_
     long tm = ((mean_rows * 5 / 4 + per_expert - 1) / per_expert + 31) / 32 * 32;
     tm = tm < kMinTileM ? kMinTileM : tm;
     return tm < tile_m_up ? static_cast<int>(tm) : tile_m_up;
-}
-
-// Whether a layer's experts run on the kernels for few rows (ffn_few.h), by the layer's own sizes, so that a launch over one
-// expert sums like a launch over all.  The large kernel needs work items (an expert's tile x 256 columns in the
-// down-projection) for the compute units; the fewer it has, the more rows per expert the other one may be given.
-// Large kernel / few rows, layer us, d 4096 f 10240: 32 experts 40 rows in all 900 / 849, 64 rows 1084 / 1074, 128 rows
-// 1239 / 1245; 64 experts 128 rows 2073 / 2046; 16 experts 64 rows 599 / 588, 128 rows 636 / 634, 256 rows 641 / 659;
-// 8 experts 64 rows 353 / 332, 128 rows 345 / 341, 192 rows 347 / 359.  Smaller layers: d 1024 f 2048 8 experts 256 rows
-// 55 / 47, 512 rows 60 / 67; d 512 f 1024 33 experts 1000 rows 61 / 56; d 2048 f 4096 16 experts 400 rows 157 / 173.
-bool few_rows(const moe_cfg& c, int n_cu) {
-    const long rows = static_cast<long>(c.T) * c.k, items = static_cast<long>(c.E) * ((c.d / 64 + 3) / 4);
-    return rows <= (2 * items < n_cu ? 32L : items <= n_cu ? 8L : 2L) * c.E;
 }
 
 int launch_pack(const moe_cfg& c, const void* Win, const void* Wgate, const void* Wout, void* packed, hipStream_t s) {
@@ -988,7 +990,7 @@ int launch_expert_ffn(const moe_cfg& c, const void* Xp, const int32_t* offsets, 
         const DeviceInfo* info = nullptr;
         if (int rc = device_info(&dev, &info)) return rc;
         const int n_cu = info->compute_units;
-        const int tile_m = ffn_tile_rows(gather != nullptr);
+        const int tile_m = ffn_tile_rows(c, gather != nullptr, n_cu);
         const int tile_m_down = ffn_down_tile_rows(c, e_count, max_rows, tile_m, n_cu);
         const long slots = max_rows / tile_m + e_count;                // upper bound of the number of row tiles
         const long slots_down = max_rows / tile_m_down + e_count;
@@ -1030,24 +1032,21 @@ int launch_expert_ffn(const moe_cfg& c, const void* Xp, const int32_t* offsets, 
         const size_t down_off = 2 * df * 2;
         if (few_rows(c, n_cu)) {
             const unsigned n_tiles = static_cast<unsigned>(max_rows < slots ? max_rows : slots);
-            const dim3 few_block(kFewWaves * 64);
-#define MOE_FFN_FEW(CB)                                                                                               \
+#define MOE_FFN_FEW(SMALL)                                                                                            \
     {                                                                                                                 \
-        hipLaunchKernelGGL((ffn_few_kernel<true, 2>), dim3(c.f / 32, n_tiles), few_block, 0, s,                   \
+        hipLaunchKernelGGL((ffn_few_kernel<true, SMALL>), dim3(c.f / few_columns(true, SMALL), n_tiles), dim3(64), 0, s, \
                            static_cast<const uint16_t*>(Xp), plan, e_first, static_cast<const char*>(W),              \
                            expert_stride_bytes, size_t(0), static_cast<uint16_t*>(H), c.d, c.f, c.act,                \
                            static_cast<const int32_t*>(nullptr), gather, c.k, c.T * c.k);                             \
         MOE_LAUNCH_CHECK("ffn_few_kernel<up>");                                                                       \
         if (between != nullptr) MOE_HIP_CHECK(hipEventRecord(between, s));                                            \
-        hipLaunchKernelGGL((ffn_few_kernel<false, CB>), dim3(c.d / (16 * CB), n_tiles), few_block, 0, s,  \
+        hipLaunchKernelGGL((ffn_few_kernel<false, SMALL>), dim3(c.d / few_columns(false, SMALL), n_tiles), dim3(64), 0, s, \
                            static_cast<const uint16_t*>(H), plan, e_first, static_cast<const char*>(W),               \
                            expert_stride_bytes, down_off, static_cast<uint16_t*>(Yp), c.f, c.d, c.act, row_map,       \
                            static_cast<const int32_t*>(nullptr), 1, c.T * c.k);                                       \
         MOE_LAUNCH_CHECK("ffn_few_kernel<down>");                                                                     \
     }
-            // the down-projection in units of 16 columns (twice the blocks) for one 16-row block at most; with two, a unit
-            // would read twice the activations its weights have (32 tokens: 787 us in units of 16 columns, 767 of 32)
-            if (c.T * c.k <= 16) MOE_FFN_FEW(1) else MOE_FFN_FEW(2)
+            if (c.T * c.k <= 16) MOE_FFN_FEW(true) else MOE_FFN_FEW(false)
 #undef MOE_FFN_FEW
             return MOE_OK;
         }

@@ -14,6 +14,11 @@ namespace moe {
 
 constexpr int kPlanHeader = 32;
 
+// Where the sum of an output column over the reduction dimension starts (step key % steps of 64; it wraps around).  It depends
+// on the expert and on the column's chunk only (1024 columns of the up-projection, 2048 of the down-projection), never on the
+// launch or on the kernel that computes the column, so that every kernel gives the same bits.
+__device__ inline unsigned sweep_key(int e, unsigned chunk) { return static_cast<unsigned>(e) * 37u + chunk; }
+
 // By one block of at least 256 threads (all of them must call; the first 256 work): offsets[e_first ..
 // e_first + e_count] -> list `list` (0: up kernel, 1: down kernel) of the plan, in tiles of at most tile_m rows.
 // `scratch` is LDS of the caller.  e_count <= 256.  The call for list 0 also clears the work counters.

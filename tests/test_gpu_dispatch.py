@@ -3,10 +3,11 @@ import numpy as np
 import pytest
 import torch
 
+import moe_workloads as W
 import paper_2106_10715_amd as M
 from oracle import moe_oracle as O
 from paper_2106_10715_amd import harness as H
-from test_gpu_stages import TOL, gpu_route, make_inputs, rel_l2, run_ffn
+from test_gpu_stages import TOL, gpu_route, make_inputs, rel_l2, rounded, run_ffn
 
 pytestmark = pytest.mark.gpu
 
@@ -76,7 +77,6 @@ def test_few_rows_expert_ffn(counts, d, f):
 
 @pytest.mark.parametrize("T,k", [(1, 1), (7, 2), (30, 1), (21, 3)])
 def test_few_rows_streamed_equals_resident(T, k):
-    import moe_workloads as W
     wl = W.Workload("few", T=T, d=256, f=384, E=6, k=k, dtype="bf16", seed=50 + T)
     L = H.build_layer(wl, host_copy=True)
     M.moe_layer_forward(L.cfg, L.x, L.Wg, L.bias, L.packed, None, L.y, L.ws)
@@ -113,3 +113,33 @@ def test_gate_many_close_tokens_in_one_block(T, E, k, renorm):
     r = O.route(x, Wg, k, None, renorm)
     assert np.array_equal(idx, r.idx)
     assert rel_l2(w, r.w) <= 1e-5
+
+
+def expert_ffn_rows(counts, rows_of, d, f, dtype, act=0):
+    """Yp per expert of a call in which expert e gets the first counts[e] of the rows rows_of(e)."""
+    E, A = len(counts), sum(counts)
+    rng = np.random.default_rng(d + f)
+    ex = [tuple(rounded(rng.standard_normal(s) * 0.05, dtype) for s in ((d, f), (d, f), (f, d))) for _ in range(E)]
+    cfg = M.MoeCfg.make(A, d, f, E, 1, dtype, 1, act)
+    packed = H.pack_experts(W.Workload("t", A, d, f, E, 1, dtype, 0), cfg, experts=lambda e: ex[e])[0]
+    offsets = np.concatenate([[0], np.cumsum(counts)]).astype(np.int32)
+    Xp = H.to_device(np.concatenate([rows_of(e)[:n] for e, n in enumerate(counts)]), dtype)
+    Yp = torch.full_like(Xp, float("nan"))
+    ws = torch.empty(M.moe_workspace_bytes(cfg), dtype=torch.uint8, device="cuda")
+    M.moe_expert_ffn(cfg, Xp, torch.from_numpy(offsets).cuda(), packed, Yp, ws)
+    torch.cuda.synchronize()
+    return [Yp[offsets[e]:offsets[e + 1]] for e in range(E)]
+
+
+@pytest.mark.parametrize("few,many", [([1, 0, 3], [300, 40, 270]), ([12, 4, 0], [33, 70, 1]), ([20, 40, 3], [257, 100, 64]),
+                                      ([64, 0, 17], [200, 30, 130])])
+@pytest.mark.parametrize("d,f,dtype", [(64, 64, "bf16"), (192, 704, "bf16"), (2112, 1088, "bf16")])
+def test_rows_have_the_same_bits_in_every_batch(d, f, dtype, few, many):
+    """An expert's row gives the same bytes whatever else is in the batch, and so whichever kernel the batch size selects."""
+    def rows_of(e):
+        return rounded(np.random.default_rng(e).standard_normal((512, d)), dtype)
+    small, large = expert_ffn_rows(few, rows_of, d, f, dtype), expert_ffn_rows(many, rows_of, d, f, dtype)
+    for e in range(len(few)):
+        n = min(few[e], many[e])
+        assert torch.isfinite(small[e].float()).all() and torch.isfinite(large[e].float()).all()
+        assert torch.equal(small[e][:n], large[e][:n]), f"expert {e}"
