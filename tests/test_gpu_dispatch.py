@@ -143,3 +143,28 @@ def test_rows_have_the_same_bits_in_every_batch(d, f, dtype, few, many):
         n = min(few[e], many[e])
         assert torch.isfinite(small[e].float()).all() and torch.isfinite(large[e].float()).all()
         assert torch.equal(small[e][:n], large[e][:n]), f"expert {e}"
+
+
+@pytest.mark.parametrize("d,E,k,renorm", [(1024, 7, 2, 0), (4160, 32, 2, 1), (2048, 60, 3, 0), (1024, 100, 2, 0), (1024, 200, 2, 1)])
+def test_gate_does_not_depend_on_the_place_in_the_batch(d, E, k, renorm):
+    """A token's experts and weights have the same bits in every place of every batch (8, 16, 32 and 64 tokens per block)."""
+    g = torch.Generator(device="cuda")
+    g.manual_seed(d + E)
+    x = torch.empty((16450, d), dtype=torch.bfloat16, device="cuda").normal_(generator=g)
+    x[300:310] = x[5:15]                           # the same token in two places
+    Wg = torch.empty((d, E), dtype=torch.bfloat16, device="cuda").normal_(0.0, d ** -0.5, generator=g)
+
+    def route(x):
+        cfg = M.MoeCfg.make(x.shape[0], d, 64, E, k, "bf16", renorm)
+        idx = torch.full((x.shape[0], k), -7, dtype=torch.int32, device="cuda")
+        w = torch.full((x.shape[0], k), float("nan"), device="cuda")
+        M.moe_route(cfg, x, Wg, None, idx, w, torch.empty(M.moe_workspace_bytes(cfg), dtype=torch.uint8, device="cuda"))
+        torch.cuda.synchronize()
+        return idx, w
+    idx, w = route(x)
+    assert torch.equal(idx[300:310], idx[5:15]) and torch.equal(w[300:310], w[5:15])
+    for part in (x[:1], x[:260], x[:4100], x[:8200]):
+        i2, w2 = route(part)
+        assert torch.equal(i2, idx[:len(part)]) and torch.equal(w2, w[:len(part)]), f"{len(part)} tokens"
+    i2, w2 = route(torch.roll(x, 1037, dims=0))
+    assert torch.equal(i2, torch.roll(idx, 1037, dims=0)) and torch.equal(w2, torch.roll(w, 1037, dims=0))
