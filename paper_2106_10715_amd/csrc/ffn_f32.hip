@@ -71,12 +71,14 @@ __device__ inline bool find_tile(const int32_t* __restrict__ offsets, int e_firs
 // What bounds it: the matrix instruction (157 TFLOP/s) once there are enough blocks, the latency of the steps of one block
 // in short launches.  The kernel it replaces (vector multiply-adds, scalar loads, no load in flight across steps) ran at
 // 18 TFLOP/s.  Whole layer before -> after, with the rows read and written through the permutation: 64 tokens, d 256, f 512,
-// 4 experts 146 -> 23 us (up 50 -> 8, down 70 -> 8); 512 tokens x 2, d 1024, f 4096, 8 experts 1389 -> 337 us (up 412 -> 233,
-// down 892 -> 147).
+// 4 experts 144 -> 23 us; 512 tokens x 2, d 1024, f 4096, 8 experts 1386 -> 340 us.
 // Two shapes of a block (four waves, each with 32 x 32 output tiles, twice that when GATED):
 //   wide   64 rows x 64 columns, a wave per quarter, 32 reduction elements per step
-//   split  32 rows x 32 columns, all four waves on the same tile, each with a quarter of every 64 reduction
-//          elements; the four partial tiles are added in wave order at the end
+//   split  32 rows x 32 columns, all four waves on the same tile, each with a quarter of the reduction dimension, 16
+//          elements per step; the four partial tiles are added in wave order at the end
+// The wide shape adds up the same four quarters one after the other, so that both give the same bits and a row's result does
+// not depend on the batch it came in; that costs nothing (d 1024, f 4096, 8 experts, k 2, one sum over the whole dimension ->
+// four quarters: 512 tokens 338 -> 340 us, 4096 tokens 1.90 -> 1.88 ms).
 // Both stage the activations ([row][k]) and the weights ([k][column]) of a step through LDS, double buffered, one barrier
 // per step; the global loads of a step are issued kAhead steps earlier into registers.  Row strides in LDS are chosen so
 // that the 16-byte activation reads and the 4-byte weight reads of a wave touch every bank once.
@@ -85,6 +87,7 @@ struct Shape {
     static constexpr int BM = SPLIT ? 32 : 64, BN = SPLIT ? 32 : 64, KC = SPLIT ? 64 : 32;
     static constexpr int kAhead = SPLIT ? 3 : 2;
     static constexpr int kWaveK = SPLIT ? KC / 4 : KC;          // reduction elements of a step one wave multiplies
+    static constexpr int kStride = kWaveK;                      // elements from one step to the next
     static constexpr int kARow = KC + 4, kBRow = BN + 8;        // floats per LDS row
 };
 
@@ -119,9 +122,10 @@ __global__ __launch_bounds__(256, 2) void ffn_f32_kernel(const float* __restrict
         const int id = tid + i * 256;
         const int r = id / kAVec, row = row_begin + min(r, rows - 1);      // rows past the end repeat the last one, not stored
         const size_t src = gather != nullptr ? static_cast<size_t>(gather[row] / gather_k) : static_cast<size_t>(row);
-        a_src[i] = A + src * K + 4 * (id % kAVec);
+        // (SPLIT: element 16 w + n of a step is element n of the step in quarter w)
+        a_src[i] = A + src * K + (SPLIT ? id % kAVec / 4 * (K / 4) + 4 * (id % 4) : 4 * (id % kAVec));
         a_dst[i] = r * S::kARow + 4 * (id % kAVec);
-        b_src[i] = static_cast<size_t>(id / kBVec) * N + 4 * (id % kBVec);
+        b_src[i] = static_cast<size_t>(SPLIT ? id / kBVec / 16 * (K / 4) + id / kBVec % 16 : id / kBVec) * N + 4 * (id % kBVec);
         b_dst[i] = kAFloats + (id / kBVec) * S::kBRow + 4 * (id % kBVec);
     }
     f32x4 ra[S::kAhead][2], rb[S::kAhead][NB][2];
@@ -130,20 +134,21 @@ __global__ __launch_bounds__(256, 2) void ffn_f32_kernel(const float* __restrict
         const int c = min(step, steps - 1);                               // past the end: the last step again, unused
 #pragma unroll
         for (int i = 0; i < 2; ++i) {
-            ra[q][i] = *reinterpret_cast<const f32x4*>(a_src[i] + c * S::KC);
+            ra[q][i] = *reinterpret_cast<const f32x4*>(a_src[i] + c * S::kStride);
 #pragma unroll
             for (int b = 0; b < NB; ++b)
-                rb[q][b][i] = *reinterpret_cast<const f32x4*>(Wb[b] + static_cast<size_t>(c) * S::KC * N + b_src[i]);
+                rb[q][b][i] = *reinterpret_cast<const f32x4*>(Wb[b] + static_cast<size_t>(c) * S::kStride * N + b_src[i]);
         }
     };
     // the wave's place in the tile: rows and columns, or (SPLIT) its part of the reduction elements of a step
     const int wrow = SPLIT ? 0 : 32 * (wave >> 1), wcol = SPLIT ? 0 : 32 * (wave & 1), wk = SPLIT ? wave * S::kWaveK : 0;
     const int h = lane >> 5, c31 = lane & 31;
-    f32x16 acc[NB];
+    f32x16 acc[NB], total[NB];                   // the quarter at hand; the quarters before it (not SPLIT)
 #pragma unroll
     for (int b = 0; b < NB; ++b)
 #pragma unroll
-        for (int v = 0; v < 16; ++v) acc[b][v] = 0.f;
+        for (int v = 0; v < 16; ++v) acc[b][v] = total[b][v] = 0.f;
+    int quarter_end = K / 4;
 #pragma unroll
     for (int q = 0; q < S::kAhead; ++q) fetch(q, q);
     for (int s0 = 0; s0 < steps; s0 += S::kAhead) {
@@ -165,6 +170,15 @@ __global__ __launch_bounds__(256, 2) void ffn_f32_kernel(const float* __restrict
             // eight reduction elements at a time: lanes 0..31 hold the first four, lanes 32..63 the others
 #pragma unroll
             for (int g = 0; g < S::kWaveK / 8; ++g) {
+                if (!SPLIT && g % 2 == 0 && s * S::KC + 8 * g == quarter_end) {       // uniform (a quarter is a multiple of 16)
+                    quarter_end += K / 4;
+#pragma unroll
+                    for (int b = 0; b < NB; ++b) {
+                        total[b] += acc[b];
+#pragma unroll
+                        for (int v = 0; v < 16; ++v) acc[b][v] = 0.f;
+                    }
+                }
                 const f32x4 av = *reinterpret_cast<const f32x4*>(pa + 8 * g);
                 float bv[NB][4];
 #pragma unroll
@@ -185,12 +199,14 @@ __global__ __launch_bounds__(256, 2) void ffn_f32_kernel(const float* __restrict
         return reinterpret_cast<f32x4*>(C + static_cast<size_t>(row_map != nullptr ? row_map[row] : row) * N + n0 + col);
     };
     if constexpr (!SPLIT) {
+#pragma unroll
+        for (int b = 0; b < NB; ++b) total[b] += acc[b];
         if (wrow + c31 < rows) {
 #pragma unroll
             for (int g = 0; g < 4; ++g) {
                 f32x4 o;
 #pragma unroll
-                for (int i = 0; i < 4; ++i) o[i] = value(acc[0][4 * g + i], acc[NB - 1][4 * g + i]);
+                for (int i = 0; i < 4; ++i) o[i] = value(total[0][4 * g + i], total[NB - 1][4 * g + i]);
                 *out_at(wrow + c31, wcol + 8 * g + 4 * h) = o;
             }
         }

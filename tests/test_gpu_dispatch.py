@@ -131,9 +131,10 @@ def expert_ffn_rows(counts, rows_of, d, f, dtype, act=0):
     return [Yp[offsets[e]:offsets[e + 1]] for e in range(E)]
 
 
-@pytest.mark.parametrize("few,many", [([1, 0, 3], [300, 40, 270]), ([12, 4, 0], [33, 70, 1]), ([20, 40, 3], [257, 100, 64]),
-                                      ([64, 0, 17], [200, 30, 130])])
-@pytest.mark.parametrize("d,f,dtype", [(64, 64, "bf16"), (192, 704, "bf16"), (2112, 1088, "bf16")])
+@pytest.mark.parametrize("few,many", [([1, 0, 3], [300, 40, 270]), ([12, 4, 0], [33, 470, 9]), ([20, 40, 3], [257, 100, 240]),
+                                      ([64, 0, 17], [200, 230, 130])])
+@pytest.mark.parametrize("d,f,dtype", [(64, 64, "bf16"), (192, 704, "bf16"), (2112, 1088, "bf16"),
+                                       (192, 4096, "f32"), (4096, 192, "f32")])      # up, down: split and wide tiles
 def test_rows_have_the_same_bits_in_every_batch(d, f, dtype, few, many):
     """An expert's row gives the same bytes whatever else is in the batch, and so whichever kernel the batch size selects."""
     def rows_of(e):
