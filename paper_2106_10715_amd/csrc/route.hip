@@ -425,53 +425,55 @@ __global__ __launch_bounds__(256) void gate_prep_kernel(const uint16_t* __restri
     }
 }
 
-// Value of column `col` of the projection of token t from exact products, by one wave, from the packed fragments:
-// lane j takes the 8-row pieces j, j + 64, ... of the column; sums in twice the fp64 precision, the pair (hi, lo) not yet
-// normalised.  Every lane gets the sum.
-__device__ __attribute__((always_inline)) inline void exact_column_dot(const uint16_t* __restrict__ x, const uint4* __restrict__ pack, size_t t,
-                                                           int col, int nS, int d, int lane, double& hi, double& lo) {
-    const int nb = col >> 5, cin = col & 31;
+// Values of two columns of the projection of token t from exact products, by one wave, from the packed fragments: lane j
+// takes the 8-row pieces j, j + 64, ... of the columns; sums in twice the fp64 precision, the pairs (hi, lo) not yet normalised.
+// Every lane gets the sums.
+__device__ __attribute__((always_inline)) inline void exact_dots(const uint16_t* __restrict__ x, const uint4* __restrict__ pack, size_t t,
+                                                     const int (&col)[2], int nS, int d, int lane, double (&hi)[2], double (&lo)[2]) {
+    constexpr int U = 4;                   // pieces requested at once
     const uint4* xr = reinterpret_cast<const uint4*>(x + t * d);
-    double sum = 0.0, low = 0.0;
-    for (int j = lane; j < nS * 8; j += 64) {
-        const int S = j >> 3, q = (j & 7) >> 1, h = j & 1;          // rows 64 S + 32 h + 8 q .. + 8
-        const uint4 wq = pack[((static_cast<size_t>(nb) * nS + S) * 4 + q) * 64 + h * 32 + cin];
-        const uint4 xq = xr[S * 8 + h * 4 + q];
-        const uint32_t xu[4] = {xq.x, xq.y, xq.z, xq.w}, wu[4] = {wq.x, wq.y, wq.z, wq.w};
+    const int pieces = nS * 8;
+    hi[0] = hi[1] = lo[0] = lo[1] = 0.0;
+    for (int j0 = 0; j0 < pieces; j0 += 64 * U) {
+        uint4 xq[U], wq[U][2];
 #pragma unroll
-        for (int i = 0; i < 4; ++i) {
-            const double x0 = static_cast<double>(__uint_as_float(xu[i] << 16)), w0 = static_cast<double>(__uint_as_float(wu[i] << 16));
-            const double x1 = static_cast<double>(__uint_as_float(xu[i] & 0xffff0000u)), w1 = static_cast<double>(__uint_as_float(wu[i] & 0xffff0000u));
-            dd_add_product(sum, low, x0, w0);
-            dd_add_product(sum, low, x1, w1);
+        for (int u = 0; u < U; ++u) {
+            if (j0 + 64 * u < pieces) {                                 // uniform
+                const int j = min(j0 + 64 * u + lane, pieces - 1);
+                const int S = j >> 3, q = (j & 7) >> 1, h = j & 1;      // rows 64 S + 32 h + 8 q .. + 8
+                xq[u] = xr[S * 8 + h * 4 + q];
+#pragma unroll
+                for (int c = 0; c < 2; ++c)
+                    wq[u][c] = pack[((static_cast<size_t>(col[c] >> 5) * nS + S) * 4 + q) * 64 + h * 32 + (col[c] & 31)];
+            }
+        }
+        asm volatile("" : : : "memory");
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            if (j0 + 64 * u < pieces) {
+                const bool in = j0 + 64 * u + lane < pieces;            // past the end: zeros, which change nothing
+                const uint32_t xu[4] = {in ? xq[u].x : 0u, in ? xq[u].y : 0u, in ? xq[u].z : 0u, in ? xq[u].w : 0u};
+#pragma unroll
+                for (int i = 0; i < 4; ++i) {
+                    const double x0 = static_cast<double>(__uint_as_float(xu[i] << 16)), x1 = static_cast<double>(__uint_as_float(xu[i] & 0xffff0000u));
+#pragma unroll
+                    for (int c = 0; c < 2; ++c) {
+                        const uint32_t wu = i == 0 ? wq[u][c].x : i == 1 ? wq[u][c].y : i == 2 ? wq[u][c].z : wq[u][c].w;
+                        dd_add_product(hi[c], lo[c], x0, static_cast<double>(__uint_as_float(wu << 16)));
+                        dd_add_product(hi[c], lo[c], x1, static_cast<double>(__uint_as_float(wu & 0xffff0000u)));
+                    }
+                }
+            }
         }
     }
 #pragma unroll
     for (int off = 32; off >= 1; off >>= 1) {
-        const double oh = __shfl_xor(sum, off), ol = __shfl_xor(low, off);
-        dd_add(sum, low, oh, ol);
-    }
-    hi = sum;
-    lo = low;
-}
-
-// Column of the n-th set bit of the masks (bit l of mask i: column l + 64 i).
-template <int NE>
-__device__ inline int nth_column(const unsigned long long (&mask)[NE], int n) {
-    int col = 0;
-    bool found = false;
 #pragma unroll
-    for (int i = 0; i < NE; ++i) {
-        const int here = __popcll(mask[i]);
-        if (!found && n < here) {
-            unsigned long long m = mask[i];
-            for (int skip = n; skip > 0; --skip) m &= m - 1ull;
-            col = __ffsll(static_cast<long long>(m)) - 1 + 64 * i;
-            found = true;
+        for (int c = 0; c < 2; ++c) {
+            const double oh = __shfl_xor(hi[c], off), ol = __shfl_xor(lo[c], off);
+            dd_add(hi[c], lo[c], oh, ol);
         }
-        n -= here;
     }
-    return col;
 }
 
 constexpr int kMaxCand = 12;     // columns of one token that are re-evaluated one by one; more than that: all columns
@@ -492,13 +494,19 @@ __global__ __launch_bounds__(kGateWaves * 64, 2) void route_mfma_kernel(const ui
     // hash: E is the number of sign bits (columns of the projection), one expert id per token, weight 1
     constexpr int EP = NB * 32;
     constexpr int kParts = gate_parts<NB>(), kRows = gate_rows(TOK);
-    __shared__ float part_tile[kParts * kRows * gate_row(EP)];     // [kParts][kRows][gate_row(EP)]: partial logit tiles
+    __shared__ __align__(16) float part_tile[kParts * kRows * gate_row(EP)];     // [kParts][kRows][gate_row(EP)]: partial logit tiles
     __shared__ float xsq_w[kGateWaves][kRows];
     __shared__ float colpart[kGateWaves * 64];             // partial column sums of squares (up to 512 columns' worth)
-    __shared__ unsigned long long many_sh;                     // those of them with more columns in reach than are evaluated one by one
     __shared__ unsigned long long close_sh;                     // tokens fp32 cannot decide, one bit each
-    __shared__ double reach_sh[kRows];                     // and from which logit on (hash: up to which magnitude) their columns matter
-    __shared__ double resc[kGateWaves][EP], resc_lo[kGateWaves][EP];    // re-evaluated logits per wave: value and low part
+    __shared__ unsigned long long many_sh;                      // and those with more columns in reach than are evaluated one by one
+    __shared__ unsigned long long tied_sh;                      // close tokens that fp64 cannot decide either
+    __shared__ uint8_t reach_count[kRows], reach_col[kRows][kMaxCand];    // columns of a close token that can change its answer
+    // their sums from exact products, eight tokens at a time: fp64 by slices of the reduction, or pairs (high, low)
+    __shared__ double close_sum[kGateWaves][kGateWaves][kMaxCand];
+    // partial sums of all columns, value and low part, of kMany tokens: in the logit tiles, which are not needed any more then
+    constexpr int kMany = kParts == kGateWaves ? kGateWaves : 1;
+    static_assert(kMany == 1 || kMany * kGateWaves * EP * 4 <= kParts * kRows * gate_row(EP), "the sums fit the tiles");
+    __shared__ double2 pair_sh[kMany == 1 ? kGateWaves * EP : 1];
     auto tile_at = [&](int p, int tok, int e) -> float& { return part_tile[(p * kRows + tok) * gate_row(EP) + e]; };
 
     const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(static_cast<int>(threadIdx.x >> 6));
@@ -586,7 +594,7 @@ __global__ __launch_bounds__(kGateWaves * 64, 2) void route_mfma_kernel(const ui
         for (int i = 0; i < kNorm; ++i) ssum += norm_g + i * G < nS ? norm[i] : 0.f;
         for (int S = norm_g + kNorm * G; S < nS; S += G) ssum += part[static_cast<size_t>(S) * EP + norm_c];
         colpart[threadIdx.x] = ssum;
-        if (threadIdx.x == 0) close_sh = many_sh = 0ull;
+        if (threadIdx.x == 0) close_sh = many_sh = tied_sh = 0ull;
     };
 
     // ---- MFMA partial tiles
@@ -806,9 +814,23 @@ __global__ __launch_bounds__(kGateWaves * 64, 2) void route_mfma_kernel(const ui
         // lower stays below all of those even with both errors against it).  Sign bits: every projection within 2 delta
         // of zero.  Usually two or three columns; the others keep their fp32 values, which cannot reach the selected ones.
         const double delta = gamma * sqrt(token_norm2(tt) * wn2) + 1.0625 * 5.9604644775390625e-8 * vmax;
-        if (real && j0 == 0 && gap <= 2.0 * delta) {
-            reach_sh[tt] = hash ? 2.0 * delta : reach_from - 2.0 * delta;
-            atomicOr(&close_sh, 1ull << tt);
+        const bool close = real && gap <= 2.0 * delta;                     // the same in the whole row
+        if (__any(close)) {
+            const double reach = hash ? 2.0 * delta : reach_from - 2.0 * delta;
+            int count = 0;
+#pragma unroll
+            for (int i = 0; i < NL; ++i) {
+                const double v = static_cast<double>(fv[i]);
+                const bool in = close && j0 + 16 * i < E && (hash ? fabs(v) <= reach : v >= reach);
+                const unsigned in_row = static_cast<unsigned>(__ballot(in) >> (lane & 48)) & 0xffffu;
+                const int at = count + __popc(in_row & ((1u << j0) - 1u));
+                if (in && at < kMaxCand) reach_col[tt][at] = static_cast<uint8_t>(j0 + 16 * i);
+                count += __popc(in_row);
+            }
+            if (close && j0 == 0) {
+                reach_count[tt] = static_cast<uint8_t>(count);             // (looked at up to kMaxCand only; E = 256 in reach: many_sh)
+                atomicOr(count > kMaxCand ? &many_sh : &close_sh, 1ull << tt);
+            }
         }
     }
     float bl[kNE];
@@ -824,49 +846,40 @@ __global__ __launch_bounds__(kGateWaves * 64, 2) void route_mfma_kernel(const ui
         return static_cast<unsigned long long>(hi) << 32 | lo;
     };
     unsigned long long todo = uniform64(close_sh);
-    // Up to kSets tokens at a time: all waves compute their share of the sums of every one, then wave i finishes token i.
-    constexpr int kSets = NB == 1 ? 4 : 8;           // sets of 16 sums per wave in the two arrays of re-evaluated logits
-    auto sums_at = [&](int n, int wv, int c) -> double& {
-        constexpr int kHalf = kSets / 2;
-        return n < kHalf ? resc[wv][16 * n + c] : resc_lo[wv][16 * (n - kHalf) + c];
-    };
-    // this lane's logits of token tt, fp32 (a -0 becomes +0: equal logits must compare equal), and which columns are in reach
-    auto look = [&](int tt, double (&lv)[kNE], double (&ll)[kNE], unsigned long long (&in_reach)[NE]) __attribute__((always_inline)) {
-        const double reach = reach_sh[tt];
-        int count = 0;
-#pragma unroll
-        for (int i = 0; i < kNE; ++i) { lv[i] = 0.0; ll[i] = 0.0; }        // (value, low part); from NE on: no expert, never looked at
-#pragma unroll
-        for (int i = 0; i < NE; ++i) {
-            const int ei = eg + 64 * i, ec = ei < E ? ei : 0;              // lanes without an expert read column 0 and drop it
-            lv[i] = ei < E ? static_cast<double>((logit(tt, ec) + bl[i]) + 0.0f) : 0.0;
-            in_reach[i] = __ballot(ei < E && (hash ? fabs(lv[i]) <= reach : lv[i] >= reach));
-            count += __popcll(in_reach[i]);
-        }
-        return count;
-    };
+    // Eight tokens at a time: all waves take the exact products of their columns in reach in turn, then wave i decides for token i.
+    // In fp64 a job is four columns in one slice of the reduction (at d_model 4096 an eighth, one 8-row piece per lane), and
+    // wave i adds the slices in order.  Where that leaves the decision inside its rounding error (in practice: exact ties), a job
+    // is two whole columns in twice the precision.  A sum is the same whichever wave takes it.
+    // Against eighths of every sum, empty ones too, and all pairs of a token by one wave, column by column: 16384 tokens, d 4096,
+    // 32 experts 46 -> 40 us; 16384 tokens that all tie, d 1024, 8 experts 465 -> 240, 32 experts (all columns) 480 -> 249.
+    const int slices = min(kGateWaves, (nS + 7) / 8);
     while (todo != 0ull) {                           // the same in every wave
-        unsigned long long batch = 0ull;
-        for (int n = 0; n < kSets && todo != 0ull; ++n) {
-            const int tt = __ffsll(static_cast<long long>(todo)) - 1, t = t0 + tt;
-            todo &= todo - 1ull;
-            batch |= 1ull << tt;
-            double lv[kNE], ll[kNE];
-            unsigned long long in_reach[NE];
-            const int count = look(tt, lv, ll, in_reach);
-            if (count > kMaxCand) continue;
-            // The columns in reach from exact products in fp64, an eighth of the reduction per wave (at d_model 4096 one
-            // 8-row piece per lane), the waves' sums added in wave order by the wave that finishes the token.
-            for (int c0 = 0; c0 < count; c0 += 4) {
+        const unsigned long long batch = todo;
+        int tokens = 0;
+        for (; tokens < kGateWaves && todo != 0ull; ++tokens) todo &= todo - 1ull;
+        auto token = [&](int n) {                    // the n-th token of the batch
+            unsigned long long m = batch;
+            for (int skip = n; skip > 0; --skip) m &= m - 1ull;
+            return __ffsll(static_cast<long long>(m)) - 1;
+        };
+        auto columns_of = [&](int tt) { return __builtin_amdgcn_readfirstlane(static_cast<int>(reach_count[tt])); };
+        auto column = [&](int tt, int c) { return __builtin_amdgcn_readfirstlane(static_cast<int>(reach_col[tt][c])); };
+        int job = 0;
+        for (int n = 0; n < tokens; ++n) {
+            const int tt = token(n), cols = columns_of(tt);
+            for (int c0 = 0; c0 < cols; c0 += 4, job += slices) {
+                const int slice = (wave - job) & (kGateWaves - 1);                  // the one of these jobs that falls to this wave
+                if (slice >= slices) continue;
+                const uint4* xr = reinterpret_cast<const uint4*>(x + static_cast<size_t>(t0 + tt) * d);
                 int col[4];
 #pragma unroll
-                for (int c = 0; c < 4; ++c) col[c] = nth_column<NE>(in_reach, min(c0 + c, count - 1));
+                for (int c = 0; c < 4; ++c) col[c] = column(tt, min(c0 + c, cols - 1));
                 double sum[4] = {0.0, 0.0, 0.0, 0.0};
-                for (int j0 = wave * 64; j0 < nS * 8; j0 += kGateWaves * 64) {
+                for (int j0 = slice * 64; j0 < nS * 8; j0 += kGateWaves * 64) {
                     const int j = min(j0 + lane, nS * 8 - 1);
                     const bool in = j0 + lane < nS * 8;
-                    const int S = j >> 3, q = (j & 7) >> 1, h = j & 1;           // rows 64 S + 32 h + 8 q .. + 8
-                    const uint4 xq = reinterpret_cast<const uint4*>(x + static_cast<size_t>(t) * d)[S * 8 + h * 4 + q];
+                    const int S = j >> 3, q = (j & 7) >> 1, h = j & 1;               // rows 64 S + 32 h + 8 q .. + 8
+                    const uint4 xq = xr[S * 8 + h * 4 + q];
                     const uint32_t xu[4] = {xq.x, xq.y, xq.z, xq.w};
                     uint4 wq[4];
 #pragma unroll
@@ -885,135 +898,157 @@ __global__ __launch_bounds__(kGateWaves * 64, 2) void route_mfma_kernel(const ui
                         sum[c] += in ? part_sum : 0.0;
                     }
                 }
+                // over the lanes; the columns part on the way: lanes 16 c .. 16 c + 15 end with column c
+                const bool upper = lane >= 32, odd = (lane & 16) != 0;
+                const double got0 = __shfl_xor(upper ? sum[0] : sum[2], 32), got1 = __shfl_xor(upper ? sum[1] : sum[3], 32);
+                const double both0 = (upper ? sum[2] : sum[0]) + got0, both1 = (upper ? sum[3] : sum[1]) + got1;
+                double total = (odd ? both1 : both0) + __shfl_xor(odd ? both0 : both1, 16);
 #pragma unroll
-                for (int off = 32; off >= 1; off >>= 1)
-#pragma unroll
-                    for (int c = 0; c < 4; ++c) sum[c] += __shfl_xor(sum[c], off);
-                if (lane == 0) {
-#pragma unroll
-                    for (int c = 0; c < 4; ++c)
-                        if (c0 + c < count) sums_at(n, wave, c0 + c) = sum[c];
-                }
+                for (int off = 8; off >= 1; off >>= 1) total += __shfl_xor(total, off);
+                if ((lane & 15) == 0 && c0 + (lane >> 4) < cols) close_sum[n][slice][c0 + (lane >> 4)] = total;
             }
         }
-        __syncthreads();
-        if (wave < __popcll(batch)) {
-            unsigned long long mine = batch;
-            for (int skip = wave; skip > 0; --skip) mine &= mine - 1ull;
-            const int tt = __ffsll(static_cast<long long>(mine)) - 1, t = t0 + tt;
-            const double xn2 = token_norm2(tt);
-            double lv[kNE], ll[kNE];
-            unsigned long long in_reach[NE];
-            if (look(tt, lv, ll, in_reach) > kMaxCand) {
-                if (lane == 0) atomicOr(&many_sh, 1ull << tt);
-            } else {
-                int before_mine = 0;
-    #pragma unroll
-                for (int i = 0; i < NE; ++i) {
-                    if ((in_reach[i] >> lane) & 1ull) {
-                        const int c = before_mine + __popcll(in_reach[i] & ((1ull << lane) - 1ull));
-                        double hi = 0.0, lo = 0.0;
-                        for (int wv = 0; wv < kGateWaves; ++wv) hi += sums_at(wave, wv, c);
+        // this wave's token: its logits, fp32 (a -0 becomes +0: equal logits must compare equal), of the columns this lane holds
+        const int tt = token(wave < tokens ? wave : 0), t = t0 + tt, cols = columns_of(tt);
+        double lv[kNE], ll[kNE];                     // value and low part; from NE on: no expert, never looked at
+#pragma unroll
+        for (int i = 0; i < kNE; ++i) {
+            const int ei = eg + 64 * i, ec = ei < E ? ei : 0;              // lanes without an expert read column 0 and drop it
+            lv[i] = i < NE && ei < E ? static_cast<double>((logit(tt, ec) + bl[i]) + 0.0f) : 0.0;
+            ll[i] = 0.0;
+        }
+        double sv[kSel];
+        int se[kSel];
+        int code = 0;
+        double gap, vmax;
+        auto decide = [&](bool pairs) __attribute__((always_inline)) {
+            for (int c = 0; c < cols; ++c) {
+                const int col = column(tt, c);
+                double hi = close_sum[wave][0][c], lo = pairs ? close_sum[wave][1][c] : 0.0;
+                if (!pairs)
+                    for (int v = 1; v < slices; ++v) hi += close_sum[wave][v][c];
+#pragma unroll
+                for (int i = 0; i < NE; ++i)
+                    if (eg + 64 * i == col) {
                         dd_add(hi, lo, static_cast<double>(bl[i]), 0.0);
                         dd_normalise(hi, lo);
                         lv[i] = hi;
+                        ll[i] = pairs ? lo : 0.0;
                     }
-                    before_mine += __popcll(in_reach[i]);
-                }
-                double sv[kSel];
-                int se[kSel];
-                int code = 0;
-                double gap, vmax;
-                auto decide = [&]() __attribute__((always_inline)) {
-                    if (hash) {
-                        sign_bits(lv, ll, eg, true, E, code, gap, vmax);
-                    } else {
-                        wave_topk(lv, ll, eg, true, E, kk_sel, sv, se);
-                        rank_gaps(sv, kk_sel, gap, vmax);
-                    }
-                };
-                decide();
-                // and once more in twice that precision if that still leaves the decision inside the rounding error (in
-                // practice: exact ties)
-                const double delta64 = 1.0625 * 1.1102230246251565e-16 * (static_cast<double>(d + 8) * sqrt(xn2 * wn2) + 2.0 * vmax);
-                if (gap <= 2.0 * delta64) {
-    #pragma unroll
-                    for (int i = 0; i < NE; ++i) {
-                        unsigned long long m = in_reach[i];
-                        while (m != 0ull) {                                    // uniform for the wave
-                            const int l = __ffsll(static_cast<long long>(m)) - 1;
-                            m &= m - 1ull;
-                            double hi, lo;
-                            exact_column_dot(x, pack, static_cast<size_t>(t), l + 64 * i, nS, d, lane, hi, lo);
-                            if (eg == l) {
-                                dd_add(hi, lo, static_cast<double>(bl[i]), 0.0);
-                                dd_normalise(hi, lo);
-                                lv[i] = hi;
-                                ll[i] = lo;
-                            }
-                        }
-                    }
-                    decide();
-                }
-                if (hash) {
-                    if (lane == 0) { idx[t] = code; w[t] = 1.f; }
-                } else {
-                    emit_token(lv, sv, se, eg, true, E, k, renorm, lane, idx + static_cast<size_t>(t) * k, w + static_cast<size_t>(t) * k);
+            }
+            if (hash) {
+                sign_bits(lv, ll, eg, true, E, code, gap, vmax);
+            } else {
+                wave_topk(lv, ll, eg, true, E, kk_sel, sv, se);
+                rank_gaps(sv, kk_sel, gap, vmax);
+            }
+        };
+        auto emit = [&]() __attribute__((always_inline)) {
+            if (hash) {
+                if (lane == 0) { idx[t] = code; w[t] = 1.f; }
+            } else {
+                emit_token(lv, sv, se, eg, true, E, k, renorm, lane, idx + static_cast<size_t>(t) * k, w + static_cast<size_t>(t) * k);
+            }
+        };
+        __syncthreads();
+        bool tied = false;
+        if (wave < tokens) {
+            decide(false);
+            const double delta64 = 1.0625 * 1.1102230246251565e-16 * (static_cast<double>(d + 8) * sqrt(token_norm2(tt) * wn2) + 2.0 * vmax);
+            tied = gap <= 2.0 * delta64;
+            if (!tied) emit();
+            else if (lane == 0) atomicOr(&tied_sh, 1ull << tt);
+        }
+        __syncthreads();
+        const unsigned long long ties = uniform64(tied_sh) & batch;
+        if (ties == 0ull) continue;
+        job = 0;
+        for (int n = 0; n < tokens; ++n) {
+            const int t2 = token(n), cols2 = columns_of(t2);
+            if (((ties >> t2) & 1ull) == 0ull) continue;
+            for (int c = 0; c < cols2; c += 2, ++job) {
+                if (job % kGateWaves != wave) continue;
+                const int last = min(c + 1, cols2 - 1);
+                const int col[2] = {column(t2, c), column(t2, last)};
+                double hi[2], lo[2];
+                exact_dots(x, pack, static_cast<size_t>(t0 + t2), col, nS, d, lane, hi, lo);
+                if (lane == 0) {
+                    close_sum[n][0][c] = hi[0];
+                    close_sum[n][1][c] = lo[0];
+                    if (last > c) { close_sum[n][0][last] = hi[1]; close_sum[n][1][last] = lo[1]; }
                 }
             }
         }
         __syncthreads();
+        if (tied) {
+            decide(true);
+            emit();
+        }
+        __syncthreads();                             // the sums have been read
     }
     unsigned long long many = uniform64(many_sh);
+    auto pair_at = [&](int n, int wv, int c) -> double2& {
+        return kMany == 1 ? pair_sh[wv * EP + c] : reinterpret_cast<double2*>(part_tile)[(n * kGateWaves + wv) * EP + c];
+    };
     while (many != 0ull) {                           // the same in every wave
-        const int tt = __ffsll(static_cast<long long>(many)) - 1, t = t0 + tt;
-        many &= many - 1ull;
-        // More than kMaxCand columns in reach: all columns in fp64 pairs, from the same packed fragments and with the same split as
-        // the MFMA pass: wave w takes the groups S = w, w+8, ..., lane (c, h) the 32 rows 64 S + 32 h .. of column c of
-        // every expert block; the two halves are added by a lane exchange, the waves in wave order.
-        const uint4* xr = reinterpret_cast<const uint4*>(x + static_cast<size_t>(t) * d + 32 * (lane >> 5));
-        double a64[NB], l64[NB];
+        const unsigned long long batch = many;
+        int tokens = 0;
+        for (; tokens < kMany && many != 0ull; ++tokens) {
+            const int tt = __ffsll(static_cast<long long>(many)) - 1, t = t0 + tt;
+            many &= many - 1ull;
+            // More than kMaxCand columns in reach: all columns in fp64 pairs, from the same packed fragments and with the same split as
+            // the MFMA pass: wave w takes the groups S = w, w+8, ..., lane (c, h) the 32 rows 64 S + 32 h .. of column c of
+            // every expert block; the two halves are added by a lane exchange, the waves in wave order.
+            const uint4* xr = reinterpret_cast<const uint4*>(x + static_cast<size_t>(t) * d + 32 * (lane >> 5));
+            double a64[NB], l64[NB];
 #pragma unroll
-        for (int nb = 0; nb < NB; ++nb) { a64[nb] = 0.0; l64[nb] = 0.0; }
-        for (int S = wave; S < nS; S += kGateWaves) {
-            uint4 xa[4];
+            for (int nb = 0; nb < NB; ++nb) { a64[nb] = 0.0; l64[nb] = 0.0; }
+            for (int S = wave; S < nS; S += kGateWaves) {
+                uint4 xa[4];
 #pragma unroll
-            for (int q = 0; q < 4; ++q) xa[q] = xr[S * 8 + q];
+                for (int q = 0; q < 4; ++q) xa[q] = xr[S * 8 + q];
 #pragma unroll
-            for (int nb = 0; nb < NB; ++nb) {
-                const uint4* bp = pack + ((static_cast<size_t>(nb) * nS + S) * 4) * 64 + lane;
-                uint4 wb[4];
+                for (int nb = 0; nb < NB; ++nb) {
+                    const uint4* bp = pack + ((static_cast<size_t>(nb) * nS + S) * 4) * 64 + lane;
+                    uint4 wb[4];
 #pragma unroll
-                for (int q = 0; q < 4; ++q) wb[q] = bp[q * 64];
+                    for (int q = 0; q < 4; ++q) wb[q] = bp[q * 64];
 #pragma unroll
-                for (int q = 0; q < 4; ++q) {
-                    const uint32_t xu[4] = {xa[q].x, xa[q].y, xa[q].z, xa[q].w};
-                    const uint32_t wu[4] = {wb[q].x, wb[q].y, wb[q].z, wb[q].w};
+                    for (int q = 0; q < 4; ++q) {
+                        const uint32_t xu[4] = {xa[q].x, xa[q].y, xa[q].z, xa[q].w};
+                        const uint32_t wu[4] = {wb[q].x, wb[q].y, wb[q].z, wb[q].w};
 #pragma unroll
-                    for (int i = 0; i < 4; ++i) {
-                        dd_add_product(a64[nb], l64[nb], static_cast<double>(__uint_as_float(xu[i] << 16)),
-                                       static_cast<double>(__uint_as_float(wu[i] << 16)));
-                        dd_add_product(a64[nb], l64[nb], static_cast<double>(__uint_as_float(xu[i] & 0xffff0000u)),
-                                       static_cast<double>(__uint_as_float(wu[i] & 0xffff0000u)));
+                        for (int i = 0; i < 4; ++i) {
+                            dd_add_product(a64[nb], l64[nb], static_cast<double>(__uint_as_float(xu[i] << 16)),
+                                           static_cast<double>(__uint_as_float(wu[i] << 16)));
+                            dd_add_product(a64[nb], l64[nb], static_cast<double>(__uint_as_float(xu[i] & 0xffff0000u)),
+                                           static_cast<double>(__uint_as_float(wu[i] & 0xffff0000u)));
+                        }
                     }
                 }
             }
-        }
 #pragma unroll
-        for (int nb = 0; nb < NB; ++nb) {
-            const double oh = __shfl_xor(a64[nb], 32), ol = __shfl_xor(l64[nb], 32);
-            dd_add(a64[nb], l64[nb], oh, ol);
-            if (lane < 32) { resc[wave][32 * nb + lane] = a64[nb]; resc_lo[wave][32 * nb + lane] = l64[nb]; }
+            for (int nb = 0; nb < NB; ++nb) {
+                const double oh = __shfl_xor(a64[nb], 32), ol = __shfl_xor(l64[nb], 32);
+                dd_add(a64[nb], l64[nb], oh, ol);
+                if (lane < 32) pair_at(tokens, wave, 32 * nb + lane) = double2{a64[nb], l64[nb]};
+            }
         }
         __syncthreads();
-        if (wave == 0) {
+        if (wave < tokens) {                         // wave i finishes token i
+            unsigned long long mine = batch;
+            for (int skip = wave; skip > 0; --skip) mine &= mine - 1ull;
+            const int t = t0 + __ffsll(static_cast<long long>(mine)) - 1;
             double lv[kNE], ll[kNE];
 #pragma unroll
             for (int i = 0; i < kNE; ++i) {
                 const int ei = eg + 64 * i;
                 double sum = 0.0, low = 0.0;
                 if (ei < E) {
-                    for (int wv = 0; wv < kGateWaves; ++wv) dd_add(sum, low, resc[wv][ei], resc_lo[wv][ei]);
+                    for (int wv = 0; wv < kGateWaves; ++wv) {
+                        const double2 part_pair = pair_at(wave, wv, ei);
+                        dd_add(sum, low, part_pair.x, part_pair.y);
+                    }
                     dd_add(sum, low, static_cast<double>(bl[i]), 0.0);
                     dd_normalise(sum, low);
                 }

@@ -169,3 +169,32 @@ def test_gate_does_not_depend_on_the_place_in_the_batch(d, E, k, renorm):
         assert torch.equal(i2, idx[:len(part)]) and torch.equal(w2, w[:len(part)]), f"{len(part)} tokens"
     i2, w2 = route(torch.roll(x, 1037, dims=0))
     assert torch.equal(i2, torch.roll(idx, 1037, dims=0)) and torch.equal(w2, torch.roll(w, 1037, dims=0))
+
+
+@pytest.mark.parametrize("T", [130, 4100, 8200, 16450])         # 8, 16, 32 and 64 tokens per block
+@pytest.mark.parametrize("E", [8, 32, 80])
+def test_gate_every_token_tied(T, E):
+    """Every column twice: each token's best two tie exactly.  Then all columns equal: every token picks the first ones."""
+    x, Wg, _ = make_inputs(T + E, T, 128, E // 2, "bf16")
+    best, _ = gpu_route(M.MoeCfg.make(T, 128, 64, E // 2, 1, "bf16"), x, Wg, None, "bf16")
+    idx, w = gpu_route(M.MoeCfg.make(T, 128, 64, E, 2, "bf16"), x, np.repeat(Wg, 2, axis=1), None, "bf16")
+    assert np.array_equal(idx, 2 * best + np.array([0, 1]))
+    assert (w == 0.5).all()
+    idx, w = gpu_route(M.MoeCfg.make(T, 128, 64, E, 4, "bf16"), x, np.repeat(Wg[:, :1], E, axis=1), None, "bf16")
+    assert np.array_equal(idx, np.tile(np.arange(4), (T, 1)))
+    assert (w == 0.25).all()
+
+
+@pytest.mark.parametrize("T,d,E,k", [(20, 4160, 32, 2), (20, 8256, 32, 1), (20, 4160, 64, 2), (20, 8256, 64, 3), (4100, 4160, 32, 2),
+                                     (8200, 4160, 32, 1)])
+def test_gate_long_rows(T, d, E, k):
+    """More groups per wave than are requested ahead, column norms of more groups than are read ahead; columns that differ in one
+    element by one unit in the last place, so that the error bound has to send their tokens to the exact branch."""
+    x, Wg, _ = make_inputs(T + d, T, d, E, "bf16")
+    Wg[:, E // 2:] = Wg[:, :E // 2]
+    Wg[d - 1, E // 2:] *= 1 + 2.0 ** -7
+    Wg = rounded(Wg, "bf16")
+    idx, w = gpu_route(M.MoeCfg.make(T, d, 64, E, k, "bf16"), x, Wg, None, "bf16")
+    r = O.route(x, Wg, k, None, 1)
+    assert np.array_equal(idx, r.idx)
+    assert rel_l2(w, r.w) <= 1e-5
