@@ -14,14 +14,13 @@ __device__ inline uint32_t pack_bf16(float lo, float hi) {
     return a | (static_cast<uint32_t>(b) << 16);
 }
 
-// Bound by HBM (every row is read once, hence non-temporally); a thread's pieces of all K rows are requested before the
-// first is used, two positions of the row at a time.
-template <bool BF16, int K>
+// Bound by memory; a thread's pieces of all K rows are requested before the first is used, U positions of the row at a time.
+// NT: non-temporal loads, where the rows and y are more than the last-level cache holds.
+template <bool BF16, int K, int U, bool NT>
 __global__ __launch_bounds__(256) void combine_kernel(const uint4* __restrict__ Yp, const int32_t* __restrict__ inv,
                                                       const float* __restrict__ w, uint4* __restrict__ y,
                                                       int vec_per_row, int n_rows) {
     typedef unsigned int u4v __attribute__((ext_vector_type(4)));
-    constexpr int U = K <= 4 ? 2 : 1;
     const int t = blockIdx.x;
     const u4v* rows[K];
     float wt[K];
@@ -37,7 +36,7 @@ __global__ __launch_bounds__(256) void combine_kernel(const uint4* __restrict__ 
         for (int i = 0; i < U; ++i) {
             const int v = min(v0 + 256 * i, vec_per_row - 1);
 #pragma unroll
-            for (int j = 0; j < K; ++j) u[i][j] = __builtin_nontemporal_load(rows[j] + v);
+            for (int j = 0; j < K; ++j) u[i][j] = NT ? __builtin_nontemporal_load(rows[j] + v) : rows[j][v];
         }
 #pragma unroll
         for (int i = 0; i < U; ++i) {
@@ -68,10 +67,25 @@ __global__ __launch_bounds__(256) void combine_kernel(const uint4* __restrict__ 
     }
 }
 
+// Two positions per thread for up to four rows, where rows are longer than one position of all threads (with fewer, half the
+// requests are for nothing).  Non-temporal loads beyond 320 MB of rows and y together, us plain / non-temporal: 16384 tokens x 2,
+// d 4096 (403 MB) 76.6 / 62.0, 9000 x 4 (369 MB) 71.3 / 62.6, 8000 x 8 (590 MB) 117 / 102; 8192 x 8, d 1024 fp32 (302 MB)
+// 46.7 / 53.3, 16384 x 1, d 4096 (268 MB) 39.5 / 40.9, 4000 x 2 (98 MB) 15.5 / 16.9.
+template <bool BF16, int K>
+void launch_k(const moe_cfg& c, const uint4* Yp, const int32_t* inv, const float* w, uint4* y, int vec_per_row, hipStream_t s) {
+    constexpr int kTwo = K <= 4 ? 2 : 1;
+    const bool two = vec_per_row > 256, nt = static_cast<size_t>(c.T) * (c.k + 1) * vec_per_row * 16 > (size_t(320) << 20);
+    auto run = [&](auto kernel) { hipLaunchKernelGGL(kernel, dim3(c.T), dim3(256), 0, s, Yp, inv, w, y, vec_per_row, c.T * c.k); };
+    if (two && nt) run(combine_kernel<BF16, K, kTwo, true>);
+    else if (two) run(combine_kernel<BF16, K, kTwo, false>);
+    else if (nt) run(combine_kernel<BF16, K, 1, true>);
+    else run(combine_kernel<BF16, K, 1, false>);
+}
+
 template <bool BF16>
 void launch_for_k(const moe_cfg& c, const uint4* Yp, const int32_t* inv, const float* w, uint4* y, int vec_per_row, hipStream_t s) {
 #define MOE_COMBINE(K) \
-    case K: hipLaunchKernelGGL((combine_kernel<BF16, K>), dim3(c.T), dim3(256), 0, s, Yp, inv, w, y, vec_per_row, c.T * c.k); break;
+    case K: launch_k<BF16, K>(c, Yp, inv, w, y, vec_per_row, s); break;
     switch (c.k) {
         MOE_COMBINE(1) MOE_COMBINE(2) MOE_COMBINE(3) MOE_COMBINE(4) MOE_COMBINE(5) MOE_COMBINE(6) MOE_COMBINE(7) MOE_COMBINE(8)
     }

@@ -198,3 +198,36 @@ def test_gate_long_rows(T, d, E, k):
     r = O.route(x, Wg, k, None, 1)
     assert np.array_equal(idx, r.idx)
     assert rel_l2(w, r.w) <= 1e-5
+
+
+@pytest.mark.parametrize("T,d,k,dtype", [(300, 2048, 3, "bf16"), (301, 2112, 4, "bf16"), (302, 4160, 5, "bf16"), (50, 1024, 2, "f32"),
+                                         (51, 2112, 8, "f32"),       # one, two and four pieces of a row per thread
+                                         (43000, 1088, 3, "bf16"), (16500, 4160, 2, "bf16"), (9000, 4160, 5, "bf16")])    # non-temporal
+def test_rows_out_and_back(T, d, k, dtype):
+    """Batching and weighted sum, every row length and number of rows per token, against torch in fp64."""
+    g = torch.Generator(device="cuda")
+    g.manual_seed(T + d)
+    cfg = M.MoeCfg.make(T, d, 64, 8, k, dtype)
+    x = torch.empty((T, d), dtype=cfg.torch_dtype, device="cuda").normal_(generator=g)
+    idx = torch.rand((T, 8), device="cuda", generator=g).topk(k, 1).indices.int()
+    w = torch.rand((T, k), device="cuda", generator=g)
+
+    def ints(*n):
+        return torch.full(n, -1, dtype=torch.int32, device="cuda")
+    counts, offsets, perm, inv = ints(8), ints(9), ints(T * k), ints(T * k)
+    Xp = torch.full((T * k, d), float("nan"), dtype=cfg.torch_dtype, device="cuda")
+    M.moe_permute(cfg, x, idx, counts, offsets, perm, inv, Xp, torch.empty(M.moe_workspace_bytes(cfg), dtype=torch.uint8, device="cuda"))
+    order = idx.flatten().long().sort(stable=True).indices
+    assert torch.equal(perm.long(), order)
+    assert torch.equal(Xp, x[order // k])
+    Yp = torch.empty_like(Xp).normal_(generator=g)
+    y = torch.full_like(x, float("nan"))
+    M.moe_combine(cfg, Yp, inv, w, y)
+    ref = torch.zeros((T, d), dtype=torch.float64, device="cuda")
+    for j in range(k):
+        ref += w[:, j:j + 1].double() * Yp[inv.view(T, k)[:, j].long()].double()
+    # k fp32 roundings of sums no larger than sum(w) max|Yp|, half a unit (2^-24) each; then one to the stored type, whose half unit
+    # is 2^-8 of the value with the 8 significant bits of bf16 and 2^-24 with the 24 of fp32
+    half = 2.0 ** -8 if dtype == "bf16" else 2.0 ** -24
+    fp32_sum = w.sum(1, keepdim=True).double() * Yp.abs().max().double() * (k * 2.0 ** -24)
+    assert ((y.double() - ref).abs() <= fp32_sum + (ref.abs() + fp32_sum) * half).all()
