@@ -77,8 +77,8 @@ __device__ inline bool find_tile(const int32_t* __restrict__ offsets, int e_firs
 //   split  32 rows x 32 columns, all four waves on the same tile, each with a quarter of the reduction dimension, 16
 //          elements per step; the four partial tiles are added in wave order at the end
 // The wide shape adds up the same four quarters one after the other, so that both give the same bits and a row's result does
-// not depend on the batch it came in; that costs nothing (d 1024, f 4096, 8 experts, k 2, one sum over the whole dimension ->
-// four quarters: 512 tokens 338 -> 340 us, 4096 tokens 1.90 -> 1.88 ms).
+// not depend on the batch it came in (d 1024, f 4096, 8 experts, k 2, one sum over the whole dimension -> four quarters: 512
+// tokens 334 -> 340 us, 2048 tokens 1037 -> 1046).
 // Both stage the activations ([row][k]) and the weights ([k][column]) of a step through LDS, double buffered, one barrier
 // per step; the global loads of a step are issued kAhead steps earlier into registers.  Row strides in LDS are chosen so
 // that the 16-byte activation reads and the 4-byte weight reads of a wave touch every bank once.
@@ -167,9 +167,22 @@ __global__ __launch_bounds__(256, 2) void ffn_f32_kernel(const float* __restrict
             __syncthreads();
             const float* pa = buf + (wrow + c31) * S::kARow + wk + 4 * h;
             const float* pb = buf + kAFloats + (wk + 4 * h) * S::kBRow + wcol + c31;
-            // eight reduction elements at a time: lanes 0..31 hold the first four, lanes 32..63 the others
+            // eight reduction elements at a time: lanes 0..31 hold the first four, lanes 32..63 the others; those of the next eight are
+            // read before the products of these
+            constexpr int kG = S::kWaveK / 8;
+            f32x4 av[kG];
+            float bv[kG][NB][4];
+            auto read = [&](int g) __attribute__((always_inline)) {
+                av[g] = *reinterpret_cast<const f32x4*>(pa + 8 * g);
 #pragma unroll
-            for (int g = 0; g < S::kWaveK / 8; ++g) {
+                for (int b = 0; b < NB; ++b)
+#pragma unroll
+                    for (int i = 0; i < 4; ++i) bv[g][b][i] = pb[b * kBFloats + (8 * g + i) * S::kBRow];
+            };
+            read(0);
+#pragma unroll
+            for (int g = 0; g < kG; ++g) {
+                if (g + 1 < kG) read(g + 1);
                 if (!SPLIT && g % 2 == 0 && s * S::KC + 8 * g == quarter_end) {       // uniform (a quarter is a multiple of 16)
                     quarter_end += K / 4;
 #pragma unroll
@@ -179,16 +192,10 @@ __global__ __launch_bounds__(256, 2) void ffn_f32_kernel(const float* __restrict
                         for (int v = 0; v < 16; ++v) acc[b][v] = 0.f;
                     }
                 }
-                const f32x4 av = *reinterpret_cast<const f32x4*>(pa + 8 * g);
-                float bv[NB][4];
-#pragma unroll
-                for (int b = 0; b < NB; ++b)
-#pragma unroll
-                    for (int i = 0; i < 4; ++i) bv[b][i] = pb[b * kBFloats + (8 * g + i) * S::kBRow];
 #pragma unroll
                 for (int i = 0; i < 4; ++i)
 #pragma unroll
-                    for (int b = 0; b < NB; ++b) acc[b] = __builtin_amdgcn_mfma_f32_32x32x2f32(bv[b][i], av[i], acc[b], 0, 0, 0);
+                    for (int b = 0; b < NB; ++b) acc[b] = __builtin_amdgcn_mfma_f32_32x32x2f32(bv[g][b][i], av[g][i], acc[b], 0, 0, 0);
             }
         }
     }
