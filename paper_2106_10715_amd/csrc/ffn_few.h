@@ -1,12 +1,12 @@
 // Expert FFN kernels for batches of few rows per expert: every product is then a read of the experts' weights and nothing
 // else, and with few experts hit, or small ones, the tiles of the large kernel are too few to have enough of that read in
-// flight.  Here a block is one wave that owns 16 columns (32 in the down-projection of more than 16 rows) for up to 64 rows of
-// an expert: ten times the blocks of the large kernel, no barrier, no LDS, weights and activations straight into operand
-// registers several steps ahead.  A column's sum is one chain over the reduction dimension that starts where the large kernel
+// flight.  Here a wave owns 16 columns (32 in the down-projection of more than 16 rows) for up to 64 rows of an expert, in blocks of
+// one or two waves that know nothing of each other: some ten times the waves of the large kernel, no barrier, no LDS, weights and
+// activations straight into operand registers several steps ahead.  A column's sum is one chain over the reduction dimension that starts where the large kernel
 // starts it: both kernels give the same bits, so a row's result depends neither on the batch it came in nor on which of the
 // two ran, and the choice between them is a question of time alone.
 // Layer of 32 experts, d 4096, f 10240, large kernel -> here: 1 token 186 -> 61 us, 4 tokens 257 -> 167, 16 tokens 540 -> 508,
-// 40 tokens 903 -> 872.  (A block of four waves that split the steps of a chain between them takes 61, 165, 494 and 863 us,
+// 40 tokens 906 -> 856.  (A block of four waves that split the steps of a chain between them takes 61, 165, 494 and 863 us,
 // but its four partial sums round differently.)
 #pragma once
 #include "common.h"
@@ -44,8 +44,10 @@ __device__ inline void ffn_few_rows(const uint16_t* A, int e, int row_begin, int
     // The units that share the 8 KiB window of a step in the packed weights (two, or four of 16 columns of W_out) go to blocks
     // of one XCD that start together: 64 experts, 64 tokens x 2: 2.29 -> 2.25 ms.
     constexpr int kShare = GATED || kColumns == 32 ? 1 : 2, kGroup = 8 << kShare;
+    // Blocks of two waves hold two neighbours.
     const int bx = blockIdx.x, inside_group = bx % kGroup;
-    const int unit = bx < static_cast<int>(gridDim.x) / kGroup * kGroup
+    const int unit = blockDim.x > 64 ? 2 * bx + __builtin_amdgcn_readfirstlane(static_cast<int>(threadIdx.x >> 6))
+                   : bx < static_cast<int>(gridDim.x) / kGroup * kGroup
                          ? bx - inside_group + ((inside_group & 7) << kShare) + (inside_group >> 3) : bx;
     const int col0 = unit * kColumns;
 
@@ -135,7 +137,7 @@ __device__ inline void ffn_few_rows(const uint16_t* A, int e, int row_begin, int
     }
 }
 
-// A block: one column unit (blockIdx.x) of one row tile (blockIdx.y, an entry of the work list, at most kFewTileM rows).
+// A wave: one column unit (from blockIdx.x) of one row tile (blockIdx.y, an entry of the work list, at most kFewTileM rows).
 template <bool GATED, bool SMALL, class Act>
 __device__ inline void ffn_few_block(const uint16_t* A, const int32_t* __restrict__ plan, int e_first, const char* W,
                                      size_t expert_stride_bytes, size_t block_offset_bytes, uint16_t* __restrict__ C, int K, int N,
