@@ -222,9 +222,10 @@ __global__ __launch_bounds__(kSmallWaves * 64) void permute_small_kernel(const i
 
 // One block per token: its row is read once and written to the batched rows of its k assignments (16-byte vectors, whole
 // rows, coalesced on both sides).  Bound by memory; a thread requests U pieces, as many as rows are long, before it stores the
-// first.  Plain loads: x has often just been written (us non-temporal / plain: 8192 tokens x 1, d 1024 20.1 / 17.2; 16384 x 2, d 4096
-// 85.1 / 70.7; 32000 x 1, d 4096, where x alone fills the last-level cache, 105 / 87).
-template <int U>
+// first.  NT: x is read non-temporally, where it is more than the last-level cache holds; else the gate, or whoever wrote x, has
+// left it there.  us non-temporal / plain, x in the cache if it fits: 8192 tokens x 1, d 1024 20.1 / 17.2; 16384 x 2, d 4096 85.1 /
+// 70.7; 32000 x 1, d 4096 (262 MB) 103 / 87; 40000 x 1 (328 MB) 126 / 132, 65536 x 1 (537 MB) 201 / 212.
+template <int U, bool NT>
 __global__ __launch_bounds__(256) void gather_rows_kernel(const uint4* __restrict__ x, const int32_t* __restrict__ inv,
                                                           int k, int vec_per_row, uint4* __restrict__ Xp) {
     // stored non-temporal: the rows are next read by the expert kernels, which want the L2 for themselves
@@ -236,7 +237,10 @@ __global__ __launch_bounds__(256) void gather_rows_kernel(const uint4* __restric
     for (int v0 = threadIdx.x; v0 < vec_per_row; v0 += 256 * U) {
         u4v piece[U];
 #pragma unroll
-        for (int i = 0; i < U; ++i) piece[i] = src[min(v0 + 256 * i, vec_per_row - 1)];
+        for (int i = 0; i < U; ++i) {
+            const u4v* from = src + min(v0 + 256 * i, vec_per_row - 1);
+            piece[i] = NT ? __builtin_nontemporal_load(from) : *from;
+        }
         for (int j = 0; j < k; ++j) {
             const size_t row = inv[t * k + j];
 #pragma unroll
@@ -272,11 +276,13 @@ int launch_permute(const moe_cfg& c, const void* x, const int32_t* idx, int32_t*
     if (chunks > 0) {
         if (Xp != nullptr) {
             const int vec_per_row = static_cast<int>(c.d * elem_size(c) / 16);
-#define MOE_GATHER(U) hipLaunchKernelGGL(gather_rows_kernel<U>, dim3(c.T), dim3(256), 0, s, static_cast<const uint4*>(x), inv, c.k, vec_per_row, static_cast<uint4*>(Xp))
-            if (vec_per_row <= 256) MOE_GATHER(1);
-            else if (vec_per_row <= 512) MOE_GATHER(2);
-            else MOE_GATHER(4);
-#undef MOE_GATHER
+auto run = [&](auto kernel) {
+                hipLaunchKernelGGL(kernel, dim3(c.T), dim3(256), 0, s, static_cast<const uint4*>(x), inv, c.k, vec_per_row, static_cast<uint4*>(Xp));
+            };
+            const bool nt = static_cast<size_t>(c.T) * vec_per_row * 16 > (size_t(288) << 20);
+            if (vec_per_row <= 256) nt ? run(gather_rows_kernel<1, true>) : run(gather_rows_kernel<1, false>);
+            else if (nt) run(gather_rows_kernel<4, true>);
+            else vec_per_row <= 512 ? run(gather_rows_kernel<2, false>) : run(gather_rows_kernel<4, false>);
             MOE_LAUNCH_CHECK("gather_rows_kernel");
         }
     }

@@ -202,7 +202,8 @@ def test_gate_long_rows(T, d, E, k):
 
 @pytest.mark.parametrize("T,d,k,dtype", [(300, 2048, 3, "bf16"), (301, 2112, 4, "bf16"), (302, 4160, 5, "bf16"), (50, 1024, 2, "f32"),
                                          (51, 2112, 8, "f32"),       # one, two and four pieces of a row per thread
-                                         (43000, 1088, 3, "bf16"), (16500, 4160, 2, "bf16"), (9000, 4160, 5, "bf16")])    # non-temporal
+                                         (43000, 1088, 3, "bf16"), (16500, 4160, 2, "bf16"), (9000, 4160, 5, "bf16"),
+                                         (165000, 1024, 1, "bf16"), (41000, 4160, 1, "bf16")])    # non-temporal sums; copies as well
 def test_rows_out_and_back(T, d, k, dtype):
     """Batching and weighted sum, every row length and number of rows per token, against torch in fp64."""
     g = torch.Generator(device="cuda")
