@@ -245,8 +245,10 @@ __device__ inline void store_a(const ARegs<MBS>& a, uint4* lds_buf, unsigned tid
 // register buffers of G fragments alternate.
 // Fragment (rb, ks) of lane l = row rb*16 + l%16, 8 elements at k = 32 ks + 8 (l / 16).
 // Why 16x16x32 and not 32x32x16, in whose operand order the weights are packed: experts with many rows are bound by the
-// power the matrix pipes draw, and the narrow instruction spends less per multiplication (a loop of nothing but MFMAs on
-// normally distributed operands: 1.97-2.03 PFLOP/s against 1.77-1.82).  Measured, whole layer, 32x32x16 -> 16x16x32:
+// power the matrix pipes draw, and the narrow instruction spends less per multiplication, in the order used here, which keeps
+// an activation fragment over the four weight fragments (a loop of nothing but MFMAs on normally distributed operands with the
+// accumulators of this kernel: 2.07 PFLOP/s against 1.85; with other orders of the narrow one 1.46 and 1.02).  Measured,
+// whole layer, 32x32x16 -> 16x16x32:
 // 65536 tokens 13.96 -> 13.36 ms, 16384 tokens x 2 skewed over 64 experts 7.70 -> 7.47 ms, 2048 tokens on 8 experts
 // 575 -> 560 us, 4096 tokens on 32 experts 1367 -> 1346 us, 512 tokens unchanged.
 template <int MBS>
@@ -345,10 +347,11 @@ __device__ inline void stage_block(u32x4& v, uint4* lds_buf, unsigned tid, int m
 //   b        : weight fragments of this step
 //   a_next, b_next : registers of the next step's activations and weights (loads in flight)
 //   issue_a  : issue_a(integral_constant mb) issues the activation load of row block mb this step prefetches
-//   issue_b  : issue_b(integral_constant i) issues load i of the kKS * NF weight loads this step prefetches
+//   issue_b  : issue_b(integral_constant i) issues load i of the kKS * 2 NF weight loads this step prefetches
 // After MFMA s of a unit comes its s-th other instruction, in this order: the LDS reads of the next
 // unit's fragments, the staging of the row blocks that fall to this unit (each behind its own wait), the
-// unit's activation load, its weight loads.  The last unit holds the barrier after its second MFMA: all
+// unit's activation load, its weight loads.  The last unit holds the barrier after its fourth MFMA (after its
+// second if it has no more than four): all
 // fragments of this step were requested a unit earlier and nxt was completed a unit earlier, so the wait
 // in front of the barrier finds nothing outstanding, and the first fragments of the next step are read
 // from nxt under the remaining MFMAs.  nxt may be written from the start of the step: its last readers
@@ -701,13 +704,13 @@ __device__ inline void ffn_tile(uint4 (&lds)[2][kTileM * kLdsRow], const uint16_
     for (int i = 0; i < kWarm; ++i) warm[i] = u32x4{0u, 0u, 0u, 0u};
     // Epilogue through LDS (the activation buffers are free now).  The weight fragment is the first MFMA
     // operand and the activation fragment the second, so the accumulators hold the transposed tile: lane l
-    // has token row l%32 of its row block and, in v = 4g..4g+3, the four neighbouring output columns
-    // 8g + 4(l/32) + 0..3.  Every wave applies the activation, rounds four neighbours to bf16 and writes them
+    // has token row l%16 of its 16-row block and the four neighbouring output columns 4(l/16) + 0..3 of 16.
+    // Every wave applies the activation, rounds four neighbours to bf16 and writes them
     // as one 8-byte piece into a row-major tile of the block's columns; then the whole block stores that tile
     // with 16 bytes per lane, whole 64-byte segments per row.  All rows are computed (clamped duplicates
     // give finite values), only real rows are stored.
     constexpr int W = 32 * (GATED ? 1 : NF);            // output columns per wave
-    constexpr int kTileRowBytes = 4 * W * 2 + 16;       // padded: 4 dwords mod 32, eight rows x two halves cover the banks once
+    constexpr int kTileRowBytes = 4 * W * 2 + 16;       // padded: neighbouring rows start 4 dwords apart mod 32
     constexpr int kRowsPerPass = W == 32 ? 256 : 128;   // tile rows that fit the LDS
     constexpr int kLanesPerRow = W / 2;                 // 16-byte stores per tile row
     constexpr int kRowsPerIter = 256 / kLanesPerRow;
@@ -733,8 +736,8 @@ __device__ inline void ffn_tile(uint4 (&lds)[2][kTileM * kLdsRow], const uint16_
 #pragma unroll
     for (int p0 = 0; p0 < MBS * 32; p0 += kRowsPerPass) {
         if (p0 > 0) __syncthreads();                    // the previous pass has been stored
-        // the choice of activation is taken once per pass, outside the value loops, so that the sixteen
-        // independent evaluations of a fragment can overlap
+        // the choice of activation is taken once per pass, outside the value loops, so that the independent
+        // evaluations of a wave can overlap
         auto fill = [&](auto exact) {
 #pragma unroll
             for (int rb = p0 / 16; rb < 2 * MBS && rb < (p0 + kRowsPerPass) / 16; ++rb) {

@@ -71,7 +71,8 @@ __device__ inline bool find_tile(const int32_t* __restrict__ offsets, int e_firs
 // What bounds it: the matrix instruction (157 TFLOP/s) once there are enough blocks, the latency of the steps of one block
 // in short launches.  The kernel it replaces (vector multiply-adds, scalar loads, no load in flight across steps) ran at
 // 18 TFLOP/s.  Whole layer before -> after, with the rows read and written through the permutation: 64 tokens, d 256, f 512,
-// 4 experts 144 -> 23 us; 512 tokens x 2, d 1024, f 4096, 8 experts 1386 -> 340 us.
+// 4 experts 144 -> 23 us; 512 tokens x 2, d 1024, f 4096, 8 experts 1386 -> 340 to
+// 365 us by the rows per expert.
 // Two shapes of a block (four waves, each with 32 x 32 output tiles, twice that when GATED):
 //   wide   64 rows x 64 columns, a wave per quarter, 32 reduction elements per step
 //   split  32 rows x 32 columns, all four waves on the same tile, each with a quarter of the reduction dimension, 16

@@ -2,8 +2,8 @@
 // else, and with few experts hit, or small ones, the tiles of the large kernel are too few to have enough of that read in
 // flight.  Here a wave owns 16 columns (32 in the down-projection of more than 16 rows) for up to 64 rows of an expert, in blocks of
 // one or two waves that know nothing of each other: some ten times the waves of the large kernel, no barrier, no LDS, weights and
-// activations straight into operand registers several steps ahead.  A column's sum is one chain over the reduction dimension that starts where the large kernel
-// starts it: both kernels give the same bits, so a row's result depends neither on the batch it came in nor on which of the
+// activations straight into operand registers several steps ahead.  A column's sum is one chain over the reduction dimension that
+// starts where the large kernel starts it: both kernels give the same bits, so a row's result depends neither on the batch it came in nor on which of the
 // two ran, and the choice between them is a question of time alone.
 // Layer of 32 experts, d 4096, f 10240, large kernel -> here: 1 token 186 -> 61 us, 4 tokens 257 -> 167, 16 tokens 540 -> 508,
 // 40 tokens 906 -> 856.  (A block of four waves that split the steps of a chain between them takes 61, 165, 494 and 863 us,

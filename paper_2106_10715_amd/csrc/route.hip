@@ -3,7 +3,8 @@
 // the lower expert index, softmax combine weights.
 //
 // The selection must be the one exact arithmetic would make.  The kernel therefore accumulates
-// in fp32 with a summation order whose rounding error has a small rigorous bound, compares the gaps
+// in fp32 with a summation order whose rounding error has a small bound (rigorous for the fp32 path; for the matrix
+// instruction of the bf16 path, whose inner rounding is not documented, the largest loss ever observed), compares the gaps
 // between the k+1 best logits with that bound, and re-evaluates only the tokens that are too close to
 // call: products of two bf16 or two fp32 values are exact in fp64, and their sum is carried in two doubles
 // (value and rounding error), which holds it exactly for any inputs of comparable magnitude, so that
@@ -379,13 +380,13 @@ __global__ __launch_bounds__(kWaves * 64) void route_kernel(const XT* __restrict
 // operand pieces: fragment (nb, S, q), slot l, element j holds
 //     W_g[64 S + 32 (l / 32) + 8 q + j, 32 nb + l % 32]            (0 beyond E).
 //
-// Error bound of an MFMA logit (measured behaviour of the instruction: the addends -- accumulator and products -- are
-// aligned to the largest of them and cut to fp32 precision, so one 16x16x32 instruction, 33 addends, loses at most
-// 34 x 2^-24 of its largest addend, which is at most the sum of |products|; 34.0 is the largest loss over 10^8 random
-// instructions, with all addends of one sign, whose sum is then some thirty times the largest): |error| <= (17 n + 8) 2^-24
-// |x_t| |W_g column| with n = two per instruction a wave chains per logit.  Tokens whose k+1 best logits are not separated
-// by twice that are
-// re-evaluated in fp64 by the whole block.
+// Error bound of an MFMA logit, empirical in one constant: the addends of an instruction (accumulator and products) behave as if
+// aligned to the largest of them and cut to fp32 precision, so that one 16x16x32 instruction, 33 addends, loses at most 34 x 2^-24
+// of its largest addend, which is at most the sum of |products|.  34.0 is also the largest loss seen over 10^8 random
+// instructions (with all addends of one sign, whose sum is then some thirty times the largest); it is used without a margin of
+// its own, beside the 1/16 on the whole bound.  |error| <= (17 n + 8) 2^-24 |x_t| |W_g column| with n = two per instruction a
+// wave chains per logit.  Tokens whose k+1 best logits are not separated by twice that are re-evaluated from exact products by
+// the whole block.
 
 constexpr int kGateWaves = 8;    // waves of a gate block; they split the reduction dimension
 

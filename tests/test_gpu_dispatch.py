@@ -67,7 +67,8 @@ def test_f32_layer_without_copy_and_combine():
                          ids=lambda c: "x".join(map(str, c[:4])) + f"-{sum(c)}")
 @pytest.mark.parametrize("d,f", [(64, 64), (192, 704), (1024, 576)])
 def test_few_rows_expert_ffn(counts, d, f):
-    """Up to 32 rows in all run on kernels of their own (16 or 32 rows per expert); 33 rows and more do not."""
+    """Blocks of 16 and 32 rows per expert, up to 16 rows in all (units of 16 columns) and more; one expert with 33 rows is past
+    the limit of 32 rows per expert."""
     got, ref, offsets = run_ffn(sum(counts), d, f, len(counts), 1, "bf16", counts, d % 128 // 64, seed=sum(counts) + d)
     for e in range(len(counts)):
         lo, hi = offsets[e], offsets[e + 1]
@@ -232,3 +233,50 @@ def test_rows_out_and_back(T, d, k, dtype):
     half = 2.0 ** -8 if dtype == "bf16" else 2.0 ** -24
     fp32_sum = w.sum(1, keepdim=True).double() * Yp.abs().max().double() * (k * 2.0 ** -24)
     assert ((y.double() - ref).abs() <= fp32_sum + (ref.abs() + fp32_sum) * half).all()
+
+
+# Limits of rows in all, by E x ceil(d / 256): 32 E below 86, 8 E up to 256, 2 E beyond (256 compute units).
+@pytest.mark.parametrize("d,E,limit", [(320, 7, 224), (1024, 22, 176), (1024, 64, 512), (1024, 65, 130)])
+@pytest.mark.parametrize("heavy", [1, 33, 64, 65, 128])
+@pytest.mark.parametrize("over", [0, 1])
+def test_few_rows_limits_and_crowded_experts(d, E, limit, heavy, over):
+    """The last batch on the kernels for few rows and the first on the others, even and with many rows on one expert."""
+    rest = limit + over - heavy
+    counts = [rest // (E - 1) + (e <= rest % (E - 1)) for e in range(E)]
+    counts[0] = heavy
+    counts[1] += limit + over - sum(counts)
+    got, ref, offsets = run_ffn(sum(counts), d, 128, E, 1, "bf16", counts, 0, seed=d + E + heavy)
+    for e in range(E):
+        lo, hi = offsets[e], offsets[e + 1]
+        if hi > lo:
+            assert rel_l2(got[lo:hi], ref[lo:hi]) <= TOL["bf16"], f"expert {e}"
+
+
+@pytest.mark.parametrize("T,crowd", [(16, 1.0), (33, 1.0), (65, 1.0), (200, 1.0), (200, 0.2), (224, 1.0)])
+def test_few_rows_gathered_equals_batched(T, crowd):
+    """The layer looks its rows up in x; with nearly all tokens on one expert as with a few, the four calls give the same bytes."""
+    d, f, E = 320, 192, 7
+    rng = np.random.default_rng(T)
+    cfg = M.MoeCfg.make(T, d, f, E, 1, "bf16")
+    x, Wg, _ = make_inputs(T, T, d, E, "bf16")
+    bias = np.zeros(E, dtype=np.float32)
+    bias[3] = 5.0 * crowd
+    ex = [tuple(rounded(rng.standard_normal(s) * 0.05, "bf16") for s in ((d, f), (d, f), (f, d))) for _ in range(E)]
+    packed = H.pack_experts(W.Workload("t", T, d, f, E, 1, "bf16", 0), cfg, experts=lambda e: ex[e])[0]
+    dx, dW, db = H.to_device(x, "bf16"), H.to_device(Wg, "bf16"), torch.from_numpy(bias).cuda()
+    ws = torch.empty(M.moe_workspace_bytes(cfg), dtype=torch.uint8, device="cuda")
+    y = torch.full_like(dx, float("nan"))
+    M.moe_layer_forward(cfg, dx, dW, db, packed, None, y, ws)
+
+    def ints(*n):
+        return torch.empty(n, dtype=torch.int32, device="cuda")
+    idx, w, counts, offsets, perm, inv = ints(T, 1), torch.empty((T, 1), device="cuda"), ints(E), ints(E + 1), ints(T), ints(T)
+    Xp, Yp, y4 = torch.empty_like(dx), torch.empty_like(dx), torch.empty_like(dx)
+    M.moe_route(cfg, dx, dW, db, idx, w, ws)
+    M.moe_permute(cfg, dx, idx, counts, offsets, perm, inv, Xp, ws)
+    M.moe_expert_ffn(cfg, Xp, offsets, packed, Yp, ws)
+    M.moe_combine(cfg, Yp, inv, w, y4)
+    torch.cuda.synchronize()
+    assert torch.equal(y, y4)
+    ref = O.layer_forward(x, Wg, lambda e: ex[e], E, 1, bias, 1)[0]
+    assert rel_l2(H.to_f64(y), ref) <= TOL["bf16"]
