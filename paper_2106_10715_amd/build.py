@@ -77,6 +77,11 @@ def _vregs(text: str) -> set:
     return out
 
 
+def _load_dst(text: str) -> set:
+    """Registers a vector memory load writes: its first operand, or none (a load into LDS, whose first operand is an address)."""
+    return set() if "_lds_" in text.split()[0] else _vregs(text.split(",")[0])
+
+
 def check_loads_in_flight(asm: str, kernel_pattern: str, what: str = "assembly") -> int:
     """The pipelined loops of the named kernels keep loads in flight that the compiler does not know about
     (it sees inline assembly that defines registers).  Whatever it schedules or copies there, no instruction
@@ -129,8 +134,7 @@ def check_loads_in_flight(asm: str, kernel_pattern: str, what: str = "assembly")
                                 raise RuntimeError(f"{what}: {kernel}: line {ln} ({t}) touches v{min(used & regs)}, whose load "
                                                    f"(line {at}) has not been waited for")
                         if op.startswith(("global_load", "buffer_load", "flat_load")):
-                            dst = _vregs(t.split(",")[0])
-                            pending.append((dst, ln))
+                            pending.append((_load_dst(t), ln))
                 checked += 1
                 n = m
         n += 1
@@ -182,7 +186,7 @@ def check_prologue_in_flight(asm: str, kernel_pattern: str, what: str = "assembl
                                 raise RuntimeError(f"{what}: {kernel}: line {m + 1} ({code}) touches v{min(used & regs)}, whose "
                                                    f"load (line {at}) has not been waited for")
                         if in_asm and op.startswith(("global_load", "buffer_load", "flat_load")):
-                            pending.append((_vregs(code.split(",")[0]), m + 1))
+                            pending.append((_load_dst(code), m + 1))
                 m += 1
             checked += 1
             n = m

@@ -151,42 +151,39 @@ __global__ __launch_bounds__(SMALL ? 64 : 128, few_waves_per_simd(SMALL)) void f
 // ------------------------------------------------------------------------------------------ bf16 MFMA
 //
 // Software pipeline of one block (4 waves, up to 256 rows of one expert, 64 reduction elements per
-// step).  In step c every thread
-//     issues its share of the activation tile of step c+1            (global -> registers)
-//     issues its wave's weight fragments of step c+2                 (global -> registers, ring of 3)
-//     runs the MFMAs of step c (weights from the ring, activations from LDS buffer c%2, the LDS
-//         reads of k-step s+1 overlapping the MFMAs of k-step s)
-//     waits for the activation registers, stores them to LDS buffer (c+1)%2, barrier.
+// step).  In step c every wave
+//     issues its share of the activation tile of step c + D          (global -> LDS buffer (c + D) % R)
+//     issues its weight fragments of step c + D                      (global -> registers, ring of R sets)
+//     runs the MFMAs of step c (weights from the ring, activations from LDS buffer c % R, the LDS reads of a group
+//         of MFMAs overlapping the group before it)
+//     waits for its loads of step c + 1, barrier.
 // The compiler would sink all those loads down to their first use and wait there, which serialises
 // the pipeline, and it removes prefetches whose result is never read, which changes how many loads
 // are in flight.  So every global load of the loop is issued from inline assembly (pinned in program
 // order, never removed) and the one wait per step is written by hand: vector memory loads return in
-// order, hence "at most 4*NF loads outstanding" at the end of step c means everything but the weight
-// fragments issued in this very step has arrived -- the activations of step c+1 and, being older, the
-// weights of step c+1.  The wait names those registers as read-write operands so that no use of them
-// can be moved above it.
+// order, hence "at most N loads outstanding", N those issued after the loads of step c + 1, means that these have
+// arrived.  The wait names the weight registers as read-write operands so that no use of them can be moved above it.
+// Why the activations go straight into the LDS: it takes the staging writes and 64 registers out of the loop, and lets the activations be
+// requested as early as the weights (loads return in order: one that is waited for soon after its issue makes every older one be waited for as
+// well).  Measured against activations staged through registers one and a half steps ahead, whole layer: 65536 tokens on 32 experts
+// 13.64 -> 12.82 ms, 16384 tokens x 2 skewed over 64 experts 7505 -> 7261 us, 2048 tokens on 8 experts 568 -> 564, 4096 on 32
+// the same.  One step more or less of lead changes nothing: a compute unit has some 44 KiB of loads in flight at most, after which their issue blocks.
 
 constexpr int kKC = 64;                 // reduction elements staged per pipeline step (2 MFMA k-steps)
 constexpr int kKS = kKC / 32;           // MFMA k-steps per pipeline step
 constexpr uint32_t kStepBytes = (kKC / 16) * 2048;   // bytes of a wave's weight stream one pipeline step spans
-constexpr int kLdsRow = 9;              // uint4 per activation row in LDS: 128 B of data + 16 B pad (conflict-free)
+constexpr int kLdsRow = 8;              // uint4 per activation row in LDS: 128 B; piece p of row r lies at place p ^ (r % 8)
+constexpr int kLdsBytes = 4 * kTileM * kLdsRow * 16;   // four activation tiles of the full height
 
 typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 
 template <int NF>
 struct BFrags { u32x4 v[kKS][2 * NF]; };    // one pipeline step of one wave: 2 k-steps x NF column units x 2 halves of 16 columns
-template <int MBS>
-struct ARegs { u32x4 v[MBS]; };         // this thread's share of one activation tile step
 
 __device__ inline bf16x8 as_bf16x8(const u32x4& u) { return __builtin_bit_cast(bf16x8, u); }
 __device__ inline bf16x8 as_bf16x8(const uint4& u) { return __builtin_bit_cast(bf16x8, u); }
 
-// 16-byte load from (uniform base + per-lane byte offset + immediate), pinned in program order.
-template <int IMM>
-__device__ inline void ld_pinned(u32x4& dst, uint32_t voff, const void* sbase) {
-    asm volatile("global_load_dwordx4 %0, %1, %2 offset:%3" : "=v"(dst) : "v"(voff), "s"(sbase), "n"(IMM) : "memory");
-}
-// The weight loads.  An expert with one row tile reads its weights once: marked non-temporal they do
+// The weight loads: 16 bytes from (uniform base + per-lane byte offset + immediate), pinned in program order.  An expert with one row tile reads its weights once: marked non-temporal they do
 // not push the activation tiles (which every column group of the expert re-reads) out of the L2, and the
 // stream itself runs faster (a plain read stream of this shape reaches 6.2 TB/s, a non-temporal one 7.1).
 // An expert with several row tiles re-reads its weights once per tile: there the plain load, which leaves them
@@ -205,43 +202,28 @@ __device__ inline void ld_pinned_stream(u32x4& dst, uint32_t voff, const void* s
 // g / 2, slot 32 (g % 2) + c (+ 16 for the upper half of the columns).  So a lane's offset inside the 4 KiB of a k-step is
 // the constant below, and one load covers four runs of 256 bytes, whole cache lines, the other half of the columns the rest.
 __device__ inline uint32_t weight_lane_offset(int lane) { return ((lane >> 5) << 11) + (((lane >> 4) & 1) << 9) + ((lane & 15) << 4); }
-// voff = weight_lane_offset + byte offset of the pipeline step in the wave's stream.
-template <bool KEEP, int NF>
-__device__ inline void load_b(BFrags<NF>& b, uint32_t voff, const void* wave_base) {
-    const uint32_t voff2 = voff + 4096;
-    ld_pinned_stream<0, KEEP>(b.v[0][0], voff, wave_base);
-    ld_pinned_stream<256, KEEP>(b.v[0][1], voff, wave_base);
-    if (NF == 2) ld_pinned_stream<1024, KEEP>(b.v[0][2 * NF - 2], voff, wave_base);
-    if (NF == 2) ld_pinned_stream<1280, KEEP>(b.v[0][2 * NF - 1], voff, wave_base);
-    ld_pinned_stream<0, KEEP>(b.v[1][0], voff2, wave_base);
-    ld_pinned_stream<256, KEEP>(b.v[1][1], voff2, wave_base);
-    if (NF == 2) ld_pinned_stream<1024, KEEP>(b.v[1][2 * NF - 2], voff2, wave_base);
-    if (NF == 2) ld_pinned_stream<1280, KEEP>(b.v[1][2 * NF - 1], voff2, wave_base);
-}
-
 // Wait until at most N_YOUNGER loads are outstanding; the registers named become usable afterwards.
-template <int N_YOUNGER, int NF, int MBS>
-__device__ inline void wait_loads(ARegs<MBS>& a, BFrags<NF>& b) {
+template <int N_YOUNGER, int NF>
+__device__ inline void wait_loads(BFrags<NF>& b) {
+    static_assert(N_YOUNGER <= 63, "the counter's range");
     asm volatile("s_waitcnt vmcnt(%0)" : : "n"(N_YOUNGER) : "memory");
-#pragma unroll
-    for (int mb = 0; mb < MBS; ++mb) asm volatile("" : "+v"(a.v[mb]));
 #pragma unroll
     for (int ks = 0; ks < kKS; ++ks)
 #pragma unroll
         for (int j = 0; j < 2 * NF; ++j) asm volatile("" : "+v"(b.v[ks][j]));
 }
-// The activation tile lives in LDS row-major, one padded row of kLdsRow uint4 per tile row.
-// Staging: thread t moves, for i < MBS, the 16-byte piece (row i*32 + t/8, piece t%8): eight
-// neighbouring lanes fetch one whole 128-byte line of a row, and write 128 contiguous bytes of LDS.
-template <int MBS>
-__device__ inline void store_a(const ARegs<MBS>& a, uint4* lds_buf, unsigned tid) {
-    u32x4* p = reinterpret_cast<u32x4*>(lds_buf) + (tid >> 3) * kLdsRow + (tid & 7);
-#pragma unroll
-    for (int mb = 0; mb < MBS; ++mb) p[mb * 32 * kLdsRow] = a.v[mb];
+// An activation tile lies in LDS row-major, 128 bytes per row.  Thread t moves, for mb < MBS, the 16 bytes at place t % 8 of row
+// 32 mb + t / 8: eight neighbouring lanes fetch one whole 128-byte line of a row, a wave fills 1 KiB, lane after lane, as the load into
+// LDS wants it.  Place p of row r holds piece p ^ (r % 8), so that the fragment reads, one piece of 16 rows each, meet all banks.
+// The load: 16 bytes per lane from (uniform base + per-lane byte offset) to LDS byte (base + OFFSET + 16 lane).
+template <int OFFSET>
+__device__ inline void ld_to_lds(uint32_t lds_base, uint32_t voff, const void* sbase) {
+    // (one wait state between the write of m0 and its use)
+    asm volatile("s_add_u32 m0, %0, %3\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2" : : "s"(lds_base), "v"(voff), "s"(sbase), "n"(OFFSET) : "memory", "scc");
 }
 
-// The MFMAs of a pipeline step are issued in units: unit u = (k-step u / H, row group u % H), H = 2 or 4 groups of
-// at most 4 blocks of 16 rows.  The A fragments of unit u+1 are read from LDS while the MFMAs of unit u run; two
+// The MFMAs of a pipeline step (RB blocks of 16 rows) are issued in units: unit u = (k-step u / H, row group u % H), H = 2 or 4
+// groups of at most 4 blocks.  The A fragments of unit u+1 are read from LDS while the MFMAs of unit u run; two
 // register buffers of G fragments alternate.
 // Fragment (rb, ks) of lane l = row rb*16 + l%16, 8 elements at k = 32 ks + 8 (l / 16).
 // Why 16x16x32 and not 32x32x16, in whose operand order the weights are packed: experts with many rows are bound by the
@@ -251,33 +233,19 @@ __device__ inline void store_a(const ARegs<MBS>& a, uint4* lds_buf, unsigned tid
 // whole layer, 32x32x16 -> 16x16x32:
 // 65536 tokens 13.96 -> 13.36 ms, 16384 tokens x 2 skewed over 64 experts 7.70 -> 7.47 ms, 2048 tokens on 8 experts
 // 575 -> 560 us, 4096 tokens on 32 experts 1367 -> 1346 us, 512 tokens unchanged.
-template <int MBS>
+template <int RB>
 struct Units {
-    static constexpr int RB = 2 * MBS;
-    static constexpr int H = MBS > 4 ? 4 : 2;
+    static constexpr int MBS = (RB + 1) / 2;                       // blocks of 32 rows the activations are staged in
+    static constexpr int H = RB > 8 ? 4 : 2;
     static constexpr int G = (RB + H - 1) / H;
     static constexpr int U = kKS * H;
+    static constexpr int R = 4;                                    // activation tiles in LDS, weight sets in registers
+    static constexpr int D = R - 1;                                // steps loads are issued ahead; a buffer is refilled one step after its own
+    static constexpr int kBuf = MBS * 32 * kLdsRow * 16;           // bytes of an activation tile
+    static_assert(R * kBuf <= kLdsBytes, "the activation tiles fit the LDS");
     static constexpr int first(int u) { return (u % H) * RB / H; }               // first 16-row block of unit u
     static constexpr int count(int u) { return (u % H + 1) * RB / H - first(u); }   // and how many it has
 };
-
-template <int MBS, int UNIT>
-__device__ inline void read_unit(uint4 (&af)[Units<MBS>::G], const uint4* lds_buf, int lane) {
-    constexpr int ks = UNIT / Units<MBS>::H, rb0 = Units<MBS>::first(UNIT);
-    const uint4* rp = lds_buf + (lane & 15) * kLdsRow + (lane >> 4) + 4 * ks;
-#pragma unroll
-    for (int i = 0; i < Units<MBS>::count(UNIT); ++i) af[i] = rp[(rb0 + i) * 16 * kLdsRow];
-}
-
-template <int NF, int MBS, int UNIT>
-__device__ inline void mma_unit(f32x4 (&acc)[2 * MBS][2 * NF], const uint4 (&af)[Units<MBS>::G], const BFrags<NF>& b) {
-    constexpr int ks = UNIT / Units<MBS>::H, rb0 = Units<MBS>::first(UNIT);
-#pragma unroll
-    for (int i = 0; i < Units<MBS>::count(UNIT); ++i)
-#pragma unroll
-        for (int j = 0; j < 2 * NF; ++j)
-            acc[rb0 + i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(as_bf16x8(b.v[ks][j]), as_bf16x8(af[i]), acc[rb0 + i][j], 0, 0, 0);
-}
 
 template <int LO, int HI, class F>
 __device__ inline void static_for(F&& f) {
@@ -291,111 +259,69 @@ __device__ inline void static_for(F&& f) {
 // MFMA: a load or an LDS access holds the wave's issue slot for some 16 cycles and the matrix pipe
 // has only one instruction queued, so a run of them lets it run dry, and a wait that directly follows
 // the LDS writes of the whole tile stalls the wave for their full latency.
-// Loads (or LDS writes) done after the units 0..u of a step that spreads n of them evenly over U units:
+// Loads done after the units 0..u of a step that spreads n of them evenly over U units:
 constexpr int loads_upto(int u, int n, int U) { return u < 0 ? 0 : ((u + 1) * n + U - 1) / U < n ? ((u + 1) * n + U - 1) / U : n; }
-// The staging writes (one per row block) go into the units before the last one, which holds the barrier:
-// spread evenly, except that one or two row blocks are staged as late as that allows.  Their steps are so
-// short (one or two MFMAs per unit) that the step time is the time their activation loads take to arrive,
-// and every unit the write waits is lead for the load.
-constexpr int writes_upto(int u, int n, int U) {
-    if (n <= 2) {
-        const int done = u - (U - 1 - n) + 1;
-        return done < 0 ? 0 : (done > n ? n : done);
-    }
-    return loads_upto(u, n, U - 1);
-}
-constexpr int unit_of_write(int w, int n, int U) {
-    int u = 0;
-    while (writes_upto(u, n, U) <= w) ++u;
-    return u;
-}
 // Global loads a step has issued before those of unit u: one activation load per unit while there are
 // row blocks left, then the unit's share of the nb weight loads.
 constexpr int issued_before(int u, int MBS, int nb, int U) { return (u < MBS ? u : MBS) + loads_upto(u - 1, nb, U); }
-// Loads younger than the activation load of row block w at the moment the next step stages that block:
-// what the issuing step issued after it, and what the staging step has issued before the unit that
-// stages it.  Loads return in order, so waiting until at most this many are outstanding means the block
-// (and every weight load older than it) has landed.
-constexpr int younger_at_write(int w, int MBS, int nb, int U) {
-    return (MBS + nb - issued_before(w, MBS, nb, U) - 1) + issued_before(unit_of_write(w, MBS, U), MBS, nb, U);
-}
 
-// fragment I of unit UNIT, from the activation tile in lds_buf
-template <int MBS, int UNIT, int I>
-__device__ inline void read_frag(uint4 (&af)[Units<MBS>::G], const uint4* lds_buf, int lane) {
-    constexpr int ks = UNIT / Units<MBS>::H, rb = Units<MBS>::first(UNIT) + I;
-    af[I] = lds_buf[(lane & 15) * kLdsRow + (lane >> 4) + 4 * ks + rb * 16 * kLdsRow];
+// fragment I of unit UNIT, from the activation tile at `tile`: lane 16 g + c holds row c of its 16-row block, piece 4 ks + g
+template <int RB, int UNIT, int I>
+__device__ inline void read_frag(uint4 (&af)[Units<RB>::G], const uint4* tile, int lane) {
+    constexpr int ks = UNIT / Units<RB>::H, rb = Units<RB>::first(UNIT) + I;
+    const int at = (lane & 15) * kLdsRow + (((lane >> 4) ^ (lane & 3)) | (lane & 4));      // ((lane >> 4) + 4 ks) ^ (lane % 8) without ks
+    af[I] = tile[(at ^ (4 * ks)) + rb * 16 * kLdsRow];
 }
 // MFMA M of unit UNIT: 16-row block M / (2 NF) of the unit, weight fragment M % (2 NF)
-template <int NF, int MBS, int UNIT, int M>
-__device__ inline void mma_one(f32x4 (&acc)[2 * MBS][2 * NF], const uint4 (&af)[Units<MBS>::G], const BFrags<NF>& b) {
-    constexpr int ks = UNIT / Units<MBS>::H, i = M / (2 * NF), j = M % (2 * NF), rb = Units<MBS>::first(UNIT) + i;
+template <int NF, int RB, int UNIT, int M>
+__device__ inline void mma_one(f32x4 (&acc)[RB][2 * NF], const uint4 (&af)[Units<RB>::G], const BFrags<NF>& b) {
+    constexpr int ks = UNIT / Units<RB>::H, i = M / (2 * NF), j = M % (2 * NF), rb = Units<RB>::first(UNIT) + i;
     acc[rb][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(as_bf16x8(b.v[ks][j]), as_bf16x8(af[i]), acc[rb][j], 0, 0, 0);
 }
-// Row block mb of the staged activations has landed once at most N_YOUNGER loads are outstanding; it goes
-// into the LDS tile (thread t holds the 16-byte piece t%8 of row mb*32 + t/8).
-template <int N_YOUNGER>
-__device__ inline void stage_block(u32x4& v, uint4* lds_buf, unsigned tid, int mb) {
-    asm volatile("s_waitcnt vmcnt(%0)" : : "n"(N_YOUNGER) : "memory");
-    asm volatile("" : "+v"(v));
-    reinterpret_cast<u32x4*>(lds_buf)[(tid >> 3) * kLdsRow + (tid & 7) + mb * 32 * kLdsRow] = v;
-}
-
 // One pipeline step.  Entering, af[0] holds the fragments of unit 0 of this step; leaving, those of
 // unit 0 of the next step.
-//   cur, nxt : LDS buffers of this and of the next step
+//   cur, nxt : activation tiles of this and of the next step
 //   b        : weight fragments of this step
-//   a_next, b_next : registers of the next step's activations and weights (loads in flight)
+//   b_next   : registers of the next step's weights (loads in flight)
 //   issue_a  : issue_a(integral_constant mb) issues the activation load of row block mb this step prefetches
 //   issue_b  : issue_b(integral_constant i) issues load i of the kKS * 2 NF weight loads this step prefetches
 // After MFMA s of a unit comes its s-th other instruction, in this order: the LDS reads of the next
-// unit's fragments, the staging of the row blocks that fall to this unit (each behind its own wait), the
-// unit's activation load, its weight loads.  The last unit holds the barrier after its fourth MFMA (after its
-// second if it has no more than four): all
-// fragments of this step were requested a unit earlier and nxt was completed a unit earlier, so the wait
-// in front of the barrier finds nothing outstanding, and the first fragments of the next step are read
-// from nxt under the remaining MFMAs.  nxt may be written from the start of the step: its last readers
-// passed the barrier of the step before.
-template <int NF, int MBS, class IssueA, class IssueB>
-__device__ inline void run_step(f32x4 (&acc)[2 * MBS][2 * NF], uint4 (&af)[2][Units<MBS>::G], const uint4* cur, uint4* nxt,
-                                const BFrags<NF>& b, ARegs<MBS>& a_next, BFrags<NF>& b_next, int lane, unsigned tid,
-                                IssueA issue_a, IssueB issue_b) {
-    constexpr int U = Units<MBS>::U, kB = kKS * 2 * NF;
+// unit's fragments, the unit's activation load, its weight loads.  The last unit holds the wait for the next step's loads and the
+// barrier after its fourth MFMA (after its second if it has no more than four): all fragments of this step were requested a unit earlier,
+// so nothing but those loads is waited for, and the first fragments of the next step are read under the remaining MFMAs.
+// The tile this step prefetches may be overwritten from its start on: its last readers passed the barrier of the step before.
+template <int NF, int RB, class IssueA, class IssueB>
+__device__ inline void run_step(f32x4 (&acc)[RB][2 * NF], uint4 (&af)[2][Units<RB>::G], const uint4* cur, const uint4* nxt,
+                                const BFrags<NF>& b, BFrags<NF>& b_next, int lane, IssueA issue_a, IssueB issue_b) {
+    constexpr int MBS = Units<RB>::MBS, U = Units<RB>::U, kB = kKS * 2 * NF;
     static_for<0, U>([&](auto uc) {
         constexpr int UU = decltype(uc)::value;
         constexpr bool kLast = UU + 1 == U;
-        constexpr int M = Units<MBS>::count(UU) * 2 * NF;          // MFMAs of this unit
+        constexpr int M = Units<RB>::count(UU) * 2 * NF;           // MFMAs of this unit
         constexpr int NU = kLast ? 0 : UU + 1;                     // the unit whose fragments are fetched meanwhile
-        constexpr int nR = Units<MBS>::count(NU);
-        constexpr int w0 = kLast ? MBS : writes_upto(UU - 1, MBS, U), nW = (kLast ? MBS : writes_upto(UU, MBS, U)) - w0;
+        constexpr int nR = Units<RB>::count(NU);
         constexpr int nA = UU < MBS ? 1 : 0;
         constexpr int b0 = loads_upto(UU - 1, kB, U), nB = loads_upto(UU, kB, U) - b0;
-        constexpr int nOther = nR + nW + nA + nB;
+        constexpr int nOther = nR + nA + nB;
         constexpr int kFirst = !kLast ? 0 : M > 4 ? 3 : 1;         // other instruction s follows MFMA kFirst + kEvery s
         constexpr int kEvery = M - kFirst >= 2 * nOther ? 2 : 1;
         auto other = [&](auto sc) {
             constexpr int s = decltype(sc)::value;
-            if constexpr (s < nR) {
-                read_frag<MBS, NU, s>(af[NU & 1], kLast ? nxt : cur, lane);
-            } else if constexpr (s < nR + nW) {
-                constexpr int w = w0 + s - nR;
-                stage_block<younger_at_write(w, MBS, kB, U)>(a_next.v[w], nxt, tid, w);
-                if constexpr (w == 0) {                            // the weights of the next step are older than its activations
-#pragma unroll
-                    for (int ks = 0; ks < kKS; ++ks)
-#pragma unroll
-                        for (int j = 0; j < 2 * NF; ++j) asm volatile("" : "+v"(b_next.v[ks][j]));
-                }
-            } else if constexpr (s < nR + nW + nA) {
+            if constexpr (s < nR)
+                read_frag<RB, NU, s>(af[NU & 1], kLast ? nxt : cur, lane);
+            else if constexpr (s < nR + nA)
                 issue_a(std::integral_constant<int, UU + 0 * s>{});     // (made dependent on s: only instantiated when taken)
-            } else {
-                issue_b(std::integral_constant<int, b0 + s - nR - nW - nA>{});
-            }
+            else
+                issue_b(std::integral_constant<int, b0 + s - nR - nA>{});
         };
         static_for<0, M>([&](auto mc) {
             constexpr int m = decltype(mc)::value;
-            mma_one<NF, MBS, UU, m>(acc, af[UU & 1], b);
-            if constexpr (kLast && m == kFirst) __syncthreads();
+            mma_one<NF, RB, UU, m>(acc, af[UU & 1], b);
+            if constexpr (kLast && m == kFirst) {
+                // younger than the loads of the next step: those of the D - 2 steps after it and what this step has issued
+                wait_loads<(Units<RB>::D - 2) * (MBS + kB) + issued_before(UU, MBS, kB, U)>(b_next);
+                __syncthreads();
+            }
             if constexpr (m >= kFirst) {
                 constexpr int before = (m - kFirst + kEvery - 1) / kEvery, lo = before < nOther ? before : nOther;
                 constexpr int upto = (m - kFirst) / kEvery + 1, hi = m == M - 1 || upto > nOther ? nOther : upto;
@@ -403,24 +329,6 @@ __device__ inline void run_step(f32x4 (&acc)[2 * MBS][2 * NF], uint4 (&af)[2][Un
             }
         });
     });
-}
-
-// A step without any overlap, for the few steps that do not fill a group of the unrolled pipeline:
-// fetch, wait, stage, compute.  Uses LDS buffer 0 and the registers passed in; nothing stays in flight.
-template <int NF, int MBS>
-__device__ inline void slow_step(f32x4 (&acc)[2 * MBS][2 * NF], uint4 (&af)[2][Units<MBS>::G], uint4* buf, ARegs<MBS>& a,
-                                 BFrags<NF>& b, int lane, unsigned tid) {
-    wait_loads<0>(a, b);
-    __syncthreads();                            // nobody reads buf any more
-    store_a(a, buf, tid);
-    __syncthreads();
-#define FFN_UNIT(UU)                                                          \
-    if constexpr ((UU) < Units<MBS>::U) {                                     \
-        read_unit<MBS, (UU)>(af[0], buf, lane);                               \
-        mma_unit<NF, MBS, (UU)>(acc, af[0], b);                               \
-    }
-    FFN_UNIT(0) FFN_UNIT(1) FFN_UNIT(2) FFN_UNIT(3) FFN_UNIT(4) FFN_UNIT(5) FFN_UNIT(6) FFN_UNIT(7)
-#undef FFN_UNIT
 }
 
 // The id of this thread inside its block, rebuilt from the wave number (which sits in a scalar
@@ -499,7 +407,26 @@ __device__ inline unsigned first_positions(unsigned x) { return (gridDim.x + 7u 
 // The first attempt is split from the rest so that its answer can arrive under other work.  Before it asks another queue
 // it looks at all counters at once (they only grow, so an old value costs a vain attempt and nothing else): at the end of a
 // launch every block finds every queue empty, and seven questions one after the other take some 10 us.
-__device__ inline unsigned take_first(const ItemQueue& Q) { return first_positions(Q.home) + atomicAdd(&Q.counters[Q.home], 1u); }
+// (Addresses and the one that is added are made opaque where they are used: constants and parts of addresses would be kept in
+// vector registers across the main loop.)
+template <class T>
+__device__ inline T opaque(T v) {
+    asm volatile("" : "+v"(v));
+    return v;
+}
+// p + offset, for a uniform p (spelled out: a zero upper half of the offset would be such a constant)
+__device__ inline const char* add_offset(const char* p, unsigned offset) {
+    const uint64_t v = reinterpret_cast<uint64_t>(p);
+    unsigned lo, hi = opaque(static_cast<unsigned>(v >> 32));
+    asm volatile("v_add_co_u32 %0, vcc, %2, %3\n\tv_addc_co_u32 %1, vcc, 0, %1, vcc" : "=&v"(lo), "+v"(hi) : "s"(static_cast<unsigned>(v)), "v"(offset) : "vcc");
+    return reinterpret_cast<const char*>(static_cast<uint64_t>(hi) << 32 | lo);
+}
+// (addressed as global memory: a flat atomic's answer would be waited for at the next barrier)
+typedef __attribute__((address_space(1))) unsigned global_counter;
+__device__ inline unsigned take_from(const ItemQueue& Q, unsigned queue) {
+    return first_positions(queue) + __hip_atomic_fetch_add(opaque((global_counter*)(Q.counters + queue)), opaque(1u), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+__device__ inline unsigned take_first(const ItemQueue& Q) { return take_from(Q, Q.home); }
 __device__ inline void take_finish(const ItemQueue& Q, unsigned v, int* sh_q, int* sh_x) {
     int got = -1;
     unsigned x = Q.home;
@@ -509,12 +436,12 @@ __device__ inline void take_finish(const ItemQueue& Q, unsigned v, int* sh_q, in
         unsigned seen[8];
 #pragma unroll
         for (unsigned i = 1; i < 8u; ++i)
-            seen[i] = __hip_atomic_load(&Q.counters[(Q.home + i) & 7u], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            seen[i] = __hip_atomic_load(opaque((global_counter*)(Q.counters + ((Q.home + i) & 7u))), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 #pragma unroll
         for (unsigned i = 1; i < 8u; ++i) {
-            const unsigned y = (Q.home + i) & 7u, first = first_positions(y);
-            if (got < 0 && first + seen[i] < Q.total_q) {
-                const unsigned w = first + atomicAdd(&Q.counters[y], 1u);
+            const unsigned y = (Q.home + i) & 7u;
+            if (got < 0 && first_positions(y) + seen[i] < Q.total_q) {
+                const unsigned w = take_from(Q, y);
                 if (w < Q.total_q) { got = static_cast<int>(w); x = y; }
             }
         }
@@ -523,7 +450,7 @@ __device__ inline void take_finish(const ItemQueue& Q, unsigned v, int* sh_q, in
     *sh_x = static_cast<int>(x);
 }
 
-// One tile of MBS 32-row blocks: the whole reduction loop and the epilogue.
+// One tile of RB blocks of 16 rows: the whole reduction loop and the epilogue.
 // Loads past the end are clamped to valid addresses (rows to the last row of the tile, pipeline steps
 // to the last step) instead of being skipped, so every step issues the same loads.  Rows that are
 // clamped duplicates only produce output rows that are never stored (an output row depends on its own
@@ -531,12 +458,13 @@ __device__ inline void take_finish(const ItemQueue& Q, unsigned v, int* sh_q, in
 // GATHER: A is not the batched row array but the token array it was gathered from, and row r of the batched
 // order is token gather[r] / gather_k of A (the batching of Section 6.2 done on the fly: the batched copy of the
 // activations is never written); every thread then keeps one byte offset per row block instead of two in all.
-template <bool GATED, int NF, int MBS, bool KEEP, bool GATHER = false>
-__device__ inline void ffn_tile(uint4 (&lds)[2][kTileM * kLdsRow], const uint16_t* __restrict__ A, int row_begin, int rows,
+template <bool GATED, int NF, int RB, bool KEEP, bool GATHER = false>
+__device__ inline void ffn_tile(uint4 (&lds)[kLdsBytes / 16], const uint16_t* __restrict__ A, int row_begin, int rows,
                                 const void* wave_base, uint16_t* __restrict__ C, int K, int N, int unit,
                                 bool active, int act, unsigned phase_key, int wave_s, const int32_t* __restrict__ row_map,
                                 const int32_t* __restrict__ gather, int gather_k, const ItemQueue& Q, int units, int* sh_q,
                                 int* sh_x, int h_rows) {
+    constexpr int MBS = Units<RB>::MBS;
     unsigned tid = thread_id(wave_s);
     const int lane = tid & 63;
     // every tile height gets its own copy of the loop bounds: shared ones would be computed once for all
@@ -544,11 +472,11 @@ __device__ inline void ffn_tile(uint4 (&lds)[2][kTileM * kLdsRow], const uint16_
     asm volatile("" : "+s"(K), "+s"(N), "+s"(phase_key));
     const int chunks = K / kKC, last = chunks - 1;
 
-    // this thread's activation sources (byte offsets from A): row mb*32 + t/8 of every block, piece t%8.
+    // this thread's activation sources (byte offsets from A): row mb*32 + t/8 of every block, the piece that lies at place t%8.
     // All blocks but the last hold 32 rows, so their rows lie a fixed stride apart; rows past the end
     // of the last block re-read the tile's last row.
     const int r0 = tid >> 3;
-    const uint32_t piece = 16u * (tid & 7);
+    const uint32_t piece = 16u * ((tid ^ (tid >> 3)) & 7);
     // Layout of A.  The up-projection reads row-major rows (K elements each).  The down-projection reads the
     // intermediate H, which only these two kernels see and which is therefore kept in the order they touch it:
     // [chunk of 64 columns][row][64 columns], all h_rows rows of a chunk back to back, so that a tile's rows of one
@@ -568,46 +496,24 @@ __device__ inline void ffn_tile(uint4 (&lds)[2][kTileM * kLdsRow], const uint16_
         }
     }
 
-    f32x4 acc[2 * MBS][2 * NF];
+    f32x4 acc[RB][2 * NF];
     // cleared in place, in the accumulation registers: a zero constant would be parked in 16 registers for all
     // tile heights and copied from there
 #pragma unroll
-    for (int rb = 0; rb < 2 * MBS; ++rb)
+    for (int rb = 0; rb < RB; ++rb)
 #pragma unroll
         for (int j = 0; j < 2 * NF; ++j)
 #pragma unroll
             for (int v = 0; v < 4; ++v) asm volatile("v_accvgpr_write_b32 %0, 0" : "=a"(acc[rb][j][v]));
 
-    // Pipeline depth: activations 2 steps ahead (two register sets), weights 3 steps ahead (ring of 4).
-    // Step c issues A(c+2) and B(c+3), spread over its MFMA units (after unit u the activation load of row
-    // block u, if there is one, and the weight loads of that unit's share), and stages A(c+1), one row
-    // block at a time, in the units before its last: row block w was requested by step c-1 in unit w and
-    // is waited for about one step later, by the count of loads younger than it (younger_at_write).
-    // Everything older, B(c+1) included, has then landed.
-    constexpr int AD = 2;
-    constexpr int R = AD + 2;                   // weight ring; register indices repeat with period R
+    constexpr int D = Units<RB>::D, R = Units<RB>::R, kBuf = Units<RB>::kBuf;       // register indices and tiles repeat with period R
     constexpr int kB = kKS * 2 * NF;            // loads of one weight step
-    constexpr int kU = Units<MBS>::U;
-    static_assert(MBS <= kU, "one activation load per unit");
-    ARegs<MBS> areg[AD];
+    static_assert(MBS <= Units<RB>::U, "one activation load per unit");
     BFrags<NF> ring[R];
-    uint4 af[2][Units<MBS>::G];
-    // the per-block and per-step parts of the address are uniform: they go into the scalar base, and the
-    // per-thread part is the same register for every block but the last
-    auto fetch_a = [&](ARegs<MBS>& dst, int chunk) {
-        const char* base = reinterpret_cast<const char*>(A) + static_cast<size_t>(chunk) * a_chunk_bytes;
-        if constexpr (GATHER) {
-#pragma unroll
-            for (int mb = 0; mb < MBS; ++mb) ld_pinned<0>(dst.v[mb], a_off[mb], base);
-        } else {
-#pragma unroll
-            for (int mb = 0; mb + 1 < MBS; ++mb) ld_pinned<0>(dst.v[mb], a_first, base + static_cast<size_t>(mb) * a_stride);
-            ld_pinned<0>(dst.v[MBS - 1], a_last, base);
-        }
-    };
-    auto fetch_b = [&](BFrags<NF>& dst, int chunk) {
-        load_b<KEEP>(dst, static_cast<uint32_t>(chunk) * kStepBytes + weight_lane_offset(lane), wave_base);
-    };
+    uint4 af[2][Units<RB>::G];
+    auto tile_of = [&](int buf) { return reinterpret_cast<const uint4*>(reinterpret_cast<const char*>(&lds[0]) + buf * kBuf); };
+    const uint32_t lds_wave = static_cast<uint32_t>(reinterpret_cast<uintptr_t>(reinterpret_cast<__attribute__((address_space(3))) char*>(
+                                  (__attribute__((address_space(3))) uint4*)&lds[0]))) + static_cast<uint32_t>(wave_s) * 1024u;
     const uint32_t lane_off = weight_lane_offset(lane);
     // Blocks that share a weight stream or an activation tile start their sweep over the reduction
     // dimension at the same step (and wrap around), other blocks at other steps, so that concurrent
@@ -616,79 +522,70 @@ __device__ inline void ffn_tile(uint4 (&lds)[2][kTileM * kLdsRow], const uint16_
     // expert sum in the same order (bitwise equal results).
     const int phase = static_cast<int>(phase_key % static_cast<unsigned>(chunks));
     auto at = [&](int i) { const int c = phase + i; return c >= chunks ? c - chunks : c; };   // i < chunks
+    // Loads of step i, row block mb / weight load i of the step, into buffer / set BUF.  The per-block and per-step parts of the address
+    // are uniform: they go into the scalar base, and the per-thread part is the same register for every block but the last.  Past the
+    // last step there is nothing left to prefetch: the loads still issue (the waits count them), but all lanes read the
+    // same 16 bytes, one cache line instead of a KiB per load.
+    struct Source { const char* a; uint32_t first, last, keep, voff; };
+    auto source = [&](int i) __attribute__((always_inline)) {
+        const int k = at(min(i, last));
+        return Source{reinterpret_cast<const char*>(A) + static_cast<size_t>(k) * a_chunk_bytes, i > last ? 0u : a_first, i > last ? 0u : a_last,
+                      i > last ? 0u : ~0u, static_cast<uint32_t>(k) * kStepBytes + (i > last ? 0u : lane_off)};
+    };
+    auto issue_a = [&](const Source& f, auto buf, auto mbc) __attribute__((always_inline)) {
+        constexpr int mb = decltype(mbc)::value, kTo = decltype(buf)::value * kBuf + mb * 4096;
+        if constexpr (GATHER)
+            ld_to_lds<kTo>(lds_wave, a_off[mb] & f.keep, f.a);
+        else if constexpr (mb + 1 < MBS)
+            ld_to_lds<kTo>(lds_wave, f.first, f.a + static_cast<size_t>(mb) * a_stride);
+        else
+            ld_to_lds<kTo>(lds_wave, f.last, f.a);
+    };
+    auto issue_b = [&](const Source& f, auto buf, auto ic) __attribute__((always_inline)) {
+        constexpr int i = decltype(ic)::value, ks = i / (2 * NF), j = i % (2 * NF);
+        ld_pinned_stream<(j >> 1) * 1024 + (j & 1) * 256, KEEP>(ring[decltype(buf)::value].v[ks][j], f.voff + ks * 4096, wave_base);
+    };
     int c = 0;
-    if (chunks >= R) {
-        asm volatile("; pipeline begin");       // from here to the matching end the build allows no spill code
-        // Prologue: A(0) B(0) B(1) A(1) B(2), each as a block; then wait for A(0), B(0).  The first steps find
-        // more loads younger than the ones they wait for than the steady state assumes, which only makes
-        // their waits stricter.
-        fetch_a(areg[0], at(0));
-        fetch_b(ring[0], at(0));
-        fetch_b(ring[1], at(1));
-        if (AD == 2) {
-            fetch_a(areg[1], at(1));
-            fetch_b(ring[2], at(2));
-        }
-        wait_loads<(AD == 2 ? 2 * kB + MBS : kB)>(areg[0], ring[0]);
-        store_a(areg[0], lds[0], tid);
-        __syncthreads();
-        read_unit<MBS, 0>(af[0], lds[0], lane);
-        // Step c = c0 + I, c0 a multiple of R (even when AD = 2): all register indices are static.
-#define FFN_STEP(I)                                                                                        \
-    {                                                                                                      \
-        const int ci = c + (I);                                                                            \
-        const char* a_base = reinterpret_cast<const char*>(A) +                                            \
-                             static_cast<size_t>(at(min(ci + AD, last))) * a_chunk_bytes;                  \
-        /* past the last step there is nothing left to prefetch: the loads still issue (the waits count   \
-           them), but all lanes read the same 16 bytes, one cache line instead of a KiB per load */       \
-        const uint32_t a_first_c = ci + AD > last ? 0u : a_first, a_last_c = ci + AD > last ? 0u : a_last; \
-        const uint32_t a_keep = ci + AD > last ? 0u : ~0u;                                                 \
-        auto issue_a = [&](auto ic) {                                                                      \
-            constexpr int mb = decltype(ic)::value;                                                        \
-            if constexpr (GATHER)                                                                          \
-                ld_pinned<0>(areg[((I) + AD) % AD].v[mb], a_off[mb] & a_keep, a_base);                     \
-            else if constexpr (mb + 1 < MBS)                                                               \
-                ld_pinned<0>(areg[((I) + AD) % AD].v[mb], a_first_c, a_base + static_cast<size_t>(mb) * a_stride); \
-            else                                                                                           \
-                ld_pinned<0>(areg[((I) + AD) % AD].v[mb], a_last_c, a_base);                               \
-        };                                                                                                 \
-        const uint32_t voff = static_cast<uint32_t>(at(min(ci + AD + 1, last))) * kStepBytes +             \
-                              (ci + AD + 1 > last ? 0u : lane_off);                                        \
-        auto issue_b = [&](auto ic) {                                                                      \
-            constexpr int i = decltype(ic)::value, ks = i / (2 * NF), j = i % (2 * NF);                    \
-            ld_pinned_stream<(j >> 1) * 1024 + (j & 1) * 256, KEEP>(ring[((I) + AD + 1) % R].v[ks][j],     \
-                                                                    voff + ks * 4096, wave_base);          \
-        };                                                                                                 \
-        run_step(acc, af, lds[ci & 1], lds[(ci + 1) & 1], ring[(I) % R], areg[((I) + 1) % AD],             \
-                 ring[((I) + 1) % R], lane, tid, issue_a, issue_b);                                        \
-    }
-        for (; c + R <= chunks; c += R) {
-            FFN_STEP(0) FFN_STEP(1) FFN_STEP(2) FFN_STEP(3)
-        }
-#undef FFN_STEP
-        asm volatile("; pipeline end");
-    }
-    // the steps that do not fill a group of R, one by one and without overlap
-    for (; c < chunks; ++c) {
-        asm volatile("s_waitcnt vmcnt(0)" : : : "memory");
-        fetch_a(areg[0], at(c));
-        fetch_b(ring[0], at(c));
-        slow_step(acc, af, lds[0], areg[0], ring[0], lane, tid);
-    }
-    // Drain the prefetches nobody consumes, and only then let go of their destination registers: a
-    // destination the compiler considers dead would be handed to something else (an LDS read, say)
-    // while the load into it is still in flight.
+    auto step = [&](auto ic) __attribute__((always_inline)) {      // step c + I, c a multiple of R: all register indices are static
+        constexpr int I = decltype(ic)::value;
+        const Source f = source(c + I + D);
+        run_step<NF, RB>(acc, af, tile_of(I % R), tile_of((I + 1) % R), ring[I % R], ring[(I + 1) % R], lane,
+                         [&](auto mb) __attribute__((always_inline)) { issue_a(f, std::integral_constant<int, (I + D) % R>{}, mb); },
+                         [&](auto i) __attribute__((always_inline)) { issue_b(f, std::integral_constant<int, (I + D) % R>{}, i); });
+    };
+    asm volatile("; pipeline begin");           // from here to the matching end the build allows no spill code
+    static_for<0, D>([&](auto jc) __attribute__((always_inline)) {
+        const Source f = source(decltype(jc)::value);
+        static_for<0, MBS>([&](auto mb) __attribute__((always_inline)) { issue_a(f, jc, mb); });
+        static_for<0, kB>([&](auto i) __attribute__((always_inline)) { issue_b(f, jc, i); });
+    });
+    wait_loads<(D - 1) * (MBS + kB)>(ring[0]);
+    __syncthreads();
+    static_for<0, Units<RB>::count(0)>([&](auto i) __attribute__((always_inline)) { read_frag<RB, 0, decltype(i)::value>(af[0], tile_of(0), lane); });
+    for (; c + R <= chunks; c += R) static_for<0, R>(step);
+    asm volatile("; pipeline end");
+    // All loads have landed, those past the last step included, and only now are their destination registers let go of: one the compiler
+    // considers dead would be handed to something else (an LDS read, say) while the load into it is still in flight.
     asm volatile("s_waitcnt vmcnt(0)" : : : "memory");
 #pragma unroll
     for (int r = 0; r < R; ++r)
 #pragma unroll
         for (int ks = 0; ks < kKS; ++ks)
 #pragma unroll
-            for (int j = 0; j < 2 * NF; ++j) asm volatile("" : : "v"(ring[r].v[ks][j]));
+            for (int j = 0; j < 2 * NF; ++j) asm volatile("" : "+v"(ring[r].v[ks][j]));
+    // the steps that do not fill a round of the loop, fewer than R and so all here: without overlap, the weights moved up after each
+    if (c < chunks) {
+        __syncthreads();                        // every wave's share of their activation tiles has landed
+        for (const uint4* tile = tile_of(0); c < chunks; ++c, tile += kBuf / 16) {
+            static_for<0, Units<RB>::U>([&](auto uc) __attribute__((always_inline)) {
+                constexpr int UU = decltype(uc)::value;
+                static_for<0, Units<RB>::count(UU)>([&](auto i) __attribute__((always_inline)) { read_frag<RB, UU, decltype(i)::value>(af[0], tile, lane); });
+                static_for<0, Units<RB>::count(UU) * 2 * NF>([&](auto m) __attribute__((always_inline)) { mma_one<NF, RB, UU, decltype(m)::value>(acc, af[0], ring[0]); });
+            });
 #pragma unroll
-    for (int i = 0; i < AD; ++i)
-#pragma unroll
-        for (int mb = 0; mb < MBS; ++mb) asm volatile("" : : "v"(areg[i].v[mb]));
+            for (int r = 0; r + 1 < R; ++r) ring[r] = ring[r + 1];
+        }
+    }
     __syncthreads();                            // the last LDS reads are done before the epilogue reuses the LDS
     tid = thread_id(wave_s);                    // rebuilt: the first copy need not survive the main loop
     // The block's next work item is taken now, by thread 0: the queue's answer arrives while the output tile is
@@ -714,7 +611,7 @@ __device__ inline void ffn_tile(uint4 (&lds)[2][kTileM * kLdsRow], const uint16_
     constexpr int kRowsPerPass = W == 32 ? 256 : 128;   // tile rows that fit the LDS
     constexpr int kLanesPerRow = W / 2;                 // 16-byte stores per tile row
     constexpr int kRowsPerIter = 256 / kLanesPerRow;
-    char* tile = reinterpret_cast<char*>(&lds[0][0]);
+    char* tile = reinterpret_cast<char*>(&lds[0]);
     static_assert(kRowsPerPass * kTileRowBytes <= static_cast<int>(sizeof(lds)), "epilogue tile must fit the LDS buffers");
     const int wave = wave_s;
     const int row_in = (tid & 15), col_in = 4 * ((tid & 63) >> 4);
@@ -729,18 +626,18 @@ __device__ inline void ffn_tile(uint4 (&lds)[2][kTileM * kLdsRow], const uint16_
         // (addressed as global memory, so that the loads return in order with the other global loads and the stores
         // that follow wait for their own operands only)
         typedef const __attribute__((address_space(1))) u32x4 global_u32x4;
-        global_u32x4* src = (global_u32x4*)(nw + static_cast<size_t>(nkey % static_cast<unsigned>(chunks)) * kStepBytes) + (tid & 63);
+        global_u32x4* src = (global_u32x4*)add_offset(nw + static_cast<size_t>(nkey % static_cast<unsigned>(chunks)) * kStepBytes, 16u * (tid & 63));
 #pragma unroll
         for (int i = 0; i < kWarm; ++i) warm[i] = src[(GATED || NF == 2) ? i * 64 : i * 128];
     };
 #pragma unroll
-    for (int p0 = 0; p0 < MBS * 32; p0 += kRowsPerPass) {
+    for (int p0 = 0; p0 < RB * 16; p0 += kRowsPerPass) {
         if (p0 > 0) __syncthreads();                    // the previous pass has been stored
         // the choice of activation is taken once per pass, outside the value loops, so that the independent
         // evaluations of a wave can overlap
         auto fill = [&](auto exact) {
 #pragma unroll
-            for (int rb = p0 / 16; rb < 2 * MBS && rb < (p0 + kRowsPerPass) / 16; ++rb) {
+            for (int rb = p0 / 16; rb < RB && rb < (p0 + kRowsPerPass) / 16; ++rb) {
                 char* trow = tile + (rb * 16 + row_in - p0) * kTileRowBytes + (wave * W + col_in) * 2;
 #pragma unroll
                 for (int j = 0; j < (GATED ? 2 : 2 * NF); ++j) {        // 16 columns each
@@ -781,7 +678,7 @@ __device__ inline void ffn_tile(uint4 (&lds)[2][kTileM * kLdsRow], const uint16_
             int out_row[kPieces];
 #pragma unroll
             for (int i = 0; i < kPieces; ++i) {
-                if (i * kRowsPerIter < MBS * 32 - p0) {                   // rows this tile height has
+                if (i * kRowsPerIter < RB * 16 - p0) {                   // rows this tile height has
                     const int r = static_cast<int>(tid) / kLanesPerRow + i * kRowsPerIter;
                     val[i] = *reinterpret_cast<const uint4*>(tile + r * kTileRowBytes + seg * 2);
                     const int row = row_begin + min(p0 + r, rows - 1);    // past the end: the last row again, not stored
@@ -791,7 +688,7 @@ __device__ inline void ffn_tile(uint4 (&lds)[2][kTileM * kLdsRow], const uint16_
             if (p0 == 0) warm_next();
 #pragma unroll
             for (int i = 0; i < kPieces; ++i) {
-                if (i * kRowsPerIter < MBS * 32 - p0) {
+                if (i * kRowsPerIter < RB * 16 - p0) {
                     const int r = static_cast<int>(tid) / kLanesPerRow + i * kRowsPerIter;
                     // written once and next read by another kernel, after far more traffic than the L2 holds: stored
                     // non-temporal, so that the rows do not take the place of weights and activation tiles there
@@ -818,8 +715,8 @@ constexpr int kKeepFromTiles = 2;       // row tiles of an expert from which its
 // GATED (NF = 2): a unit is 32 output columns whose two fragments per k-step are (W_gate, W_in); the
 //   epilogue writes act(gate) * in.
 // otherwise a unit is 32 * NF output columns of W_out.
-// Weight fragments stream HBM -> registers through a ring of buffers so that several KiB per
-// wave are always in flight; the activation tile goes through LDS, double buffered.
+// Weight fragments stream HBM -> registers and activation tiles HBM -> LDS through rings of buffers, so that several KiB per
+// wave are always in flight.
 //
 // One block per compute unit stays resident and takes work items from 8 queues, one per XCD (blocks go
 // round-robin to the XCDs, each with its own L2, so blockIdx % 8 names the XCD): position q of a
@@ -838,7 +735,7 @@ __global__ __launch_bounds__(256) void ffn_mfma_kernel(const uint16_t* __restric
                                                        int y_shift, int mt_shift, const int32_t* __restrict__ row_map,
                                                        const int32_t* __restrict__ gather, int gather_k, int h_rows,
                                                        int list, int max_tiles) {
-    __shared__ uint4 lds[2][kTileM * kLdsRow];     // 2 x 36 KiB activation tiles, padded rows
+    __shared__ uint4 lds[kLdsBytes / 16];          // activation tiles; between items, the output tile
     __shared__ int sh_q, sh_x;
     ItemQueue Q;
     Q.tiles = plan[16 + list];
@@ -881,18 +778,27 @@ __global__ __launch_bounds__(256) void ffn_mfma_kernel(const uint16_t* __restric
         const void* wave_w = wave_stream<GATED, NF>(Q, e, it.block_y, wave, units, Kl, key);
         // weights of an expert with two row tiles or more are left in the L2 for its other tiles
         const bool keep = tiles_of_expert >= kKeepFromTiles;
-        const int blocks = min((rows + 31) >> 5, GATHER ? kGatherTileM / 32 : kTileM / 32);
-#define FFN_TILE(M, KP)                                                                                              \
-    ffn_tile<GATED, NF, M, KP, GATHER>(lds, A, row_begin, rows, wave_w, C, Kl, Nl, unit, active, act, key, wave, row_map, \
-                                       gather, gather_k, Q, units, &sh_q, &sh_x, h_rows)
-#define FFN_CASE(M)                                                                                                  \
-    case M:                                                                                                          \
-        if (keep) FFN_TILE(M, true); else FFN_TILE(M, false);                                                        \
+        // a single block runs as two: its steps of four MFMAs per unit are too short (600 tokens, d 768, f 3072, 33 experts 122 -> 120 us)
+        const int blocks = min((rows + 15) >> 4, (GATHER ? kGatherTileM : kTileM) / 16);
+#define FFN_TILE(RB, KP)                                                                                             \
+    ffn_tile<GATED, NF, RB, KP, GATHER>(lds, A, row_begin, rows, wave_w, C, Kl, Nl, unit, active, act, key, wave, row_map, \
+                                        gather, gather_k, Q, units, &sh_q, &sh_x, h_rows)
+#define FFN_CASE(RB)                                                                                                 \
+    case RB:                                                                                                         \
+        if (keep) FFN_TILE(RB, true); else FFN_TILE(RB, false);                                                      \
         break;
         if constexpr (GATHER) {
-            switch (blocks) { FFN_CASE(1) FFN_CASE(2) FFN_CASE(3) FFN_CASE(4) FFN_CASE(5) FFN_CASE(6) default: if (keep) FFN_TILE(kGatherTileM / 32, true); else FFN_TILE(kGatherTileM / 32, false); break; }
+            switch (blocks) {
+                case 1: FFN_CASE(2) FFN_CASE(3) FFN_CASE(4) FFN_CASE(5) FFN_CASE(6) FFN_CASE(7) FFN_CASE(8) FFN_CASE(9)
+                FFN_CASE(10) FFN_CASE(11) FFN_CASE(12) FFN_CASE(13)
+                default: if (keep) FFN_TILE(kGatherTileM / 16, true); else FFN_TILE(kGatherTileM / 16, false); break;
+            }
         } else {
-            switch (blocks) { FFN_CASE(1) FFN_CASE(2) FFN_CASE(3) FFN_CASE(4) FFN_CASE(5) FFN_CASE(6) FFN_CASE(7) default: if (keep) FFN_TILE(8, true); else FFN_TILE(8, false); break; }
+            switch (blocks) {
+                case 1: FFN_CASE(2) FFN_CASE(3) FFN_CASE(4) FFN_CASE(5) FFN_CASE(6) FFN_CASE(7) FFN_CASE(8) FFN_CASE(9)
+                FFN_CASE(10) FFN_CASE(11) FFN_CASE(12) FFN_CASE(13) FFN_CASE(14) FFN_CASE(15)
+                default: if (keep) FFN_TILE(kTileM / 16, true); else FFN_TILE(kTileM / 16, false); break;
+            }
         }
 #undef FFN_CASE
 #undef FFN_TILE

@@ -33,20 +33,29 @@ __device__ inline void ffn_plan_block(const int32_t* offsets, int e_first, int e
         lo = min(max(offsets[e_first + t], 0), total_rows);
         cnt = min(max(offsets[e_first + t + 1] - lo, 0), total_rows - lo);
     }
+    // The highest tiles first, so that the last items are the short ones; among equals the expert with more rows, then by index.
+    // (By rows alone: 2048 tokens on 8 experts, whose tiles are 16 blocks high up to 256 rows and 8 or 9 above, ended with the 16;
+    // 65536 tokens on 32 experts 12424 -> 12334 us.)
+    constexpr int kRowBits = 26;               // rows < 2^31 / 64, height <= 16
+    int key = 0;
+    if (cnt > 0) {
+        const int tiles = (cnt + tile_m - 1) / tile_m;
+        key = ((cnt + 15) / 16 + tiles - 1) / tiles << kRowBits | cnt;
+    }
     if (worker) {
-        n[t] = cnt;
+        n[t] = key;
         first[t] = lo;
         order[t] = t;
         tl[t] = 0;
     }
     __syncthreads();
     if (worker && t < e_count) {
-        int rank = 0;                   // more rows first, equal counts by expert index: a permutation of 0..e_count-1
-        for (int u = 0; u < e_count; ++u) rank += (n[u] > cnt || (n[u] == cnt && u < t)) ? 1 : 0;
+        int rank = 0;                   // a permutation of 0..e_count-1
+        for (int u = 0; u < e_count; ++u) rank += (n[u] > key || (n[u] == key && u < t)) ? 1 : 0;
         order[rank] = t;
     }
     __syncthreads();
-    const int mine = worker ? order[t] : 0, my_n = worker && t < e_count ? n[mine] : 0;
+    const int mine = worker ? order[t] : 0, my_n = worker && t < e_count ? n[mine] & ((1 << kRowBits) - 1) : 0;
     const int my_tiles = (my_n + tile_m - 1) / tile_m;
     if (worker) tl[t] = my_tiles;
     __syncthreads();
@@ -55,10 +64,13 @@ __device__ inline void ffn_plan_block(const int32_t* offsets, int e_first, int e
     const int upto = t < e_count ? t : e_count;
     for (int r = 0; r < upto; ++r) start += tl[r];
     if (my_tiles > 0) {
-        const int per_tile = min(tile_m, ((my_n + my_tiles - 1) / my_tiles + 31) & ~31);
+        // the expert's blocks of 16 rows spread evenly: block i of b goes to tile i t / b of t
+        const int blocks = (my_n + 15) / 16;
         int4* tiles = reinterpret_cast<int4*>(plan + kPlanHeader + 4 * list * max_tiles);
-        for (int mt = 0; mt < my_tiles && start + mt < max_tiles; ++mt)
-            tiles[start + mt] = make_int4(e_first + mine, first[mine] + mt * per_tile, min(per_tile, my_n - mt * per_tile), my_tiles);
+        for (int mt = 0; mt < my_tiles && start + mt < max_tiles; ++mt) {
+            const int lo = mt * blocks / my_tiles * 16, hi = min((mt + 1) * blocks / my_tiles * 16, my_n);
+            tiles[start + mt] = make_int4(e_first + mine, first[mine] + lo, hi - lo, my_tiles);
+        }
     }
     if (t == 255) plan[16 + list] = min(start + my_tiles, max_tiles);
     if (list == 0 && t < 16) plan[t] = 0;

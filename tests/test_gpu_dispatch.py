@@ -280,3 +280,47 @@ def test_few_rows_gathered_equals_batched(T, crowd):
     assert torch.equal(y, y4)
     ref = O.layer_forward(x, Wg, lambda e: ex[e], E, 1, bias, 1)[0]
     assert rel_l2(H.to_f64(y), ref) <= TOL["bf16"]
+
+
+def _four_calls(cfg, dx, dW, db, packed, ws):
+    """(y of the four calls, y of the layer)"""
+    A, E = cfg.T * cfg.k, cfg.E
+
+    def ints(*n):
+        return torch.empty(n, dtype=torch.int32, device="cuda")
+    idx, w, counts, offsets, perm, inv = ints(cfg.T, cfg.k), torch.empty((cfg.T, cfg.k), device="cuda"), ints(E), ints(E + 1), ints(A), ints(A)
+    Xp = torch.empty((A, cfg.d), dtype=dx.dtype, device="cuda")
+    Yp, y4, y = torch.empty_like(Xp), torch.full_like(dx, float("nan")), torch.full_like(dx, float("nan"))
+    M.moe_route(cfg, dx, dW, db, idx, w, ws)
+    M.moe_permute(cfg, dx, idx, counts, offsets, perm, inv, Xp, ws)
+    M.moe_expert_ffn(cfg, Xp, offsets, packed, Yp, ws)
+    M.moe_combine(cfg, Yp, inv, w, y4)
+    M.moe_layer_forward(cfg, dx, dW, db, packed, None, y, ws)
+    torch.cuda.synchronize()
+    return y4, y
+
+
+# chunks of 64 in the two reductions: 1 and 3, 2 and 5, 4 and 6, 7 and 8, 9 and 4 (rounds of four, and what does not fill one)
+@pytest.mark.parametrize("d,f", [(64, 192), (128, 320), (256, 384), (448, 512), (576, 256)])
+def test_expert_ffn_every_tile_height(d, f):
+    """Tiles of 1 to 16 blocks of 16 rows, full and not, and experts split evenly over two and three of them."""
+    counts = [16 * b - b % 3 for b in range(1, 17)] + [257, 513, 700]
+    got, ref, offsets = run_ffn(sum(counts), d, f, len(counts), 1, "bf16", counts, 0, seed=d + f)
+    for e in range(len(counts)):
+        lo, hi = offsets[e], offsets[e + 1]
+        assert rel_l2(got[lo:hi], ref[lo:hi]) <= TOL["bf16"], f"expert {e}"
+
+
+@pytest.mark.parametrize("T,E,d,f", [(2100, 16, 320, 192), (2100, 16, 576, 448)])
+def test_gathered_tiles_equal_batched(T, E, d, f):
+    """Rows looked up in x, tiles of many heights: the layer gives the bytes of the four calls."""
+    rng = np.random.default_rng(T + d)
+    cfg = M.MoeCfg.make(T, d, f, E, 1, "bf16")
+    x, Wg, _ = make_inputs(T, T, d, E, "bf16")
+    ex = [tuple(rounded(rng.standard_normal(s) * 0.05, "bf16") for s in ((d, f), (d, f), (f, d))) for _ in range(E)]
+    packed = H.pack_experts(W.Workload("t", T, d, f, E, 1, "bf16", 0), cfg, experts=lambda e: ex[e])[0]
+    bias = torch.linspace(-1.0, 1.0, E, device="cuda")
+    ws = torch.empty(M.moe_workspace_bytes(cfg), dtype=torch.uint8, device="cuda")
+    y4, y = _four_calls(cfg, H.to_device(x, "bf16"), H.to_device(Wg, "bf16"), bias, packed, ws)
+    assert torch.isfinite(y.float()).all()
+    assert torch.equal(y, y4)
