@@ -5,6 +5,7 @@
 //   1. chunk_hist_kernel : LDS histogram of each chunk of kPermChunk assignments
 //   2. scan_kernel       : counts, offsets and, per chunk, the first row of every expert
 //   3. scatter_kernel    : stable rank inside the chunk from wave ballots (no ordered atomics)
+//      (up to 65536 assignments batch_kernel is all three)
 //   4. gather_rows_kernel: 16-byte-vector row copy
 #include "common.h"
 #include "ffn_plan.h"
@@ -129,94 +130,106 @@ __global__ __launch_bounds__(256) void scatter_kernel(const int32_t* __restrict_
     }
 }
 
-// Short batches: the same three steps by one block of 16 waves, with no trip through memory between them:
-// LDS histogram of all assignments, exclusive scan over the experts, then the stable scatter in rounds
-// of 1024 assignments (rank inside the wave from ballots, waves in order, rounds in order).
-constexpr int kSmallWaves = 16;
-constexpr int kSmallMaxA = 16 * kSmallWaves * 64;      // beyond this the chunked kernels spread the work over the chip
+// Up to kOneLaunchMaxA assignments: the same in one launch.  Every block reads all of idx and counts, beside the totals, what lies
+// before its own kPermChunk assignments, so that no block needs anything of another.  The work list of the expert kernels that follow, when the caller wants it from here
+// (saves a launch), is made by a block of its own, or by two when the down kernel does not read the up kernel's list.  Bound by the latency of its few steps (launch, the read of idx, counting, scan, stores):
+// every assignment is counted by every block, which takes longer than the three kernels above only far beyond the limit.  us, against one block in
+// rounds of 1024 (up to 16384) and the three kernels (beyond): 2050 assignments to 33 experts with the list 8.5 -> 5.0, 32768 to 64 experts without
+// 14.7 -> 6.9; whole calls: 4096 tokens on 32 experts 1346 -> 1317, 60000 x 1, d 1024, f 64, 8 experts (a list by a kernel of its own before) 196.8 -> 194.7.
+constexpr int kBatchWaves = kPermChunk / 64;           // one assignment of the block's own chunk per thread
+constexpr int kCopies = 4;                              // histograms the counting is spread over: equal experts in a wave wait for each other
+constexpr int kOneLaunchMaxA = 64 * kPermChunk;
 
-__global__ __launch_bounds__(kSmallWaves * 64) void permute_small_kernel(const int32_t* __restrict__ idx, int A, int E,
-                                                                         int32_t* __restrict__ counts, int32_t* __restrict__ offsets,
-                                                                         int32_t* __restrict__ perm, int32_t* __restrict__ inv,
-                                                                         int32_t* __restrict__ plan, int plan_max_tiles,
-                                                                         int plan_tile_rows, int plan_tile_rows_down) {
-    __shared__ int run[256];                       // histogram, then the next free row of each expert
-    __shared__ int wcnt[kSmallWaves][256];         // per wave, rows each expert takes in the current round
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    if (threadIdx.x < 256) {
-        run[threadIdx.x] = 0;
-#pragma unroll
-        for (int wv = 0; wv < kSmallWaves; ++wv) wcnt[wv][threadIdx.x] = 0;
-    }
+__global__ __launch_bounds__(kPermChunk) void batch_kernel(const int32_t* __restrict__ idx, int A, int E, int chunks,
+                                                           int32_t* __restrict__ counts, int32_t* __restrict__ offsets,
+                                                           int32_t* __restrict__ perm, int32_t* __restrict__ inv,
+                                                           int32_t* __restrict__ plan, int plan_max_tiles, int plan_tile_rows,
+                                                           int plan_tile_rows_down) {
+    __shared__ int hist[2][kCopies][256];              // assignments before the block's chunk, and from there on
+    __shared__ int wcnt[kBatchWaves][256];             // per wave, rows each expert takes
+    __shared__ int run[256], start[257];               // first row of each expert, of the chunk's and of all
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const bool plans = static_cast<int>(blockIdx.x) >= chunks;
+    const int a0 = plans ? 0 : blockIdx.x * kPermChunk, a = a0 + tid;
+    const bool valid = !plans && a < A;
+    const int mine = valid ? clamp_expert(idx[a], E) : 0;
+    for (int i = tid; i < 2 * kCopies * 256; i += kPermChunk) (&hist[0][0][0])[i] = 0;
+    for (int i = tid; i < kBatchWaves * 256; i += kPermChunk) (&wcnt[0][0])[i] = 0;
     __syncthreads();
-    for (int a = threadIdx.x; a < A; a += kSmallWaves * 64) atomicAdd(&run[clamp_expert(idx[a], E)], 1);   // integer counts: order cannot matter
+    // integer counts: order cannot matter
+    auto count = [&](int at, int e) { atomicAdd(&hist[at >= a0 ? 1 : 0][lane & (kCopies - 1)][clamp_expert(e, E)], 1); };
+    if ((reinterpret_cast<uintptr_t>(idx) & 15) == 0) {                    // uniform
+        const int whole = A / 4;
+        for (int q0 = tid; q0 < whole; q0 += 4 * kPermChunk) {
+            int4 v[4];
+#pragma unroll
+            for (int u = 0; u < 4; ++u) v[u] = reinterpret_cast<const int4*>(idx)[min(q0 + u * kPermChunk, whole - 1)];
+#pragma unroll
+            for (int u = 0; u < 4; ++u) {
+                const int at = 4 * (q0 + u * kPermChunk);                  // (a chunk starts at a multiple of 4)
+                if (q0 + u * kPermChunk < whole) { count(at, v[u].x); count(at, v[u].y); count(at, v[u].z); count(at, v[u].w); }
+            }
+        }
+        if (tid < (A & 3)) count(4 * whole + tid, idx[4 * whole + tid]);
+    } else {
+        for (int at = tid; at < A; at += kPermChunk) count(at, idx[at]);
+    }
+    // the block's own chunk: lanes of this wave that hold the same expert
+    int rank = 0;
+    if (!plans) {                                                          // uniform
+        int bits = 0;
+        while ((1 << bits) < E) ++bits;
+        unsigned long long peers = __ballot(valid);
+        for (int b = 0; b < bits; ++b) {
+            const bool bit = (mine >> b) & 1;
+            const unsigned long long bal = __ballot(bit);
+            peers &= bit ? bal : ~bal;
+        }
+        rank = __popcll(peers & ((1ull << lane) - 1ull));
+        if (valid && rank == 0) wcnt[wave][mine] = __popcll(peers);
+    }
     __syncthreads();
     if (wave == 0) {
         // exclusive scan of up to 256 counts by one wave: four experts per lane, then across the lanes
-        int c[4], sum = 0;
+        int c[4], before[4], sum = 0;
 #pragma unroll
-        for (int j = 0; j < 4; ++j) { c[j] = run[4 * lane + j]; sum += c[j]; }
+        for (int j = 0; j < 4; ++j) {
+            c[j] = before[j] = 0;
+#pragma unroll
+            for (int q = 0; q < kCopies; ++q) { before[j] += hist[0][q][4 * lane + j]; c[j] += hist[1][q][4 * lane + j]; }
+            c[j] += before[j];
+            sum += c[j];
+        }
         int incl = sum;
 #pragma unroll
         for (int off = 1; off < 64; off <<= 1) {
             const int up = __shfl_up(incl, off);
             if (lane >= off) incl += up;
         }
-        int start = incl - sum;
+        int at = incl - sum;
 #pragma unroll
         for (int j = 0; j < 4; ++j) {
             const int e = 4 * lane + j;
-            if (e < E) { counts[e] = c[j]; offsets[e] = start; }
-            run[e] = start;
-            start += c[j];
+            if (blockIdx.x == 0 && e < E) { counts[e] = c[j]; offsets[e] = at; }
+            start[e] = at;
+            run[e] = at + before[j];
+            at += c[j];
         }
-        if (lane == 63) offsets[E] = incl;         // experts past E hold no assignment, so this is the total
+        if (lane == 63) {                              // experts past E hold no assignment, so this is the total
+            start[256] = incl;
+            if (blockIdx.x == 0) offsets[E] = incl;
+        }
     }
     __syncthreads();
-    // the work list of the expert kernels that follow, when the caller wants it from here (saves a launch)
-    if (plan != nullptr) {
-        int (&scratch)[4][256] = reinterpret_cast<int (&)[4][256]>(wcnt);      // not in use yet; cleared again below
-        ffn_plan_block(offsets, 0, E, plan_tile_rows, plan, A, plan_max_tiles, scratch, 0);
-        if (plan_tile_rows_down != plan_tile_rows) {        // else the down kernel reads the up kernel's list
-            __syncthreads();
-            ffn_plan_block(offsets, 0, E, plan_tile_rows_down, plan, A, plan_max_tiles, scratch, 1);
-        }
-        __syncthreads();
-        if (threadIdx.x < 256) {
-#pragma unroll
-            for (int wv = 0; wv < 4; ++wv) wcnt[wv][threadIdx.x] = 0;
-        }
-        __syncthreads();
-    }
-    int bits = 0;
-    while ((1 << bits) < E) ++bits;
-    for (int a0 = 0; a0 < A; a0 += kSmallWaves * 64) {
-        const int a = a0 + threadIdx.x;
-        const bool valid = a < A;
-        const int e = valid ? clamp_expert(idx[a], E) : 0;
-        unsigned long long peers = __ballot(valid);       // lanes of this wave that hold the same expert
-        for (int b = 0; b < bits; ++b) {
-            const bool bit = (e >> b) & 1;
-            const unsigned long long bal = __ballot(bit);
-            peers &= bit ? bal : ~bal;
-        }
-        const int rank = __popcll(peers & ((1ull << lane) - 1ull));
-        if (valid && rank == 0) wcnt[wave][e] = __popcll(peers);
-        __syncthreads();
-        if (valid) {
-            int row = run[e] + rank;
-            for (int wv = 0; wv < wave; ++wv) row += wcnt[wv][e];
-            perm[row] = a;
-            inv[a] = row;
-        }
-        __syncthreads();
-        if (threadIdx.x < 256) {
-            int taken = 0;
-#pragma unroll
-            for (int wv = 0; wv < kSmallWaves; ++wv) { taken += wcnt[wv][threadIdx.x]; wcnt[wv][threadIdx.x] = 0; }
-            run[threadIdx.x] += taken;
-        }
-        __syncthreads();
+    if (plans) {
+        int (&scratch)[4][256] = reinterpret_cast<int (&)[4][256]>(wcnt);
+        const int list = blockIdx.x - chunks;
+        ffn_plan_block(start, 0, E, list == 0 ? plan_tile_rows : plan_tile_rows_down, plan, A, plan_max_tiles, scratch, list);
+    } else if (valid) {
+        int row = run[mine] + rank;
+        for (int wv = 0; wv < wave; ++wv) row += wcnt[wv][mine];
+        perm[row] = a;
+        inv[a] = row;
     }
 }
 
@@ -258,11 +271,12 @@ int launch_permute(const moe_cfg& c, const void* x, const int32_t* idx, int32_t*
     if (planned != nullptr) *planned = false;
     const int A = c.T * c.k;
     const int chunks = (A + kPermChunk - 1) / kPermChunk;
-    if (A <= kSmallMaxA) {
+    if (A <= kOneLaunchMaxA) {
         const bool with_plan = plan != nullptr && planned != nullptr && c.dtype == MOE_BF16 && A > 0;
-        hipLaunchKernelGGL(permute_small_kernel, dim3(1), dim3(kSmallWaves * 64), 0, s, idx, A, c.E, counts, offsets, perm, inv,
+        const int own = chunks > 0 ? chunks : 1;       // (no assignments: the counts are still written)
+        hipLaunchKernelGGL(batch_kernel, dim3(own + (!with_plan ? 0 : plan_tile_rows_down != plan_tile_rows ? 2 : 1)), dim3(kPermChunk), 0, s, idx, A, c.E, own, counts, offsets, perm, inv,
                            with_plan ? plan : nullptr, plan_max_tiles, plan_tile_rows, plan_tile_rows_down);
-        MOE_LAUNCH_CHECK("permute_small_kernel");
+        MOE_LAUNCH_CHECK("batch_kernel");
         if (with_plan) *planned = true;
     } else {
         if (chunk_hist == nullptr) return fail(MOE_ERR_WORKSPACE, "the batching of %d assignments needs scratch memory", A);
@@ -276,7 +290,7 @@ int launch_permute(const moe_cfg& c, const void* x, const int32_t* idx, int32_t*
     if (chunks > 0) {
         if (Xp != nullptr) {
             const int vec_per_row = static_cast<int>(c.d * elem_size(c) / 16);
-auto run = [&](auto kernel) {
+            auto run = [&](auto kernel) {
                 hipLaunchKernelGGL(kernel, dim3(c.T), dim3(256), 0, s, static_cast<const uint4*>(x), inv, c.k, vec_per_row, static_cast<uint4*>(Xp));
             };
             const bool nt = static_cast<size_t>(c.T) * vec_per_row * 16 > (size_t(288) << 20);

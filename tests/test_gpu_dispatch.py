@@ -324,3 +324,28 @@ def test_gathered_tiles_equal_batched(T, E, d, f):
     y4, y = _four_calls(cfg, H.to_device(x, "bf16"), H.to_device(Wg, "bf16"), bias, packed, ws)
     assert torch.isfinite(y.float()).all()
     assert torch.equal(y, y4)
+
+
+# one chunk, chunk edges, the last batch of one launch and the first of the chunked kernels
+@pytest.mark.parametrize("A", [1, 63, 1023, 1024, 1025, 4099, 65535, 65536, 65537])
+@pytest.mark.parametrize("E", [1, 33, 256])
+@pytest.mark.parametrize("shift", [0, 1])               # idx at a 16-byte boundary and not
+def test_batching_in_one_launch(A, E, shift):
+    g = torch.Generator(device="cuda")
+    g.manual_seed(A + E)
+    buf = torch.empty(A + 4, dtype=torch.int32, device="cuda")
+    idx = buf[shift:shift + A]
+    idx.copy_((torch.rand(A, device="cuda", generator=g) ** 3 * (E + 2)).int() - 1)        # skewed, and some out of range: clamped
+    e = idx.long().clamp(0, E - 1)
+
+    def ints(n):
+        return torch.full((n,), -1, dtype=torch.int32, device="cuda")
+    cfg = M.MoeCfg.make(A, 64, 64, E, 1, "bf16")
+    counts, offsets, perm, inv = ints(E), ints(E + 1), ints(A), ints(A)
+    M.moe_permute(cfg, None, idx.view(A, 1), counts, offsets, perm, inv, None, torch.empty(M.moe_workspace_bytes(cfg), dtype=torch.uint8, device="cuda"))
+    torch.cuda.synchronize()
+    order = e.sort(stable=True).indices
+    assert torch.equal(perm.long(), order)
+    assert torch.equal(inv.long()[order], torch.arange(A, device="cuda"))
+    assert torch.equal(counts.long(), torch.bincount(e, minlength=E))
+    assert offsets.tolist() == [0] + torch.cumsum(counts, 0).tolist()
