@@ -388,25 +388,29 @@ int layer_forward(const moe_cfg* cfg, const void* x, const void* W_g, const floa
     if (all_stages) MOE_HIP_CHECK(hipEventRecord(tev[1], s));
     bool planned = false;          // resident mode: the work list of the one FFN launch may come from the batching kernel
     int plan_rows = kTileM, plan_rows_down = kTileM;      // (resident mode) the tile heights of the launch over all experts
-    if (sctx == nullptr && c.dtype == MOE_BF16) {
+    bool reads_idx = false;        // (resident mode) the expert kernels look through the assignments themselves: nothing is batched
+    if (sctx == nullptr) {
         int dev = 0;
         const DeviceInfo* info = nullptr;
         if (int rc = device_info(&dev, &info)) return rc;
+        reads_idx = ffn_reads_idx(c, info->compute_units);
         plan_rows = ffn_tile_rows(c, gather_rows, info->compute_units);
         plan_rows_down = ffn_down_tile_rows(c, c.E, A, plan_rows, info->compute_units);
     }
-    if (int rc = launch_permute(c, x, idx, counts, offsets, perm, inv, gather_rows ? nullptr : base + L.Xp,
-                                reinterpret_cast<int32_t*>(base + L.chunk_hist), s,
-                                sctx == nullptr ? reinterpret_cast<int32_t*>(base + L.ffn_plan) : nullptr,
-                                static_cast<int>(ffn_plan_tiles(c)), sctx == nullptr ? &planned : nullptr,
-                                plan_rows, plan_rows_down))
-        return rc;
+    if (!reads_idx)
+        if (int rc = launch_permute(c, x, idx, counts, offsets, perm, inv, gather_rows ? nullptr : base + L.Xp,
+                                    reinterpret_cast<int32_t*>(base + L.chunk_hist), s,
+                                    sctx == nullptr ? reinterpret_cast<int32_t*>(base + L.ffn_plan) : nullptr,
+                                    static_cast<int>(ffn_plan_tiles(c)), sctx == nullptr ? &planned : nullptr,
+                                    plan_rows, plan_rows_down))
+            return rc;
     if (all_stages) MOE_HIP_CHECK(hipEventRecord(tev[2], s));
 
     if (sctx == nullptr) {
-        if (int rc = launch_expert_ffn(c, ffn_in, offsets, 0, c.E, W_packed, eb, A, base + L.H, ffn_out,
+        if (int rc = launch_expert_ffn(c, reads_idx ? x : ffn_in, offsets, 0, c.E, W_packed, eb, A, base + L.H, ffn_out,
                                        reinterpret_cast<int32_t*>(base + L.ffn_plan), s, tev ? tev[3] : nullptr,
-                                       tev && up_only ? tev[2] : nullptr, row_map, planned, gather))
+                                       tev && up_only ? tev[2] : nullptr, reads_idx ? nullptr : row_map, planned,
+                                       reads_idx ? nullptr : gather, reads_idx ? idx : nullptr))
             return rc;
         if (all_stages) MOE_HIP_CHECK(hipEventRecord(tev[4], s));
     } else {
@@ -485,7 +489,7 @@ int layer_forward(const moe_cfg* cfg, const void* x, const void* W_g, const floa
         guard.ok = true;
     }
     if (!direct)
-        if (int rc = launch_combine(c, base + L.Yp, inv, w, y, s)) return rc;
+        if (int rc = launch_combine(c, base + L.Yp, reads_idx ? nullptr : inv, w, y, s)) return rc;
     if (all_stages) MOE_HIP_CHECK(hipEventRecord(tev[5], s));
     return MOE_OK;
 }

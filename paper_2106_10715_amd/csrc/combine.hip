@@ -26,7 +26,7 @@ __global__ __launch_bounds__(256) void combine_kernel(const uint4* __restrict__ 
     float wt[K];
 #pragma unroll
     for (int j = 0; j < K; ++j) {
-        const int row = min(max(inv[static_cast<size_t>(t) * K + j], 0), n_rows - 1);   // never outside Yp
+        const int row = inv == nullptr ? t * K + j : min(max(inv[static_cast<size_t>(t) * K + j], 0), n_rows - 1);   // never outside Yp
         rows[j] = reinterpret_cast<const u4v*>(Yp) + static_cast<size_t>(row) * vec_per_row;
         wt[j] = w[static_cast<size_t>(t) * K + j];
     }

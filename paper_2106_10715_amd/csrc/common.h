@@ -94,13 +94,18 @@ int launch_pack(const moe_cfg& c, const void* Win, const void* Wgate, const void
 int launch_expert_ffn(const moe_cfg& c, const void* Xp, const int32_t* offsets, int e_first, int e_count,
                       const void* W, size_t expert_stride_bytes, long max_rows, void* H, void* Yp, int32_t* plan,
                       hipStream_t s, hipEvent_t between = nullptr, hipEvent_t before_up = nullptr,
-                      const int32_t* row_map = nullptr, bool plan_ready = false, const int32_t* gather = nullptr);
+                      const int32_t* row_map = nullptr, bool plan_ready = false, const int32_t* gather = nullptr,
+                      const int32_t* idx = nullptr);
 // gather: Xp is then the token array x[T, d] itself and batched row r is its row gather[r] / k (gather = the
 // perm written by the batching step), so the batched copy of the activations need not exist.  A bf16 work list written elsewhere (plan_ready) must
 // have been cut to tiles of ffn_tile_rows(c, gather != NULL, n_cu) rows.
+// idx (whole layer of at most kDirectRows assignments, ffn_reads_idx): nothing has batched the assignments; Xp is x, offsets, plan, row_map
+// and gather are not read, and the kernels find an expert's rows in idx [T, k] themselves.  Row a of H and Yp is then assignment a.
+constexpr int kDirectRows = 64;
+bool ffn_reads_idx(const moe_cfg& c, int n_cu);
 int launch_expert_ffn_f32(const moe_cfg& c, const float* Xp, const int32_t* offsets, int e_first, int e_count, const float* W,
                           size_t expert_stride_elems, long max_rows, float* H, float* Yp, hipStream_t s, hipEvent_t between,
-                          const int32_t* row_map, const int32_t* gather);
+                          const int32_t* row_map, const int32_t* gather, const int32_t* idx);
 // Rows of a bf16 row tile of the up-projection (and of the down-projection, unless ffn_down_tile_rows says less).
 int ffn_tile_rows(const moe_cfg& c, bool gather, int n_cu);
 // Height of the down-projection's row tiles for a launch over e_count experts with at most max_rows rows in all (the two
@@ -117,6 +122,21 @@ int schedule_order(const int32_t* counts, int E, double tokens_per_load, int K, 
 // Slot and load decision for every expert of a call when slots keep their experts; see schedule.hip.
 int plan_slots(const int32_t* order, int n, int K, int32_t* slot_expert, int64_t* slot_tick, int64_t* tick,
                int32_t* slot_of, int32_t* load);
+// inv NULL: row a of Yp is assignment a.
 int launch_combine(const moe_cfg& c, const void* Yp, const int32_t* inv, const float* w, void* y, hipStream_t s);
+
+// Batches of at most kDirectRows assignments, by one wave (all lanes; lane = assignment): the lanes that hold the same expert as this one
+// (0 where there is no assignment).  Values out of range are clamped, as in the batching kernels.
+__device__ inline unsigned long long direct_peers(const int32_t* __restrict__ idx, int A, int E, int lane, int& expert) {
+    const bool valid = lane < A;
+    expert = valid ? min(max(idx[lane], 0), E - 1) : 0;
+    unsigned long long peers = __ballot(valid);
+    for (int b = 0; (1 << b) < E; ++b) {
+        const bool bit = (expert >> b) & 1;
+        const unsigned long long bal = __ballot(bit);
+        peers &= bit ? bal : ~bal;
+    }
+    return valid ? peers : 0ull;
+}
 
 }  // namespace moe

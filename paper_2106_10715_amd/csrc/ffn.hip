@@ -142,8 +142,8 @@ template <bool GATED, bool SMALL>
 __global__ __launch_bounds__(SMALL ? 64 : 128, few_waves_per_simd(SMALL)) void ffn_few_kernel(
     const uint16_t* A, const int32_t* __restrict__ plan, int e_first, const char* W, size_t expert_stride_bytes, size_t block_offset_bytes,
     uint16_t* __restrict__ C, int K, int N, int act, const int32_t* __restrict__ row_map, const int32_t* __restrict__ gather,
-    int gather_k, int h_rows) {
-    ffn_few_block<GATED, SMALL>(A, plan, e_first, W, expert_stride_bytes, block_offset_bytes, C, K, N, row_map, gather, gather_k, h_rows,
+    int gather_k, int h_rows, const int32_t* __restrict__ idx, int E) {
+    ffn_few_block<GATED, SMALL>(A, plan, e_first, W, expert_stride_bytes, block_offset_bytes, C, K, N, row_map, gather, gather_k, h_rows, idx, h_rows, E,
                                 [act](float z) { return act_fn_bf16(z, act); });
 }
 
@@ -845,6 +845,10 @@ bool few_rows(const moe_cfg& c, int n_cu) {
     return rows <= (3 * items < n_cu ? 32L : items <= n_cu ? 8L : 2L) * c.E;
 }
 
+bool ffn_reads_idx(const moe_cfg& c, int n_cu) {
+    return static_cast<long>(c.T) * c.k <= kDirectRows && (c.dtype == MOE_F32 || few_rows(c, n_cu));
+}
+
 int ffn_tile_rows(const moe_cfg& c, bool gather, int n_cu) { return few_rows(c, n_cu) ? kFewTileM : gather ? kGatherTileM : kTileM; }
 size_t ffn_plan_bytes(const moe_cfg& c) { return (kPlanHeader + 2 * 4 * ffn_plan_tiles(c)) * sizeof(int32_t); }
 
@@ -889,7 +893,7 @@ int launch_pack(const moe_cfg& c, const void* Win, const void* Wgate, const void
 int launch_expert_ffn(const moe_cfg& c, const void* Xp, const int32_t* offsets, int e_first, int e_count,
                       const void* W, size_t expert_stride_bytes, long max_rows, void* H, void* Yp, int32_t* plan,
                       hipStream_t s, hipEvent_t between, hipEvent_t before_up, const int32_t* row_map, bool plan_ready,
-                      const int32_t* gather) {
+                      const int32_t* gather, const int32_t* idx) {
     if (max_rows <= 0 || e_count <= 0) return MOE_OK;
     const size_t df = static_cast<size_t>(c.d) * c.f;
     if (c.dtype == MOE_BF16) {
@@ -932,7 +936,7 @@ int launch_expert_ffn(const moe_cfg& c, const void* Xp, const int32_t* offsets, 
         };
         const int max_tiles = static_cast<int>(ffn_plan_tiles(c));
         const int down_list = tile_m_down != tile_m ? 1 : 0;       // equal heights: one list serves both kernels
-        if (!plan_ready) {          // else the kernel that batched the tokens has written the work list as well
+        if (!plan_ready && idx == nullptr) {          // else the kernel that batched the tokens has written the work list as well
             hipLaunchKernelGGL(ffn_plan_kernel, dim3(1), dim3(256), 0, s, offsets, e_first, e_count, tile_m, tile_m_down, plan,
                                c.T * c.k, max_tiles);
             MOE_LAUNCH_CHECK("ffn_plan_kernel");
@@ -950,13 +954,13 @@ int launch_expert_ffn(const moe_cfg& c, const void* Xp, const int32_t* offsets, 
         hipLaunchKernelGGL((ffn_few_kernel<true, SMALL>), dim3(c.f / few_columns(true, SMALL) / up_waves, n_tiles), dim3(64 * up_waves), 0, s, \
                            static_cast<const uint16_t*>(Xp), plan, e_first, static_cast<const char*>(W),              \
                            expert_stride_bytes, size_t(0), static_cast<uint16_t*>(H), c.d, c.f, c.act,                \
-                           static_cast<const int32_t*>(nullptr), gather, c.k, c.T * c.k);                             \
+                           static_cast<const int32_t*>(nullptr), gather, c.k, c.T * c.k, idx, c.E);                   \
         MOE_LAUNCH_CHECK("ffn_few_kernel<up>");                                                                       \
         if (between != nullptr) MOE_HIP_CHECK(hipEventRecord(between, s));                                            \
         hipLaunchKernelGGL((ffn_few_kernel<false, SMALL>), dim3(c.d / few_columns(false, SMALL), n_tiles), dim3(64), 0, s, \
                            static_cast<const uint16_t*>(H), plan, e_first, static_cast<const char*>(W),               \
                            expert_stride_bytes, down_off, static_cast<uint16_t*>(Yp), c.f, c.d, c.act, row_map,       \
-                           static_cast<const int32_t*>(nullptr), 1, c.T * c.k);                                       \
+                           static_cast<const int32_t*>(nullptr), 1, c.T * c.k, idx, c.E);                             \
         MOE_LAUNCH_CHECK("ffn_few_kernel<down>");                                                                     \
     }
             if (c.T * c.k <= 16) MOE_FFN_FEW(true) else MOE_FFN_FEW(false)
@@ -992,7 +996,7 @@ int launch_expert_ffn(const moe_cfg& c, const void* Xp, const int32_t* offsets, 
     }
     return launch_expert_ffn_f32(c, static_cast<const float*>(Xp), offsets, e_first, e_count, static_cast<const float*>(W),
                                  expert_stride_bytes / 4, max_rows, static_cast<float*>(H), static_cast<float*>(Yp), s, between,
-                                 row_map, gather);
+                                 row_map, gather, idx);
 }
 
 #endif  // FFN_PART

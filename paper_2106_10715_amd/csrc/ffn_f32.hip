@@ -68,6 +68,37 @@ __device__ inline bool find_tile(const int32_t* __restrict__ offsets, int e_firs
     return true;
 }
 
+// The same for at most kDirectRows assignments that nothing has batched: the experts in the order of their first assignments, row r of an expert
+// is assignment sh_row[row_begin + r].
+__device__ inline bool find_tile_direct(const int32_t* __restrict__ idx, int A, int E, int tile_m, int slot, int (&sh_row)[kDirectRows], int& e_out,
+                                        int& row_begin, int& rows) {
+    __shared__ int sh_e, sh_mt, sh_n;
+    if (threadIdx.x < 64) {
+        const int lane = threadIdx.x;
+        int expert;
+        const unsigned long long peers = direct_peers(idx, A, E, lane, expert), below = (1ull << lane) - 1ull;
+        const bool first = peers != 0ull && (peers & below) == 0ull;
+        const int tiles = (__popcll(peers) + tile_m - 1) / tile_m;         // one or two
+        const unsigned long long two = __ballot(first && tiles == 2);
+        const int start = __popcll(__ballot(first) & below) + __popcll(two & below);
+        const unsigned long long found = __ballot(first && start <= slot && slot < start + tiles);
+        if (found == 0ull) {
+            if (lane == 0) sh_e = -1;
+        } else {
+            const int leader = __ffsll(static_cast<long long>(found)) - 1;
+            if (lane == leader) { sh_e = expert; sh_mt = slot - start; sh_n = __popcll(peers); }
+            if (peers != 0ull && (peers >> leader) & 1ull) sh_row[__popcll(peers & below)] = lane;
+        }
+    }
+    __syncthreads();
+    if (sh_e < 0) return false;
+    e_out = sh_e;
+    const int tiles = (sh_n + tile_m - 1) / tile_m, per_tile = min(tile_m, ((sh_n + tiles - 1) / tiles + 31) & ~31);
+    row_begin = sh_mt * per_tile;
+    rows = min(per_tile, sh_n - row_begin);
+    return true;
+}
+
 // What bounds it: the matrix instruction (157 TFLOP/s) once there are enough blocks, the latency of the steps of one block
 // in short launches.  The kernel it replaces (vector multiply-adds, scalar loads, no load in flight across steps) ran at
 // 18 TFLOP/s.  Whole layer before -> after, with the rows read and written through the permutation: 64 tokens, d 256, f 512,
@@ -100,13 +131,19 @@ __global__ __launch_bounds__(256, 2) void ffn_f32_kernel(const float* __restrict
                                                          size_t expert_stride_elems, size_t off_b0, size_t off_b1,
                                                          float* __restrict__ C, int K, int N, int act, int total_rows,
                                                          const int32_t* __restrict__ gather, int gather_k,
-                                                         const int32_t* __restrict__ row_map) {
+                                                         const int32_t* __restrict__ row_map, const int32_t* __restrict__ idx, int E) {
     using S = Shape<SPLIT>;
     constexpr int NB = GATED ? 2 : 1;
     constexpr int kAFloats = S::BM * S::kARow, kBFloats = S::KC * S::kBRow, kBuf = kAFloats + NB * kBFloats;
     __shared__ __align__(16) float lds[2][kBuf];
     int e, row_begin, rows;
-    if (!find_tile(offsets, e_first, e_count, S::BM, blockIdx.y, total_rows, e, row_begin, rows)) return;
+    __shared__ int sh_row[kDirectRows];
+    const bool direct = idx != nullptr;
+    if (direct) {
+        if (!find_tile_direct(idx, total_rows, E, S::BM, blockIdx.y, sh_row, e, row_begin, rows)) return;
+    } else {
+        if (!find_tile(offsets, e_first, e_count, S::BM, blockIdx.y, total_rows, e, row_begin, rows)) return;
+    }
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int n0 = blockIdx.x * S::BN;
     const float* Wb[NB];
@@ -121,8 +158,9 @@ __global__ __launch_bounds__(256, 2) void ffn_f32_kernel(const float* __restrict
 #pragma unroll
     for (int i = 0; i < 2; ++i) {
         const int id = tid + i * 256;
-        const int r = id / kAVec, row = row_begin + min(r, rows - 1);      // rows past the end repeat the last one, not stored
-        const size_t src = gather != nullptr ? static_cast<size_t>(gather[row] / gather_k) : static_cast<size_t>(row);
+        const int r = id / kAVec, at = row_begin + min(r, rows - 1);       // rows past the end repeat the last one, not stored
+        const int row = direct ? sh_row[at] : at;
+        const size_t src = GATED && direct ? static_cast<size_t>(row / gather_k) : gather != nullptr ? static_cast<size_t>(gather[row] / gather_k) : static_cast<size_t>(row);
         // (SPLIT: element 16 w + n of a step is element n of the step in quarter w)
         a_src[i] = A + src * K + (SPLIT ? id % kAVec / 4 * (K / 4) + 4 * (id % 4) : 4 * (id % kAVec));
         a_dst[i] = r * S::kARow + 4 * (id % kAVec);
@@ -203,7 +241,7 @@ __global__ __launch_bounds__(256, 2) void ffn_f32_kernel(const float* __restrict
     // the weights are the first operand: lane l holds token row l % 32 and, in v = 4 g .. 4 g + 3, columns 8 g + 4 (l / 32) + 0..3
     auto value = [&](float gate, float in) { return GATED ? act_f32(gate, act) * in : gate; };
     auto out_at = [&](int r, int col) {
-        const int row = row_begin + r;
+        const int row = direct ? sh_row[row_begin + r] : row_begin + r;
         return reinterpret_cast<f32x4*>(C + static_cast<size_t>(row_map != nullptr ? row_map[row] : row) * N + n0 + col);
     };
     if constexpr (!SPLIT) {
@@ -251,7 +289,7 @@ __global__ __launch_bounds__(256, 2) void ffn_f32_kernel(const float* __restrict
 
 int launch_expert_ffn_f32(const moe_cfg& c, const float* Xp, const int32_t* offsets, int e_first, int e_count, const float* W,
                           size_t expert_stride_elems, long max_rows, float* H, float* Yp, hipStream_t s, hipEvent_t between,
-                          const int32_t* row_map, const int32_t* gather) {
+                          const int32_t* row_map, const int32_t* gather, const int32_t* idx) {
     const size_t df = static_cast<size_t>(c.d) * c.f;
     int dev = 0;
     const DeviceInfo* info = nullptr;
@@ -272,21 +310,21 @@ int launch_expert_ffn_f32(const moe_cfg& c, const float* Xp, const int32_t* offs
     if (up_split)
         hipLaunchKernelGGL((ffn_f32_kernel<true, true>), grid_for(true, c.f), block, 0, s, Xp, offsets, e_first, e_count, W,
                            expert_stride_elems, size_t(0), df, H, c.d, c.f, c.act, c.T * c.k, gather, c.k,
-                           static_cast<const int32_t*>(nullptr));
+                           static_cast<const int32_t*>(nullptr), idx, c.E);
     else
         hipLaunchKernelGGL((ffn_f32_kernel<true, false>), grid_for(false, c.f), block, 0, s, Xp, offsets, e_first, e_count, W,
                            expert_stride_elems, size_t(0), df, H, c.d, c.f, c.act, c.T * c.k, gather, c.k,
-                           static_cast<const int32_t*>(nullptr));
+                           static_cast<const int32_t*>(nullptr), idx, c.E);
     MOE_LAUNCH_CHECK("ffn_f32_kernel<up>");
     if (between != nullptr) MOE_HIP_CHECK(hipEventRecord(between, s));
     if (down_split)
         hipLaunchKernelGGL((ffn_f32_kernel<false, true>), grid_for(true, c.d), block, 0, s, H, offsets, e_first, e_count, W,
                            expert_stride_elems, 2 * df, 2 * df, Yp, c.f, c.d, c.act, c.T * c.k,
-                           static_cast<const int32_t*>(nullptr), 1, row_map);
+                           static_cast<const int32_t*>(nullptr), 1, row_map, idx, c.E);
     else
         hipLaunchKernelGGL((ffn_f32_kernel<false, false>), grid_for(false, c.d), block, 0, s, H, offsets, e_first, e_count, W,
                            expert_stride_elems, 2 * df, 2 * df, Yp, c.f, c.d, c.act, c.T * c.k,
-                           static_cast<const int32_t*>(nullptr), 1, row_map);
+                           static_cast<const int32_t*>(nullptr), 1, row_map, idx, c.E);
     MOE_LAUNCH_CHECK("ffn_f32_kernel<down>");
     return MOE_OK;
 }

@@ -24,12 +24,20 @@ constexpr int few_depth(bool up, bool small, int RB) { return small ? (up ? 4 : 
 constexpr int few_waves_per_simd(bool small) { return small ? 4 : 2; }
 constexpr int few_columns(bool up, bool small) { return up || small ? 16 : 32; }
 
+// The rows of a tile: row_begin, row_begin + 1, ... of the batched order; or, where the kernel reads idx itself, in the order of the
+// assignments, lane r holding the r-th.
+struct FewRows {
+    int e, row_begin, rows, assignment;
+    bool direct;
+    __device__ int row(int r) const { return direct ? __builtin_amdgcn_ds_bpermute(4 * r, assignment) : row_begin + r; }
+};
+
 // GATED: H = act(A W_gate) * (A W_in), 16 columns of d_ff per block; else 16 or 32 columns of W_out.  Rows row_begin ..
 // row_begin + rows of the batched order, rows <= 16 RB, all of expert e.  Act: act(z) of the gate.  A: GATED, the token array
 // (row r of the batched order is row gather[r] / gather_k) or the batched rows (gather NULL); else H in its chunked order,
 // [chunk of 64 columns][row][64].
 template <bool GATED, bool SMALL, int RB, class Act>
-__device__ inline void ffn_few_rows(const uint16_t* A, int e, int row_begin, int rows, int e_first, const char* W,
+__device__ inline void ffn_few_rows(const uint16_t* A, const FewRows& tile, int e_first, const char* W,
                                     size_t expert_stride_bytes, size_t block_offset_bytes, uint16_t* __restrict__ C, int K, int N,
                                     const int32_t* __restrict__ row_map, const int32_t* __restrict__ gather, int gather_k,
                                     int h_rows, Act act) {
@@ -41,6 +49,7 @@ __device__ inline void ffn_few_rows(const uint16_t* A, int e, int row_begin, int
     constexpr int NJ = GATED ? 2 : kColumns / 16;   // weight operands of a k-step of 32: gate and in, or 16 columns each
     constexpr int kDepth = few_depth(GATED, SMALL, RB);
     const int lane = threadIdx.x & 63, c15 = lane & 15, g = lane >> 4;
+    const int e = tile.e, rows = tile.rows;
     // The units that share the 8 KiB window of a step in the packed weights (two, or four of 16 columns of W_out) go to blocks
     // of one XCD that start together: 64 experts, 64 tokens x 2: 2.29 -> 2.25 ms.
     constexpr int kShare = GATED || kColumns == 32 ? 1 : 2, kGroup = 8 << kShare;
@@ -72,8 +81,8 @@ __device__ inline void ffn_few_rows(const uint16_t* A, int e, int row_begin, int
     uint32_t a_lane[RB];
 #pragma unroll
     for (int rb = 0; rb < RB; ++rb) {
-        const int row = row_begin + min(rb * 16 + c15, rows - 1);       // past the end: the last row again, not stored
-        const int src = GATED && gather != nullptr ? gather[row] / gather_k : row;
+        const int row = tile.row(min(rb * 16 + c15, rows - 1));         // past the end: the last row again, not stored
+        const int src = !GATED ? row : tile.direct ? row / gather_k : gather != nullptr ? gather[row] / gather_k : row;
         a_lane[rb] = static_cast<uint32_t>(src) * (GATED ? static_cast<uint32_t>(K) * 2u : 128u) + 16u * g;
     }
     ux4 wr[kDepth][2][NJ], ar[kDepth][2][RB];
@@ -120,8 +129,8 @@ __device__ inline void ffn_few_rows(const uint16_t* A, int e, int row_begin, int
     // the weights are the first operand: lane 16 g + c holds row c of its row block and columns 4 g .. 4 g + 3 of every 16
 #pragma unroll
     for (int rb = 0; rb < RB; ++rb) {
+        const int row = tile.row(rb * 16 + c15);                        // (all lanes: it may be a lane exchange)
         if (rb * 16 + c15 < rows) {
-            const int row = row_begin + rb * 16 + c15;
             const size_t out_row = GATED || row_map == nullptr ? row : row_map[row];
 #pragma unroll
             for (int j = 0; j < kColumns / 16; ++j) {
@@ -138,19 +147,46 @@ __device__ inline void ffn_few_rows(const uint16_t* A, int e, int row_begin, int
 }
 
 // A wave: one column unit (from blockIdx.x) of one row tile (blockIdx.y, an entry of the work list, at most kFewTileM rows).
+// idx: there is no work list and no batched order; tile blockIdx.y is the expert whose first assignment is the blockIdx.y-th such, and all A
+// assignments are looked through here (one read and a few lane votes, against a launch and three dependent reads: 1 token
+// 59.7 -> 55.2 us, 30 tokens x 2 on 8 experts, d 1024, f 2048 37.6 -> 33.3; fp32, 64 tokens, d 256, f 512, 4 experts 23.3 -> 19.7).
 template <bool GATED, bool SMALL, class Act>
 __device__ inline void ffn_few_block(const uint16_t* A, const int32_t* __restrict__ plan, int e_first, const char* W,
                                      size_t expert_stride_bytes, size_t block_offset_bytes, uint16_t* __restrict__ C, int K, int N,
                                      const int32_t* __restrict__ row_map, const int32_t* __restrict__ gather, int gather_k,
-                                     int h_rows, Act act) {
+                                     int h_rows, const int32_t* __restrict__ idx, int n_idx, int E, Act act) {
     const int tile = blockIdx.y;
-    const int n_tiles = plan[16];
-    const int4 t = reinterpret_cast<const int4*>(plan + kPlanHeader)[tile];      // (the list has room for every tile of the grid)
-    if (tile >= n_tiles) return;                    // uniform: fewer experts have rows than the grid provides for
-    // the same for all lanes: kept in scalar registers
-    const int e = __builtin_amdgcn_readfirstlane(t.x), row_begin = __builtin_amdgcn_readfirstlane(t.y), rows = __builtin_amdgcn_readfirstlane(t.z);
+    FewRows at;
+    at.direct = idx != nullptr;
+    if (idx != nullptr) {
+        const int lane = threadIdx.x & 63;
+        int expert;
+        const unsigned long long peers = direct_peers(idx, n_idx, E, lane, expert), below = (1ull << lane) - 1ull;
+        const bool first = peers != 0ull && (peers & below) == 0ull;
+        const unsigned long long firsts = __ballot(first);
+        if (tile >= __popcll(firsts)) return;       // uniform: fewer experts have rows than the grid provides for
+        const int leader = __ffsll(static_cast<long long>(__ballot(first && __popcll(firsts & below) == tile))) - 1;
+        const unsigned lo = __builtin_amdgcn_readlane(static_cast<int>(peers), leader), hi = __builtin_amdgcn_readlane(static_cast<int>(peers >> 32), leader);
+        const unsigned long long members = static_cast<unsigned long long>(hi) << 32 | lo;
+        at.e = __builtin_amdgcn_readlane(expert, leader);
+        at.rows = __popcll(members);
+        at.row_begin = 0;
+        // every lane sends its number to its place: the members in order, the others behind them
+        const int place = (members >> lane) & 1ull ? __popcll(members & below) : at.rows + __popcll(~members & below);
+        at.assignment = __builtin_amdgcn_ds_permute(4 * place, lane);
+    } else {
+        const int n_tiles = plan[16];
+        const int4 t = reinterpret_cast<const int4*>(plan + kPlanHeader)[tile];      // (the list has room for every tile of the grid)
+        if (tile >= n_tiles) return;                // uniform, as above
+        // the same for all lanes: kept in scalar registers
+        at.e = __builtin_amdgcn_readfirstlane(t.x);
+        at.row_begin = __builtin_amdgcn_readfirstlane(t.y);
+        at.rows = __builtin_amdgcn_readfirstlane(t.z);
+        at.assignment = 0;
+    }
+    const int rows = at.rows;
     auto run = [&](auto rb) __attribute__((always_inline)) {
-        ffn_few_rows<GATED, SMALL, decltype(rb)::value>(A, e, row_begin, rows, e_first, W, expert_stride_bytes, block_offset_bytes, C, K, N,
+        ffn_few_rows<GATED, SMALL, decltype(rb)::value>(A, at, e_first, W, expert_stride_bytes, block_offset_bytes, C, K, N,
                                                         row_map, gather, gather_k, h_rows, act);
     };
     if constexpr (SMALL) {

@@ -349,3 +349,23 @@ def test_batching_in_one_launch(A, E, shift):
     assert torch.equal(inv.long()[order], torch.arange(A, device="cuda"))
     assert torch.equal(counts.long(), torch.bincount(e, minlength=E))
     assert offsets.tolist() == [0] + torch.cumsum(counts, 0).tolist()
+
+
+@pytest.mark.parametrize("T,k", [(1, 1), (2, 8), (16, 1), (17, 1), (21, 3), (32, 2), (64, 1), (65, 1)])
+@pytest.mark.parametrize("E,crowd", [(9, 0.0), (9, 8.0), (256, 0.0), (64, 3.0)])
+@pytest.mark.parametrize("dtype,renorm", [("bf16", 1), ("bf16", 0), ("f32", 1)])
+def test_layer_without_batching(T, k, E, crowd, dtype, renorm):
+    """Up to 64 assignments the expert kernels find their rows in idx themselves: the bytes of the four calls, with experts of one row
+    and with all rows on a few (up to 64 rows: two tiles of the fp32 kernel)."""
+    d, f = 128, 192
+    rng = np.random.default_rng(T + E)
+    cfg = M.MoeCfg.make(T, d, f, E, k, dtype, renorm)
+    x, Wg, _ = make_inputs(T, T, d, E, dtype)
+    ex = [tuple(rounded(rng.standard_normal(s) * 0.05, dtype) for s in ((d, f), (d, f), (f, d))) for _ in range(min(E, 9))]
+    packed = H.pack_experts(W.Workload("t", T, d, f, E, k, dtype, 0), cfg, experts=lambda e: ex[e % len(ex)])[0]
+    bias = torch.zeros(E, device="cuda")
+    bias[E // 2:E // 2 + k] = crowd
+    ws = torch.empty(M.moe_workspace_bytes(cfg), dtype=torch.uint8, device="cuda")
+    y4, y = _four_calls(cfg, H.to_device(x, dtype), H.to_device(Wg, dtype), bias, packed, ws)
+    assert torch.isfinite(y.float()).all()
+    assert torch.equal(y, y4)
