@@ -3,14 +3,16 @@
 //     H  = act(Xp W_gate[e]) * (Xp W_in[e])        "up",   epilogue fused
 //     Yp = H W_out[e]                               "down"
 //
-// on the fp32 matrix instruction 32x32x2, whose products and sums are fp32 fused multiply-adds.
+// on the bf16 matrix instruction, with every fp32 value as the sum of three bf16 values that together hold all its 24 bits.
 #include "common.h"
 
 namespace moe {
 namespace {
 
-typedef float f32x16 __attribute__((ext_vector_type(16)));
+typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
+typedef float f32x2 __attribute__((ext_vector_type(2)));
 typedef float f32x4 __attribute__((ext_vector_type(4)));
+typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 
 __device__ inline float act_f32(float z, int act) {
     if (act == 0) return 0.5f * z * (1.0f + erff(z * 0.70710678118654752f));
@@ -58,231 +60,262 @@ __device__ inline bool find_tile(const int32_t* __restrict__ offsets, int e_firs
     __syncthreads();
     if (sh_e < 0) return false;
     e_out = e_first + sh_e;
-    // the expert's rows are split evenly over its tiles (in multiples of 32 rows), not into full tiles
+    // the expert's rows are split evenly over its tiles (in multiples of 16 rows), not into full tiles
     // and a small remainder: equal tiles finish together and none is nearly empty
     const int lo = seg_lo(e_out), hi = seg_hi(e_out), n = hi - lo;
     const int tiles = (n + tile_m - 1) / tile_m;
-    const int per_tile = min(tile_m, ((n + tiles - 1) / tiles + 31) & ~31);
+    const int per_tile = min(tile_m, ((n + tiles - 1) / tiles + 15) & ~15);
     row_begin = lo + sh_mt * per_tile;
     rows = min(per_tile, hi - row_begin);
     return true;
 }
 
-// The same for at most kDirectRows assignments that nothing has batched: the experts in the order of their first assignments, row r of an expert
-// is assignment sh_row[row_begin + r].
-__device__ inline bool find_tile_direct(const int32_t* __restrict__ idx, int A, int E, int tile_m, int slot, int (&sh_row)[kDirectRows], int& e_out,
-                                        int& row_begin, int& rows) {
-    __shared__ int sh_e, sh_mt, sh_n;
+// The same for at most kDirectRows assignments that nothing has batched, no more than a tile of any expert: the experts in the order of their
+// first assignments, row r of the tile is assignment sh_row[r].
+__device__ inline bool find_tile_direct(const int32_t* __restrict__ idx, int A, int E, int slot, int (&sh_row)[kDirectRows], int& e_out, int& rows) {
+    __shared__ int sh_e, sh_n;
     if (threadIdx.x < 64) {
         const int lane = threadIdx.x;
         int expert;
         const unsigned long long peers = direct_peers(idx, A, E, lane, expert), below = (1ull << lane) - 1ull;
         const bool first = peers != 0ull && (peers & below) == 0ull;
-        const int tiles = (__popcll(peers) + tile_m - 1) / tile_m;         // one or two
-        const unsigned long long two = __ballot(first && tiles == 2);
-        const int start = __popcll(__ballot(first) & below) + __popcll(two & below);
-        const unsigned long long found = __ballot(first && start <= slot && slot < start + tiles);
+        const unsigned long long firsts = __ballot(first), found = __ballot(first && __popcll(firsts & below) == slot);
         if (found == 0ull) {
             if (lane == 0) sh_e = -1;
         } else {
             const int leader = __ffsll(static_cast<long long>(found)) - 1;
-            if (lane == leader) { sh_e = expert; sh_mt = slot - start; sh_n = __popcll(peers); }
-            if (peers != 0ull && (peers >> leader) & 1ull) sh_row[__popcll(peers & below)] = lane;
+            if (lane == leader) { sh_e = expert; sh_n = __popcll(peers); }
+            if ((peers >> leader) & 1ull) sh_row[__popcll(peers & below)] = lane;
         }
     }
     __syncthreads();
     if (sh_e < 0) return false;
     e_out = sh_e;
-    const int tiles = (sh_n + tile_m - 1) / tile_m, per_tile = min(tile_m, ((sh_n + tiles - 1) / tiles + 31) & ~31);
-    row_begin = sh_mt * per_tile;
-    rows = min(per_tile, sh_n - row_begin);
+    rows = sh_n;
     return true;
 }
 
-// What bounds it: the matrix instruction (157 TFLOP/s) once there are enough blocks, the latency of the steps of one block
-// in short launches.  The kernel it replaces (vector multiply-adds, scalar loads, no load in flight across steps) ran at
-// 18 TFLOP/s.  Whole layer before -> after, with the rows read and written through the permutation: 64 tokens, d 256, f 512,
-// 4 experts 144 -> 23 us; 512 tokens x 2, d 1024, f 4096, 8 experts 1386 -> 340 to
-// 365 us by the rows per expert.
-// Two shapes of a block (four waves, each with 32 x 32 output tiles, twice that when GATED):
-//   wide   64 rows x 64 columns, a wave per quarter, 32 reduction elements per step
-//   split  32 rows x 32 columns, all four waves on the same tile, each with a quarter of the reduction dimension, 16
-//          elements per step; the four partial tiles are added in wave order at the end
-// The wide shape adds up the same four quarters one after the other, so that both give the same bits and a row's result does
-// not depend on the batch it came in (d 1024, f 4096, 8 experts, k 2, one sum over the whole dimension -> four quarters: 512
-// tokens 334 -> 340 us, 2048 tokens 1037 -> 1046).
-// Both stage the activations ([row][k]) and the weights ([k][column]) of a step through LDS, double buffered, one barrier
-// per step; the global loads of a step are issued kAhead steps earlier into registers.  Row strides in LDS are chosen so
-// that the 16-byte activation reads and the 4-byte weight reads of a wave touch every bank once.
-template <bool SPLIT>
-struct Shape {
-    static constexpr int BM = SPLIT ? 32 : 64, BN = SPLIT ? 32 : 64, KC = SPLIT ? 64 : 32;
-    static constexpr int kAhead = SPLIT ? 3 : 2;
-    static constexpr int kWaveK = SPLIT ? KC / 4 : KC;          // reduction elements of a step one wave multiplies
-    static constexpr int kStride = kWaveK;                      // elements from one step to the next
-    static constexpr int kARow = KC + 4, kBRow = BN + 8;        // floats per LDS row
-};
-
-// GATED: C = act(A B0) * (A B1), else C = A B0.  gather (may be NULL): row r of the batched order is row gather[r] / gather_k
-// of A; row_map (may be NULL): row r is written to row row_map[r] of C.
-template <bool GATED, bool SPLIT>
-__global__ __launch_bounds__(256, 2) void ffn_f32_kernel(const float* __restrict__ A, const int32_t* __restrict__ offsets,
-                                                         int e_first, int e_count, const float* __restrict__ W,
-                                                         size_t expert_stride_elems, size_t off_b0, size_t off_b1,
-                                                         float* __restrict__ C, int K, int N, int act, int total_rows,
-                                                         const int32_t* __restrict__ gather, int gather_k,
-                                                         const int32_t* __restrict__ row_map, const int32_t* __restrict__ idx, int E) {
-    using S = Shape<SPLIT>;
-    constexpr int NB = GATED ? 2 : 1;
-    constexpr int kAFloats = S::BM * S::kARow, kBFloats = S::KC * S::kBRow, kBuf = kAFloats + NB * kBFloats;
-    __shared__ __align__(16) float lds[2][kBuf];
-    int e, row_begin, rows;
-    __shared__ int sh_row[kDirectRows];
-    const bool direct = idx != nullptr;
-    if (direct) {
-        if (!find_tile_direct(idx, total_rows, E, S::BM, blockIdx.y, sh_row, e, row_begin, rows)) return;
-    } else {
-        if (!find_tile(offsets, e_first, e_count, S::BM, blockIdx.y, total_rows, e, row_begin, rows)) return;
-    }
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    const int n0 = blockIdx.x * S::BN;
-    const float* Wb[NB];
-    Wb[0] = W + static_cast<size_t>(e - e_first) * expert_stride_elems + off_b0 + n0;
-    if (GATED) Wb[NB - 1] = W + static_cast<size_t>(e - e_first) * expert_stride_elems + off_b1 + n0;
-
-    // this thread's two 16-byte pieces of the activation tile and of every weight tile
-    constexpr int kAVec = S::KC / 4, kBVec = S::BN / 4;          // pieces per row
-    const float* a_src[2];
-    int a_dst[2], b_dst[2];
-    size_t b_src[2];
+// Eight values as three bf16 operands: the upper 16 bits of the value, of what they leave, and of what is left then (8 + 8 + 8
+// significant bits, nothing is rounded).
+struct Split { u32x4 v[3]; };
+__device__ __attribute__((always_inline)) inline Split split8(const float (&x)[8]) {
+    Split s;
 #pragma unroll
-    for (int i = 0; i < 2; ++i) {
-        const int id = tid + i * 256;
-        const int r = id / kAVec, at = row_begin + min(r, rows - 1);       // rows past the end repeat the last one, not stored
+    for (int p = 0; p < 4; ++p) {
+        uint32_t bits[2][3];
+#pragma unroll
+        for (int h = 0; h < 2; ++h) {
+            const float v = x[2 * p + h];
+            const float rest = v - __uint_as_float(__float_as_uint(v) & 0xffff0000u);
+            const float last = rest - __uint_as_float(__float_as_uint(rest) & 0xffff0000u);
+            bits[h][0] = __float_as_uint(v);
+            bits[h][1] = __float_as_uint(rest);
+            bits[h][2] = __float_as_uint(last);
+        }
+#pragma unroll
+        for (int q = 0; q < 3; ++q) s.v[q][p] = __builtin_amdgcn_perm(bits[1][q], bits[0][q], 0x07060302u);      // the upper halves
+    }
+    return s;
+}
+__device__ __attribute__((always_inline)) inline f32x4 mfma(const u32x4& w, const u32x4& a, const f32x4& c) {
+    return __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, w), __builtin_bit_cast(bf16x8, a), c, 0, 0, 0);
+}
+
+constexpr int kRows = 64;                                // rows of a tile
+constexpr int kPartRow = 68;                             // floats per row of a partial tile in LDS: up to 64 and 4 of padding
+// Columns of a lane, of each matrix: a block has 16 times as many.
+constexpr int lane_columns(bool gated, bool narrow) { return (gated ? 2 : 4) >> (narrow ? 1 : 0); }
+
+// What bounds it: the vector instructions that split the operands (1024 rows of 8 experts, d 1024, f 4096: half of the cycles, the matrix
+// instructions 29 %, little of them at once with two waves per SIMD); the latency of a block's few steps in short launches.  Six of the nine products of the parts are formed (the other three
+// are below 2^-24 of the whole) by six bf16 instructions, in 96 cycles for 32 reduction elements where the fp32 instruction takes 256.
+// They are added up smallest first from zero and the sum then to the running one in fp32, one addition per 32 elements: against 64 bits
+// a sum of 4096 products is 1.5e-7 off (normally distributed; positive 0.7e-7), the fp32 instruction's chain of additions in four quarters 5.7e-7 (2.4e-7).
+// A block is one tile of up to 64 rows by 64 weight columns (GATED: 32 of each matrix), or half as many; its four waves take a quarter of the
+// reduction dimension each and share nothing until their partial tiles are added in wave order at the end, so there is no barrier
+// in the loop, no LDS, and every row's sum has the same order in every tile and batch.  Weights and activations go straight into registers in operand order: a lane's
+// eight reduction elements are 4 g .. 4 g + 3 and 16 + 4 g .. of 32 (g = lane / 16), its two or four columns are neighbours.
+// A value that comes out infinite or NaN is computed again by plain fp32 multiply-adds: the parts of an infinity are no numbers, and the
+// order of the sums decides where an overflow shows.
+// Against tiles of 64 x 64 and 32 x 32 through LDS with the fp32 instruction, layers in us: 512 tokens x 2, d 1024, f 4096, 8 experts 344 -> 273 (up 218 ->
+// 168, down 138 -> 91), 1024 x 2 on 4 experts 568 -> 378, 16 x 1 on 8 138 -> 103, 1000 x 1, f 1024, 5 experts 121 -> 90, 100 x 1, d 512, f 2048, 4 experts
+// 45.8 -> 39.6, 64 x 1, d 256, f 512, 4 experts 19.7 -> 17.5.  Blocks that take several column groups one after the other: 5-15 % slower.
+template <bool GATED, bool NARROW, int RB>
+__device__ inline void ffn_f32_tile(const float* A, const int32_t* gather, int gather_k, bool direct, const int (&sh_row)[kDirectRows], int row_begin,
+                                    int rows, const float* W0, const float* W1, float* C, int K, int N, int n0, int act, const int32_t* row_map,
+                                    float (&part)[4][kRows * kPartRow]) {
+    constexpr int kDepth = RB >= 3 ? 1 : RB == 2 ? 2 : 3;                   // steps requested ahead, as the registers allow
+    constexpr int NC = lane_columns(GATED, NARROW), NM = GATED ? 2 : 1, NJ = NM * NC;     // a lane's columns, matrices, operands
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6), c15 = lane & 15, g = lane >> 4;
+    const int steps = K / 32, s_lo = wave * steps / 4, s_hi = (wave + 1) * steps / 4;
+    auto in_row = [&](int r) {                                              // where row r of the tile is read
+        const int at = row_begin + min(r, rows - 1);                        // past the end: the last row again, not stored
         const int row = direct ? sh_row[at] : at;
-        const size_t src = GATED && direct ? static_cast<size_t>(row / gather_k) : gather != nullptr ? static_cast<size_t>(gather[row] / gather_k) : static_cast<size_t>(row);
-        // (SPLIT: element 16 w + n of a step is element n of the step in quarter w)
-        a_src[i] = A + src * K + (SPLIT ? id % kAVec / 4 * (K / 4) + 4 * (id % 4) : 4 * (id % kAVec));
-        a_dst[i] = r * S::kARow + 4 * (id % kAVec);
-        b_src[i] = static_cast<size_t>(SPLIT ? id / kBVec / 16 * (K / 4) + id / kBVec % 16 : id / kBVec) * N + 4 * (id % kBVec);
-        b_dst[i] = kAFloats + (id / kBVec) * S::kBRow + 4 * (id % kBVec);
-    }
-    f32x4 ra[S::kAhead][2], rb[S::kAhead][NB][2];
-    const int steps = K / S::KC;
-    auto fetch = [&](int q, int step) {
-        const int c = min(step, steps - 1);                               // past the end: the last step again, unused
-#pragma unroll
-        for (int i = 0; i < 2; ++i) {
-            ra[q][i] = *reinterpret_cast<const f32x4*>(a_src[i] + c * S::kStride);
-#pragma unroll
-            for (int b = 0; b < NB; ++b)
-                rb[q][b][i] = *reinterpret_cast<const f32x4*>(Wb[b] + static_cast<size_t>(c) * S::kStride * N + b_src[i]);
-        }
+        return GATED && direct ? row / gather_k : gather != nullptr ? gather[row] / gather_k : row;
     };
-    // the wave's place in the tile: rows and columns, or (SPLIT) its part of the reduction elements of a step
-    const int wrow = SPLIT ? 0 : 32 * (wave >> 1), wcol = SPLIT ? 0 : 32 * (wave & 1), wk = SPLIT ? wave * S::kWaveK : 0;
-    const int h = lane >> 5, c31 = lane & 31;
-    f32x16 acc[NB], total[NB];                   // the quarter at hand; the quarters before it (not SPLIT)
+    typedef float wcols __attribute__((ext_vector_type(NC)));
+    const float* a_src[RB];                                                 // next to be requested
 #pragma unroll
-    for (int b = 0; b < NB; ++b)
+    for (int rb = 0; rb < RB; ++rb) a_src[rb] = A + static_cast<size_t>(in_row(16 * rb + c15)) * K + 4 * g + 32 * min(s_lo, steps - 1);
+    const uint32_t w_lane = static_cast<uint32_t>(4 * g * N + NC * c15) * 4u;
+    f32x4 acc[RB][NJ];
 #pragma unroll
-        for (int v = 0; v < 16; ++v) acc[b][v] = total[b][v] = 0.f;
-    int quarter_end = K / 4;
+    for (int rb = 0; rb < RB; ++rb)
 #pragma unroll
-    for (int q = 0; q < S::kAhead; ++q) fetch(q, q);
-    for (int s0 = 0; s0 < steps; s0 += S::kAhead) {
+        for (int j = 0; j < NJ; ++j) acc[rb][j] = f32x4{0.f, 0.f, 0.f, 0.f};
+    float aw[kDepth][RB][8], ww[kDepth][8][NJ];
+    // (steps past the wave's last one are read from that one and not used; a fence after every batch of loads, and pointers that are
+    // not __restrict__: the compiler would move the loads down to their use.  The same for all lanes up to the lane's 32-bit offset.)
+    auto load_w = [&](int q, int s) __attribute__((always_inline)) {
+        const size_t at = (static_cast<size_t>(32 * max(min(s, s_hi - 1), 0)) * N + n0) * 4;
 #pragma unroll
-        for (int q = 0; q < S::kAhead; ++q) {
+        for (int m = 0; m < NM; ++m)
+#pragma unroll
+            for (int j = 0; j < 8; ++j) {
+                const char* from = reinterpret_cast<const char*>(m == 0 ? W0 : W1) + (at + static_cast<size_t>(j < 4 ? j : 12 + j) * N * 4);
+                const wcols u = *reinterpret_cast<const wcols*>(from + w_lane);
+#pragma unroll
+                for (int i = 0; i < NC; ++i) ww[q][j][m * NC + i] = u[i];
+            }
+    };
+    auto load_a = [&](int q, int rb, int s) __attribute__((always_inline)) {
+        const f32x4 u = *reinterpret_cast<const f32x4*>(a_src[rb]), v = *reinterpret_cast<const f32x4*>(a_src[rb] + 16);
+        if (s + 1 < s_hi) a_src[rb] += 32;                                  // uniform
+#pragma unroll
+        for (int i = 0; i < 4; ++i) { aw[q][rb][i] = u[i]; aw[q][rb][4 + i] = v[i]; }
+    };
+#pragma unroll
+    for (int q = 0; q < kDepth; ++q) {
+        load_w(q, s_lo + q);
+#pragma unroll
+        for (int rb = 0; rb < RB; ++rb) load_a(q, rb, s_lo + q);
+        asm volatile("" : : : "memory");
+    }
+    for (int s0 = s_lo; s0 < s_hi; s0 += kDepth) {
+#pragma unroll
+        for (int q = 0; q < kDepth; ++q) {
             const int s = s0 + q;
-            if (s >= steps) break;                                        // uniform
-            float* buf = lds[s & 1];         // its last readers passed the barrier of the step before
+            if (s >= s_hi) break;                                           // uniform
+            // The next loads go out as soon as their registers are free, and the operands of a row block are split under the products
+            // of the one before: nothing is moved across the barriers of the scheduler.
+            Split w[NJ], a;
 #pragma unroll
-            for (int i = 0; i < 2; ++i) {
-                *reinterpret_cast<f32x4*>(buf + a_dst[i]) = ra[q][i];
-#pragma unroll
-                for (int b = 0; b < NB; ++b) *reinterpret_cast<f32x4*>(buf + b_dst[i] + b * kBFloats) = rb[q][b][i];
+            for (int j = 0; j < NJ; ++j) {
+                const float x[8] = {ww[q][0][j], ww[q][1][j], ww[q][2][j], ww[q][3][j], ww[q][4][j], ww[q][5][j], ww[q][6][j], ww[q][7][j]};
+                w[j] = split8(x);
             }
-            fetch(q, s + S::kAhead);
-            __syncthreads();
-            const float* pa = buf + (wrow + c31) * S::kARow + wk + 4 * h;
-            const float* pb = buf + kAFloats + (wk + 4 * h) * S::kBRow + wcol + c31;
-            // eight reduction elements at a time: lanes 0..31 hold the first four, lanes 32..63 the others; those of the next eight are
-            // read before the products of these
-            constexpr int kG = S::kWaveK / 8;
-            f32x4 av[kG];
-            float bv[kG][NB][4];
-            auto read = [&](int g) __attribute__((always_inline)) {
-                av[g] = *reinterpret_cast<const f32x4*>(pa + 8 * g);
+            a = split8(aw[q][0]);
+            __builtin_amdgcn_sched_barrier(0);
+            load_w(q, s + kDepth);
+            load_a(q, 0, s + kDepth);
+            asm volatile("" : : : "memory");
+            __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-                for (int b = 0; b < NB; ++b)
+            for (int rb = 0; rb < RB; ++rb) {
+                Split next;
+                if (rb + 1 < RB) next = split8(aw[q][rb + 1 < RB ? rb + 1 : rb]);
+                f32x4 z[NJ];
 #pragma unroll
-                    for (int i = 0; i < 4; ++i) bv[g][b][i] = pb[b * kBFloats + (8 * g + i) * S::kBRow];
-            };
-            read(0);
+                for (int j = 0; j < NJ; ++j) z[j] = mfma(w[j].v[2], a.v[0], f32x4{0.f, 0.f, 0.f, 0.f});
 #pragma unroll
-            for (int g = 0; g < kG; ++g) {
-                if (g + 1 < kG) read(g + 1);
-                if (!SPLIT && g % 2 == 0 && s * S::KC + 8 * g == quarter_end) {       // uniform (a quarter is a multiple of 16)
-                    quarter_end += K / 4;
+                for (int j = 0; j < NJ; ++j) z[j] = mfma(w[j].v[0], a.v[2], z[j]);
 #pragma unroll
-                    for (int b = 0; b < NB; ++b) {
-                        total[b] += acc[b];
+                for (int j = 0; j < NJ; ++j) z[j] = mfma(w[j].v[1], a.v[1], z[j]);
 #pragma unroll
-                        for (int v = 0; v < 16; ++v) acc[b][v] = 0.f;
+                for (int j = 0; j < NJ; ++j) z[j] = mfma(w[j].v[1], a.v[0], z[j]);
+#pragma unroll
+                for (int j = 0; j < NJ; ++j) z[j] = mfma(w[j].v[0], a.v[1], z[j]);
+#pragma unroll
+                for (int j = 0; j < NJ; ++j) z[j] = mfma(w[j].v[0], a.v[0], z[j]);
+#pragma unroll
+                for (int j = 0; j < NJ; ++j) acc[rb][j] += z[j];
+                if (rb + 1 < RB) {
+#pragma unroll
+                    for (int i = 0; i < 6 * NJ; ++i) {
+                        __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);      // one MFMA,
+                        __builtin_amdgcn_sched_group_barrier(0x002, 8 / NJ, 0);  // some of the splitting
                     }
+                    __builtin_amdgcn_sched_barrier(0);
+                    load_a(q, rb + 1, s + kDepth);
+                    asm volatile("" : : : "memory");
+                    a = next;
                 }
-#pragma unroll
-                for (int i = 0; i < 4; ++i)
-#pragma unroll
-                    for (int b = 0; b < NB; ++b) acc[b] = __builtin_amdgcn_mfma_f32_32x32x2f32(bv[g][b][i], av[g][i], acc[b], 0, 0, 0);
+                __builtin_amdgcn_sched_barrier(0);
             }
         }
     }
-    // the weights are the first operand: lane l holds token row l % 32 and, in v = 4 g .. 4 g + 3, columns 8 g + 4 (l / 32) + 0..3
-    auto value = [&](float gate, float in) { return GATED ? act_f32(gate, act) * in : gate; };
-    auto out_at = [&](int r, int col) {
-        const int row = direct ? sh_row[row_begin + r] : row_begin + r;
-        return reinterpret_cast<f32x4*>(C + static_cast<size_t>(row_map != nullptr ? row_map[row] : row) * N + n0 + col);
-    };
-    if constexpr (!SPLIT) {
+    // the weights are the first operand: lane 16 g + c holds row c of its block and, in acc[..][m NC + j][i], column NC (4 g + i) + j of matrix m.
+    // Partial tile: a row's columns of the first matrix, then those of the second.
+    float* mine = part[wave];
 #pragma unroll
-        for (int b = 0; b < NB; ++b) total[b] += acc[b];
-        if (wrow + c31 < rows) {
+    for (int rb = 0; rb < RB; ++rb)
 #pragma unroll
-            for (int g = 0; g < 4; ++g) {
+        for (int m = 0; m < NM; ++m) {
+            float* to = mine + (16 * rb + c15) * kPartRow + 16 * NC * m + NC * 4 * g;
+#pragma unroll
+            for (int v = 0; v < NC; ++v) {
                 f32x4 o;
 #pragma unroll
-                for (int i = 0; i < 4; ++i) o[i] = value(total[0][4 * g + i], total[NB - 1][4 * g + i]);
-                *out_at(wrow + c31, wcol + 8 * g + 4 * h) = o;
+                for (int i = 0; i < 4; ++i) o[i] = acc[rb][m * NC + (4 * v + i) % NC][(4 * v + i) / NC];
+                *reinterpret_cast<f32x4*>(to + 4 * v) = o;
             }
         }
-    } else {
-        constexpr int kPRow = 36;                                         // floats per row of a partial tile
-        static_assert(4 * NB * 32 * kPRow <= 2 * kBuf, "the partial tiles fit the staging buffers");
-        float* part = &lds[0][0];
-        __syncthreads();
+    __syncthreads();
+    constexpr int kVec = 16 * NC / 4;                                       // 16-byte pieces of an output row
+    for (int id = tid; id < RB * 16 * kVec; id += 256) {
+        const int r = id / kVec, col = 4 * (id % kVec);
+        f32x4 sum[NM];
 #pragma unroll
-        for (int b = 0; b < NB; ++b)
+        for (int m = 0; m < NM; ++m) {
+            sum[m] = *reinterpret_cast<const f32x4*>(part[0] + r * kPartRow + 16 * NC * m + col);
 #pragma unroll
-            for (int g = 0; g < 4; ++g)
-                *reinterpret_cast<f32x4*>(part + ((wave * NB + b) * 32 + c31) * kPRow + 8 * g + 4 * h) =
-                    f32x4{acc[b][4 * g], acc[b][4 * g + 1], acc[b][4 * g + 2], acc[b][4 * g + 3]};
-        __syncthreads();
-        const int r = tid >> 3, col = 4 * (tid & 7);
-        f32x4 sum[NB];
-#pragma unroll
-        for (int b = 0; b < NB; ++b) {
-            sum[b] = *reinterpret_cast<const f32x4*>(part + (b * 32 + r) * kPRow + col);
-#pragma unroll
-            for (int w = 1; w < 4; ++w) sum[b] += *reinterpret_cast<const f32x4*>(part + ((w * NB + b) * 32 + r) * kPRow + col);
+            for (int v = 1; v < 4; ++v) sum[m] += *reinterpret_cast<const f32x4*>(part[v] + r * kPartRow + 16 * NC * m + col);
         }
-        if (r < rows) {
-            f32x4 o;
+        if (r >= rows) continue;
+        f32x4 o;
 #pragma unroll
-            for (int i = 0; i < 4; ++i) o[i] = value(sum[0][i], sum[NB - 1][i]);
-            *out_at(r, col) = o;
+        for (int i = 0; i < 4; ++i) {
+            float v[2] = {sum[0][i], sum[NM - 1][i]};
+#pragma unroll
+            for (int m = 0; m < NM; ++m)
+                if (!(fabsf(v[m]) <= 3.402823466e38f)) {
+                    const float *a = A + static_cast<size_t>(in_row(r)) * K, *w = (m == 0 ? W0 : W1) + n0 + col + i;
+                    float total = 0.f;
+                    for (int k = 0; k < K; ++k) total = fmaf(a[k], w[static_cast<size_t>(k) * N], total);
+                    v[m] = total;
+                }
+            o[i] = GATED ? act_f32(v[0], act) * v[1] : v[0];
         }
+        const int at = row_begin + r, row = direct ? sh_row[at] : at;
+        *reinterpret_cast<f32x4*>(C + static_cast<size_t>(row_map != nullptr ? row_map[row] : row) * N + n0 + col) = o;
     }
+}
+
+// GATED: C = act(A B0) * (A B1), else C = A B0.  gather (may be NULL): row r of the batched order is row gather[r] / gather_k
+// of A; row_map (may be NULL): row r is written to row row_map[r] of C.  idx (may be NULL): nothing has batched the assignments.
+template <bool GATED, bool NARROW>
+__global__ __launch_bounds__(256, 2) void ffn_f32_kernel(const float* A, const int32_t* __restrict__ offsets, int e_first, int e_count, const float* W,
+                                                         size_t expert_stride_elems, size_t off_b0, size_t off_b1, float* C, int K, int N, int act,
+                                                         int total_rows, const int32_t* __restrict__ gather, int gather_k,
+                                                         const int32_t* __restrict__ row_map, const int32_t* __restrict__ idx, int E) {
+    __shared__ __align__(16) float part[4][kRows * kPartRow];
+    __shared__ int sh_row[kDirectRows];
+    int e, row_begin = 0, rows;
+    const bool direct = idx != nullptr;
+    if (direct) {
+        if (!find_tile_direct(idx, total_rows, E, blockIdx.y, sh_row, e, rows)) return;
+    } else {
+        if (!find_tile(offsets, e_first, e_count, kRows, blockIdx.y, total_rows, e, row_begin, rows)) return;
+    }
+    const int n0 = blockIdx.x * 16 * lane_columns(GATED, NARROW);
+    const float* Wb = W + static_cast<size_t>(e - e_first) * expert_stride_elems;
+    const int blocks = __builtin_amdgcn_readfirstlane((rows + 15) >> 4);
+#define MOE_F32_TILE(RB)                                                                                                              \
+    case RB:                                                                                                                          \
+        ffn_f32_tile<GATED, NARROW, RB>(A, gather, gather_k, direct, sh_row, row_begin, rows, Wb + off_b0, Wb + off_b1, C, K, N, n0, act, row_map, part); \
+        break;
+    switch (blocks) { MOE_F32_TILE(1) MOE_F32_TILE(2) MOE_F32_TILE(3) MOE_F32_TILE(4) }
+#undef MOE_F32_TILE
 }
 
 }  // namespace
@@ -291,40 +324,30 @@ int launch_expert_ffn_f32(const moe_cfg& c, const float* Xp, const int32_t* offs
                           size_t expert_stride_elems, long max_rows, float* H, float* Yp, hipStream_t s, hipEvent_t between,
                           const int32_t* row_map, const int32_t* gather, const int32_t* idx) {
     const size_t df = static_cast<size_t>(c.d) * c.f;
+    if (max_rows / kRows + e_count > 65535) return fail(MOE_ERR_UNSUPPORTED, "too many row tiles for one launch (%ld)", max_rows / kRows + e_count);
+    const unsigned tiles = static_cast<unsigned>(max_rows / kRows + e_count);
     int dev = 0;
     const DeviceInfo* info = nullptr;
     if (int rc = device_info(&dev, &info)) return rc;
-    // Which shape: by the layer's own sizes, not the launch's, so that a launch over one expert sums like a launch over all.
-    const long rows = static_cast<long>(c.T) * c.k;
-    auto split_for = [&](int N) {
-        const long tiles = rows / 64 > c.E ? rows / 64 : c.E;
-        return tiles * (N / 64) < 2L * info->compute_units;
-    };
-    auto grid_for = [&](bool split, int N) {
-        const int bm = split ? 32 : 64;
-        return dim3(N / bm, static_cast<unsigned>(max_rows / bm + e_count));
-    };
-    if (max_rows / 64 + e_count > 65535) return fail(MOE_ERR_UNSUPPORTED, "too many row tiles for one launch (%ld)", max_rows / 64 + e_count);
-    const bool up_split = split_for(c.f), down_split = split_for(c.d);
+    // Blocks of half the columns when there are fewer than compute units (100 tokens, d 512, f 2048, 4 experts 49.2 -> 39.6 us); with more the rows are
+    // split too often (the f32 layer of 512 tokens x 2 with 320 blocks in the down-projection: 273 -> 295).
+    const long likely = max_rows / kRows > e_count ? max_rows / kRows : e_count < max_rows ? e_count : max_rows;
+    const bool up_narrow = likely * (c.f / 32) < info->compute_units, down_narrow = likely * (c.d / 64) < info->compute_units;
     const dim3 block(256);
-    if (up_split)
-        hipLaunchKernelGGL((ffn_f32_kernel<true, true>), grid_for(true, c.f), block, 0, s, Xp, offsets, e_first, e_count, W,
-                           expert_stride_elems, size_t(0), df, H, c.d, c.f, c.act, c.T * c.k, gather, c.k,
-                           static_cast<const int32_t*>(nullptr), idx, c.E);
-    else
-        hipLaunchKernelGGL((ffn_f32_kernel<true, false>), grid_for(false, c.f), block, 0, s, Xp, offsets, e_first, e_count, W,
-                           expert_stride_elems, size_t(0), df, H, c.d, c.f, c.act, c.T * c.k, gather, c.k,
-                           static_cast<const int32_t*>(nullptr), idx, c.E);
+    auto up = [&](auto kernel, int columns) {
+        hipLaunchKernelGGL(kernel, dim3(c.f / columns, tiles), block, 0, s, Xp, offsets, e_first, e_count, W, expert_stride_elems, size_t(0), df, H, c.d,
+                           c.f, c.act, c.T * c.k, gather, c.k, static_cast<const int32_t*>(nullptr), idx, c.E);
+    };
+    if (up_narrow) up(ffn_f32_kernel<true, true>, 16);
+    else up(ffn_f32_kernel<true, false>, 32);
     MOE_LAUNCH_CHECK("ffn_f32_kernel<up>");
     if (between != nullptr) MOE_HIP_CHECK(hipEventRecord(between, s));
-    if (down_split)
-        hipLaunchKernelGGL((ffn_f32_kernel<false, true>), grid_for(true, c.d), block, 0, s, H, offsets, e_first, e_count, W,
-                           expert_stride_elems, 2 * df, 2 * df, Yp, c.f, c.d, c.act, c.T * c.k,
-                           static_cast<const int32_t*>(nullptr), 1, row_map, idx, c.E);
-    else
-        hipLaunchKernelGGL((ffn_f32_kernel<false, false>), grid_for(false, c.d), block, 0, s, H, offsets, e_first, e_count, W,
-                           expert_stride_elems, 2 * df, 2 * df, Yp, c.f, c.d, c.act, c.T * c.k,
-                           static_cast<const int32_t*>(nullptr), 1, row_map, idx, c.E);
+    auto down = [&](auto kernel, int columns) {
+        hipLaunchKernelGGL(kernel, dim3(c.d / columns, tiles), block, 0, s, H, offsets, e_first, e_count, W, expert_stride_elems, 2 * df, 2 * df, Yp, c.f,
+                           c.d, c.act, c.T * c.k, static_cast<const int32_t*>(nullptr), 1, row_map, idx, c.E);
+    };
+    if (down_narrow) down(ffn_f32_kernel<false, true>, 32);
+    else down(ffn_f32_kernel<false, false>, 64);
     MOE_LAUNCH_CHECK("ffn_f32_kernel<down>");
     return MOE_OK;
 }

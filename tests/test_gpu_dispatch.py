@@ -369,3 +369,40 @@ def test_layer_without_batching(T, k, E, crowd, dtype, renorm):
     y4, y = _four_calls(cfg, H.to_device(x, dtype), H.to_device(Wg, dtype), bias, packed, ws)
     assert torch.isfinite(y.float()).all()
     assert torch.equal(y, y4)
+
+
+# row blocks 1 to 4 and a second tile; narrow and wide blocks of columns in both products; quarters of the reduction of 0, 1 and more steps
+@pytest.mark.parametrize("d,f", [(64, 64), (64, 4096), (2048, 128), (192, 8192)])
+def test_f32_expert_ffn_row_blocks(d, f):
+    counts = [1, 16, 17, 33, 48, 64, 65, 97, 129]
+    got, ref, offsets = run_ffn(sum(counts), d, f, len(counts), 1, "f32", counts, 1, seed=d + f)
+    for e in range(len(counts)):
+        lo, hi = offsets[e], offsets[e + 1]
+        # two chained sums; one addition of 2^-24 per 32 elements in each, and the rounding inside the instruction is of the same size
+        assert rel_l2(got[lo:hi], ref[lo:hi]) <= 1e-6, f"expert {e}"
+
+
+def test_f32_expert_ffn_large_and_infinite_values():
+    """The parts of an infinity are no numbers, and the partial sums of large values may overflow where the whole does not."""
+    d, f, E = 64, 128, 2
+    rng = np.random.default_rng(0)
+    ex = [tuple(rng.standard_normal(s).astype(np.float32) * 0.05 for s in ((d, f), (d, f), (f, d))) for _ in range(E)]
+    cfg = M.MoeCfg.make(6, d, f, E, 1, "f32")
+    packed = H.pack_experts(W.Workload("t", 6, d, f, E, 1, "f32", 0), cfg, experts=lambda e: ex[e])[0]
+    x = rng.standard_normal((6, d)).astype(np.float32)
+    x[1, 3], x[2, 5], x[3, 7] = np.inf, -np.inf, np.nan
+    x[4] *= np.float32(1e18)                     # H about 1e36, finite
+    Yp = torch.empty((6, d), device="cuda")
+    M.moe_expert_ffn(cfg, torch.from_numpy(x).cuda(), torch.tensor([0, 5, 6], dtype=torch.int32, device="cuda"), packed, Yp,
+                     torch.empty(M.moe_workspace_bytes(cfg), dtype=torch.uint8, device="cuda"))
+    torch.cuda.synchronize()
+    got = Yp.cpu().double()
+    for r in range(6):
+        W_in, W_gate, W_out = (torch.from_numpy(m).double() for m in ex[0 if r < 5 else 1])
+        t = torch.from_numpy(x[r]).double()
+        h = torch.nn.functional.gelu(t @ W_gate) * (t @ W_in)
+        ref = h @ W_out
+        if r in (1, 2, 3):
+            assert torch.equal(torch.isnan(got[r]), torch.isnan(ref.float())) and torch.equal(torch.isinf(got[r]), torch.isinf(ref.float()))
+        else:
+            assert rel_l2(got[r].numpy(), ref.numpy()) <= 1e-6
