@@ -406,3 +406,18 @@ def test_f32_expert_ffn_large_and_infinite_values():
             assert torch.equal(torch.isnan(got[r]), torch.isnan(ref.float())) and torch.equal(torch.isinf(got[r]), torch.isinf(ref.float()))
         else:
             assert rel_l2(got[r].numpy(), ref.numpy()) <= 1e-6
+
+
+@pytest.mark.parametrize("E,k,renorm", [(6, 2, 1), (40, 1, 1), (40, 3, 0), (70, 2, 0)])
+@pytest.mark.parametrize("special", [float("inf"), float("-inf"), float("nan")])
+def test_gate_infinite_logits_keep_the_fp32_order(E, k, renorm, special):
+    """Tokens with an infinity or a NaN have no error bound and go through the exact branch, where the columns in reach have no order of
+    their own: experts stay in range, and the other tokens of the block are what they are without them."""
+    x, Wg, _ = make_inputs(E, 20, 256, E, "bf16")
+    cfg = M.MoeCfg.make(20, 256, 64, E, k, "bf16", renorm)
+    idx0, w0 = gpu_route(cfg, x, Wg, None, "bf16")
+    y = x.copy()
+    y[7, 100] = special
+    idx, w = gpu_route(cfg, y, Wg, None, "bf16")
+    others = np.arange(20) != 7
+    assert np.array_equal(idx[others], idx0[others]) and np.array_equal(w[others], w0[others])
