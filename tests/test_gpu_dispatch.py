@@ -421,3 +421,14 @@ def test_gate_infinite_logits_keep_the_fp32_order(E, k, renorm, special):
     idx, w = gpu_route(cfg, y, Wg, None, "bf16")
     others = np.arange(20) != 7
     assert np.array_equal(idx[others], idx0[others]) and np.array_equal(w[others], w0[others])
+
+
+@pytest.mark.parametrize("counts", [[700, 10, 300, 0, 257, 40, 600, 33, 513, 5, 270, 120], [300] * 7 + [90, 200], [260, 255, 256] * 3, [2000, 1, 1, 1]],
+                         ids=lambda c: f"{len(c)}-{sum(c)}")
+def test_expert_ffn_merged_work_list(counts):
+    """Experts of several tiles among experts of one: 192 rows per expert and more, where the work list merges the two kinds."""
+    got, ref, offsets = run_ffn(sum(counts), 128, 320, len(counts), 1, "bf16", counts, 0, seed=sum(counts))
+    for e in range(len(counts)):
+        lo, hi = offsets[e], offsets[e + 1]
+        if hi > lo:
+            assert rel_l2(got[lo:hi], ref[lo:hi]) <= TOL["bf16"], f"expert {e}"
