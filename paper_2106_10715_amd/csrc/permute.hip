@@ -222,7 +222,7 @@ __global__ __launch_bounds__(kPermChunk) void batch_kernel(const int32_t* __rest
     }
     __syncthreads();
     if (plans) {
-        int (&scratch)[4][256] = reinterpret_cast<int (&)[4][256]>(wcnt);
+        int (&scratch)[kPlanScratch][256] = reinterpret_cast<int (&)[kPlanScratch][256]>(wcnt);
         const int list = blockIdx.x - chunks;
         ffn_plan_block(start, 0, E, list == 0 ? plan_tile_rows : plan_tile_rows_down, plan, A, plan_max_tiles, scratch, list);
     } else if (valid) {
