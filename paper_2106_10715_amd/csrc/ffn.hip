@@ -8,8 +8,8 @@
 // bf16 path: 16x16x32 bf16 MFMA, fp32 accumulate.  One block = up to 256 rows of one expert x 4 waves;
 // every wave owns its own output columns for all rows, so a weight fragment is needed by exactly
 // one wave: weights go HBM -> registers directly in pre-packed fragment order (no LDS, fully
-// coalesced 1 KiB reads), only the activation tile is shared through LDS (padded rows,
-// conflict-free 16-byte reads and writes).  With few rows per expert the layer is bound by streaming the
+// coalesced 1 KiB reads), only the activation tile is shared through LDS (loaded
+// straight into it, conflict-free 16-byte reads).  With few rows per expert the layer is bound by streaming the
 // weights once from HBM, which is what this layout is built for.
 // fp32 path: ffn_f32.hip.
 #include "common.h"
@@ -18,7 +18,7 @@
 
 #include <type_traits>
 
-// This file is compiled in five parts side by side (FFN_PART 0..4; a kernel holds the tile code for eight heights in two
+// This file is compiled in five parts side by side (FFN_PART 0..4; a kernel holds the tile code for 13 or 15 heights in two
 // load flavours and takes minutes): the four instantiations of ffn_mfma_kernel, and everything else.
 #ifndef FFN_PART
 #error "compile with -DFFN_PART=0..4"
@@ -710,7 +710,7 @@ __device__ inline void ffn_tile(uint4 (&lds)[kLdsBytes / 16], const uint16_t* __
 constexpr int kKeepFromTiles = 2;       // row tiles of an expert from which its weights are worth keeping in the L2
 
 // C[rows of one expert tile, N] = A[rows, K] * B_e, B_e in packed fragment order.
-// A work item is one row tile (up to 256 rows of one expert; only the 32-row blocks that hold rows are
+// A work item is one row tile (up to 256 rows of one expert; only the 16-row blocks that hold rows are
 // computed) by one column group of 4 units, one unit per wave, for all rows.
 // GATED (NF = 2): a unit is 32 output columns whose two fragments per k-step are (W_gate, W_in); the
 //   epilogue writes act(gate) * in.
@@ -762,7 +762,7 @@ __global__ __launch_bounds__(256) void ffn_mfma_kernel(const uint16_t* __restric
     __syncthreads();
     for (;;) {
         if (sh_q < 0) return;                      // every queue is empty (uniform for the block)
-        // The tile code below is compiled for eight tile heights; values that do not change from item to
+        // The tile code below is compiled for 13 or 15 tile heights; values that do not change from item to
         // item would be hoisted out of this loop and held in registers across all of them.  The inputs
         // are made opaque per iteration instead.
         int Kl = K, Nl = N;
