@@ -31,7 +31,7 @@ __device__ inline void ffn_plan_block(const int32_t* offsets, int e_first, int e
     if (worker && t < e_count) {
         // whatever the offsets hold, no tile may reach outside the total_rows rows or the work list
         lo = min(max(offsets[e_first + t], 0), total_rows);
-        cnt = min(max(offsets[e_first + t + 1] - lo, 0), total_rows - lo);
+        cnt = min(max(offsets[e_first + t + 1], lo), total_rows) - lo;
     }
     // The highest tiles first among those of either kind below, so that the last items are the short ones; among equals the expert with more
     // rows, then by index.
@@ -61,11 +61,11 @@ __device__ inline void ffn_plan_block(const int32_t* offsets, int e_first, int e
     if (worker) tl[t] = my_tiles;
     __syncthreads();
     int4* tiles = reinterpret_cast<int4*>(plan + kPlanHeader + 4 * list * max_tiles);
-    // tile mt of an expert with n_e rows and n_tiles tiles, its blocks of 16 rows spread evenly (block i of b goes to tile i t / b of t), at
-    // place `at` of the list
+    // tile mt of an expert with n_e rows and n_tiles tiles, its blocks of 16 rows spread evenly (the first tiles have one more where they do not
+    // divide), at place `at` of the list.  No product is larger than the number of blocks.
     auto put = [&](int e, int n_e, int n_tiles, int mt, int at) {
-        const int blocks = (n_e + 15) / 16;
-        const int lo = mt * blocks / n_tiles * 16, hi = min((mt + 1) * blocks / n_tiles * 16, n_e);
+        const int blocks = (n_e + 15) / 16, each = blocks / n_tiles, more = blocks - each * n_tiles;
+        const int lo = (mt * each + min(mt, more)) * 16, hi = min(lo + (each + (mt < more ? 1 : 0)) * 16, n_e);
         if (at < max_tiles) tiles[at] = make_int4(e_first + e, first[e] + lo, hi - lo, n_tiles);
     };
     // Experts with several tiles, bound by the matrix pipes, and those with one, bound by reading their weights, take turns over the whole list,

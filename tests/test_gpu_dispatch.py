@@ -432,3 +432,24 @@ def test_expert_ffn_merged_work_list(counts):
         lo, hi = offsets[e], offsets[e + 1]
         if hi > lo:
             assert rel_l2(got[lo:hi], ref[lo:hi]) <= TOL["bf16"], f"expert {e}"
+
+
+def test_three_million_rows_on_one_expert():
+    """More rows on one expert than a 32-bit product of its tiles and blocks holds: every row is what it is in a batch of its own."""
+    T, d, f = 3_000_000, 64, 64
+    cfg = M.MoeCfg.make(T, d, f, 1, 1, "bf16")
+    g = torch.Generator(device="cuda")
+    g.manual_seed(1)
+    x = torch.empty((T, d), dtype=torch.bfloat16, device="cuda").normal_(generator=g)
+    ex = [torch.empty(s, dtype=torch.bfloat16, device="cuda").normal_(0.0, 0.1, generator=g) for s in ((d, f), (d, f), (f, d))]
+    packed = torch.empty((1, M.moe_expert_bytes(cfg)), dtype=torch.uint8, device="cuda")
+    M.moe_pack_weights(cfg, *ex, packed[0])
+    Wg = torch.zeros((d, 1), dtype=torch.bfloat16, device="cuda")
+    y = torch.full_like(x, float("nan"))
+    M.moe_layer_forward(cfg, x, Wg, None, packed, None, y, torch.empty(M.moe_workspace_bytes(cfg), dtype=torch.uint8, device="cuda"))
+    part = 1 << 17
+    small = M.MoeCfg.make(part, d, f, 1, 1, "bf16")
+    ws, want = torch.empty(M.moe_workspace_bytes(small), dtype=torch.uint8, device="cuda"), torch.empty((part, d), dtype=torch.bfloat16, device="cuda")
+    for lo in [*range(0, T - part, part), T - part]:
+        M.moe_layer_forward(small, x[lo:lo + part], Wg, None, packed, None, want, ws)
+        assert torch.equal(y[lo:lo + part], want), f"rows {lo}..{lo + part}"
