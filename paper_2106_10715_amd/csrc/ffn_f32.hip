@@ -126,20 +126,23 @@ constexpr int kPartRow = 68;                             // floats per row of a 
 // Columns of a lane, of each matrix: a block has 16 times as many.
 constexpr int lane_columns(bool gated, bool narrow) { return (gated ? 2 : 4) >> (narrow ? 1 : 0); }
 
-// What bounds it: the vector instructions that split the operands (1024 rows of 8 experts, d 1024, f 4096: half of the cycles, the matrix
-// instructions 29 %, little of them at once with two waves per SIMD); the latency of a block's few steps in short launches.  Six of the nine products of the parts are formed (the other three
-// are below 2^-24 of the whole) by six bf16 instructions, in 96 cycles for 32 reduction elements where the fp32 instruction takes 256.
-// They are added up smallest first from zero and the sum then to the running one in fp32, one addition per 32 elements: against 64 bits
-// a sum of 4096 products is 1.5e-7 off (normally distributed; positive 0.7e-7), the fp32 instruction's chain of additions in four quarters 5.7e-7 (2.4e-7).
+// What bounds it: the vector instructions that split the operands and add the sums (half of the cycles at 1024 rows of 8 experts, d 1024, f 4096); the
+// latency of a block's few steps in short launches.  Eight of the nine products of the parts are formed, so that a product has all its bits: the one
+// left out, of the two last parts, is below 2^-30 of the whole (second part < 2^-7 of the value, third < 2^-15).  The instruction cuts off where it adds, so the product of the first parts, which for one
+// product is exact, is added to the sum of the seven small ones outside of it, and both to the running sum, in fp32: two roundings per 32 elements.
+// Relative error against 64 bits, sums of normally distributed products, here / by chains of fp32 multiply-adds in four quarters: 4096 products 1.2e-7 / 5.7e-7
+// (positive ones 0.6e-7 / 2.5e-7), 64 products 4.7e-8 / 8.4e-8, 16 5.3e-8 / 5.8e-8, one 2.6e-8 (half of the last bit at most) / the same; 1024 equal
+// products (1/3 squared) 0.8e-7 / 27e-7.  Six products (without second x third) and one addition take 10 % less time, but leave out up to 2^-21 of a
+// product, always of its sign (one product 6.9e-8).
 // A block is one tile of up to 64 rows by 64 weight columns (GATED: 32 of each matrix), or half as many; its four waves take a quarter of the
 // reduction dimension each and share nothing until their partial tiles are added in wave order at the end, so there is no barrier
 // in the loop, no LDS, and every row's sum has the same order in every tile and batch.  Weights and activations go straight into registers in operand order: a lane's
 // eight reduction elements are 4 g .. 4 g + 3 and 16 + 4 g .. of 32 (g = lane / 16), its two or four columns are neighbours.
 // A value that comes out infinite or NaN is computed again by plain fp32 multiply-adds: the parts of an infinity are no numbers, and the
 // order of the sums decides where an overflow shows.
-// Against tiles of 64 x 64 and 32 x 32 through LDS with the fp32 instruction, layers in us: 512 tokens x 2, d 1024, f 4096, 8 experts 344 -> 273 (up 218 ->
-// 168, down 138 -> 91), 1024 x 2 on 4 experts 568 -> 378, 16 x 1 on 8 138 -> 103, 1000 x 1, f 1024, 5 experts 121 -> 90, 100 x 1, d 512, f 2048, 4 experts
-// 45.8 -> 39.6, 64 x 1, d 256, f 512, 4 experts 19.7 -> 17.5.  Blocks that take several column groups one after the other: 5-15 % slower.
+// Against tiles of 64 x 64 and 32 x 32 through LDS with the fp32 instruction, layers in us: 512 tokens x 2, d 1024, f 4096, 8 experts 341 -> 295, 4096 x 2 1947 ->
+// 1671, 8192 x 1, d 512, f 2048 555 -> 477, 16 x 1 on 8 142 -> 105, 1000 x 1, f 1024, 5 experts 120 -> 95, 100 x 1, d 512, f 2048, 4 experts
+// 45.4 -> 43.6, 64 x 1, d 256, f 512, 4 experts 23.1 -> 18.1.  Blocks that take several column groups one after the other: 5-15 % slower.
 template <bool GATED, bool NARROW, int RB>
 __device__ inline void ffn_f32_tile(const float* A, const int32_t* gather, int gather_k, bool direct, const int (&sh_row)[kDirectRows], int row_begin,
                                     int rows, const float* W0, const float* W1, float* C, int K, int N, int n0, int act, const int32_t* row_map,
@@ -216,7 +219,11 @@ __device__ inline void ffn_f32_tile(const float* A, const int32_t* gather, int g
                 if (rb + 1 < RB) next = split8(aw[q][rb + 1 < RB ? rb + 1 : rb]);
                 f32x4 z[NJ];
 #pragma unroll
-                for (int j = 0; j < NJ; ++j) z[j] = mfma(w[j].v[2], a.v[0], f32x4{0.f, 0.f, 0.f, 0.f});
+                for (int j = 0; j < NJ; ++j) z[j] = mfma(w[j].v[2], a.v[1], f32x4{0.f, 0.f, 0.f, 0.f});
+#pragma unroll
+                for (int j = 0; j < NJ; ++j) z[j] = mfma(w[j].v[1], a.v[2], z[j]);
+#pragma unroll
+                for (int j = 0; j < NJ; ++j) z[j] = mfma(w[j].v[2], a.v[0], z[j]);
 #pragma unroll
                 for (int j = 0; j < NJ; ++j) z[j] = mfma(w[j].v[0], a.v[2], z[j]);
 #pragma unroll
@@ -226,14 +233,12 @@ __device__ inline void ffn_f32_tile(const float* A, const int32_t* gather, int g
 #pragma unroll
                 for (int j = 0; j < NJ; ++j) z[j] = mfma(w[j].v[0], a.v[1], z[j]);
 #pragma unroll
-                for (int j = 0; j < NJ; ++j) z[j] = mfma(w[j].v[0], a.v[0], z[j]);
-#pragma unroll
-                for (int j = 0; j < NJ; ++j) acc[rb][j] += z[j];
+                for (int j = 0; j < NJ; ++j) acc[rb][j] += z[j] + mfma(w[j].v[0], a.v[0], f32x4{0.f, 0.f, 0.f, 0.f});
                 if (rb + 1 < RB) {
 #pragma unroll
-                    for (int i = 0; i < 6 * NJ; ++i) {
+                    for (int i = 0; i < 8 * NJ; ++i) {
                         __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);      // one MFMA,
-                        __builtin_amdgcn_sched_group_barrier(0x002, 8 / NJ, 0);  // some of the splitting
+                        __builtin_amdgcn_sched_group_barrier(0x002, 7 / NJ, 0);  // some of the splitting
                     }
                     __builtin_amdgcn_sched_barrier(0);
                     load_a(q, rb + 1, s + kDepth);
@@ -329,8 +334,8 @@ int launch_expert_ffn_f32(const moe_cfg& c, const float* Xp, const int32_t* offs
     int dev = 0;
     const DeviceInfo* info = nullptr;
     if (int rc = device_info(&dev, &info)) return rc;
-    // Blocks of half the columns when there are fewer than compute units (100 tokens, d 512, f 2048, 4 experts 49.2 -> 39.6 us); with more the rows are
-    // split too often (the f32 layer of 512 tokens x 2 with 320 blocks in the down-projection: 273 -> 295).
+    // Blocks of half the columns when there are fewer than compute units (100 tokens, d 512, f 2048, 4 experts 52.7 -> 43.7 us); with more the rows are
+    // split too often (up to twice as many: 512 tokens x 2, d 1024, f 4096, 8 experts 294 -> 311, 1000 x 1, f 1024, 5 experts 94 -> 103).
     const long likely = max_rows / kRows > e_count ? max_rows / kRows : e_count < max_rows ? e_count : max_rows;
     const bool up_narrow = likely * (c.f / 32) < info->compute_units, down_narrow = likely * (c.d / 64) < info->compute_units;
     const dim3 block(256);

@@ -453,3 +453,43 @@ def test_three_million_rows_on_one_expert():
     for lo in [*range(0, T - part, part), T - part]:
         M.moe_layer_forward(small, x[lo:lo + part], Wg, None, packed, None, want, ws)
         assert torch.equal(y[lo:lo + part], want), f"rows {lo}..{lo + part}"
+
+
+def _f32_sums(x, W):
+    """16 x W by the fp32 expert kernel (x [T, K], W [K, N], N <= K; column 0 of x and row 0 of W are used up: the gate is 16 exactly, GELU(16) = 16 in
+    fp32, and the down-projection an identity), and the same in 64 bits."""
+    (T, K), N = x.shape, W.shape[1]
+    x, W, gate = x.clone(), W.clone(), torch.zeros_like(W)
+    x[:, 0], W[0], gate[0] = 16.0, 0.0, 1.0
+    cfg = M.MoeCfg.make(T, K, N, 1, 1, "f32")
+    packed = torch.empty((1, M.moe_expert_bytes(cfg)), dtype=torch.uint8, device="cuda")
+    M.moe_pack_weights(cfg, W, gate, torch.eye(N, K, device="cuda"), packed[0])
+    Y = torch.full((T, K), float("nan"), device="cuda")
+    M.moe_expert_ffn(cfg, x, torch.tensor([0, T], dtype=torch.int32, device="cuda"), packed, Y,
+                     torch.empty(M.moe_workspace_bytes(cfg), dtype=torch.uint8, device="cuda"))
+    torch.cuda.synchronize()
+    return Y[:, :N], 16 * (x[:, 1:].double() @ W[1:].double())
+
+
+def _normal(*shape, seed):
+    g = torch.Generator(device="cuda")
+    g.manual_seed(seed)
+    return torch.empty(shape, device="cuda").normal_(generator=g)
+
+
+@pytest.mark.parametrize("K", [64, 512])
+def test_f32_expert_ffn_single_products(K):
+    """Rows with one value: the sum is one product, and right to half of its last bit (1/64 more for the part of the product that is left out and for
+    the instruction's cutting off of the small parts)."""
+    x, at = torch.zeros((200, K), device="cuda"), torch.arange(200, device="cuda") % (K - 1) + 1
+    x[torch.arange(200, device="cuda"), at] = _normal(200, seed=1)
+    got, ref = _f32_sums(x, _normal(K, 64, seed=2))
+    assert ((got.double() - ref).abs() <= ref.abs() * 2.0 ** -24 * (1 + 2.0 ** -6)).all()
+
+
+@pytest.mark.parametrize("value", [1 + 2.0 ** -7 - 2.0 ** -23, 1 + 2.0 ** -8 + 2.0 ** -17 - 2.0 ** -23, 1 / 3])
+def test_f32_expert_ffn_equal_products(value):
+    """63 times the same product: its error comes 63 times with one sign.  Two steps of 32 in two of the four quarters, each rounded three times to 2^-24 of
+    at most the sum (inside the instruction, twice outside), and the sum of the two."""
+    got, ref = _f32_sums(torch.full((20, 64), value, device="cuda"), torch.full((64, 64), value, device="cuda"))
+    assert ((got.double() - ref).abs() <= ref.abs() * 2.0 ** -24 * 4).all()
