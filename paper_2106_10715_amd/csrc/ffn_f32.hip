@@ -138,8 +138,9 @@ constexpr int lane_columns(bool gated, bool narrow) { return (gated ? 2 : 4) >> 
 // reduction dimension each and share nothing until their partial tiles are added in wave order at the end, so there is no barrier
 // in the loop, no LDS, and every row's sum has the same order in every tile and batch.  Weights and activations go straight into registers in operand order: a lane's
 // eight reduction elements are 4 g .. 4 g + 3 and 16 + 4 g .. of 32 (g = lane / 16), its two or four columns are neighbours.
-// A value that comes out infinite or NaN is computed again by plain fp32 multiply-adds: the parts of an infinity are no numbers, and the
-// order of the sums decides where an overflow shows.
+// A value that comes out infinite or NaN is computed again in fp64, by one thread per four columns: the parts of an infinity are no numbers, and
+// partial sums may overflow where the whole does not.  So the result is infinite only where the sum is.  It is slow: 512 tokens x 2 of the layer below take 0.5 ms with one NaN
+// among them and 2 ms if all are (0.3 ms without).
 // Against tiles of 64 x 64 and 32 x 32 through LDS with the fp32 instruction, layers in us: 512 tokens x 2, d 1024, f 4096, 8 experts 341 -> 295, 4096 x 2 1947 ->
 // 1671, 8192 x 1, d 512, f 2048 555 -> 477, 16 x 1 on 8 142 -> 105, 1000 x 1, f 1024, 5 experts 120 -> 95, 100 x 1, d 512, f 2048, 4 experts
 // 45.4 -> 43.6, 64 x 1, d 256, f 512, 4 experts 23.1 -> 18.1.  Blocks that take several column groups one after the other: 5-15 % slower.
@@ -277,20 +278,44 @@ __device__ inline void ffn_f32_tile(const float* A, const int32_t* gather, int g
             for (int v = 1; v < 4; ++v) sum[m] += *reinterpret_cast<const f32x4*>(part[v] + r * kPartRow + 16 * NC * m + col);
         }
         if (r >= rows) continue;
-        f32x4 o;
+        bool finite = true;
 #pragma unroll
-        for (int i = 0; i < 4; ++i) {
-            float v[2] = {sum[0][i], sum[NM - 1][i]};
+        for (int m = 0; m < NM; ++m)
+#pragma unroll
+            for (int i = 0; i < 4; ++i) finite = finite && fabsf(sum[m][i]) <= 3.402823466e38f;
+        if (!finite) {
+            constexpr int kAhead = 16 / NM;
+            const float* a = A + static_cast<size_t>(in_row(r)) * K;
+            double total[NM][4];
 #pragma unroll
             for (int m = 0; m < NM; ++m)
-                if (!(fabsf(v[m]) <= 3.402823466e38f)) {
-                    const float *a = A + static_cast<size_t>(in_row(r)) * K, *w = (m == 0 ? W0 : W1) + n0 + col + i;
-                    float total = 0.f;
-                    for (int k = 0; k < K; ++k) total = fmaf(a[k], w[static_cast<size_t>(k) * N], total);
-                    v[m] = total;
-                }
-            o[i] = GATED ? act_f32(v[0], act) * v[1] : v[0];
+#pragma unroll
+                for (int i = 0; i < 4; ++i) total[m][i] = 0.0;
+            for (int k0 = 0; k0 < K; k0 += kAhead) {
+                f32x4 av[kAhead / 4], wv[NM][kAhead];
+#pragma unroll
+                for (int q = 0; q < kAhead / 4; ++q) av[q] = *reinterpret_cast<const f32x4*>(a + k0 + 4 * q);
+#pragma unroll
+                for (int m = 0; m < NM; ++m)
+#pragma unroll
+                    for (int q = 0; q < kAhead; ++q) wv[m][q] = *reinterpret_cast<const f32x4*>((m == 0 ? W0 : W1) + static_cast<size_t>(k0 + q) * N + n0 + col);
+                asm volatile("" : : : "memory");
+#pragma unroll
+                for (int q = 0; q < kAhead; ++q)
+#pragma unroll
+                    for (int m = 0; m < NM; ++m)
+#pragma unroll
+                        for (int i = 0; i < 4; ++i) total[m][i] = fma(static_cast<double>(av[q / 4][q % 4]), static_cast<double>(wv[m][q][i]), total[m][i]);
+            }
+#pragma unroll
+            for (int m = 0; m < NM; ++m)
+#pragma unroll
+                for (int i = 0; i < 4; ++i)
+                    if (!(fabsf(sum[m][i]) <= 3.402823466e38f)) sum[m][i] = static_cast<float>(total[m][i]);
         }
+        f32x4 o;
+#pragma unroll
+        for (int i = 0; i < 4; ++i) o[i] = GATED ? act_f32(sum[0][i], act) * sum[NM - 1][i] : sum[0][i];
         const int at = row_begin + r, row = direct ? sh_row[at] : at;
         *reinterpret_cast<f32x4*>(C + static_cast<size_t>(row_map != nullptr ? row_map[row] : row) * N + n0 + col) = o;
     }

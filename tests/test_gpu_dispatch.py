@@ -383,7 +383,7 @@ def test_f32_expert_ffn_row_blocks(d, f):
 
 
 def test_f32_expert_ffn_large_and_infinite_values():
-    """The parts of an infinity are no numbers, and the partial sums of large values may overflow where the whole does not."""
+    """The parts of an infinity are no numbers: rows that hold one, or a NaN, and a row of large finite values."""
     d, f, E = 64, 128, 2
     rng = np.random.default_rng(0)
     ex = [tuple(rng.standard_normal(s).astype(np.float32) * 0.05 for s in ((d, f), (d, f), (f, d))) for _ in range(E)]
@@ -493,3 +493,25 @@ def test_f32_expert_ffn_equal_products(value):
     at most the sum (inside the instruction, twice outside), and the sum of the two."""
     got, ref = _f32_sums(torch.full((20, 64), value, device="cuda"), torch.full((64, 64), value, device="cuda"))
     assert ((got.double() - ref).abs() <= ref.abs() * 2.0 ** -24 * 4).all()
+
+
+@pytest.mark.parametrize("up,down", [(1e30, 1e-30), (3e37, 0.1), (1e10, 1e25)])
+def test_f32_expert_ffn_large_values(up, down):
+    """Operands and sums up to the upper end of fp32 are summed in 64 bits where the products of parts are infinite, else as any others."""
+    got, ref = _f32_sums(_normal(70, 128, seed=5) * up, _normal(128, 64, seed=6) * down / 64)
+    assert torch.isfinite(got).all()
+    assert rel_l2(got.cpu().numpy(), ref.cpu().numpy()) <= 2.0 ** -22
+
+
+def test_f32_expert_ffn_partial_sums_overflow():
+    """Half of the products are 2e38 and half -2e38: the sum of a quarter, and of 32 products, is past the end of fp32, the whole is not.  A NaN, and
+    an infinity (times the gate's zeros), stay in their rows."""
+    x, W = torch.full((5, 64), 1e19, device="cuda"), torch.full((64, 64), 2e19, device="cuda")
+    x[:, 32:] *= -1
+    x[1, 40] = -0.96e19
+    x[2, 3], x[3, 5] = float("inf"), float("nan")
+    x[:, 33] = 0
+    got, ref = _f32_sums(x, W)
+    assert torch.equal(got[[0, 4]], torch.zeros_like(got[[0, 4]]))
+    assert torch.isnan(got[2:4]).all()
+    assert ((got[1].double() - ref[1]).abs() <= ref[1].abs() * 2.0 ** -23).all() and (ref[1] > 1e38).all()
