@@ -95,8 +95,10 @@ __device__ inline bool find_tile_direct(const int32_t* __restrict__ idx, int A, 
     return true;
 }
 
-// Eight values as three bf16 operands: the upper 16 bits of the value, of what they leave, and of what is left then (8 + 8 + 8
-// significant bits, nothing is rounded).
+// Eight values, times 2^16, as three bf16 operands: the upper 16 bits of the value, of what they leave, and of what is left then (8 + 8 + 8
+// significant bits, nothing is rounded).  Without the factor the last bits of values below 2^-110 would lie below the smallest bf16 (2^-133; the
+// instruction takes those below its normal range as they are); values of 2^112 and more become infinite by it.
+constexpr float kUp = 65536.0f, kDown = 1.0f / (kUp * kUp);                  // of an operand, of a product
 struct Split { u32x4 v[3]; };
 __device__ __attribute__((always_inline)) inline Split split8(const float (&x)[8]) {
     Split s;
@@ -105,7 +107,7 @@ __device__ __attribute__((always_inline)) inline Split split8(const float (&x)[8
         uint32_t bits[2][3];
 #pragma unroll
         for (int h = 0; h < 2; ++h) {
-            const float v = x[2 * p + h];
+            const float v = x[2 * p + h] * kUp;
             const float rest = v - __uint_as_float(__float_as_uint(v) & 0xffff0000u);
             const float last = rest - __uint_as_float(__float_as_uint(rest) & 0xffff0000u);
             bits[h][0] = __float_as_uint(v);
@@ -139,7 +141,7 @@ constexpr int lane_columns(bool gated, bool narrow) { return (gated ? 2 : 4) >> 
 // in the loop, no LDS, and every row's sum has the same order in every tile and batch.  Weights and activations go straight into registers in operand order: a lane's
 // eight reduction elements are 4 g .. 4 g + 3 and 16 + 4 g .. of 32 (g = lane / 16), its two or four columns are neighbours.
 // A value that comes out infinite or NaN is computed again in fp64, by one thread per four columns: the parts of an infinity are no numbers, and
-// partial sums may overflow where the whole does not.  So the result is infinite only where the sum is.  It is slow: 512 tokens x 2 of the layer below take 0.5 ms with one NaN
+// the operands' factor may have made it one.  So the result is infinite only where the sum is.  It is slow: 512 tokens x 2 of the layer below take 0.5 ms with one NaN
 // among them and 2 ms if all are (0.3 ms without).
 // Against tiles of 64 x 64 and 32 x 32 through LDS with the fp32 instruction, layers in us: 512 tokens x 2, d 1024, f 4096, 8 experts 341 -> 295, 4096 x 2 1947 ->
 // 1671, 8192 x 1, d 512, f 2048 555 -> 477, 16 x 1 on 8 142 -> 105, 1000 x 1, f 1024, 5 experts 120 -> 95, 100 x 1, d 512, f 2048, 4 experts
@@ -282,7 +284,10 @@ __device__ inline void ffn_f32_tile(const float* A, const int32_t* gather, int g
 #pragma unroll
         for (int m = 0; m < NM; ++m)
 #pragma unroll
-            for (int i = 0; i < 4; ++i) finite = finite && fabsf(sum[m][i]) <= 3.402823466e38f;
+            for (int i = 0; i < 4; ++i) {
+                finite = finite && fabsf(sum[m][i]) <= 3.402823466e38f;
+                sum[m][i] *= kDown;                                         // (an infinity or a NaN stays one)
+            }
         if (!finite) {
             constexpr int kAhead = 16 / NM;
             const float* a = A + static_cast<size_t>(in_row(r)) * K;

@@ -515,3 +515,12 @@ def test_f32_expert_ffn_partial_sums_overflow():
     assert torch.equal(got[[0, 4]], torch.zeros_like(got[[0, 4]]))
     assert torch.isnan(got[2:4]).all()
     assert ((got[1].double() - ref[1]).abs() <= ref[1].abs() * 2.0 ** -23).all() and (ref[1] > 1e38).all()
+
+
+@pytest.mark.parametrize("scale", [2.0 ** -60, 2.0 ** -112, 2.0 ** -125])
+def test_f32_expert_ffn_small_values(scale):
+    """Operands down to the lower end of fp32 (values 1 to 2 times the scale, last bit 2^-23 of it): a power of two changes no bit of the sums."""
+    x, W = 1 + _normal(70, 128, seed=3).abs().remainder(1.0), 1 + _normal(128, 64, seed=4).abs().remainder(1.0)
+    want = _f32_sums(x, W)[0]
+    assert torch.equal(_f32_sums(x * scale, W)[0], want * scale)
+    assert torch.equal(_f32_sums(x, W * scale)[0], want * scale)
