@@ -135,9 +135,14 @@ __global__ __launch_bounds__(256) void scatter_kernel(const int32_t* __restrict_
 // (saves a launch), is made by a block of its own, or by two when the down kernel does not read the up kernel's list.  Bound by the latency of its few steps (launch, the read of idx, counting, scan, stores):
 // every assignment is counted by every block, which takes longer than the three kernels above only far beyond the limit.  us, against one block in
 // rounds of 1024 (up to 16384) and the three kernels (beyond): 2050 assignments to 33 experts with the list 8.5 -> 5.0, 32768 to 64 experts without
-// 14.7 -> 6.9; whole calls: 4096 tokens on 32 experts 1346 -> 1317, 60000 x 1, d 1024, f 64, 8 experts (a list by a kernel of its own before) 196.8 -> 194.7.
+// 14.7 -> 6.7; whole calls: 4096 tokens on 32 experts 1346 -> 1317, 60000 x 1, d 1024, f 64, 8 experts (a list by a kernel of its own before) 196.8 -> 194.7.
 constexpr int kBatchWaves = kPermChunk / 64;           // one assignment of the block's own chunk per thread
-constexpr int kCopies = 4;                              // histograms the counting is spread over: equal experts in a wave wait for each other
+// Histograms the counting is spread over (equal experts in a wave wait for each other, and so do different ones in one bank: hence the odd row).  A
+// short batch has less to count than to clear and add up.  Kernel us, three kernels / four copies in one bank / as here: 65536 assignments to one expert
+// 12.0 / 30.8 / 8.6, half of 65536 to one of 64 14.5 / 19.3 / 10.0, 65536 spread over 64 14.3 / 9.0 / 9.0, 32768 to one 10.3 / 17.3 / 7.6, spread over 64
+// 12.3 / 6.5 / 6.7 (with 16 copies 7.0), 8193 over 32 - / 4.8 / 5.1 (5.5).
+constexpr int kCopies = 16, kHistRow = 257;
+__device__ inline int copies_for(int A) { return A <= 8192 ? 4 : A <= 32768 ? 8 : kCopies; }
 constexpr int kOneLaunchMaxA = 64 * kPermChunk;
 
 __global__ __launch_bounds__(kPermChunk) void batch_kernel(const int32_t* __restrict__ idx, int A, int E, int chunks,
@@ -145,7 +150,7 @@ __global__ __launch_bounds__(kPermChunk) void batch_kernel(const int32_t* __rest
                                                            int32_t* __restrict__ perm, int32_t* __restrict__ inv,
                                                            int32_t* __restrict__ plan, int plan_max_tiles, int plan_tile_rows,
                                                            int plan_tile_rows_down) {
-    __shared__ int hist[2][kCopies][256];              // assignments before the block's chunk, and from there on
+    __shared__ int hist[2][kCopies][kHistRow];         // assignments before the block's chunk, and from there on
     __shared__ int wcnt[kBatchWaves][256];             // per wave, rows each expert takes
     __shared__ int run[256], start[257];               // first row of each expert, of the chunk's and of all
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
@@ -153,11 +158,12 @@ __global__ __launch_bounds__(kPermChunk) void batch_kernel(const int32_t* __rest
     const int a0 = plans ? 0 : blockIdx.x * kPermChunk, a = a0 + tid;
     const bool valid = !plans && a < A;
     const int mine = valid ? clamp_expert(idx[a], E) : 0;
-    for (int i = tid; i < 2 * kCopies * 256; i += kPermChunk) (&hist[0][0][0])[i] = 0;
+    const int copies = copies_for(A);
+    for (int i = tid; i < copies * kHistRow; i += kPermChunk) (&hist[0][0][0])[i] = (&hist[1][0][0])[i] = 0;
     for (int i = tid; i < kBatchWaves * 256; i += kPermChunk) (&wcnt[0][0])[i] = 0;
     __syncthreads();
     // integer counts: order cannot matter
-    auto count = [&](int at, int e) { atomicAdd(&hist[at >= a0 ? 1 : 0][lane & (kCopies - 1)][clamp_expert(e, E)], 1); };
+    auto count = [&](int at, int e) { atomicAdd(&hist[at >= a0 ? 1 : 0][lane & (copies - 1)][clamp_expert(e, E)], 1); };
     if ((reinterpret_cast<uintptr_t>(idx) & 15) == 0) {                    // uniform
         const int whole = A / 4;
         for (int q0 = tid; q0 < whole; q0 += 4 * kPermChunk) {
@@ -191,12 +197,14 @@ __global__ __launch_bounds__(kPermChunk) void batch_kernel(const int32_t* __rest
     __syncthreads();
     if (wave == 0) {
         // exclusive scan of up to 256 counts by one wave: four experts per lane, then across the lanes
-        int c[4], before[4], sum = 0;
+        int c[4] = {0, 0, 0, 0}, before[4] = {0, 0, 0, 0}, sum = 0;
+        for (int q0 = 0; q0 < copies; q0 += 4)         // uniform
+#pragma unroll
+            for (int q = q0; q < q0 + 4; ++q)
+#pragma unroll
+                for (int j = 0; j < 4; ++j) { before[j] += hist[0][q][4 * lane + j]; c[j] += hist[1][q][4 * lane + j]; }
 #pragma unroll
         for (int j = 0; j < 4; ++j) {
-            c[j] = before[j] = 0;
-#pragma unroll
-            for (int q = 0; q < kCopies; ++q) { before[j] += hist[0][q][4 * lane + j]; c[j] += hist[1][q][4 * lane + j]; }
             c[j] += before[j];
             sum += c[j];
         }

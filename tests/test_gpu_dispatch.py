@@ -336,7 +336,11 @@ def test_batching_in_one_launch(A, E, shift):
     buf = torch.empty(A + 4, dtype=torch.int32, device="cuda")
     idx = buf[shift:shift + A]
     idx.copy_((torch.rand(A, device="cuda", generator=g) ** 3 * (E + 2)).int() - 1)        # skewed, and some out of range: clamped
-    e = idx.long().clamp(0, E - 1)
+    _check_batching(idx, E)
+
+
+def _check_batching(idx, E):
+    A, e = idx.numel(), idx.long().clamp(0, E - 1)
 
     def ints(n):
         return torch.full((n,), -1, dtype=torch.int32, device="cuda")
@@ -349,6 +353,17 @@ def test_batching_in_one_launch(A, E, shift):
     assert torch.equal(inv.long()[order], torch.arange(A, device="cuda"))
     assert torch.equal(counts.long(), torch.bincount(e, minlength=E))
     assert offsets.tolist() == [0] + torch.cumsum(counts, 0).tolist()
+
+
+# the sizes where the counting goes over to more histograms
+@pytest.mark.parametrize("A", [8192, 8193, 32768, 32769, 65536])
+@pytest.mark.parametrize("E,share", [(1, 1.0), (256, 1.0), (256, 0.5)])
+def test_batching_with_one_dominant_expert(A, E, share):
+    g = torch.Generator(device="cuda")
+    g.manual_seed(A)
+    idx = torch.randint(0, E, (A,), dtype=torch.int32, device="cuda", generator=g)
+    idx[torch.rand(A, device="cuda", generator=g) < share] = E - 1
+    _check_batching(idx, E)
 
 
 @pytest.mark.parametrize("T,k", [(1, 1), (2, 8), (16, 1), (17, 1), (21, 3), (32, 2), (64, 1), (65, 1)])
