@@ -18,7 +18,7 @@
 
 #include <type_traits>
 
-// This file is compiled in five parts side by side (FFN_PART 0..4; a kernel holds the tile code for 13 or 15 heights in two
+// This file is compiled in five parts side by side (FFN_PART 0..4; a kernel holds the tile code for 12 or 14 heights in two
 // load flavours and takes minutes): the four instantiations of ffn_mfma_kernel, and everything else.
 #ifndef FFN_PART
 #error "compile with -DFFN_PART=0..4"
@@ -615,8 +615,11 @@ __device__ inline void ffn_tile(uint4 (&lds)[kLdsBytes / 16], const uint16_t* __
     static_assert(kRowsPerPass * kTileRowBytes <= static_cast<int>(sizeof(lds)), "epilogue tile must fit the LDS buffers");
     const int wave = wave_s;
     const int row_in = (tid & 15), col_in = 4 * ((tid & 63) >> 4);
-    // the first step of this wave's weight stream in the block's next item (plain loads: they stay in the L2)
+    // the first step of this wave's weight stream in the block's next item (plain loads: they stay in the L2).  The end of the item waits for them, which
+    // short reductions with their short items lose more by than the next item gains: none up to 12 steps (300, 600 and 1000 tokens on 33 experts, d 768, f 3072
+    // 116.3 -> 113.7, 119.1 -> 117.0 and 126.8 -> 122.4 us; d 1024 equal, 1000 tokens 206 -> 209; d 2048 and 4096 lose 0.5-0.8 % without them).
     auto warm_next = [&]() {
+        if (chunks <= 12) return;                       // uniform
         const int nq = __builtin_amdgcn_readfirstlane(*sh_q);
         if (nq < 0) return;
         const Item nx = decode_item(Q, static_cast<unsigned>(nq), static_cast<unsigned>(__builtin_amdgcn_readfirstlane(*sh_x)), units);
@@ -762,7 +765,7 @@ __global__ __launch_bounds__(256) void ffn_mfma_kernel(const uint16_t* __restric
     __syncthreads();
     for (;;) {
         if (sh_q < 0) return;                      // every queue is empty (uniform for the block)
-        // The tile code below is compiled for 13 or 15 tile heights; values that do not change from item to
+        // The tile code below is compiled for 12 or 14 tile heights; values that do not change from item to
         // item would be hoisted out of this loop and held in registers across all of them.  The inputs
         // are made opaque per iteration instead.
         int Kl = K, Nl = N;
@@ -778,7 +781,9 @@ __global__ __launch_bounds__(256) void ffn_mfma_kernel(const uint16_t* __restric
         const void* wave_w = wave_stream<GATED, NF>(Q, e, it.block_y, wave, units, Kl, key);
         // weights of an expert with two row tiles or more are left in the L2 for its other tiles
         const bool keep = tiles_of_expert >= kKeepFromTiles;
-        // a single block runs as two: its steps of four MFMAs per unit are too short (600 tokens, d 768, f 3072, 33 experts 122 -> 120 us)
+        // A single block runs as two: its steps of four MFMAs per unit are too short (600 tokens, d 768, f 3072, 33 experts 122 -> 120 us).  Three run as
+        // four: a height of their own gains nothing where the weights are the bound, and costs a short launch the fetching of its code (1500 tokens,
+        // d 512, f 1024, 33 experts of 45 rows 52.8 -> 51.3 us, 1200 53.1 -> 52.0; with seven as eight too 900 tokens on 8 experts, d 4096 381 -> 386).
         const int blocks = min((rows + 15) >> 4, (GATHER ? kGatherTileM : kTileM) / 16);
 #define FFN_TILE(RB, KP)                                                                                             \
     ffn_tile<GATED, NF, RB, KP, GATHER>(lds, A, row_begin, rows, wave_w, C, Kl, Nl, unit, active, act, key, wave, row_map, \
@@ -789,13 +794,13 @@ __global__ __launch_bounds__(256) void ffn_mfma_kernel(const uint16_t* __restric
         break;
         if constexpr (GATHER) {
             switch (blocks) {
-                case 1: FFN_CASE(2) FFN_CASE(3) FFN_CASE(4) FFN_CASE(5) FFN_CASE(6) FFN_CASE(7) FFN_CASE(8) FFN_CASE(9)
+                case 1: FFN_CASE(2) case 3: FFN_CASE(4) FFN_CASE(5) FFN_CASE(6) FFN_CASE(7) FFN_CASE(8) FFN_CASE(9)
                 FFN_CASE(10) FFN_CASE(11) FFN_CASE(12) FFN_CASE(13)
                 default: if (keep) FFN_TILE(kGatherTileM / 16, true); else FFN_TILE(kGatherTileM / 16, false); break;
             }
         } else {
             switch (blocks) {
-                case 1: FFN_CASE(2) FFN_CASE(3) FFN_CASE(4) FFN_CASE(5) FFN_CASE(6) FFN_CASE(7) FFN_CASE(8) FFN_CASE(9)
+                case 1: FFN_CASE(2) case 3: FFN_CASE(4) FFN_CASE(5) FFN_CASE(6) FFN_CASE(7) FFN_CASE(8) FFN_CASE(9)
                 FFN_CASE(10) FFN_CASE(11) FFN_CASE(12) FFN_CASE(13) FFN_CASE(14) FFN_CASE(15)
                 default: if (keep) FFN_TILE(kTileM / 16, true); else FFN_TILE(kTileM / 16, false); break;
             }
