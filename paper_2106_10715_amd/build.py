@@ -141,6 +141,27 @@ def check_loads_in_flight(asm: str, kernel_pattern: str, what: str = "assembly")
     return checked
 
 
+def check_m0_free(asm: str, kernel_pattern: str, what: str = "assembly") -> int:
+    """The loads into LDS set m0 in the inline assembly that issues them.  The register is a reserved one, which a clobber list cannot
+    name; so no instruction of the named kernels outside of inline assembly may touch it, else it would find the loads' value there or they
+    its.  Raises on one; returns the number of lines of inline assembly that write it."""
+    kernel, in_asm, written = None, False, 0
+    for n, line in enumerate(asm.splitlines(), 1):
+        text = line.strip()
+        if line.startswith("_Z") and ":" in line:
+            name = line.split(":")[0]
+            kernel = name if kernel_pattern in name else None
+        elif text.startswith((".end_amdhsa_kernel", ".Lfunc_end")):
+            kernel = None
+        if text.startswith((";;#ASMSTART", ";;#ASMEND")):
+            in_asm = text.startswith(";;#ASMSTART")
+        elif kernel is not None and re.search(r"\bm0\b", text.split(";")[0]):
+            if not in_asm:
+                raise RuntimeError(f"{what}: {kernel}: line {n} ({text}) touches m0, which the loads into LDS set without the compiler's knowledge")
+            written += 1
+    return written
+
+
 def check_prologue_in_flight(asm: str, kernel_pattern: str, what: str = "assembly") -> int:
     """The same rule for the code that leads up to each pipelined loop (from "; pipeline begin" to the loop's
     first block, in layout order, across block labels): the loads written as inline assembly are in flight from
@@ -212,8 +233,9 @@ def _check(src: str, part: int) -> None:
     text = open(asm).read()
     check_no_spill(text, NO_SPILL[src], src)
     loops = check_loads_in_flight(text, NO_SPILL[src], src), check_prologue_in_flight(text, NO_SPILL[src], src)
-    if part > 0 and 0 in loops:
-        raise RuntimeError(f"{src}: no pipelined loop found to verify (markers missing?)")
+    m0 = check_m0_free(text, NO_SPILL[src], src)
+    if part > 0 and (0 in loops or m0 == 0):
+        raise RuntimeError(f"{src}: no pipelined loop, or no load into LDS, found to verify (markers missing?)")
 
 
 def _compile(src: str, part: int) -> str:

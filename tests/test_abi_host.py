@@ -241,3 +241,14 @@ def test_gate_and_timer_arguments_are_checked_on_the_host():
     big = M.MoeCfg.make(262145, 64, 64, 4)
     assert L.moe_permute_static(C.byref(big), None, C.c_void_p(8), C.c_void_p(8), C.c_void_p(8), C.c_void_p(8), C.c_void_p(8), None, None) == -3
     assert b"262144" in L.moe_last_error()
+
+
+def test_build_refuses_m0_outside_of_the_loads_into_lds():
+    from paper_2106_10715_amd import build as B
+    load = "\t;;#ASMSTART\n\ts_add_u32 m0, s92, 0x1000\n\ts_nop 0\n\tglobal_load_lds_dwordx4 v1, s[60:61]\n\t;;#ASMEND\n"
+    kernel = "_Zk_ffn_mfma: ; @k\n" + load + "{}" + load + ".Lfunc_end0:\n"
+    assert B.check_m0_free(kernel.format("\ts_mov_b32 s0, s1 ; m0 is free\n"), "ffn_mfma") == 2
+    for use in ("\ts_mov_b32 m0, s1\n", "\tv_readlane_b32 s3, v0, m0\n"):
+        with pytest.raises(RuntimeError, match="m0"):
+            B.check_m0_free(kernel.format(use), "ffn_mfma")
+    assert B.check_m0_free("_Zother:\n\ts_mov_b32 m0, s1\n.Lfunc_end0:\n", "ffn_mfma") == 0
