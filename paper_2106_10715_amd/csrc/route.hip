@@ -43,14 +43,16 @@ __device__ inline void dd_add(double& hi, double& lo, double h2, double l2) {
     hi = sum;
 }
 __device__ inline void dd_add_product(double& hi, double& lo, double x, double w) { dd_add(hi, lo, x * w, 0.0); }
+// (A sum with an infinity in it has no rounding error: what dd_add keeps then is a NaN, and the sum is the high part.)
 __device__ inline void dd_normalise(double& hi, double& lo) {
+    if (lo != lo) lo = 0.0;
     const double sum = hi + lo, bb = sum - hi;
-    lo = (hi - (sum - bb)) + (lo - bb);
+    lo = fabs(sum) == INFINITY ? 0.0 : (hi - (sum - bb)) + (lo - bb);
     hi = sum;
 }
 
 // The kk best of the wave's candidates, in order.  Lane `eg` owns experts eg + 64 i (i < kNE) when
-// `owner`; every lane receives the same result.
+// `owner`; every lane receives the same result.  A NaN ranks with the smallest, so that there are always kk experts.
 __device__ __attribute__((always_inline)) inline void wave_topk(const double (&lv)[kNE], const double (&ll)[kNE], int eg, bool owner, int E, int kk,
                                  double (&outv)[kSel], int (&oute)[kSel]) {
     unsigned taken = 0;
@@ -62,7 +64,9 @@ __device__ __attribute__((always_inline)) inline void wave_topk(const double (&l
 #pragma unroll
             for (int i = 0; i < kNE; ++i) {
                 const int ei = eg + 64 * i;
-                if (owner && ei < E && !((taken >> i) & 1u) && before(lv[i], ll[i], ei, v, l, e)) { v = lv[i]; l = ll[i]; e = ei; }
+                const bool number = lv[i] == lv[i];
+                const double lvi = number ? lv[i] : -INFINITY, lli = number ? ll[i] : 0.0;
+                if (owner && ei < E && !((taken >> i) & 1u) && before(lvi, lli, ei, v, l, e)) { v = lvi; l = lli; e = ei; }
             }
 #pragma unroll
             for (int off = 32; off >= 1; off >>= 1) {

@@ -423,19 +423,32 @@ def test_f32_expert_ffn_large_and_infinite_values():
             assert rel_l2(got[r].numpy(), ref.numpy()) <= 1e-6
 
 
-@pytest.mark.parametrize("E,k,renorm", [(6, 2, 1), (40, 1, 1), (40, 3, 0), (70, 2, 0)])
+@pytest.mark.parametrize("dtype", ["bf16", "f32"])
+@pytest.mark.parametrize("E,k,renorm", [(6, 2, 1), (40, 1, 1), (40, 3, 0), (70, 2, 0), (1, 1, 1), (3, 3, 1), (12, 12, 0)])
 @pytest.mark.parametrize("special", [float("inf"), float("-inf"), float("nan")])
-def test_gate_infinite_logits_keep_the_fp32_order(E, k, renorm, special):
-    """Tokens with an infinity or a NaN have no error bound and go through the exact branch, where the columns in reach have no order of
-    their own: experts stay in range, and the other tokens of the block are what they are without them."""
-    x, Wg, _ = make_inputs(E, 20, 256, E, "bf16")
-    cfg = M.MoeCfg.make(20, 256, 64, E, k, "bf16", renorm)
-    idx0, w0 = gpu_route(cfg, x, Wg, None, "bf16")
+def test_gate_infinite_logits_keep_the_fp32_order(E, k, renorm, special, dtype):
+    """Tokens with an infinity or a NaN have no error bound and go through the exact branch.  There infinite logits are ordered as in fp32 (+inf first,
+    equal ones by column), logits that are no numbers come with the smallest, experts stay in range and differ, and the other tokens of the block are
+    what they are without them."""
+    k = min(k, 8)
+    x, Wg, _ = make_inputs(E, 20, 256, E, dtype)
+    cfg = M.MoeCfg.make(20, 256, 64, E, k, dtype, renorm)
+    idx0, w0 = gpu_route(cfg, x, Wg, None, dtype)
     y = x.copy()
     y[7, 100] = special
-    idx, w = gpu_route(cfg, y, Wg, None, "bf16")
+    idx, w = gpu_route(cfg, y, Wg, None, dtype)
     others = np.arange(20) != 7
     assert np.array_equal(idx[others], idx0[others]) and np.array_equal(w[others], w0[others])
+    assert idx[7].min() >= 0 and idx[7].max() < E and len(set(idx[7].tolist())) == k
+    if np.isinf(special):
+        logit = Wg[100] * special
+        assert np.array_equal(idx[7], np.argsort(-logit, kind="stable")[:k])
+        Wg[100, E // 2 + 1:] = 0                     # infinity times zero
+        idx, _ = gpu_route(cfg, y, Wg, None, dtype)
+        some = np.argsort(-logit[:E // 2 + 1], kind="stable")[:k]
+        some = some[logit[some] > 0]                 # the infinite ones; what comes after ranks with the logits that are no numbers
+        assert np.array_equal(idx[7][:len(some)], some)
+        assert idx[7].min() >= 0 and idx[7].max() < E and len(set(idx[7].tolist())) == k
 
 
 @pytest.mark.parametrize("counts", [[700, 10, 300, 0, 257, 40, 600, 33, 513, 5, 270, 120], [300] * 7 + [90, 200], [260, 255, 256] * 3, [2000, 1, 1, 1]],
