@@ -552,3 +552,24 @@ def test_f32_expert_ffn_small_values(scale):
     want = _f32_sums(x, W)[0]
     assert torch.equal(_f32_sums(x * scale, W)[0], want * scale)
     assert torch.equal(_f32_sums(x, W * scale)[0], want * scale)
+
+
+def _ffn_by_expert(counts, d, f, seed):
+    got, ref, offsets = run_ffn(sum(counts), d, f, len(counts), 1, "bf16", counts, 0, seed=seed)
+    for e in range(len(counts)):
+        lo, hi = offsets[e], offsets[e + 1]
+        if hi > lo:
+            assert rel_l2(got[lo:hi], ref[lo:hi]) <= TOL["bf16"], f"expert {e}"
+
+
+# steps of the down-projection: 3, 4 + 1, 4 + 2, 4 + 3 (rounds of four, and what does not fill one)
+@pytest.mark.parametrize("f", [192, 320, 384, 448])
+def test_expert_ffn_every_tile_height_of_the_wide_down_projection(f):
+    """32 experts x 16 column groups: units of 64 columns and, with fewer than 192 rows per expert, the sorted list."""
+    _ffn_by_expert([16 * b - b % 3 for b in range(1, 17)] * 2, 4096, f, seed=f)
+
+
+def test_expert_ffn_tall_tiles_in_a_merged_work_list():
+    """More than 224 rows per expert and a column group for every compute unit: the down-projection's tiles have the full height, experts of several
+    among experts of one."""
+    _ffn_by_expert([700, 256, 513, 230, 257, 100, 768, 144, 260, 200, 300, 176, 512, 60, 1000, 0], 4096, 192, seed=7)
