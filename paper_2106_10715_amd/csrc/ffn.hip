@@ -616,10 +616,11 @@ __device__ inline void ffn_tile(uint4 (&lds)[kLdsBytes / 16], const uint16_t* __
     const int wave = wave_s;
     const int row_in = (tid & 15), col_in = 4 * ((tid & 63) >> 4);
     // the first step of this wave's weight stream in the block's next item (plain loads: they stay in the L2).  The end of the item waits for them, which
-    // short reductions with their short items lose more by than the next item gains: none up to 12 steps (300, 600 and 1000 tokens on 33 experts, d 768, f 3072
-    // 116.3 -> 113.7, 119.1 -> 117.0 and 126.8 -> 122.4 us; d 1024 equal, 1000 tokens 206 -> 209; d 2048 and 4096 lose 0.5-0.8 % without them).
+    // low tiles with short reductions lose more by than the next item gains: none up to 12 steps (300, 600 and 1000 tokens on 33 experts, d 768, f 3072
+    // 116.3 -> 113.7, 119.1 -> 117.0 and 126.8 -> 122.4 us; d 1024 equal, 1000 tokens 206 -> 209; d 2048 and 4096 lose 0.5-0.8 % without them, and tall
+    // tiles lose 3-6 % at 4 and 8 steps: the two products of 20000 rows on 64 experts, d 256, f 512 27.7 -> 28.4 and 20.0 -> 21.2).
     auto warm_next = [&]() {
-        if (chunks <= 12) return;                       // uniform
+        if (RB <= 4 && chunks <= 12) return;            // uniform
         const int nq = __builtin_amdgcn_readfirstlane(*sh_q);
         if (nq < 0) return;
         const Item nx = decode_item(Q, static_cast<unsigned>(nq), static_cast<unsigned>(__builtin_amdgcn_readfirstlane(*sh_x)), units);
