@@ -130,11 +130,12 @@ __global__ __launch_bounds__(256) void copy_vec_kernel(const uint4* __restrict__
 __global__ __launch_bounds__(256) void ffn_plan_kernel(const int32_t* __restrict__ offsets, int e_first, int e_count,
                                                        int tile_m_up, int tile_m_down, int32_t* __restrict__ plan, int total_rows,
                                                        int max_tiles) {
-    __shared__ int scratch[kPlanScratch][256];
-    ffn_plan_block(offsets, e_first, e_count, tile_m_up, plan, total_rows, max_tiles, scratch, 0);
-    if (tile_m_down != tile_m_up) {             // else the down kernel reads the up kernel's list
-        __syncthreads();
-        ffn_plan_block(offsets, e_first, e_count, tile_m_down, plan, total_rows, max_tiles, scratch, 1);
+    __shared__ __align__(16) int scratch[kPlanScratch][256];
+    // (a loop, not two calls: the code is fetched anew in every launch)
+#pragma unroll 1
+    for (int list = 0; list < (tile_m_down != tile_m_up ? 2 : 1); ++list) {      // one: the down kernel reads the up kernel's list
+        if (list > 0) __syncthreads();
+        ffn_plan_block(offsets, e_first, e_count, list == 0 ? tile_m_up : tile_m_down, plan, total_rows, max_tiles, scratch, list);
     }
 }
 

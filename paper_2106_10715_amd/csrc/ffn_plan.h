@@ -12,7 +12,7 @@
 namespace moe {
 
 constexpr int kPlanHeader = 32;
-constexpr int kPlanScratch = 6;           // arrays of 256 numbers in LDS
+constexpr int kPlanScratch = 7;           // arrays of 256 numbers in LDS, the first at a 16-byte boundary
 
 // Where the sum of an output column over the reduction dimension starts (step key % steps of 64; it wraps around).  It depends
 // on the expert and on the column's chunk only (1024 columns of the up-projection, 2048 of the down-projection), never on the
@@ -51,15 +51,19 @@ __device__ inline void ffn_plan_block(const int32_t* offsets, int e_first, int e
     }
     __syncthreads();
     if (worker && t < e_count) {
-        int rank = 0;                   // a permutation of 0..e_count-1
-        for (int u = 0; u < e_count; ++u) rank += (n[u] > key || (n[u] == key && u < t)) ? 1 : 0;
+        int rank = 0;                   // a permutation of 0..e_count-1 (keys past the last are 0 and count for nobody)
+#pragma unroll 1
+        for (int u = 0; u < e_count; u += 4) {
+            const int4 v = *reinterpret_cast<const int4*>(&n[u]);
+            rank += (v.x > key || (v.x == key && u < t)) + (v.y > key || (v.y == key && u + 1 < t)) + (v.z > key || (v.z == key && u + 2 < t)) +
+                    (v.w > key || (v.w == key && u + 3 < t));
+        }
         order[rank] = t;
     }
     __syncthreads();
     const int mine = worker ? order[t] : 0, my_n = worker && t < e_count ? n[mine] & ((1 << kRowBits) - 1) : 0;
     const int my_tiles = (my_n + tile_m - 1) / tile_m;
     if (worker) tl[t] = my_tiles;
-    __syncthreads();
     int4* tiles = reinterpret_cast<int4*>(plan + kPlanHeader + 4 * list * max_tiles);
     // tile mt of an expert with n_e rows and n_tiles tiles, its blocks of 16 rows spread evenly (the first tiles have one more where they do not
     // divide), at place `at` of the list.  No product is larger than the number of blocks.
@@ -73,41 +77,60 @@ __device__ inline void ffn_plan_block(const int32_t* offsets, int e_first, int e
     // one L2) among groups of four of the rest, evenly.  Whole layers, sorted -> merged: 16384 tokens x 2 skewed over 64 experts 7067 -> 6992 us,
     // 16000 x 1 on 64 4086 -> 3867, 8192 x 1 on 32 2123 -> 2074, 2048 on 8 567 -> 565, 65536 on 32 equal.  Small layers of few rows per expert, where
     // hardly any has several tiles, only pay for the longer code (1025 x 2 on 33, d 320 47.2 -> 48.5 us): hence the limits.
+    // The list is bound by the latency of its steps and by the fetching of its code, which every launch does anew.
     if (total_rows < 192 * e_count && total_rows < 16384) {                        // uniform
+        __syncthreads();
         int start = 0;
         const int upto = t < e_count ? t : e_count;
         for (int r = 0; r < upto; ++r) start += tl[r];
         for (int mt = 0; mt < my_tiles; ++mt) put(mine, my_n, my_tiles, mt, start + mt);
         if (t == 255) plan[16 + list] = min(start + my_tiles, max_tiles);
     } else {
-        int total = 0, several = 0, several_before = 0, one_before = 0;
-        for (int r = 0; r < e_count; ++r) {
-            const int v = tl[r], many = v > 1 ? v : 0;
-            total += v;
-            several += many;
-            if (r < t) { several_before += many; one_before += v - many; }
+        // Sums over the ranks of the tiles, and of those of experts with several: in the waves, then over the four that work.  The tiles are then
+        // spread over all threads (an expert with half of the rows of a skewed batch has dozens).  Kernel us, sums by a loop over the experts and
+        // tiles spread over 256 threads -> as here: the list of 20000 rows on 64 experts 12.2 -> 8.9 (sorted by such a loop and not merged 7.3), of 60000 on
+        // 256 20.0 -> 12.7; the batching of 32768 skewed on 64 with the list 19.5 -> 14.
+        int (&start)[256] = scratch[4], (&several_start)[256] = scratch[5], (&sums)[256] = scratch[6];
+        const int lane = t & 63, wave = t >> 6, my_several = my_tiles > 1 ? my_tiles : 0;
+        int incl = my_tiles, incl_several = my_several;
+#pragma unroll
+        for (int off = 1; off < 64; off <<= 1) {
+            const int v = __shfl_up(incl, off), w = __shfl_up(incl_several, off);
+            if (lane >= off) { incl += v; incl_several += w; }
         }
-        const int groups = several / 4, other_groups = (total - 4 * groups) / 4;   // (what does not fill a group of the first kind counts as the rest)
-        // The tiles are spread over the threads (an expert with half of the rows of a skewed batch has dozens: 28.8 -> 23.1 us of the batching).
-        int (&start)[256] = scratch[4], (&several_start)[256] = scratch[5];
-        if (worker) {
-            start[t] = several_before + one_before;
-            several_start[t] = several_before;
+        if (worker && lane == 63) {
+            sums[wave] = incl;
+            sums[4 + wave] = incl_several;
         }
         __syncthreads();
-        for (int s = worker ? t : total; s < total; s += 256) {
+        int total = 0, several = 0;
+#pragma unroll
+        for (int w = 0; w < 4; ++w) {
+            if (w < wave) { incl += sums[w]; incl_several += sums[4 + w]; }
+            total += sums[w];
+            several += sums[4 + w];
+        }
+        if (worker) {
+            start[t] = incl - my_tiles;
+            several_start[t] = incl_several - my_several;
+        }
+        __syncthreads();
+        const int groups = several / 4, other_groups = (total - 4 * groups) / 4;   // (what does not fill a group of the first kind counts as the rest)
+#pragma unroll 1
+        for (int s = t; s < total; s += blockDim.x) {
             int r = 0;                             // the last expert, in the order of the ranks, that starts at or before s
+#pragma unroll
             for (int step = 128; step > 0; step >>= 1)
                 if (r + step < e_count && start[r + step] <= s) r += step;
             const int e = order[r], mt = s - start[r], n_tiles = tl[r], before = several_start[r];
             // group g of G comes after those of the H others whose middle, (2 i + 1) / 2 H, lies before its own
             const bool grouped = n_tiles > 1 && before + mt < 4 * groups;
             const int in_kind = grouped ? before + mt : n_tiles > 1 ? before + mt - 4 * groups : several - 4 * groups + start[r] - before;
-            const int g = in_kind / 4;
-            int at;
-            if (grouped) at = 4 * (g + (other_groups > 0 ? min((((2 * g + 1) * other_groups - 1) / groups + 1) / 2, other_groups) : 0)) + in_kind % 4;
-            else if (g < other_groups) at = 4 * (g + (groups > 0 ? min(((2 * g + 1) * groups / other_groups + 1) / 2, groups) : 0)) + in_kind % 4;
-            else at = 4 * groups + in_kind;                                        // what does not fill a group of the rest comes last
+            const int g = in_kind / 4, own = grouped ? groups : other_groups, other = grouped ? other_groups : groups;
+            // what does not fill a group of the rest comes last
+            const int at = !grouped && g >= other_groups
+                               ? 4 * groups + in_kind
+                               : 4 * (g + (other > 0 ? min((((2 * g + 1) * other - (grouped ? 1 : 0)) / own + 1) / 2, other) : 0)) + in_kind % 4;
             put(e, n[e] & ((1 << kRowBits) - 1), n_tiles, mt, at);
         }
         if (t == 0) plan[16 + list] = min(total, max_tiles);

@@ -151,7 +151,7 @@ __global__ __launch_bounds__(kPermChunk) void batch_kernel(const int32_t* __rest
                                                            int32_t* __restrict__ plan, int plan_max_tiles, int plan_tile_rows,
                                                            int plan_tile_rows_down) {
     __shared__ int hist[2][kCopies][kHistRow];         // assignments before the block's chunk, and from there on
-    __shared__ int wcnt[kBatchWaves][256];             // per wave, rows each expert takes
+    __shared__ __align__(16) int wcnt[kBatchWaves][256];     // per wave, rows each expert takes
     __shared__ int run[256], start[257];               // first row of each expert, of the chunk's and of all
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const bool plans = static_cast<int>(blockIdx.x) >= chunks;
