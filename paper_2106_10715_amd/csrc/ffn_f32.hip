@@ -6,6 +6,8 @@
 // on the bf16 matrix instruction, with every fp32 value as the sum of three bf16 values that together hold all its 24 bits.
 #include "common.h"
 
+#include <math.h>
+
 namespace moe {
 namespace {
 
@@ -70,22 +72,29 @@ __device__ inline bool find_tile(const int32_t* __restrict__ offsets, int e_firs
     return true;
 }
 
-// The same for at most kDirectRows assignments that nothing has batched, no more than a tile of any expert: the experts in the order of their
+// The same for at most kDirectRows assignments that nothing has batched: the experts in the order of their
 // first assignments, row r of the tile is assignment sh_row[r].
-__device__ inline bool find_tile_direct(const int32_t* __restrict__ idx, int A, int E, int slot, int (&sh_row)[kDirectRows], int& e_out, int& rows) {
+__device__ inline bool find_tile_direct(const int32_t* __restrict__ idx, int A, int E, int tile_m, int slot, int (&sh_row)[kDirectRows], int& e_out, int& rows) {
     __shared__ int sh_e, sh_n;
     if (threadIdx.x < 64) {
         const int lane = threadIdx.x;
         int expert;
         const unsigned long long peers = direct_peers(idx, A, E, lane, expert), below = (1ull << lane) - 1ull;
+        const int n = __popcll(peers), tiles = (n + tile_m - 1) / tile_m;
         const bool first = peers != 0ull && (peers & below) == 0ull;
-        const unsigned long long firsts = __ballot(first), found = __ballot(first && __popcll(firsts & below) == slot);
+        // tiles of the experts before this lane's; an expert has at most kDirectRows / 16
+        int start = 0;
+#pragma unroll
+        for (int i = 0; i < kDirectRows / 16; ++i) start += __popcll(__ballot(first && tiles > i) & below);
+        const unsigned long long found = __ballot(first && slot >= start && slot < start + tiles);
         if (found == 0ull) {
             if (lane == 0) sh_e = -1;
         } else {
             const int leader = __ffsll(static_cast<long long>(found)) - 1;
-            if (lane == leader) { sh_e = expert; sh_n = __popcll(peers); }
-            if ((peers >> leader) & 1ull) sh_row[__popcll(peers & below)] = lane;
+            const int per_tile = min(tile_m, ((n + tiles - 1) / max(tiles, 1) + 15) & ~15), lo = (slot - __shfl(start, leader)) * per_tile;
+            if (lane == leader) { sh_e = expert; sh_n = min(per_tile, n - lo); }
+            const int at = __popcll(peers & below) - lo;
+            if (((peers >> leader) & 1ull) && at >= 0 && at < per_tile) sh_row[at] = lane;
         }
     }
     __syncthreads();
@@ -332,15 +341,15 @@ template <bool GATED, bool NARROW>
 __global__ __launch_bounds__(256, 2) void ffn_f32_kernel(const float* A, const int32_t* __restrict__ offsets, int e_first, int e_count, const float* W,
                                                          size_t expert_stride_elems, size_t off_b0, size_t off_b1, float* C, int K, int N, int act,
                                                          int total_rows, const int32_t* __restrict__ gather, int gather_k,
-                                                         const int32_t* __restrict__ row_map, const int32_t* __restrict__ idx, int E) {
+                                                         const int32_t* __restrict__ row_map, const int32_t* __restrict__ idx, int E, int tile_rows) {
     __shared__ __align__(16) float part[4][kRows * kPartRow];
     __shared__ int sh_row[kDirectRows];
     int e, row_begin = 0, rows;
     const bool direct = idx != nullptr;
     if (direct) {
-        if (!find_tile_direct(idx, total_rows, E, blockIdx.y, sh_row, e, rows)) return;
+        if (!find_tile_direct(idx, total_rows, E, tile_rows, blockIdx.y, sh_row, e, rows)) return;
     } else {
-        if (!find_tile(offsets, e_first, e_count, kRows, blockIdx.y, total_rows, e, row_begin, rows)) return;
+        if (!find_tile(offsets, e_first, e_count, tile_rows, blockIdx.y, total_rows, e, row_begin, rows)) return;
     }
     const int n0 = blockIdx.x * 16 * lane_columns(GATED, NARROW);
     const float* Wb = W + static_cast<size_t>(e - e_first) * expert_stride_elems;
@@ -360,26 +369,44 @@ int launch_expert_ffn_f32(const moe_cfg& c, const float* Xp, const int32_t* offs
                           const int32_t* row_map, const int32_t* gather, const int32_t* idx) {
     const size_t df = static_cast<size_t>(c.d) * c.f;
     if (max_rows / kRows + e_count > 65535) return fail(MOE_ERR_UNSUPPORTED, "too many row tiles for one launch (%ld)", max_rows / kRows + e_count);
-    const unsigned tiles = static_cast<unsigned>(max_rows / kRows + e_count);
     int dev = 0;
     const DeviceInfo* info = nullptr;
     if (int rc = device_info(&dev, &info)) return rc;
-    // Blocks of half the columns when there are fewer than compute units (100 tokens, d 512, f 2048, 4 experts 52.7 -> 43.7 us); with more the rows are
-    // split too often (up to twice as many: 512 tokens x 2, d 1024, f 4096, 8 experts 294 -> 311, 1000 x 1, f 1024, 5 experts 94 -> 103).
+    // Blocks of half the columns when there are too few for the compute units.  us, wide / half, by the wide blocks likely: up-projection 64 (191 x 2, d 512,
+    // f 256, 8 experts) 35.8 / 32.3, 90 (239 x 1, d 576, f 576, 5) 40.7 / 37.8, 110 (22 x 1, d 576, f 704, 5) 30.5 / 31.5, 160 (22 x 2, d 1024, f 1024, 5) 43.0 / 49.1,
+    // 240 (31 x 1, d 640, f 960, 8) 36.6 / 40.5; down-projection 96 (300 x 1, d 768, f 1600, 8) 68.6 / 61.0, 128 (200 x 1, d 1024, f 2048, 8) 79.7 / 70.8, 160
+    // (700 x 1, d 1024, f 1024, 8) 76.8 / 78.4, 240 (968 x 1, d 1024, f 384, 8) 60.1 / 63.0.
     const long likely = max_rows / kRows > e_count ? max_rows / kRows : e_count < max_rows ? e_count : max_rows;
-    const bool up_narrow = likely * (c.f / 32) < info->compute_units, down_narrow = likely * (c.d / 64) < info->compute_units;
+    const bool up_narrow = 5 * likely * (c.f / 32) < 2L * info->compute_units, down_narrow = 5 * likely * (c.d / 64) < 3L * info->compute_units;
+    // Tiles of 32 or 16 rows where those give no more blocks than run at once, for experts of two standard deviations above the mean (tiles
+    // of the mean would often leave a few rows over): a wave then has less to do in each
+    // step of a chain that nothing else hides.  us, 64 / 32 / 16 rows in the down-projection: 117 x 1, d 256, f 3136, 4 experts 50.9 / 47.0 / 43.0, 242 x 2,
+    // d 192, f 2752, 4 66.8 / 59.0 / 55.7, 201 x 2, d 576, f 2240, 4 72.9 / 68.4 / 71.9, 239 x 1, d 576, f 576, 5 37.7 / 37.3 / 39.5, 216 x 2, d 640, f 960, 8
+    // 53.8 / 57.3 / 61.3.  The up-projection, whose reductions are shorter, has less to gain: 185 x 1, d 704, f 320, 4 32.7 / 32.6 / 33.5, 31 x 2, d 512, f 704, 4
+    // 25.5 / 25.1 / 28.6.
+    const long hit = e_count < max_rows ? e_count : max_rows;
+    const double mean = static_cast<double>(max_rows) / hit;
+    const long most = static_cast<long>(mean + 2.0 * sqrt(mean));
+    auto tile_rows = [&](long columns, long limit) {
+        int rows = kRows;
+        while (rows > 16 && hit * ((most + rows / 2 - 1) / (rows / 2)) * columns <= limit) rows /= 2;
+        return rows;
+    };
+    const int up_rows = tile_rows(c.f / 16, info->compute_units * 3L / 4), down_rows = tile_rows(c.d / 32, info->compute_units * 9L / 8);
     const dim3 block(256);
     auto up = [&](auto kernel, int columns) {
-        hipLaunchKernelGGL(kernel, dim3(c.f / columns, tiles), block, 0, s, Xp, offsets, e_first, e_count, W, expert_stride_elems, size_t(0), df, H, c.d,
-                           c.f, c.act, c.T * c.k, gather, c.k, static_cast<const int32_t*>(nullptr), idx, c.E);
+        hipLaunchKernelGGL(kernel, dim3(c.f / columns, static_cast<unsigned>(max_rows / up_rows + e_count)), block, 0, s, Xp, offsets, e_first, e_count, W,
+                           expert_stride_elems, size_t(0), df, H, c.d, c.f, c.act, c.T * c.k, gather, c.k, static_cast<const int32_t*>(nullptr), idx, c.E,
+                           up_rows);
     };
     if (up_narrow) up(ffn_f32_kernel<true, true>, 16);
     else up(ffn_f32_kernel<true, false>, 32);
     MOE_LAUNCH_CHECK("ffn_f32_kernel<up>");
     if (between != nullptr) MOE_HIP_CHECK(hipEventRecord(between, s));
     auto down = [&](auto kernel, int columns) {
-        hipLaunchKernelGGL(kernel, dim3(c.d / columns, tiles), block, 0, s, H, offsets, e_first, e_count, W, expert_stride_elems, 2 * df, 2 * df, Yp, c.f,
-                           c.d, c.act, c.T * c.k, static_cast<const int32_t*>(nullptr), 1, row_map, idx, c.E);
+        hipLaunchKernelGGL(kernel, dim3(c.d / columns, static_cast<unsigned>(max_rows / down_rows + e_count)), block, 0, s, H, offsets, e_first, e_count, W,
+                           expert_stride_elems, 2 * df, 2 * df, Yp, c.f, c.d, c.act, c.T * c.k, static_cast<const int32_t*>(nullptr), 1, row_map, idx, c.E,
+                           down_rows);
     };
     if (down_narrow) down(ffn_f32_kernel<false, true>, 32);
     else down(ffn_f32_kernel<false, false>, 64);

@@ -573,3 +573,25 @@ def test_expert_ffn_tall_tiles_in_a_merged_work_list():
     """More than 224 rows per expert and a column group for every compute unit: the down-projection's tiles have the full height, experts of several
     among experts of one."""
     _ffn_by_expert([700, 256, 513, 230, 257, 100, 768, 144, 260, 200, 300, 176, 512, 60, 1000, 0], 4096, 192, seed=7)
+
+
+@pytest.mark.parametrize("d,f", [(192, 640), (704, 320)])
+def test_f32_rows_keep_their_bits_in_every_tile_height(d, f):
+    """Blocks of 64, 32 and 16 rows, of all the columns and of half: a row has the same bits in a batch of 1500 rows as in short ones."""
+    x = _normal(1500, d, seed=8)
+    ex = [_normal(*s, seed=9 + i) * 0.05 for i, s in enumerate(((d, f), (d, f), (f, d)))]
+
+    def run(rows):
+        T = len(rows)
+        cfg = M.MoeCfg.make(T, d, f, 1, 1, "f32")
+        packed = torch.empty((1, M.moe_expert_bytes(cfg)), dtype=torch.uint8, device="cuda")
+        M.moe_pack_weights(cfg, *ex, packed[0])
+        Y = torch.full((T, d), float("nan"), device="cuda")
+        M.moe_expert_ffn(cfg, rows, torch.tensor([0, T], dtype=torch.int32, device="cuda"), packed, Y,
+                         torch.empty(M.moe_workspace_bytes(cfg), dtype=torch.uint8, device="cuda"))
+        torch.cuda.synchronize()
+        return Y
+    want = run(x)
+    assert torch.isfinite(want).all()
+    for n in (1, 17, 40, 100, 333, 700):
+        assert torch.equal(run(x[:n].clone()), want[:n]), f"{n} rows"
