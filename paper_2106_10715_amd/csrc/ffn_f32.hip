@@ -132,13 +132,13 @@ __device__ __attribute__((always_inline)) inline f32x4 mfma(const u32x4& w, cons
     return __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, w), __builtin_bit_cast(bf16x8, a), c, 0, 0, 0);
 }
 
-constexpr int kRows = 64;                                // rows of a tile
+constexpr int kRows = 64;                                // most rows of a tile
 constexpr int kPartRow = 68;                             // floats per row of a partial tile in LDS: up to 64 and 4 of padding
 // Columns of a lane, of each matrix: a block has 16 times as many.
 constexpr int lane_columns(bool gated, bool narrow) { return (gated ? 2 : 4) >> (narrow ? 1 : 0); }
 
-// What bounds it: the vector instructions that split the operands and add the sums (half of the cycles at 1024 rows of 8 experts, d 1024, f 4096); the
-// latency of a block's few steps in short launches.  Eight of the nine products of the parts are formed, so that a product has all its bits: the one
+// What bounds it: the vector instructions that split the operands and add the sums (58 % of the cycles at 1024 rows of 8 experts, d 1024, f 4096, the matrix
+// instructions 35 %); the latency of a block's few steps in short launches.  Eight of the nine products of the parts are formed, so that a product has all its bits: the one
 // left out, of the two last parts, is below 2^-30 of the whole (second part < 2^-7 of the value, third < 2^-15).  The instruction cuts off where it adds, so the product of the first parts, which for one
 // product is exact, is added to the sum of the seven small ones outside of it, and both to the running sum, in fp32: two roundings per 32 elements.
 // Relative error against 64 bits, sums of normally distributed products, here / by chains of fp32 multiply-adds in four quarters: 4096 products 1.2e-7 / 5.7e-7
@@ -152,9 +152,10 @@ constexpr int lane_columns(bool gated, bool narrow) { return (gated ? 2 : 4) >> 
 // A value that comes out infinite or NaN is computed again in fp64, by one thread per four columns: the parts of an infinity are no numbers, and
 // the operands' factor may have made it one.  So the result is infinite only where the sum is.  It is slow: 512 tokens x 2 of the layer below take 0.5 ms with one NaN
 // among them and 2 ms if all are (0.3 ms without).
-// Against tiles of 64 x 64 and 32 x 32 through LDS with the fp32 instruction, layers in us: 512 tokens x 2, d 1024, f 4096, 8 experts 341 -> 295, 4096 x 2 1947 ->
-// 1671, 8192 x 1, d 512, f 2048 555 -> 477, 16 x 1 on 8 142 -> 105, 1000 x 1, f 1024, 5 experts 120 -> 95, 100 x 1, d 512, f 2048, 4 experts
-// 45.4 -> 43.6, 64 x 1, d 256, f 512, 4 experts 23.1 -> 18.1.  Blocks that take several column groups one after the other: 5-15 % slower.
+// Against tiles of 64 x 64 and 32 x 32 through LDS with the fp32 instruction, layers in us: 512 tokens x 2, d 1024, f 4096, 8 experts 354 -> 297, 4096 x 2 1947 ->
+// 1671, 8192 x 1, d 512, f 2048 555 -> 477, 16 x 1 on 8 142 -> 106, 1000 x 1, f 1024, 5 experts 119 -> 94, 100 x 1, d 512, f 2048, 4 experts
+// 45.4 -> 38.8, 64 x 1, d 256, f 512, 4 experts 23.2 -> 19.2; 142 x 2, d 192, f 576, 4 experts 26.4 -> 28.7 and others of that size lose 1-2 us to the
+// start of a block. Blocks that take several column groups one after the other: 5-15 % slower.
 template <bool GATED, bool NARROW, int RB>
 __device__ inline void ffn_f32_tile(const float* A, const int32_t* gather, int gather_k, bool direct, const int (&sh_row)[kDirectRows], int row_begin,
                                     int rows, const float* W0, const float* W1, float* C, int K, int N, int n0, int act, const int32_t* row_map,
