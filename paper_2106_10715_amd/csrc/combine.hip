@@ -16,7 +16,8 @@ __device__ inline uint32_t pack_bf16(float lo, float hi) {
 
 // Bound by memory; a thread's pieces of all K rows are requested before the first is used, U positions of the row at a time.
 // NT: non-temporal loads, where the rows and y are more than the last-level cache holds.
-template <bool BF16, int K, int U, bool NT>
+// DIRECT: there is no inv, row a of Yp is assignment a (known to the compiler: the K look-ups are else issued one after the other).
+template <bool BF16, int K, int U, bool NT, bool DIRECT>
 __global__ __launch_bounds__(256) void combine_kernel(const uint4* __restrict__ Yp, const int32_t* __restrict__ inv,
                                                       const float* __restrict__ w, uint4* __restrict__ y,
                                                       int vec_per_row, int n_rows) {
@@ -26,7 +27,7 @@ __global__ __launch_bounds__(256) void combine_kernel(const uint4* __restrict__ 
     float wt[K];
 #pragma unroll
     for (int j = 0; j < K; ++j) {
-        const int row = inv == nullptr ? t * K + j : min(max(inv[static_cast<size_t>(t) * K + j], 0), n_rows - 1);   // never outside Yp
+        const int row = DIRECT ? t * K + j : min(max(inv[static_cast<size_t>(t) * K + j], 0), n_rows - 1);   // never outside Yp
         rows[j] = reinterpret_cast<const u4v*>(Yp) + static_cast<size_t>(row) * vec_per_row;
         wt[j] = w[static_cast<size_t>(t) * K + j];
     }
@@ -76,10 +77,11 @@ void launch_k(const moe_cfg& c, const uint4* Yp, const int32_t* inv, const float
     constexpr int kTwo = K <= 4 ? 2 : 1;
     const bool two = vec_per_row > 256, nt = static_cast<size_t>(c.T) * (c.k + 1) * vec_per_row * 16 > (size_t(320) << 20);
     auto run = [&](auto kernel) { hipLaunchKernelGGL(kernel, dim3(c.T), dim3(256), 0, s, Yp, inv, w, y, vec_per_row, c.T * c.k); };
-    if (two && nt) run(combine_kernel<BF16, K, kTwo, true>);
-    else if (two) run(combine_kernel<BF16, K, kTwo, false>);
-    else if (nt) run(combine_kernel<BF16, K, 1, true>);
-    else run(combine_kernel<BF16, K, 1, false>);
+    if (inv == nullptr) two ? run(combine_kernel<BF16, K, kTwo, false, true>) : run(combine_kernel<BF16, K, 1, false, true>);      // at most kDirectRows rows
+    else if (two && nt) run(combine_kernel<BF16, K, kTwo, true, false>);
+    else if (two) run(combine_kernel<BF16, K, kTwo, false, false>);
+    else if (nt) run(combine_kernel<BF16, K, 1, true, false>);
+    else run(combine_kernel<BF16, K, 1, false, false>);
 }
 
 template <bool BF16>

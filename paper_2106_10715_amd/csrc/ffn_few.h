@@ -26,18 +26,18 @@ constexpr int few_columns(bool up, bool small) { return up || small ? 16 : 32; }
 
 // The rows of a tile: row_begin, row_begin + 1, ... of the batched order; or, where the kernel reads idx itself, in the order of the
 // assignments, lane r holding the r-th.
+template <bool DIRECT>
 struct FewRows {
     int e, row_begin, rows, assignment;
-    bool direct;
-    __device__ int row(int r) const { return direct ? __builtin_amdgcn_ds_bpermute(4 * r, assignment) : row_begin + r; }
+    __device__ int row(int r) const { return DIRECT ? __builtin_amdgcn_ds_bpermute(4 * r, assignment) : row_begin + r; }
 };
 
 // GATED: H = act(A W_gate) * (A W_in), 16 columns of d_ff per block; else 16 or 32 columns of W_out.  Rows row_begin ..
 // row_begin + rows of the batched order, rows <= 16 RB, all of expert e.  Act: act(z) of the gate.  A: GATED, the token array
 // (row r of the batched order is row gather[r] / gather_k) or the batched rows (gather NULL); else H in its chunked order,
 // [chunk of 64 columns][row][64].
-template <bool GATED, bool SMALL, int RB, class Act>
-__device__ inline void ffn_few_rows(const uint16_t* A, const FewRows& tile, int e_first, const char* W,
+template <bool GATED, bool SMALL, int RB, bool DIRECT, class Act>
+__device__ inline void ffn_few_rows(const uint16_t* A, const FewRows<DIRECT>& tile, int e_first, const char* W,
                                     size_t expert_stride_bytes, size_t block_offset_bytes, uint16_t* __restrict__ C, int K, int N,
                                     const int32_t* __restrict__ row_map, const int32_t* __restrict__ gather, int gather_k,
                                     int h_rows, Act act) {
@@ -82,7 +82,7 @@ __device__ inline void ffn_few_rows(const uint16_t* A, const FewRows& tile, int 
 #pragma unroll
     for (int rb = 0; rb < RB; ++rb) {
         const int row = tile.row(min(rb * 16 + c15, rows - 1));         // past the end: the last row again, not stored
-        const int src = !GATED ? row : tile.direct ? row / gather_k : gather != nullptr ? gather[row] / gather_k : row;
+        const int src = !GATED ? row : DIRECT ? row / gather_k : gather != nullptr ? gather[row] / gather_k : row;
         a_lane[rb] = static_cast<uint32_t>(src) * (GATED ? static_cast<uint32_t>(K) * 2u : 128u) + 16u * g;
     }
     ux4 wr[kDepth][2][NJ], ar[kDepth][2][RB];
@@ -147,18 +147,17 @@ __device__ inline void ffn_few_rows(const uint16_t* A, const FewRows& tile, int 
 }
 
 // A wave: one column unit (from blockIdx.x) of one row tile (blockIdx.y, an entry of the work list, at most kFewTileM rows).
-// idx: there is no work list and no batched order; tile blockIdx.y is the expert whose first assignment is the blockIdx.y-th such, and all A
+// DIRECT: there is no work list and no batched order, but idx; tile blockIdx.y is the expert whose first assignment is the blockIdx.y-th such, and all A
 // assignments are looked through here (one read and a few lane votes, against a launch and three dependent reads: 1 token
 // 59.7 -> 55.2 us, 30 tokens x 2 on 8 experts, d 1024, f 2048 37.6 -> 33.3; fp32, 64 tokens, d 256, f 512, 4 experts 23.3 -> 19.7).
-template <bool GATED, bool SMALL, class Act>
+template <bool GATED, bool SMALL, bool DIRECT, class Act>
 __device__ inline void ffn_few_block(const uint16_t* A, const int32_t* __restrict__ plan, int e_first, const char* W,
                                      size_t expert_stride_bytes, size_t block_offset_bytes, uint16_t* __restrict__ C, int K, int N,
                                      const int32_t* __restrict__ row_map, const int32_t* __restrict__ gather, int gather_k,
                                      int h_rows, const int32_t* __restrict__ idx, int n_idx, int E, Act act) {
     const int tile = blockIdx.y;
-    FewRows at;
-    at.direct = idx != nullptr;
-    if (idx != nullptr) {
+    FewRows<DIRECT> at;
+    if constexpr (DIRECT) {
         const int lane = threadIdx.x & 63;
         int expert;
         const unsigned long long peers = direct_peers(idx, n_idx, E, lane, expert), below = (1ull << lane) - 1ull;
@@ -186,7 +185,7 @@ __device__ inline void ffn_few_block(const uint16_t* A, const int32_t* __restric
     }
     const int rows = at.rows;
     auto run = [&](auto rb) __attribute__((always_inline)) {
-        ffn_few_rows<GATED, SMALL, decltype(rb)::value>(A, at, e_first, W, expert_stride_bytes, block_offset_bytes, C, K, N,
+        ffn_few_rows<GATED, SMALL, decltype(rb)::value, DIRECT>(A, at, e_first, W, expert_stride_bytes, block_offset_bytes, C, K, N,
                                                         row_map, gather, gather_k, h_rows, act);
     };
     if constexpr (SMALL) {
