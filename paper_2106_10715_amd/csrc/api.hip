@@ -394,7 +394,7 @@ int layer_forward(const moe_cfg* cfg, const void* x, const void* W_g, const floa
         const DeviceInfo* info = nullptr;
         if (int rc = device_info(&dev, &info)) return rc;
         reads_idx = ffn_reads_idx(c, info->compute_units);
-        plan_rows = ffn_tile_rows(c, gather_rows, info->compute_units);
+        plan_rows = ffn_tile_rows(c, gather_rows, info->compute_units, c.E, A);
         plan_rows_down = ffn_down_tile_rows(c, c.E, A, plan_rows, info->compute_units);
     }
     if (!reads_idx)

@@ -42,8 +42,8 @@ inline bool aligned16(const void* p) { return (reinterpret_cast<uintptr_t>(p) & 
 
 // Assignments handled by one block of the histogram / scatter kernels of the permutation.
 constexpr int kPermChunk = 1024;
-// Rows of one expert segment covered by one block of the FFN kernels.
-constexpr int kTileM = 256;
+// Most rows of one expert segment covered by one block of the FFN kernels.
+constexpr int kTileM = 320;
 
 // Byte offsets of every region inside the caller's workspace.
 struct WsLayout {
@@ -98,7 +98,7 @@ int launch_expert_ffn(const moe_cfg& c, const void* Xp, const int32_t* offsets, 
                       const int32_t* idx = nullptr);
 // gather: Xp is then the token array x[T, d] itself and batched row r is its row gather[r] / k (gather = the
 // perm written by the batching step), so the batched copy of the activations need not exist.  A bf16 work list written elsewhere (plan_ready) must
-// have been cut to tiles of ffn_tile_rows(c, gather != NULL, n_cu) rows.
+// have been cut to tiles of ffn_tile_rows(c, gather != NULL, n_cu, e_count, max_rows) rows.
 // idx (whole layer of at most kDirectRows assignments, ffn_reads_idx): nothing has batched the assignments; Xp is x, offsets, plan, row_map
 // and gather are not read, and the kernels find an expert's rows in idx [T, k] themselves.  Row a of H and Yp is then assignment a.
 constexpr int kDirectRows = 64;
@@ -107,7 +107,7 @@ int launch_expert_ffn_f32(const moe_cfg& c, const float* Xp, const int32_t* offs
                           size_t expert_stride_elems, long max_rows, float* H, float* Yp, hipStream_t s, hipEvent_t between,
                           const int32_t* row_map, const int32_t* gather, const int32_t* idx);
 // Rows of a bf16 row tile of the up-projection (and of the down-projection, unless ffn_down_tile_rows says less).
-int ffn_tile_rows(const moe_cfg& c, bool gather, int n_cu);
+int ffn_tile_rows(const moe_cfg& c, bool gather, int n_cu, int e_count, long max_rows);
 // Height of the down-projection's row tiles for a launch over e_count experts with at most max_rows rows in all (the two
 // kernels have a tile list each); n_cu: compute units of the device.
 int ffn_down_tile_rows(const moe_cfg& c, int e_count, long max_rows, int tile_m_up, int n_cu);

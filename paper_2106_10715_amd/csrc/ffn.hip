@@ -5,7 +5,7 @@
 //     H  = act(Xp W_gate[e]) * (Xp W_in[e])        "up"   grouped GEMM, epilogue fused
 //     Yp = H W_out[e]                               "down" grouped GEMM
 //
-// bf16 path: 16x16x32 bf16 MFMA, fp32 accumulate.  One block = up to 256 rows of one expert x 4 waves;
+// bf16 path: 16x16x32 bf16 MFMA, fp32 accumulate.  One block = up to 320 rows of one expert x 4 waves;
 // every wave owns its own output columns for all rows, so a weight fragment is needed by exactly
 // one wave: weights go HBM -> registers directly in pre-packed fragment order (no LDS, fully
 // coalesced 1 KiB reads), only the activation tile is shared through LDS (loaded
@@ -16,9 +16,11 @@
 #include "ffn_few.h"
 #include "ffn_plan.h"
 
+#include <math.h>
+
 #include <type_traits>
 
-// This file is compiled in five parts side by side (FFN_PART 0..4; a kernel holds the tile code for 12 or 14 heights in two
+// This file is compiled in five parts side by side (FFN_PART 0..4; a kernel holds the tile code for 12 or 18 heights in two
 // load flavours and takes minutes): the four instantiations of ffn_mfma_kernel, and everything else.
 #ifndef FFN_PART
 #error "compile with -DFFN_PART=0..4"
@@ -152,7 +154,7 @@ __global__ __launch_bounds__(SMALL ? 64 : 128, few_waves_per_simd(SMALL)) void f
 #else   // FFN_PART 1..4
 // ------------------------------------------------------------------------------------------ bf16 MFMA
 //
-// Software pipeline of one block (4 waves, up to 256 rows of one expert, 64 reduction elements per
+// Software pipeline of one block (4 waves, up to 320 rows of one expert, 64 reduction elements per
 // step).  In step c every wave
 //     issues its share of the activation tile of step c + D          (global -> LDS buffer (c + D) % R)
 //     issues its weight fragments of step c + D                      (global -> registers, ring of R sets)
@@ -175,7 +177,7 @@ constexpr int kKC = 64;                 // reduction elements staged per pipelin
 constexpr int kKS = kKC / 32;           // MFMA k-steps per pipeline step
 constexpr uint32_t kStepBytes = (kKC / 16) * 2048;   // bytes of a wave's weight stream one pipeline step spans
 constexpr int kLdsRow = 8;              // uint4 per activation row in LDS: 128 B; piece p of row r lies at place p ^ (r % 8)
-constexpr int kLdsBytes = 4 * kTileM * kLdsRow * 16;   // four activation tiles of the full height
+constexpr int kLdsBytes = 4 * 288 * kLdsRow * 16;   // four activation tiles of the full height, in blocks of 32 rows
 
 typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 
@@ -238,10 +240,10 @@ __device__ inline void ld_to_lds(uint32_t lds_base, uint32_t voff, const void* s
 template <int RB>
 struct Units {
     static constexpr int MBS = (RB + 1) / 2;                       // blocks of 32 rows the activations are staged in
-    static constexpr int H = RB > 8 ? 4 : 2;
+    static constexpr int H = RB > 16 ? 5 : RB > 8 ? 4 : 2;
     static constexpr int G = (RB + H - 1) / H;
     static constexpr int U = kKS * H;
-    static constexpr int R = 4;                                    // activation tiles in LDS, weight sets in registers
+    static constexpr int R = RB > 18 ? 3 : 4;                                    // activation tiles in LDS, weight sets in registers
     static constexpr int D = R - 1;                                // steps loads are issued ahead; a buffer is refilled one step after its own
     static constexpr int kBuf = MBS * 32 * kLdsRow * 16;           // bytes of an activation tile
     static_assert(R * kBuf <= kLdsBytes, "the activation tiles fit the LDS");
@@ -274,11 +276,18 @@ __device__ inline void read_frag(uint4 (&af)[Units<RB>::G], const uint4* tile, i
     const int at = (lane & 15) * kLdsRow + (((lane >> 4) ^ (lane & 3)) | (lane & 4));      // ((lane >> 4) + 4 ks) ^ (lane % 8) without ks
     af[I] = tile[(at ^ (4 * ks)) + rb * 16 * kLdsRow];
 }
+// Row blocks whose sums fill the 256 accumulation registers (four fragments of four registers each).  Those of further blocks stay in vector registers: the
+// instruction takes its sums from either kind, but the compiler only from the first and would move these there and back in every step, hence the
+// assembly; nothing but the same instruction, dozens of others later, uses a sum before the end of the loop.
+constexpr int acc_blocks(int RB) { return RB > 18 ? 15 : 16; }
 // MFMA M of unit UNIT: 16-row block M / (2 NF) of the unit, weight fragment M % (2 NF)
 template <int NF, int RB, int UNIT, int M>
 __device__ inline void mma_one(f32x4 (&acc)[RB][2 * NF], const uint4 (&af)[Units<RB>::G], const BFrags<NF>& b) {
     constexpr int ks = UNIT / Units<RB>::H, i = M / (2 * NF), j = M % (2 * NF), rb = Units<RB>::first(UNIT) + i;
-    acc[rb][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(as_bf16x8(b.v[ks][j]), as_bf16x8(af[i]), acc[rb][j], 0, 0, 0);
+    if constexpr (rb < acc_blocks(RB))
+        acc[rb][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(as_bf16x8(b.v[ks][j]), as_bf16x8(af[i]), acc[rb][j], 0, 0, 0);
+    else
+        asm volatile("v_mfma_f32_16x16x32_bf16 %0, %1, %2, %0" : "+v"(acc[rb][j]) : "v"(as_bf16x8(b.v[ks][j])), "v"(as_bf16x8(af[i])));
 }
 // One pipeline step.  Entering, af[0] holds the fragments of unit 0 of this step; leaving, those of
 // unit 0 of the next step.
@@ -506,7 +515,10 @@ __device__ inline void ffn_tile(uint4 (&lds)[kLdsBytes / 16], const uint16_t* __
 #pragma unroll
         for (int j = 0; j < 2 * NF; ++j)
 #pragma unroll
-            for (int v = 0; v < 4; ++v) asm volatile("v_accvgpr_write_b32 %0, 0" : "=a"(acc[rb][j][v]));
+            for (int v = 0; v < 4; ++v) {
+                if (rb < acc_blocks(RB)) asm volatile("v_accvgpr_write_b32 %0, 0" : "=a"(acc[rb][j][v]));
+                else asm volatile("v_mov_b32 %0, 0" : "=v"(acc[rb][j][v]));
+            }
 
     constexpr int D = Units<RB>::D, R = Units<RB>::R, kBuf = Units<RB>::kBuf;       // register indices and tiles repeat with period R
     constexpr int kB = kKS * 2 * NF;            // loads of one weight step
@@ -565,6 +577,8 @@ __device__ inline void ffn_tile(uint4 (&lds)[kLdsBytes / 16], const uint16_t* __
     __syncthreads();
     static_for<0, Units<RB>::count(0)>([&](auto i) __attribute__((always_inline)) { read_frag<RB, 0, decltype(i)::value>(af[0], tile_of(0), lane); });
     for (; c + R <= chunks; c += R) static_for<0, R>(step);
+    // (the sums written by assembly, of whose latency the compiler knows nothing: 18 wait states before anything else reads them)
+    if constexpr (RB > acc_blocks(RB)) asm volatile("s_nop 15\n\ts_nop 15" : : : "memory");
     asm volatile("; pipeline end");
     // All loads have landed, those past the last step included, and only now are their destination registers let go of: one the compiler
     // considers dead would be handed to something else (an LDS read, say) while the load into it is still in flight.
@@ -587,6 +601,7 @@ __device__ inline void ffn_tile(uint4 (&lds)[kLdsBytes / 16], const uint16_t* __
 #pragma unroll
             for (int r = 0; r + 1 < R; ++r) ring[r] = ring[r + 1];
         }
+        if constexpr (RB > acc_blocks(RB)) asm volatile("s_nop 15\n\ts_nop 15" : : : "memory");
     }
     __syncthreads();                            // the last LDS reads are done before the epilogue reuses the LDS
     tid = thread_id(wave_s);                    // rebuilt: the first copy need not survive the main loop
@@ -610,7 +625,7 @@ __device__ inline void ffn_tile(uint4 (&lds)[kLdsBytes / 16], const uint16_t* __
     // give finite values), only real rows are stored.
     constexpr int W = 32 * (GATED ? 1 : NF);            // output columns per wave
     constexpr int kTileRowBytes = 4 * W * 2 + 16;       // padded: neighbouring rows start 4 dwords apart mod 32
-    constexpr int kRowsPerPass = W == 32 ? 256 : 128;   // tile rows that fit the LDS
+    constexpr int kRowsPerPass = W == 32 ? kTileM : 128;   // tile rows that fit the LDS
     constexpr int kLanesPerRow = W / 2;                 // 16-byte stores per tile row
     constexpr int kRowsPerIter = 256 / kLanesPerRow;
     char* tile = reinterpret_cast<char*>(&lds[0]);
@@ -716,7 +731,7 @@ __device__ inline void ffn_tile(uint4 (&lds)[kLdsBytes / 16], const uint16_t* __
 constexpr int kKeepFromTiles = 2;       // row tiles of an expert from which its weights are worth keeping in the L2
 
 // C[rows of one expert tile, N] = A[rows, K] * B_e, B_e in packed fragment order.
-// A work item is one row tile (up to 256 rows of one expert; only the 16-row blocks that hold rows are
+// A work item is one row tile (up to 320 rows of one expert; only the 16-row blocks that hold rows are
 // computed) by one column group of 4 units, one unit per wave, for all rows.
 // GATED (NF = 2): a unit is 32 output columns whose two fragments per k-step are (W_gate, W_in); the
 //   epilogue writes act(gate) * in.
@@ -768,7 +783,7 @@ __global__ __launch_bounds__(256) void ffn_mfma_kernel(const uint16_t* __restric
     __syncthreads();
     for (;;) {
         if (sh_q < 0) return;                      // every queue is empty (uniform for the block)
-        // The tile code below is compiled for 12 or 14 tile heights; values that do not change from item to
+        // The tile code below is compiled for 12 or 18 tile heights; values that do not change from item to
         // item would be hoisted out of this loop and held in registers across all of them.  The inputs
         // are made opaque per iteration instead.
         int Kl = K, Nl = N;
@@ -804,7 +819,7 @@ __global__ __launch_bounds__(256) void ffn_mfma_kernel(const uint16_t* __restric
         } else {
             switch (blocks) {
                 case 1: FFN_CASE(2) case 3: FFN_CASE(4) FFN_CASE(5) FFN_CASE(6) FFN_CASE(7) FFN_CASE(8) FFN_CASE(9)
-                FFN_CASE(10) FFN_CASE(11) FFN_CASE(12) FFN_CASE(13) FFN_CASE(14) FFN_CASE(15)
+                FFN_CASE(10) FFN_CASE(11) FFN_CASE(12) FFN_CASE(13) FFN_CASE(14) FFN_CASE(15) FFN_CASE(16) FFN_CASE(17) FFN_CASE(18) FFN_CASE(19)
                 default: if (keep) FFN_TILE(kTileM / 16, true); else FFN_TILE(kTileM / 16, false); break;
             }
         }
@@ -857,7 +872,40 @@ bool ffn_reads_idx(const moe_cfg& c, int n_cu) {
     return static_cast<long>(c.T) * c.k <= kDirectRows && (c.dtype == MOE_F32 || few_rows(c, n_cu));
 }
 
-int ffn_tile_rows(const moe_cfg& c, bool gather, int n_cu) { return few_rows(c, n_cu) ? kFewTileM : gather ? kGatherTileM : kTileM; }
+// Highest row tile of the up-projection.  A tile of 17 or 18 blocks of 16 rows costs less than two of 9, which read the weights twice and need 1.5
+// times the bytes per product, and experts that all have as many tiles keep the rounds of the compute units even; so what matters is where the limit lies
+// against the mean and its spread.  Layer us by limit (d 4096, f 10240; tokens / experts):
+//            2048/8  2300/8  4096/8  4500/8  6000/8  4300/16  8192/32  9000/32  16384/32  20000/64  28000/32  65536/32
+//   160         552     591     978    1004    1385     1096     2133     2197      3665      5116      6056     13055
+//   224         549     593     977    1037    1201     1089     2143     2194      3558      4644      5541     12561
+//   256         540     590     952    1035    1270     1156     2086     2268      3441      4643      5347     12486
+//   288         521     604     850    1006    1272      953     1932     2085      3440      4668      5361     12155
+//   320         519     568     844     920    1272      949     1862     1975      3339      4440      5540     12145
+// Hence 320 up to two such tiles per expert, and beyond as many rows as give nearly all experts the same number of tiles of at most 288 rows: tiles of 19
+// and 20 blocks, with three steps of loads ahead instead of four, gain nothing where the matrix pipes are the bound.
+// With fewer items than compute units the tiles are cut lower until there are as many, as in the down-projection (1100 tokens on 4 experts, d 1024, f 4096 320 /
+// 192 rows 101.9 / 93.6 us; 4000 on 8, d 512, f 1024 66 / 59); and where the experts have several tiles, one more each if the items then take their rounds
+// in less time, by their blocks and 4 for what an item costs beside them (3000 tokens on 4 experts, d 2048, f 6144 285 -> 257; 6000 on 8 as above).
+int ffn_tile_rows(const moe_cfg& c, bool gather, int n_cu, int e_count, long max_rows) {
+    if (few_rows(c, n_cu)) return kFewTileM;
+    if (gather) return kGatherTileM;
+    const long mean_rows = max_rows / (e_count > 0 ? e_count : 1), columns = static_cast<long>(e_count) * ((c.f / 32 + 3) / 4);
+    if (mean_rows <= 224) return kTileM;
+    const double most = mean_rows + 2.5 * sqrt(static_cast<double>(mean_rows));       // rows of nearly all experts, if the loads are even
+    auto rows_for = [&](long n) { return (static_cast<long>(most / n) + 16) / 16 * 16; };
+    long limit = kTileM, tiles = (mean_rows + limit - 1) / limit;
+    if (tiles > 2) {
+        tiles = static_cast<long>(most / 288) + 1;
+        limit = rows_for(tiles);
+    }
+    if (columns * tiles < n_cu) {
+        const long per_expert = (n_cu + columns - 1) / columns, rows = ((mean_rows * 5 / 4 + per_expert - 1) / per_expert + 31) / 32 * 32;
+        return static_cast<int>(rows < kMinTileM ? kMinTileM : rows < limit ? rows : limit);
+    }
+    auto cost = [&](long n) { return (columns * n + n_cu - 1) / n_cu * (4 + ((mean_rows + n - 1) / n + 15) / 16); };
+    if (tiles > 1 && cost(tiles + 1) <= cost(tiles)) limit = rows_for(tiles + 1) < limit ? rows_for(tiles + 1) : limit;
+    return static_cast<int>(limit);
+}
 size_t ffn_plan_bytes(const moe_cfg& c) { return (kPlanHeader + 2 * 4 * ffn_plan_tiles(c)) * sizeof(int32_t); }
 
 // Height of the down-projection's row tiles.  Its work items are (row tile x 256 output columns): with few experts of
@@ -911,7 +959,7 @@ int launch_expert_ffn(const moe_cfg& c, const void* Xp, const int32_t* offsets, 
         const DeviceInfo* info = nullptr;
         if (int rc = device_info(&dev, &info)) return rc;
         const int n_cu = info->compute_units;
-        const int tile_m = ffn_tile_rows(c, gather != nullptr, n_cu);
+        const int tile_m = ffn_tile_rows(c, gather != nullptr, n_cu, e_count, max_rows);
         const int tile_m_down = ffn_down_tile_rows(c, e_count, max_rows, tile_m, n_cu);
         const long slots = max_rows / tile_m + e_count;                // upper bound of the number of row tiles
         const long slots_down = max_rows / tile_m_down + e_count;

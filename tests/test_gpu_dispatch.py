@@ -595,3 +595,34 @@ def test_f32_rows_keep_their_bits_in_every_tile_height(d, f):
     assert torch.isfinite(want).all()
     for n in (1, 17, 40, 100, 333, 700):
         assert torch.equal(run(x[:n].clone()), want[:n]), f"{n} rows"
+
+
+# (narrow units of the down-projection; wide ones need a column group for every compute unit)
+@pytest.mark.parametrize("d,f,rest", [(192, 320, 12), (320, 448, 12), (4096, 192, 290), (4096, 256, 290)])
+def test_expert_ffn_tiles_of_more_than_256_rows(d, f, rest):
+    """17 and 18 blocks of 16 rows, whose last sums lie in other registers than the rest: at their edges, alone and among several tiles of one expert,
+    reductions of 3 steps to 64; and a row has the bits that it has in a short batch."""
+    counts = [257, 272, 273, 288, 289, 576, 560, 5] + [rest] * 8
+    _ffn_by_expert(counts, d, f, seed=d + f)
+    T, E = sum(counts), len(counts)
+    cfg = M.MoeCfg.make(T, d, f, E, 1, "bf16")
+    x = _normal(T, d, seed=5).bfloat16()
+    packed = torch.empty((E, M.moe_expert_bytes(cfg)), dtype=torch.uint8, device="cuda")
+    for e in range(E):
+        M.moe_pack_weights(cfg, *((_normal(*s, seed=6 + i) * 0.05).bfloat16() for i, s in enumerate(((d, f), (d, f), (f, d)))), packed[e])
+
+    def run(cfg, rows, offsets):
+        Y = torch.full((cfg.T, d), float("nan"), dtype=torch.bfloat16, device="cuda")
+        M.moe_expert_ffn(cfg, rows, torch.tensor(offsets, dtype=torch.int32, device="cuda"), packed, Y,
+                         torch.empty(M.moe_workspace_bytes(cfg), dtype=torch.uint8, device="cuda"))
+        torch.cuda.synchronize()
+        return Y
+    offsets = [0]
+    for c in counts:
+        offsets.append(offsets[-1] + c)
+    want = run(cfg, x, offsets)
+    assert torch.isfinite(want).all()
+    for e in range(5):                               # the last 40 rows of an expert, alone
+        lo, hi = offsets[e + 1] - 40, offsets[e + 1]
+        alone = run(M.MoeCfg.make(40, d, f, E, 1, "bf16"), x[lo:hi].clone(), [0] * (e + 1) + [40] * (E - e))
+        assert torch.equal(alone, want[lo:hi]), f"expert {e}"
