@@ -243,7 +243,7 @@ struct Units {
     static constexpr int H = RB > 16 ? 5 : RB > 8 ? 4 : 2;
     static constexpr int G = (RB + H - 1) / H;
     static constexpr int U = kKS * H;
-    static constexpr int R = RB > 18 ? 3 : 4;                                    // activation tiles in LDS, weight sets in registers
+    static constexpr int R = RB > 18 ? 3 : 4;                      // activation tiles in LDS, weight sets in registers
     static constexpr int D = R - 1;                                // steps loads are issued ahead; a buffer is refilled one step after its own
     static constexpr int kBuf = MBS * 32 * kLdsRow * 16;           // bytes of an activation tile
     static_assert(R * kBuf <= kLdsBytes, "the activation tiles fit the LDS");
