@@ -142,12 +142,12 @@ __global__ __launch_bounds__(256) void ffn_plan_kernel(const int32_t* __restrict
 }
 
 // (DIRECT is known to the compiler: one kernel for both takes the batched calls 0.3 us longer, 37 tokens x 2, d 1152, f 320, 4 experts 6.7 + 4.1 -> 7.2 + 4.3)
-template <bool GATED, bool SMALL, bool DIRECT>
-__global__ __launch_bounds__(SMALL ? 64 : 128, few_waves_per_simd(SMALL)) void ffn_few_kernel(
+template <bool GATED, bool SMALL, bool DIRECT, bool DEEP = false>
+__global__ __launch_bounds__(SMALL ? 64 : 128, few_waves_per_simd(SMALL, DEEP)) void ffn_few_kernel(
     const uint16_t* A, const int32_t* __restrict__ plan, int e_first, const char* W, size_t expert_stride_bytes, size_t block_offset_bytes,
     uint16_t* __restrict__ C, int K, int N, int act, const int32_t* __restrict__ row_map, const int32_t* __restrict__ gather,
     int gather_k, int h_rows, const int32_t* __restrict__ idx, int E) {
-    ffn_few_block<GATED, SMALL, DIRECT>(A, plan, e_first, W, expert_stride_bytes, block_offset_bytes, C, K, N, row_map, gather, gather_k, h_rows, idx, h_rows, E,
+    ffn_few_block<GATED, SMALL, DEEP, DIRECT>(A, plan, e_first, W, expert_stride_bytes, block_offset_bytes, C, K, N, row_map, gather, gather_k, h_rows, idx, h_rows, E,
                                 [act](float z) { return act_fn_bf16(z, act); });
 }
 
@@ -1005,6 +1005,13 @@ int launch_expert_ffn(const moe_cfg& c, const void* Xp, const int32_t* offsets, 
             // to fill the chip, or all rows on one of them, smaller blocks spread better.  us, one / two waves: 40 tokens on 32
             // experts 869 / 856, 128 on 16 641 / 629, 64 on 8 319 / 319; 64 rows on one expert (FFN alone) 109 / 126.
             const int up_waves = c.T * c.k > 16 && c.E >= 16 ? 2 : 1;
+// (few_depth: the rows have an expert each at most)
+            const bool deep = static_cast<long>(n_tiles) * (c.d / few_columns(false, true)) <= n_cu && c.f >= 4096;
+#define MOE_FFN_FEW_DOWN(SMALL, DIRECT, DEEP)                                                                                 \
+    hipLaunchKernelGGL((ffn_few_kernel<false, SMALL, DIRECT, DEEP>), dim3(c.d / few_columns(false, SMALL), n_tiles), dim3(64), 0, s, \
+                       static_cast<const uint16_t*>(H), plan, e_first, static_cast<const char*>(W),                           \
+                       expert_stride_bytes, down_off, static_cast<uint16_t*>(Yp), c.f, c.d, c.act, row_map,                   \
+                       static_cast<const int32_t*>(nullptr), 1, c.T * c.k, idx, c.E)
 #define MOE_FFN_FEW(SMALL, DIRECT)                                                                                            \
     {                                                                                                                 \
         hipLaunchKernelGGL((ffn_few_kernel<true, SMALL, DIRECT>), dim3(c.f / few_columns(true, SMALL) / up_waves, n_tiles), dim3(64 * up_waves), 0, s, \
@@ -1013,10 +1020,8 @@ int launch_expert_ffn(const moe_cfg& c, const void* Xp, const int32_t* offsets, 
                            static_cast<const int32_t*>(nullptr), gather, c.k, c.T * c.k, idx, c.E);                   \
         MOE_LAUNCH_CHECK("ffn_few_kernel<up>");                                                                       \
         if (between != nullptr) MOE_HIP_CHECK(hipEventRecord(between, s));                                            \
-        hipLaunchKernelGGL((ffn_few_kernel<false, SMALL, DIRECT>), dim3(c.d / few_columns(false, SMALL), n_tiles), dim3(64), 0, s, \
-                           static_cast<const uint16_t*>(H), plan, e_first, static_cast<const char*>(W),               \
-                           expert_stride_bytes, down_off, static_cast<uint16_t*>(Yp), c.f, c.d, c.act, row_map,       \
-                           static_cast<const int32_t*>(nullptr), 1, c.T * c.k, idx, c.E);                             \
+        if (SMALL && deep) MOE_FFN_FEW_DOWN(SMALL, DIRECT, SMALL);                                                    \
+        else MOE_FFN_FEW_DOWN(SMALL, DIRECT, false);                                                                  \
         MOE_LAUNCH_CHECK("ffn_few_kernel<down>");                                                                     \
     }
             if (idx != nullptr) {
@@ -1024,6 +1029,7 @@ int launch_expert_ffn(const moe_cfg& c, const void* Xp, const int32_t* offsets, 
             } else {
                 if (c.T * c.k <= 16) MOE_FFN_FEW(true, false) else MOE_FFN_FEW(false, false)
             }
+#undef MOE_FFN_FEW_DOWN
 #undef MOE_FFN_FEW
             return MOE_OK;
         }

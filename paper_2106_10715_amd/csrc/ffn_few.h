@@ -20,8 +20,11 @@ constexpr int kFewTileM = 64;                        // rows of a tile: with mor
 
 // Steps of 64 reduction elements in flight, as the registers of 2 to 4 waves per SIMD allow.  SMALL (16 rows in all), steps of the
 // down-projection and waves: 8 and 3 / 7 and 4 / 6 and 4 measure 59.6 / 60.8 / 62.7 us for one token, 523 / 508 / 509 for 16.
-constexpr int few_depth(bool up, bool small, int RB) { return small ? (up ? 4 : 7) : RB == 1 ? 8 : RB == 2 ? 6 : 3; }
-constexpr int few_waves_per_simd(bool small) { return small ? 4 : 2; }
+// DEEP, a down-projection with a wave per compute unit at most, which then has the unit's loads in flight to itself (one token: 14 KiB of the 44 that a unit
+// can have): 7 / 14 / 24 steps take 56.0 / 54.4 / 55.3 us for one token on 32 experts, 57.4 / 54.0 / 54.2 on 8; two tokens, whose units
+// have two waves, 91.7 / 92.9 / 94.0, and 32 steps in all (4 tokens on 8 experts, d 512, f 2048) 16.0 / 16.5 / 17.5.
+constexpr int few_depth(bool up, bool small, bool deep, int RB) { return deep ? 14 : small ? (up ? 4 : 7) : RB == 1 ? 8 : RB == 2 ? 6 : 3; }
+constexpr int few_waves_per_simd(bool small, bool deep) { return small && !deep ? 4 : 2; }
 constexpr int few_columns(bool up, bool small) { return up || small ? 16 : 32; }
 
 // The rows of a tile: row_begin, row_begin + 1, ... of the batched order; or, where the kernel reads idx itself, in the order of the
@@ -36,7 +39,7 @@ struct FewRows {
 // row_begin + rows of the batched order, rows <= 16 RB, all of expert e.  Act: act(z) of the gate.  A: GATED, the token array
 // (row r of the batched order is row gather[r] / gather_k) or the batched rows (gather NULL); else H in its chunked order,
 // [chunk of 64 columns][row][64].
-template <bool GATED, bool SMALL, int RB, bool DIRECT, class Act>
+template <bool GATED, bool SMALL, bool DEEP, int RB, bool DIRECT, class Act>
 __device__ inline void ffn_few_rows(const uint16_t* A, const FewRows<DIRECT>& tile, int e_first, const char* W,
                                     size_t expert_stride_bytes, size_t block_offset_bytes, uint16_t* __restrict__ C, int K, int N,
                                     const int32_t* __restrict__ row_map, const int32_t* __restrict__ gather, int gather_k,
@@ -47,7 +50,7 @@ __device__ inline void ffn_few_rows(const uint16_t* A, const FewRows<DIRECT>& ti
     typedef uint32_t ux4 __attribute__((ext_vector_type(4)));
     constexpr int kColumns = few_columns(GATED, SMALL);
     constexpr int NJ = GATED ? 2 : kColumns / 16;   // weight operands of a k-step of 32: gate and in, or 16 columns each
-    constexpr int kDepth = few_depth(GATED, SMALL, RB);
+    constexpr int kDepth = few_depth(GATED, SMALL, DEEP, RB);
     const int lane = threadIdx.x & 63, c15 = lane & 15, g = lane >> 4;
     const int e = tile.e, rows = tile.rows;
     // The units that share the 8 KiB window of a step in the packed weights (two, or four of 16 columns of W_out) go to blocks
@@ -150,7 +153,7 @@ __device__ inline void ffn_few_rows(const uint16_t* A, const FewRows<DIRECT>& ti
 // DIRECT: there is no work list and no batched order, but idx; tile blockIdx.y is the expert whose first assignment is the blockIdx.y-th such, and all A
 // assignments are looked through here (one read and a few lane votes, against a launch and three dependent reads: 1 token
 // 59.7 -> 55.2 us, 30 tokens x 2 on 8 experts, d 1024, f 2048 37.6 -> 33.3; fp32, 64 tokens, d 256, f 512, 4 experts 23.3 -> 19.7).
-template <bool GATED, bool SMALL, bool DIRECT, class Act>
+template <bool GATED, bool SMALL, bool DEEP, bool DIRECT, class Act>
 __device__ inline void ffn_few_block(const uint16_t* A, const int32_t* __restrict__ plan, int e_first, const char* W,
                                      size_t expert_stride_bytes, size_t block_offset_bytes, uint16_t* __restrict__ C, int K, int N,
                                      const int32_t* __restrict__ row_map, const int32_t* __restrict__ gather, int gather_k,
@@ -185,7 +188,7 @@ __device__ inline void ffn_few_block(const uint16_t* A, const int32_t* __restric
     }
     const int rows = at.rows;
     auto run = [&](auto rb) __attribute__((always_inline)) {
-        ffn_few_rows<GATED, SMALL, decltype(rb)::value, DIRECT>(A, at, e_first, W, expert_stride_bytes, block_offset_bytes, C, K, N,
+        ffn_few_rows<GATED, SMALL, DEEP, decltype(rb)::value, DIRECT>(A, at, e_first, W, expert_stride_bytes, block_offset_bytes, C, K, N,
                                                         row_map, gather, gather_k, h_rows, act);
     };
     if constexpr (SMALL) {
