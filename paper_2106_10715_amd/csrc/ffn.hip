@@ -883,8 +883,8 @@ bool ffn_reads_idx(const moe_cfg& c, int n_cu) {
 //   320         519     568     844     920    1272      949     1862     1975      3339      4440      5540     12145
 // Hence 320 up to two such tiles per expert, and beyond as many rows as give nearly all experts the same number of tiles of at most 288 rows: tiles of 19
 // and 20 blocks, with three steps of loads ahead instead of four, gain nothing where the matrix pipes are the bound.
-// With fewer items than compute units the tiles are cut lower until there are as many, as in the down-projection (1100 tokens on 4 experts, d 1024, f 4096 320 /
-// 192 rows 101.9 / 93.6 us; 4000 on 8, d 512, f 1024 66 / 59); and where the experts have several tiles, one more each if the items then take their rounds
+// With fewer items than compute units the tiles are cut as low as leaves no more items than those (1100 tokens on 4 experts, d 1024, f 4096 320 /
+// 160 rows 101.9 / 93.5 us; 4000 on 8, d 512, f 1024 66 / 59); and where the experts have several tiles, one more each if the items then take their rounds
 // in less time, by their blocks and 4 for what an item costs beside them (3000 tokens on 4 experts, d 2048, f 6144 285 -> 257; 6000 on 8 as above).
 int ffn_tile_rows(const moe_cfg& c, bool gather, int n_cu, int e_count, long max_rows) {
     if (few_rows(c, n_cu)) return kFewTileM;
@@ -899,7 +899,7 @@ int ffn_tile_rows(const moe_cfg& c, bool gather, int n_cu, int e_count, long max
         limit = rows_for(tiles);
     }
     if (columns * tiles < n_cu) {
-        const long per_expert = (n_cu + columns - 1) / columns, rows = ((mean_rows * 5 / 4 + per_expert - 1) / per_expert + 31) / 32 * 32;
+        const long rows = rows_for(n_cu / columns);
         return static_cast<int>(rows < kMinTileM ? kMinTileM : rows < limit ? rows : limit);
     }
     auto cost = [&](long n) { return (columns * n + n_cu - 1) / n_cu * (4 + ((mean_rows + n - 1) / n + 15) / 16); };
