@@ -884,23 +884,26 @@ bool ffn_reads_idx(const moe_cfg& c, int n_cu) {
 // Hence 320 up to two such tiles per expert, and beyond as many rows as give nearly all experts the same number of tiles of at most 288 rows: tiles of 19
 // and 20 blocks, with three steps of loads ahead instead of four, gain nothing where the matrix pipes are the bound.
 // With fewer items than compute units the tiles are cut as low as leaves no more items than those (1100 tokens on 4 experts, d 1024, f 4096 320 /
-// 160 rows 101.9 / 93.5 us; 4000 on 8, d 512, f 1024 66 / 59); and where the experts have several tiles, one more each if the items then take their rounds
+// 160 rows 101.9 / 93.5 us; 4000 on 8, d 512, f 1024 66 / 59; whole experts / cut, 400 on 4, d 512, f 1024 36.2 / 26.4, 820 on 4, d 1024, f 1024 64.5 / 50.4, 700 on
+// 4, d 768, f 3072 72.2 / 59.4, 1500 on 12, d 320, f 640 39.1 / 33.6, 300 on 4, d 1024, f 2048 53.9 / 47.9, but 1200 on 16, d 1024, f 512 49.8 / 53.0); and where the experts have several tiles, one more each if the items then take their rounds
 // in less time, by their blocks and 4 for what an item costs beside them (3000 tokens on 4 experts, d 2048, f 6144 285 -> 257; 6000 on 8 as above).
 int ffn_tile_rows(const moe_cfg& c, bool gather, int n_cu, int e_count, long max_rows) {
     if (few_rows(c, n_cu)) return kFewTileM;
-    if (gather) return kGatherTileM;
     const long mean_rows = max_rows / (e_count > 0 ? e_count : 1), columns = static_cast<long>(e_count) * ((c.f / 32 + 3) / 4);
-    if (mean_rows <= 224) return kTileM;
     const double most = mean_rows + 2.5 * sqrt(static_cast<double>(mean_rows));       // rows of nearly all experts, if the loads are even
     auto rows_for = [&](long n) { return (static_cast<long>(most / n) + 16) / 16 * 16; };
-    long limit = kTileM, tiles = (mean_rows + limit - 1) / limit;
+    long limit = gather ? kGatherTileM : kTileM, tiles = (mean_rows + limit - 1) / limit;
     if (tiles > 2) {
         tiles = static_cast<long>(most / 288) + 1;
         limit = rows_for(tiles);
     }
     if (columns * tiles < n_cu) {
-        const long rows = rows_for(n_cu / columns);
-        return static_cast<int>(rows < kMinTileM ? kMinTileM : rows < limit ? rows : limit);
+        long n = n_cu / columns;
+        // (tiles of fewer than 48 rows, whose steps take as long as theirs, only where the down-projection needs them as well)
+        const bool low = 8L * e_count * ((c.d / 32 + 3) / 4) <= 3L * n_cu;
+        while (n > 1 && (rows_for(n) < kMinTileM || (!low && mean_rows < 48 * n))) --n;
+        const long rows = rows_for(n) < kMinTileM ? kMinTileM : rows_for(n);
+        return static_cast<int>(rows < limit ? rows : limit);
     }
     auto cost = [&](long n) { return (columns * n + n_cu - 1) / n_cu * (4 + ((mean_rows + n - 1) / n + 15) / 16); };
     if (tiles > 1 && cost(tiles + 1) <= cost(tiles)) limit = rows_for(tiles + 1) < limit ? rows_for(tiles + 1) : limit;
