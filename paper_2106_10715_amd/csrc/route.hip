@@ -570,8 +570,12 @@ constexpr int gate_rows(int tok) { return tok > 32 ? tok : 32; }     // token ro
 // TOK: tokens of a block (64, 32, 16 or 8; with 8, the 16 rows of a matrix tile repeat them).  A short batch gets more,
 // smaller blocks: a block's time is mostly its own loads through one compute unit, and 128 blocks leave half the chip idle.
 // A long one gets fewer, larger ones: every block reads the whole gate from the L2, beside its own tokens.
-template <int NB, int TOK>
-__global__ __launch_bounds__(kGateWaves * 64, 2) void route_mfma_kernel(const uint16_t* __restrict__ x,
+// PAIRS: two blocks per compute unit, of 128 registers a thread, where there are that many: one ranks its tokens and decides the close ones while the other loads.
+// The gate fragments are then requested half a group ahead, the token pieces two groups.  us, one block / two (64 experts): 16384 tokens, d 4096 57.3 / 54.5, 32768
+// 95.7 / 88.2, 16384, d 2048 32.6 / 29.7, 20000, d 1024 34.6 / 25.0; with a block more per compute unit for some only, 10000, d 4096 44.1 / 45.8, 8192 28.6 /
+// 29.9; 32 experts, whose blocks of 64 tokens take less of the gate, 16384 42.4 / 44.5.
+template <int NB, int TOK, bool PAIRS = false>
+__global__ __launch_bounds__(kGateWaves * 64, PAIRS ? 4 : 2) void route_mfma_kernel(const uint16_t* __restrict__ x,
                                                          const uint4* __restrict__ pack, const float* __restrict__ part,
                                                          const float* __restrict__ bias, int32_t* __restrict__ idx,
                                                          float* __restrict__ w, int T, int d, int E, int k, int renorm,
@@ -629,6 +633,7 @@ __global__ __launch_bounds__(kGateWaves * 64, 2) void route_mfma_kernel(const ui
         return *reinterpret_cast<const uint4*>(reinterpret_cast<const char*>(pack) + (static_cast<size_t>(nb) * nS + S) * 4096 + 2048 * m + 256 * cb + w_lane);
     };
     struct XGroup { uint4 v[2][RB]; };
+    struct WHalf { uint4 v[NB][2]; };                      // of one k-step
     struct WGroup { uint4 v[NB][2][2]; };
     f32x4 acc[RB][NB][2];
     float xs[RB];
@@ -638,26 +643,29 @@ __global__ __launch_bounds__(kGateWaves * 64, 2) void route_mfma_kernel(const ui
 #pragma unroll
         for (int nb = 0; nb < NB; ++nb) acc[rb][nb][0] = acc[rb][nb][1] = f32x4{0.f, 0.f, 0.f, 0.f};
     }
+    // k-step m of a group; gate(nb, cb): the fragment of column half cb of block nb
+    auto multiply_step = [&](const XGroup& xg, int m, auto&& gate) __attribute__((always_inline)) {
+#pragma unroll
+        for (int rb = 0; rb < RB; ++rb) {
+            const uint4 piece = xg.v[m][rb];
+            const uint32_t u[4] = {piece.x, piece.y, piece.z, piece.w};
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+                const float lo = __uint_as_float(u[i] << 16), hi = __uint_as_float(u[i] & 0xffff0000u);
+                xs[rb] = fmaf(lo, lo, xs[rb]);
+                xs[rb] = fmaf(hi, hi, xs[rb]);
+            }
+#pragma unroll
+            for (int nb = 0; nb < NB; ++nb)
+#pragma unroll
+                for (int cb = 0; cb < 2; ++cb)
+                    acc[rb][nb][cb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, piece),
+                                                                              __builtin_bit_cast(bf16x8, gate(nb, cb)), acc[rb][nb][cb], 0, 0, 0);
+        }
+    };
     auto multiply = [&](const XGroup& xg, const WGroup& wg) __attribute__((always_inline)) {
 #pragma unroll
-        for (int m = 0; m < 2; ++m)
-#pragma unroll
-            for (int rb = 0; rb < RB; ++rb) {
-                const uint4 piece = xg.v[m][rb];
-                const uint32_t u[4] = {piece.x, piece.y, piece.z, piece.w};
-#pragma unroll
-                for (int i = 0; i < 4; ++i) {
-                    const float lo = __uint_as_float(u[i] << 16), hi = __uint_as_float(u[i] & 0xffff0000u);
-                    xs[rb] = fmaf(lo, lo, xs[rb]);
-                    xs[rb] = fmaf(hi, hi, xs[rb]);
-                }
-#pragma unroll
-                for (int nb = 0; nb < NB; ++nb)
-#pragma unroll
-                    for (int cb = 0; cb < 2; ++cb)
-                        acc[rb][nb][cb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, piece),
-                                                                                  __builtin_bit_cast(bf16x8, wg.v[nb][m][cb]), acc[rb][nb][cb], 0, 0, 0);
-            }
+        for (int m = 0; m < 2; ++m) multiply_step(xg, m, [&](int nb, int cb) __attribute__((always_inline)) { return wg.v[nb][m][cb]; });
     };
     auto load_x = [&](int S, XGroup& dst) __attribute__((always_inline)) {
 #pragma unroll
@@ -687,10 +695,9 @@ __global__ __launch_bounds__(kGateWaves * 64, 2) void route_mfma_kernel(const ui
         // The token pieces come from HBM: a ring of kXDepth groups is requested ahead, for as many groups as the registers
         // hold (at d_model 4096 a wave has eight).  The gate fragments, which every block re-reads from the L2, are requested
         // kWRing - 1 groups ahead, the first ones before the token pieces (loads return in order).
-        constexpr int kXDepth = TOK == 64 ? 2 : TOK == 32 && NB == 2 ? 4 : 8, kWRing = 2;
+        constexpr int kXDepth = PAIRS || TOK == 64 ? 2 : TOK == 32 && NB == 2 ? 4 : 8, kWRing = 2;
         const int n_mine = (nS - wave + kGateWaves - 1) / kGateWaves;      // this wave's groups (0 when d is short)
         XGroup xv[kXDepth];
-        WGroup wv[kWRing];
         // The odd waves take their groups from the middle on: with all waves of all blocks at the same place of rows that lie a
         // power of two apart, half of the memory channels would idle (8192 tokens, d 4096: 31.6 -> 25.2 us at 8 experts, 34.4 ->
         // 29.7 at 64).  The order depends on the wave only, so a logit has the same bits wherever its token lies in the batch.
@@ -708,26 +715,55 @@ __global__ __launch_bounds__(kGateWaves * 64, 2) void route_mfma_kernel(const ui
             load_w(group_of(i), dst);
             asm volatile("" : : : "memory");
         };
+        if constexpr (PAIRS) {
+            WHalf half[2];
+            auto fetch_half = [&](int i, int m, WHalf& dst) __attribute__((always_inline)) {
+                const int S = group_of(i);
 #pragma unroll
-        for (int p = 0; p + 1 < kWRing; ++p) fetch_w(p, wv[p]);
-        fetch_x(0, xv[0]);
-        if (TOK >= 32 || n_mine > 1) {               // (short batches: nothing to request ahead when d is short)
+                for (int nb = 0; nb < NB; ++nb)
 #pragma unroll
-            for (int p = 1; p < kXDepth; ++p) fetch_x(p, xv[p]);
-        }
-        norms_to_lds();
-        for (int i0 = 0; i0 < n_mine; i0 += kXDepth) {
-            auto groups = [&](auto more) __attribute__((always_inline)) {  // more: the ring is refilled behind the groups used
+                    for (int cb = 0; cb < 2; ++cb) dst.v[nb][cb] = w_piece(S, nb, m, cb);
+                asm volatile("" : : : "memory");
+            };
+            auto gate_of = [](const WHalf& h) __attribute__((always_inline)) { return [&h](int nb, int cb) __attribute__((always_inline)) { return h.v[nb][cb]; }; };
+            fetch_half(0, 0, half[0]);
+#pragma unroll
+            for (int p = 0; p < kXDepth; ++p) fetch_x(p, xv[p]);
+            norms_to_lds();
+            for (int i0 = 0; i0 < n_mine; i0 += kXDepth) {
 #pragma unroll
                 for (int p = 0; p < kXDepth; ++p) {
                     const int i = i0 + p;
-                    if ((p + kWRing - 1 < kXDepth && (TOK >= 32 || n_mine > 1)) || decltype(more)::value) fetch_w(i + kWRing - 1, wv[(p + kWRing - 1) % kWRing]);
-                    if (i < n_mine) multiply(xv[p], wv[p % kWRing]);       // uniform for the wave
-                    if (decltype(more)::value) fetch_x(i + kXDepth, xv[p]);
+                    fetch_half(i, 1, half[1]);
+                    if (i < n_mine) multiply_step(xv[p], 0, gate_of(half[0]));     // uniform for the wave
+                    fetch_half(i + 1, 0, half[0]);
+                    if (i < n_mine) multiply_step(xv[p], 1, gate_of(half[1]));
+                    fetch_x(i + kXDepth, xv[p]);
                 }
-            };
-            if (i0 + kXDepth < n_mine) groups(std::true_type{});
-            else groups(std::false_type{});
+            }
+        } else {
+            WGroup wv[kWRing];
+#pragma unroll
+            for (int p = 0; p + 1 < kWRing; ++p) fetch_w(p, wv[p]);
+            fetch_x(0, xv[0]);
+            if (TOK >= 32 || n_mine > 1) {               // (short batches: nothing to request ahead when d is short)
+#pragma unroll
+                for (int p = 1; p < kXDepth; ++p) fetch_x(p, xv[p]);
+            }
+            norms_to_lds();
+            for (int i0 = 0; i0 < n_mine; i0 += kXDepth) {
+                auto groups = [&](auto more) __attribute__((always_inline)) {  // more: the ring is refilled behind the groups used
+#pragma unroll
+                    for (int p = 0; p < kXDepth; ++p) {
+                        const int i = i0 + p;
+                        if ((p + kWRing - 1 < kXDepth && (TOK >= 32 || n_mine > 1)) || decltype(more)::value) fetch_w(i + kWRing - 1, wv[(p + kWRing - 1) % kWRing]);
+                        if (i < n_mine) multiply(xv[p], wv[p % kWRing]);       // uniform for the wave
+                        if (decltype(more)::value) fetch_x(i + kXDepth, xv[p]);
+                    }
+                };
+                if (i0 + kXDepth < n_mine) groups(std::true_type{});
+                else groups(std::false_type{});
+            }
         }
     } else {
         // more expert blocks: as many groups of token pieces at a time and gate fragments ahead as the registers hold
@@ -1253,12 +1289,16 @@ int launch_route(const moe_cfg& c, const void* x, const void* Wg, const float* b
         // as many tokens per block as still give every compute unit a block
         const int tok = NB == 1 && (c.T + 63) / 64 >= n_cu ? 64 : (c.T + 31) / 32 >= n_cu ? 32 : (c.T + 15) / 16 >= n_cu ? 16 : 8;
         dim3 grid((c.T + tok - 1) / tok), block(kGateWaves * 64);
-#define MOE_ROUTE_LAUNCH(N, TK)                                                                                       \
-    hipLaunchKernelGGL((route_mfma_kernel<N, TK>), grid, block, 0, s, static_cast<const uint16_t*>(x), pack, part, bias, idx,  \
+        // (close to two blocks for every compute unit, or more)
+        const bool pairs = NB == 2 && tok == 32 && 10L * grid.x >= 19L * n_cu;
+#define MOE_ROUTE_LAUNCH(N, TK) MOE_ROUTE_LAUNCH_AS((route_mfma_kernel<N, TK>))
+#define MOE_ROUTE_LAUNCH_AS(KERNEL)                                                                                   \
+    hipLaunchKernelGGL(KERNEL, grid, block, 0, s, static_cast<const uint16_t*>(x), pack, part, bias, idx,  \
                        w, c.T, c.d, cols, c.k, c.renorm, hash)
 #define MOE_ROUTE_CASE(N)                                                                                             \
     case N:                                                                                                           \
         if (tok == 64) MOE_ROUTE_LAUNCH(1, 64);                                                                       \
+        else if (pairs) MOE_ROUTE_LAUNCH_AS((route_mfma_kernel<2, 32, true>));                                        \
         else if (tok == 32) MOE_ROUTE_LAUNCH(N, 32);                                                                  \
         else if (tok == 16) MOE_ROUTE_LAUNCH(N, 16);                                                                  \
         else MOE_ROUTE_LAUNCH(N, 8);                                                                                  \
@@ -1269,6 +1309,7 @@ int launch_route(const moe_cfg& c, const void* x, const void* Wg, const float* b
             default: return fail(MOE_ERR_UNSUPPORTED, "E = %d is out of range", c.E);
         }
 #undef MOE_ROUTE_LAUNCH
+#undef MOE_ROUTE_LAUNCH_AS
 #undef MOE_ROUTE_CASE
         MOE_LAUNCH_CHECK("route_mfma_kernel");
         return MOE_OK;

@@ -656,3 +656,26 @@ def test_f32_gate_by_four_columns(T, d, E, k, renorm):
     bound = 2 * (d / 64 + 40) * 2.0 ** -24 * float(x.norm(dim=1).max() * W.norm(dim=0).max()) + 1e-6
     for _, w in out:
         assert ((w.double() - want).abs() <= bound * want).all()
+
+
+@pytest.mark.parametrize("T,d,E,k,renorm", [(15570, 64, 33, 1, 1), (15571, 192, 64, 2, 0), (16400, 1088, 40, 3, 1), (33000, 576, 50, 2, 0)])
+def test_gate_with_two_blocks_per_compute_unit(T, d, E, k, renorm):
+    """Long batches on 33 to 64 experts: the experts are those of 64-bit arithmetic (two columns tie in every token, so close ones are in every block), and
+    a token has the same weights, bit for bit, as in a short batch."""
+    x, W = _normal(T, d, seed=31).bfloat16(), (_normal(d, E, seed=32) * d ** -0.5).bfloat16()
+    W[:, E - 1] = W[:, E // 2]
+
+    def route(x):
+        n = x.shape[0]
+        cfg = M.MoeCfg.make(n, d, 64, E, k, "bf16", renorm)
+        idx, w = torch.full((n, k), -1, dtype=torch.int32, device="cuda"), torch.full((n, k), float("nan"), device="cuda")
+        M.moe_route(cfg, x, W, None, idx, w, torch.empty(M.moe_workspace_bytes(cfg), dtype=torch.uint8, device="cuda"))
+        torch.cuda.synchronize()
+        return idx, w
+    idx, w = route(x)
+    logits = x.double() @ W.double()
+    logits[:, E - 1] = logits[:, E // 2]             # (the same sum, whatever order the product above adds in)
+    assert torch.equal(idx.long(), logits.sort(dim=1, descending=True, stable=True).indices[:, :k])
+    for lo in (0, T // 2, T - 300):
+        short = route(x[lo:lo + 300].clone())
+        assert torch.equal(short[0], idx[lo:lo + 300]) and torch.equal(short[1], w[lo:lo + 300])
