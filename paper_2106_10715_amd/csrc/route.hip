@@ -510,10 +510,28 @@ __global__ __launch_bounds__(256) void gate_prep_kernel(const uint16_t* __restri
     }
 }
 
+// Where the gate kernel finds the gate: the packed fragments, or (RAW) W_g itself, whose 16-byte pieces it then puts together.
+template <bool RAW>
+struct Gate {
+    const void* gate;
+    int nS, E;
+    // the piece of rows 64 S + 32 h + 8 q .. + 8 of a column (0 beyond E)
+    __device__ __attribute__((always_inline)) uint4 piece(int col, int S, int q, int h) const {
+        if constexpr (!RAW) return static_cast<const uint4*>(gate)[((static_cast<size_t>(col >> 5) * nS + S) * 4 + q) * 64 + h * 32 + (col & 31)];
+        const uint16_t* from = static_cast<const uint16_t*>(gate) + static_cast<size_t>(64 * S + 32 * h + 8 * q) * E + min(col, E - 1);
+        uint32_t v[8];
+#pragma unroll
+        for (int j = 0; j < 8; ++j) v[j] = from[static_cast<size_t>(j) * E];
+        const uint32_t keep = col < E ? ~0u : 0u;
+        return uint4{(v[0] | v[1] << 16) & keep, (v[2] | v[3] << 16) & keep, (v[4] | v[5] << 16) & keep, (v[6] | v[7] << 16) & keep};
+    }
+};
+
 // Values of two columns of the projection of token t from exact products, by one wave, from the packed fragments: lane j
 // takes the 8-row pieces j, j + 64, ... of the columns; sums in twice the fp64 precision, the pairs (hi, lo) not yet normalised.
 // Every lane gets the sums.
-__device__ __attribute__((always_inline)) inline void exact_dots(const uint16_t* __restrict__ x, const uint4* __restrict__ pack, size_t t,
+template <bool RAW>
+__device__ __attribute__((always_inline)) inline void exact_dots(const uint16_t* __restrict__ x, const Gate<RAW>& gate, size_t t,
                                                      const int (&col)[2], int nS, int d, int lane, double (&hi)[2], double (&lo)[2]) {
     constexpr int U = 4;                   // pieces requested at once
     const uint4* xr = reinterpret_cast<const uint4*>(x + t * d);
@@ -529,7 +547,7 @@ __device__ __attribute__((always_inline)) inline void exact_dots(const uint16_t*
                 xq[u] = xr[S * 8 + h * 4 + q];
 #pragma unroll
                 for (int c = 0; c < 2; ++c)
-                    wq[u][c] = pack[((static_cast<size_t>(col[c] >> 5) * nS + S) * 4 + q) * 64 + h * 32 + (col[c] & 31)];
+                    wq[u][c] = gate.piece(col[c], S, q, h);
             }
         }
         asm volatile("" : : : "memory");
@@ -574,7 +592,10 @@ constexpr int gate_rows(int tok) { return tok > 32 ? tok : 32; }     // token ro
 // The gate fragments are then requested half a group ahead, the token pieces two groups.  us, one block / two (64 experts): 16384 tokens, d 4096 57.3 / 54.5, 32768
 // 95.7 / 88.2, 16384, d 2048 32.6 / 29.7, 20000, d 1024 34.6 / 25.0; with a block more per compute unit for some only, 10000, d 4096 44.1 / 45.8, 8192 28.6 /
 // 29.9; 32 experts, whose blocks of 64 tokens take less of the gate, 16384 42.4 / 44.5.
-template <int NB, int TOK, bool PAIRS = false>
+// RAW: `pack` is W_g itself, for a matrix that is not packed and of at most 512 rows, one group of 64 for each wave: its pieces are put together from single
+// values, all requested at once, and its column norms are added up on the way, in the order of gate_prep_kernel, whose launch that saves. us, packed by the call / RAW: 1025
+// tokens, d 320, 33 experts 11.0 / 8.3, 500, d 512, 64 10.5 / 7.8, 300, d 512, 8 10.7 / 8.0, 4000, d 512, 31 13.1 / 11.1, 2500, d 448, 64 13.2 / 12.2.
+template <int NB, int TOK, bool PAIRS = false, bool RAW = false>
 __global__ __launch_bounds__(kGateWaves * 64, PAIRS ? 4 : 2) void route_mfma_kernel(const uint16_t* __restrict__ x,
                                                          const uint4* __restrict__ pack, const float* __restrict__ part,
                                                          const float* __restrict__ bias, int32_t* __restrict__ idx,
@@ -601,6 +622,7 @@ __global__ __launch_bounds__(kGateWaves * 64, PAIRS ? 4 : 2) void route_mfma_ker
     const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(static_cast<int>(threadIdx.x >> 6));
     const int t0 = blockIdx.x * TOK;
     const int nS = d / 64;
+    const Gate<RAW> gate{pack, nS, E};
 
     // ---- column norms of W_g, for the error bound: thread (g, c) adds the per-group sums S = g, g + G, ... of column c; the
     // partial sums are added up where they are used, after the barrier that publishes the logits.  The first kNorm
@@ -609,7 +631,7 @@ __global__ __launch_bounds__(kGateWaves * 64, PAIRS ? 4 : 2) void route_mfma_ker
     const int norm_c = static_cast<int>(threadIdx.x) % EP, norm_g = static_cast<int>(threadIdx.x) / EP;
     float norm[kNorm];                     // (threads past the last whole group of columns, EP = 96 and others, hold unused sums)
 #pragma unroll
-    for (int i = 0; i < kNorm; ++i) {
+    for (int i = 0; i < kNorm && !RAW; ++i) {
         const int S = norm_g + i * G;
         norm[i] = part[static_cast<size_t>(S < nS ? S : 0) * EP + norm_c];
     }
@@ -630,6 +652,7 @@ __global__ __launch_bounds__(kGateWaves * 64, PAIRS ? 4 : 2) void route_mfma_ker
         return *reinterpret_cast<const uint4*>(reinterpret_cast<const char*>(x) + static_cast<size_t>(S) * 128 + 32 * m + x_lane[rb]);
     };
     auto w_piece = [&](int S, int nb, int m, int cb) __attribute__((always_inline)) {
+        if constexpr (RAW) return gate.piece(32 * nb + 16 * cb + c15, S, 2 * m + (g4 >> 1), g4 & 1);
         return *reinterpret_cast<const uint4*>(reinterpret_cast<const char*>(pack) + (static_cast<size_t>(nb) * nS + S) * 4096 + 2048 * m + 256 * cb + w_lane);
     };
     struct XGroup { uint4 v[2][RB]; };
@@ -681,6 +704,34 @@ __global__ __launch_bounds__(kGateWaves * 64, PAIRS ? 4 : 2) void route_mfma_ker
 #pragma unroll
                 for (int cb = 0; cb < 2; ++cb) dst.v[nb][m][cb] = w_piece(S, nb, m, cb);
     };
+    // RAW: the sums of squares of the wave's one group, the block's place for column c of wave w
+    auto norms_of_group = [&](const WGroup& wg, bool has) __attribute__((always_inline)) {
+        float mine = 0.f;
+#pragma unroll
+        for (int nb = 0; nb < NB; ++nb)
+#pragma unroll
+            for (int cb = 0; cb < 2; ++cb) {
+                float ss[2];                                   // rows 8 q .. of both halves, q = 2 m + g / 2
+#pragma unroll
+                for (int m = 0; m < 2; ++m) {
+                    const uint4 v = wg.v[nb][m][cb];
+                    const uint32_t u[4] = {v.x, v.y, v.z, v.w};
+                    ss[m] = 0.f;
+#pragma unroll
+                    for (int i = 0; i < 4; ++i) {
+                        const float lo = __uint_as_float(u[i] << 16), hi = __uint_as_float(u[i] & 0xffff0000u);
+                        ss[m] = fmaf(lo, lo, ss[m]);
+                        ss[m] = fmaf(hi, hi, ss[m]);
+                    }
+                    ss[m] += __shfl_xor(ss[m], 16);
+                }
+                const float other = __shfl_xor(ss[1], 32), q2 = g4 >> 1 ? other : ss[1], q3 = g4 >> 1 ? ss[1] : other;
+                const float total = ((ss[0] + __shfl_xor(ss[0], 32)) + q2) + q3;
+                if (EP == 64 ? (lane >> 5 == nb && ((lane >> 4) & 1) == cb) : lane >> 4 == cb) mine = total;
+            }
+        colpart[threadIdx.x] = has ? mine : 0.f;               // (32 columns: the wave's other 32 lanes add zeros)
+        if (threadIdx.x == 0) close_sh = many_sh = tied_sh = 0ull;
+    };
     auto norms_to_lds = [&]() __attribute__((always_inline)) {
         float ssum = 0.f;
 #pragma unroll
@@ -715,7 +766,14 @@ __global__ __launch_bounds__(kGateWaves * 64, PAIRS ? 4 : 2) void route_mfma_ker
             load_w(group_of(i), dst);
             asm volatile("" : : : "memory");
         };
-        if constexpr (PAIRS) {
+        if constexpr (RAW) {
+            static_assert(EP <= 64, "a column for each lane of a wave");
+            WGroup wg;
+            fetch_w(0, wg);
+            fetch_x(0, xv[0]);
+            norms_of_group(wg, n_mine > 0);
+            if (n_mine > 0) multiply(xv[0], wg);                           // uniform for the wave
+        } else if constexpr (PAIRS) {
             WHalf half[2];
             auto fetch_half = [&](int i, int m, WHalf& dst) __attribute__((always_inline)) {
                 const int S = group_of(i);
@@ -1005,7 +1063,7 @@ __global__ __launch_bounds__(kGateWaves * 64, PAIRS ? 4 : 2) void route_mfma_ker
                     uint4 wq[4];
 #pragma unroll
                     for (int c = 0; c < 4; ++c)
-                        wq[c] = pack[((static_cast<size_t>(col[c] >> 5) * nS + S) * 4 + q) * 64 + h * 32 + (col[c] & 31)];
+                        wq[c] = gate.piece(col[c], S, q, h);
 #pragma unroll
                     for (int c = 0; c < 4; ++c) {
                         const uint32_t wu[4] = {wq[c].x, wq[c].y, wq[c].z, wq[c].w};
@@ -1130,7 +1188,7 @@ __global__ __launch_bounds__(kGateWaves * 64, PAIRS ? 4 : 2) void route_mfma_ker
                 const int last = min(c + 1, cols2 - 1);
                 const int col[2] = {column(t2, c), column(t2, last)};
                 double hi[2], lo[2];
-                exact_dots(x, pack, static_cast<size_t>(t0 + t2), col, nS, d, lane, hi, lo);
+                exact_dots(x, gate, static_cast<size_t>(t0 + t2), col, nS, d, lane, hi, lo);
                 if (lane == 0) {
                     close_sum[n][0][c] = hi[0];
                     close_sum[n][1][c] = lo[0];
@@ -1168,10 +1226,9 @@ __global__ __launch_bounds__(kGateWaves * 64, PAIRS ? 4 : 2) void route_mfma_ker
                 for (int q = 0; q < 4; ++q) xa[q] = xr[S * 8 + q];
 #pragma unroll
                 for (int nb = 0; nb < NB; ++nb) {
-                    const uint4* bp = pack + ((static_cast<size_t>(nb) * nS + S) * 4) * 64 + lane;
                     uint4 wb[4];
 #pragma unroll
-                    for (int q = 0; q < 4; ++q) wb[q] = bp[q * 64];
+                    for (int q = 0; q < 4; ++q) wb[q] = gate.piece(32 * nb + (lane & 31), S, q, lane >> 5);
 #pragma unroll
                     for (int q = 0; q < 4; ++q) {
                         const uint32_t xu[4] = {xa[q].x, xa[q].y, xa[q].z, xa[q].w};
@@ -1275,19 +1332,21 @@ int launch_route(const moe_cfg& c, const void* x, const void* Wg, const float* b
     if (c.dtype == MOE_BF16) {
         const int NB = (cols + 31) / 32;
         const size_t EP = static_cast<size_t>(NB) * 32;
-        // a gate packed once by the caller (it is frozen: Section 2.3) is read where it lies; else it is packed
-        // into the workspace first, by every call
-        if (!c.gate_packed)
-            if (int rc = launch_pack_gate(c, Wg, scratch, s)) return rc;
-        const char* gate = static_cast<const char*>(c.gate_packed ? Wg : scratch);
-        const uint4* pack = reinterpret_cast<const uint4*>(gate);
-        const float* part = reinterpret_cast<const float*>(gate + align256(EP * c.d * 2));
         int dev = 0;
         const DeviceInfo* info = nullptr;
         if (int rc = device_info(&dev, &info)) return rc;
         const int n_cu = info->compute_units;
+        // a gate packed once by the caller (it is frozen: Section 2.3) is read where it lies; else it is packed
+        // into the workspace first, by every call
+        // (but for short reductions and batches, where the kernel is as well off with the matrix itself: RAW)
+        const bool raw = !c.gate_packed && NB <= 2 && c.d <= 64 * kGateWaves && (c.T + 15) / 16 < n_cu;
+        if (!c.gate_packed && !raw)
+            if (int rc = launch_pack_gate(c, Wg, scratch, s)) return rc;
+        const char* gate = static_cast<const char*>(c.gate_packed || raw ? Wg : scratch);
+        const uint4* pack = reinterpret_cast<const uint4*>(gate);
+        const float* part = reinterpret_cast<const float*>(gate + align256(EP * c.d * 2));
         // as many tokens per block as still give every compute unit a block
-        const int tok = NB == 1 && (c.T + 63) / 64 >= n_cu ? 64 : (c.T + 31) / 32 >= n_cu ? 32 : (c.T + 15) / 16 >= n_cu ? 16 : 8;
+        const int tok = raw ? 8 : NB == 1 && (c.T + 63) / 64 >= n_cu ? 64 : (c.T + 31) / 32 >= n_cu ? 32 : (c.T + 15) / 16 >= n_cu ? 16 : 8;
         dim3 grid((c.T + tok - 1) / tok), block(kGateWaves * 64);
         // (close to two blocks for every compute unit, or more)
         const bool pairs = NB == 2 && tok == 32 && 10L * grid.x >= 19L * n_cu;
@@ -1297,7 +1356,8 @@ int launch_route(const moe_cfg& c, const void* x, const void* Wg, const float* b
                        w, c.T, c.d, cols, c.k, c.renorm, hash)
 #define MOE_ROUTE_CASE(N)                                                                                             \
     case N:                                                                                                           \
-        if (tok == 64) MOE_ROUTE_LAUNCH(1, 64);                                                                       \
+        if (raw) MOE_ROUTE_LAUNCH_AS((route_mfma_kernel<(N <= 2 ? N : 1), 8, false, true>));                          \
+        else if (tok == 64) MOE_ROUTE_LAUNCH(1, 64);                                                                       \
         else if (pairs) MOE_ROUTE_LAUNCH_AS((route_mfma_kernel<2, 32, true>));                                        \
         else if (tok == 32) MOE_ROUTE_LAUNCH(N, 32);                                                                  \
         else if (tok == 16) MOE_ROUTE_LAUNCH(N, 16);                                                                  \

@@ -679,3 +679,28 @@ def test_gate_with_two_blocks_per_compute_unit(T, d, E, k, renorm):
     for lo in (0, T // 2, T - 300):
         short = route(x[lo:lo + 300].clone())
         assert torch.equal(short[0], idx[lo:lo + 300]) and torch.equal(short[1], w[lo:lo + 300])
+
+
+@pytest.mark.parametrize("T,d,E,k,renorm,gate", [(1, 64, 1, 1, 1, "topk"), (9, 512, 33, 2, 0, "topk"), (300, 448, 32, 1, 0, "topk"), (515, 320, 64, 3, 1, "topk"),
+                                                 (4080, 128, 31, 2, 0, "topk"), (77, 512, 64, 1, 1, "hash"), (40, 64, 16, 1, 1, "hash"), (33, 576, 40, 2, 0, "topk")])
+def test_gate_matrix_as_it_is(T, d, E, k, renorm, gate):
+    """A gate that the call reads as it is, 2 bytes off any boundary, against the same gate packed: the same experts and the same bits, ties and all columns in
+    reach included (d 576: the limit, packed by the call)."""
+    cols = E if gate == "topk" else E.bit_length() - 1
+    x, W = _normal(T, d, seed=41).bfloat16(), (_normal(d, cols, seed=42) * d ** -0.5).bfloat16()
+    W[:, cols - 1] = W[:, 0]
+    x[T // 2] = 0                                    # every column ties
+    shifted = torch.empty(d * cols + 1, dtype=torch.bfloat16, device="cuda")[1:].view(d, cols)
+    shifted.copy_(W)
+    cfg = M.MoeCfg.make(T, d, 64, E, k, "bf16", renorm, 0, M.GATE_HASH if gate == "hash" else M.GATE_TOPK)
+    block = torch.empty(M.moe_gate_bytes(cfg), dtype=torch.uint8, device="cuda")
+    M.moe_pack_gate(cfg, W, block)
+    ws = torch.empty(M.moe_workspace_bytes(cfg), dtype=torch.uint8, device="cuda")
+    out = []
+    for c, Wg in ((cfg, shifted), (cfg.with_packed_gate(True), block)):
+        idx, w = torch.full((T, k), -1, dtype=torch.int32, device="cuda"), torch.full((T, k), float("nan"), device="cuda")
+        M.moe_route(c, x, Wg, None, idx, w, ws)
+        torch.cuda.synchronize()
+        out.append((idx, w))
+    assert torch.equal(out[0][0], out[1][0]) and torch.equal(out[0][1], out[1][1])
+    assert out[0][0].min() >= 0 and out[0][0].max() < E and torch.isfinite(out[0][1]).all()
