@@ -882,7 +882,7 @@ bool ffn_reads_idx(const moe_cfg& c, int n_cu) {
 //   288         521     604     850    1006    1272      953     1932     2085      3440      4668      5361     12155
 //   320         519     568     844     920    1272      949     1862     1975      3339      4440      5540     12145
 // Hence 320 up to two such tiles per expert, and beyond as many rows as give nearly all experts the same number of tiles of at most 288 rows: tiles of 19
-// and 20 blocks, with three steps of loads ahead instead of four, gain nothing where the matrix pipes are the bound.
+// and 20 blocks, with two steps of loads ahead instead of three, gain nothing where the matrix pipes are the bound.
 // With fewer items than compute units the tiles are cut as low as leaves no more items than those (1100 tokens on 4 experts, d 1024, f 4096 320 /
 // 160 rows 101.9 / 93.5 us; 4000 on 8, d 512, f 1024 66 / 59; whole experts / cut, 400 on 4, d 512, f 1024 36.2 / 26.4, 820 on 4, d 1024, f 1024 64.5 / 50.4, 700 on
 // 4, d 768, f 3072 72.2 / 59.4, 1500 on 12, d 320, f 640 39.1 / 33.6, 300 on 4, d 1024, f 2048 53.9 / 47.9, but 1200 on 16, d 1024, f 512 49.8 / 53.0); and where the experts have several tiles, one more each if the items then take their rounds
