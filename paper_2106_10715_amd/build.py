@@ -162,6 +162,61 @@ def check_m0_free(asm: str, kernel_pattern: str, what: str = "assembly") -> int:
     return written
 
 
+_SUM = re.compile(r"v_mfma\S+ v\[(\d+):(\d+)\], ([^,]+), ([^,]+),")
+_SETTLE = 18                             # wait states after which the longest of these instructions has written its sum
+
+
+def check_sums_settle(asm: str, kernel_pattern: str, what: str = "assembly") -> int:
+    """The sums that do not fit the accumulation registers come from matrix instructions in inline assembly, whose latency the compiler
+    does not know.  Nothing but the same kind of instruction, as its sum, may touch such registers before _SETTLE wait states have passed
+    (an instruction is one, "s_nop N" N + 1), in layout order and at the targets of branches.  Raises on one; returns the number of those instructions."""
+    lines = asm.splitlines()
+    labels = {l.split(":")[0]: i for i, l in enumerate(lines) if l.startswith(".LBB")}
+    kernel, in_asm, found, now, written = None, False, 0, 0, {}
+
+    def step(n, text, at, sums):                       # the wait state after this line; sums: register -> when it was written
+        op = text.split()[0]
+        if op == "s_nop":
+            return at + int(text.split()[1], 0) + 1
+        got = _SUM.match(text)
+        used = _vregs(got[3] + "," + got[4]) if got else _vregs(text)
+        for reg in used:
+            if reg in sums and at - sums[reg] < _SETTLE:
+                raise RuntimeError(f"{what}: {kernel}: line {n + 1} ({text}) touches v{reg} {at - sums[reg]} wait states after a matrix instruction in assembly")
+        return at + 1
+
+    for n, line in enumerate(lines):
+        text = line.strip()
+        if line.startswith("_Z") and ":" in line:
+            name = line.split(":")[0]
+            kernel, written = (name if kernel_pattern in name else None), {}
+        elif text.startswith((".end_amdhsa_kernel", ".Lfunc_end")):
+            kernel = None
+        if text.startswith((";;#ASMSTART", ";;#ASMEND")):
+            in_asm = text.startswith(";;#ASMSTART")
+        code = text.split(";")[0].strip()
+        if kernel is None or not code or code.startswith(".") or code.endswith(":"):
+            continue
+        now = step(n, code, now, written)
+        got = _SUM.match(code)
+        if got and in_asm:
+            found += 1
+            written.update((reg, now) for reg in range(int(got[1]), int(got[2]) + 1))
+        elif code.startswith(("s_branch", "s_cbranch")):
+            fresh = {reg: at for reg, at in written.items() if now - at < _SETTLE}
+            at, m = now, labels.get(code.split()[-1], len(lines)) + 1
+            while fresh and m < len(lines) and at - now < _SETTLE and not lines[m].startswith("_Z"):
+                there = lines[m].strip().split(";")[0].strip()
+                if there and not there.startswith(".") and not there.endswith(":"):
+                    if there.startswith(("s_branch", "s_endpgm")):
+                        break
+                    at = step(m, there, at, fresh)
+                m += 1
+        if code.startswith(("s_branch", "s_endpgm", "s_setpc")):
+            written = {}                               # what follows in the file is not what follows in time
+    return found
+
+
 def check_prologue_in_flight(asm: str, kernel_pattern: str, what: str = "assembly") -> int:
     """The same rule for the code that leads up to each pipelined loop (from "; pipeline begin" to the loop's
     first block, in layout order, across block labels): the loads written as inline assembly are in flight from
@@ -234,6 +289,7 @@ def _check(src: str, part: int) -> None:
     check_no_spill(text, NO_SPILL[src], src)
     loops = check_loads_in_flight(text, NO_SPILL[src], src), check_prologue_in_flight(text, NO_SPILL[src], src)
     m0 = check_m0_free(text, NO_SPILL[src], src)
+    check_sums_settle(text, NO_SPILL[src], src)
     if part > 0 and (0 in loops or m0 == 0):
         raise RuntimeError(f"{src}: no pipelined loop, or no load into LDS, found to verify (markers missing?)")
 

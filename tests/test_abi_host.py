@@ -252,3 +252,17 @@ def test_build_refuses_m0_outside_of_the_loads_into_lds():
         with pytest.raises(RuntimeError, match="m0"):
             B.check_m0_free(kernel.format(use), "ffn_mfma")
     assert B.check_m0_free("_Zother:\n\ts_mov_b32 m0, s1\n.Lfunc_end0:\n", "ffn_mfma") == 0
+
+
+def test_build_refuses_sums_of_matrix_instructions_in_assembly_touched_early():
+    from paper_2106_10715_amd import build as B
+    mfma = "\t;;#ASMSTART\n\tv_mfma_f32_16x16x32_bf16 v[4:7], v[8:11], v[12:15], v[4:7]\n\t;;#ASMEND\n"
+    def kernel(*body):
+        return "_Zk_ffn_mfma: ; @k\n.LBB0_1:\n" + "".join(body) + "\ts_endpgm\n.Lfunc_end0:\n"
+    use, wait = "\tv_mov_b32_e32 v1, v6\n", "\ts_nop 15\n\ts_nop 15\n"
+    assert B.check_sums_settle(kernel(mfma, mfma, wait, use), "ffn_mfma") == 2          # the same sum again, and the use in time
+    for bad in (kernel(mfma, use), kernel(mfma, "\ts_nop 15\n", use), kernel(use, mfma, "\ts_cbranch_scc1 .LBB0_1\n"),
+                kernel(mfma, mfma.replace("v[4:7], v[8:11]", "v[20:23], v[4:7]").replace(", v[4:7]\n", ", v[20:23]\n"))):
+        with pytest.raises(RuntimeError, match="wait states"):
+            B.check_sums_settle(bad, "ffn_mfma")
+    assert B.check_sums_settle(kernel(mfma, use).replace("ffn_mfma", "other"), "ffn_mfma") == 0
