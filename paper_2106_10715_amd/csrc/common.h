@@ -5,6 +5,7 @@
 #include <stddef.h>
 #include <stdint.h>
 
+#include "ffn_tiles.h"
 #include "moe355.h"
 
 namespace moe {
@@ -42,8 +43,6 @@ inline bool aligned16(const void* p) { return (reinterpret_cast<uintptr_t>(p) & 
 
 // Assignments handled by one block of the histogram / scatter kernels of the permutation.
 constexpr int kPermChunk = 1024;
-// Most rows of one expert segment covered by one block of the FFN kernels.
-constexpr int kTileM = 320;
 
 // Byte offsets of every region inside the caller's workspace.
 struct WsLayout {
@@ -106,11 +105,6 @@ bool ffn_reads_idx(const moe_cfg& c, int n_cu);
 int launch_expert_ffn_f32(const moe_cfg& c, const float* Xp, const int32_t* offsets, int e_first, int e_count, const float* W,
                           size_t expert_stride_elems, long max_rows, float* H, float* Yp, hipStream_t s, hipEvent_t between,
                           const int32_t* row_map, const int32_t* gather, const int32_t* idx);
-// Rows of a bf16 row tile of the up-projection (and of the down-projection, unless ffn_down_tile_rows says less).
-int ffn_tile_rows(const moe_cfg& c, bool gather, int n_cu, int e_count, long max_rows);
-// Height of the down-projection's row tiles for a launch over e_count experts with at most max_rows rows in all (the two
-// kernels have a tile list each); n_cu: compute units of the device.
-int ffn_down_tile_rows(const moe_cfg& c, int e_count, long max_rows, int tile_m_up, int n_cu);
 // row_map: row r of the batched order is written to row row_map[r] of Yp instead of row r, which
 // turns the down-projection's output into the layer's output when no weighting follows (see moe_layer_forward).
 // `plan`: ffn_plan_bytes(c) bytes of workspace, rewritten by every launch_expert_ffn (room for ffn_plan_tiles(c) row tiles).

@@ -16,8 +16,6 @@
 
 namespace moe {
 
-constexpr int kFewTileM = 64;                        // rows of a tile: with more on one expert, its tiles run side by side
-
 // Steps of 64 reduction elements in flight, as the registers of 2 to 4 waves per SIMD allow.  SMALL (16 rows in all), steps of the
 // down-projection and waves: 8 and 3 / 7 and 4 / 6 and 4 measure 59.6 / 60.8 / 62.7 us for one token, 523 / 508 / 509 for 16.
 // DEEP, a down-projection with a wave per compute unit at most, which then has the unit's loads in flight to itself (one token: 14 KiB of the 44 that a unit

@@ -704,3 +704,43 @@ def test_gate_matrix_as_it_is(T, d, E, k, renorm, gate):
         out.append((idx, w))
     assert torch.equal(out[0][0], out[1][0]) and torch.equal(out[0][1], out[1][1])
     assert out[0][0].min() >= 0 and out[0][0].max() < E and torch.isfinite(out[0][1]).all()
+
+
+@pytest.mark.parametrize("T,E,d,f,crowd", [(2000, 16, 256, 10240, 700), (2000, 16, 256, 10240, 1500), (2500, 16, 64, 10240, 2449), (2560, 16, 1024, 4096, 2048)])
+@pytest.mark.parametrize("mode", ["ascending", "greedy", "kept"])
+def test_streamed_crowded_expert_equals_resident(T, E, d, f, crowd, mode):
+    """A layer of few rows per expert, whose streamed experts look their rows up in x, with most of them on one: every row has the bytes of the resident call."""
+    heavy = 5
+    want = torch.tensor([heavy] * crowd + [e for i in range(T) for e in [i % E] if e != heavy][:T - crowd], device="cuda")
+    g = torch.Generator(device="cuda")
+    g.manual_seed(T + crowd)
+    want = want[torch.randperm(T, generator=g, device="cuda")]
+    x = _normal(T, d, seed=51)
+    x[:, :E] = 4.0 * torch.nn.functional.one_hot(want, E)
+    x, Wg = x.bfloat16(), torch.eye(d, E, device="cuda").bfloat16()
+    cfg = M.MoeCfg.make(T, d, f, E, 1, "bf16")
+    packed = torch.empty((E, M.moe_expert_bytes(cfg)), dtype=torch.uint8, device="cuda")
+    for e in range(E):
+        M.moe_pack_weights(cfg, *((_normal(*s, seed=60 + 3 * e + i) * 0.05).bfloat16() for i, s in enumerate(((d, f), (d, f), (f, d)))), packed[e])
+    host = torch.empty(packed.shape, dtype=torch.uint8, pin_memory=True)
+    host.copy_(packed)
+
+    def run(ctx):
+        ws = torch.full((M.moe_workspace_bytes(cfg) // 2,), float("nan"), dtype=torch.bfloat16, device="cuda").view(torch.uint8)
+        y = torch.full((T, d), float("nan"), dtype=torch.bfloat16, device="cuda")
+        M.moe_layer_forward(cfg, x, Wg, None, None if ctx else packed, ctx, y, ws)
+        torch.cuda.synchronize()
+        return y
+    resident = run(None)
+    assert torch.isfinite(resident).all()
+    K = 4
+    ctx = M.StreamCtx(cfg, host, torch.empty((K, packed.shape[1]), dtype=torch.uint8, device="cuda"), K)
+    if mode == "greedy":
+        ctx.set_order(M.ORDER_GREEDY, 100.0, 2)
+    if mode == "kept":
+        ctx.keep_experts(True)
+    for _ in range(2):
+        y = run(ctx)
+        wrong = (y.view(torch.int16) != resident.view(torch.int16)).any(1).sum().item()
+        assert wrong == 0, f"{wrong} rows differ"
+    ctx.close()
