@@ -387,29 +387,28 @@ int layer_forward(const moe_cfg* cfg, const void* x, const void* W_g, const floa
     if (int rc = launch_route(c, x, W_g, gate_bias, idx, w, base + L.route, s)) return rc;
     if (all_stages) MOE_HIP_CHECK(hipEventRecord(tev[1], s));
     bool planned = false;          // resident mode: the work list of the one FFN launch may come from the batching kernel
-    int plan_rows = kTileM, plan_rows_down = kTileM;      // (resident mode) the tile heights of the launch over all experts
+    FfnTiles tiles{kTileM, kTileM, false};                // (resident mode) how the launch over all experts is cut
     bool reads_idx = false;        // (resident mode) the expert kernels look through the assignments themselves: nothing is batched
     if (sctx == nullptr) {
         int dev = 0;
         const DeviceInfo* info = nullptr;
         if (int rc = device_info(&dev, &info)) return rc;
         reads_idx = ffn_reads_idx(c, info->compute_units);
-        plan_rows = ffn_tile_rows(c, gather_rows, info->compute_units, c.E, A);
-        plan_rows_down = ffn_down_tile_rows(c, c.E, A, plan_rows, info->compute_units);
+        if (c.dtype == MOE_BF16) tiles = ffn_tiles(c, gather_rows, info->compute_units, c.E, A);
     }
     if (!reads_idx)
         if (int rc = launch_permute(c, x, idx, counts, offsets, perm, inv, gather_rows ? nullptr : base + L.Xp,
                                     reinterpret_cast<int32_t*>(base + L.chunk_hist), s,
                                     sctx == nullptr ? reinterpret_cast<int32_t*>(base + L.ffn_plan) : nullptr,
                                     static_cast<int>(ffn_plan_tiles(c)), sctx == nullptr ? &planned : nullptr,
-                                    plan_rows, plan_rows_down))
+                                    tiles.up, tiles.down))
             return rc;
     if (all_stages) MOE_HIP_CHECK(hipEventRecord(tev[2], s));
 
     if (sctx == nullptr) {
         if (int rc = launch_expert_ffn(c, reads_idx ? x : ffn_in, offsets, 0, c.E, W_packed, eb, A, base + L.H, ffn_out,
                                        reinterpret_cast<int32_t*>(base + L.ffn_plan), s, tev ? tev[3] : nullptr,
-                                       tev && up_only ? tev[2] : nullptr, reads_idx ? nullptr : row_map, planned,
+                                       tev && up_only ? tev[2] : nullptr, reads_idx ? nullptr : row_map, planned ? &tiles : nullptr,
                                        reads_idx ? nullptr : gather, reads_idx ? idx : nullptr))
             return rc;
         if (all_stages) MOE_HIP_CHECK(hipEventRecord(tev[4], s));
@@ -453,7 +452,7 @@ int layer_forward(const moe_cfg* cfg, const void* x, const void* W_g, const floa
             // one launch over all experts instead of one per expert.
             for (int pos = 0; pos < n_order; ++pos) MOE_HIP_CHECK(hipStreamWaitEvent(s, sctx->loaded[slot_of[pos]], 0));
             if (int rc = launch_expert_ffn(c, ffn_in, offsets, 0, c.E, sctx->dev_slots, eb, A, base + L.H, ffn_out,
-                                           reinterpret_cast<int32_t*>(base + L.ffn_plan), s, nullptr, nullptr, row_map, false, gather))
+                                           reinterpret_cast<int32_t*>(base + L.ffn_plan), s, nullptr, nullptr, row_map, nullptr, gather))
                 return rc;
             for (int pos = 0; pos < n_order; ++pos)
                 if (int rc = record_release(sctx, slot_of[pos], s)) return rc;
@@ -475,7 +474,7 @@ int layer_forward(const moe_cfg* cfg, const void* x, const void* W_g, const floa
             }
             MOE_HIP_CHECK(hipStreamWaitEvent(s, sctx->loaded[slot], 0));   // also when kept: its load may still be running
             if (int rc = launch_expert_ffn(c, ffn_in, offsets, e, 1, dst, eb, n_e, base + L.H, ffn_out,
-                                           reinterpret_cast<int32_t*>(base + L.ffn_plan), s, nullptr, nullptr, row_map, false, gather))
+                                           reinterpret_cast<int32_t*>(base + L.ffn_plan), s, nullptr, nullptr, row_map, nullptr, gather))
                 return rc;
             if (int rc = record_release(sctx, slot, s)) return rc;
         }

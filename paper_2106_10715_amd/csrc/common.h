@@ -78,7 +78,7 @@ int launch_permute(const moe_cfg& c, const void* x, const int32_t* idx, int32_t*
                    int plan_tile_rows_down = kTileM);
 // plan/planned: for short bf16 batches the kernel that batches the tokens also writes the work list of the expert
 // FFN launch over all experts that follows (room for plan_max_tiles row tiles) and sets *planned; the caller then
-// passes plan_ready to launch_expert_ffn.
+// tells launch_expert_ffn.
 // The same with the chunk histograms in a fixed array of the library instead of the caller's workspace (at most
 // permute_static_max_assignments() assignments); never writes a work list.
 int launch_permute_static(const moe_cfg& c, const void* x, const int32_t* idx, int32_t* counts, int32_t* offsets,
@@ -93,11 +93,11 @@ int launch_pack(const moe_cfg& c, const void* Win, const void* Wgate, const void
 int launch_expert_ffn(const moe_cfg& c, const void* Xp, const int32_t* offsets, int e_first, int e_count,
                       const void* W, size_t expert_stride_bytes, long max_rows, void* H, void* Yp, int32_t* plan,
                       hipStream_t s, hipEvent_t between = nullptr, hipEvent_t before_up = nullptr,
-                      const int32_t* row_map = nullptr, bool plan_ready = false, const int32_t* gather = nullptr,
+                      const int32_t* row_map = nullptr, const FfnTiles* listed = nullptr, const int32_t* gather = nullptr,
                       const int32_t* idx = nullptr);
 // gather: Xp is then the token array x[T, d] itself and batched row r is its row gather[r] / k (gather = the
-// perm written by the batching step), so the batched copy of the activations need not exist.  A bf16 work list written elsewhere (plan_ready) must
-// have been cut to tiles of ffn_tile_rows(c, gather != NULL, n_cu, e_count, max_rows) rows.
+// perm written by the batching step), so the batched copy of the activations need not exist.
+// listed: how the bf16 work list of this launch is cut that has been written already, by ffn_tiles(c, gather != NULL, n_cu, e_count, max_rows); NULL: it has not.
 // idx (whole layer of at most kDirectRows assignments, ffn_reads_idx): nothing has batched the assignments; Xp is x, offsets, plan, row_map
 // and gather are not read, and the kernels find an expert's rows in idx [T, k] themselves.  Row a of H and Yp is then assignment a.
 constexpr int kDirectRows = 64;

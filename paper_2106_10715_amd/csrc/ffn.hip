@@ -874,7 +874,7 @@ int launch_pack(const moe_cfg& c, const void* Win, const void* Wgate, const void
 
 int launch_expert_ffn(const moe_cfg& c, const void* Xp, const int32_t* offsets, int e_first, int e_count,
                       const void* W, size_t expert_stride_bytes, long max_rows, void* H, void* Yp, int32_t* plan,
-                      hipStream_t s, hipEvent_t between, hipEvent_t before_up, const int32_t* row_map, bool plan_ready,
+                      hipStream_t s, hipEvent_t between, hipEvent_t before_up, const int32_t* row_map, const FfnTiles* listed,
                       const int32_t* gather, const int32_t* idx) {
     if (max_rows <= 0 || e_count <= 0) return MOE_OK;
     const size_t df = static_cast<size_t>(c.d) * c.f;
@@ -885,8 +885,8 @@ int launch_expert_ffn(const moe_cfg& c, const void* Xp, const int32_t* offsets, 
         const DeviceInfo* info = nullptr;
         if (int rc = device_info(&dev, &info)) return rc;
         const int n_cu = info->compute_units;
-        const int tile_m = ffn_tile_rows(c, gather != nullptr, n_cu, e_count, max_rows);
-        const int tile_m_down = ffn_down_tile_rows(c, e_count, max_rows, tile_m, n_cu);
+        const FfnTiles cut = listed != nullptr ? *listed : ffn_tiles(c, gather != nullptr, n_cu, e_count, max_rows);
+        const int tile_m = cut.up, tile_m_down = cut.down;
         if (tile_m > (gather != nullptr ? kGatherTileM : kTileM) || tile_m_down > kTileM)       // rows past those the kernel has code for would be left out
             return fail(MOE_ERR_INVALID_ARG, "row tiles of %d and %d rows are too high for the expert kernels", tile_m, tile_m_down);
         const long slots = max_rows / tile_m + e_count;                // upper bound of the number of row tiles
@@ -920,7 +920,7 @@ int launch_expert_ffn(const moe_cfg& c, const void* Xp, const int32_t* offsets, 
         };
         const int max_tiles = static_cast<int>(ffn_plan_tiles(c));
         const int down_list = tile_m_down != tile_m ? 1 : 0;       // equal heights: one list serves both kernels
-        if (!plan_ready && idx == nullptr) {          // else the kernel that batched the tokens has written the work list as well
+        if (listed == nullptr && idx == nullptr) {          // else the kernel that batched the tokens has written the work list as well
             hipLaunchKernelGGL(ffn_plan_kernel, dim3(1), dim3(256), 0, s, offsets, e_first, e_count, tile_m, tile_m_down, plan,
                                c.T * c.k, max_tiles);
             MOE_LAUNCH_CHECK("ffn_plan_kernel");
@@ -971,19 +971,12 @@ int launch_expert_ffn(const moe_cfg& c, const void* Xp, const int32_t* offsets, 
         else launch_ffn_up(up, s);
         MOE_LAUNCH_CHECK("ffn_mfma_kernel<up>");
         if (between != nullptr) MOE_HIP_CHECK(hipEventRecord(between, s));
-        // down-projection: narrow (32-column) units when wide ones would leave compute units idle
-        const long tiles_hint = (max_rows + tile_m - 1) / tile_m > e_count ? (max_rows + tile_m - 1) / tile_m : e_count;
-        // (only while the experts are likely to have a single tile each, mean rows up to 224, and their items are
-        // bound by the weight stream: on 256-row tiles, and once experts spill into second tiles, the narrow unit's
-        // second LDS read per MFMA costs more than the idle compute units do; measured on 8 experts: 128 rows per
-        // expert 0.148 ms narrow against 0.177 ms wide, 256 rows 0.274 against 0.239)
-        const bool narrow = tiles_hint * ((c.d / 64 + 3) / 4) < 2 * 256 && mean_rows <= 224;
         FfnLaunch down{H, plan, 8, e_first, W, expert_stride_bytes, down_off, Yp, c.f, c.d, c.act, 0, 0, mt_shift_down, row_map, nullptr,
                        1, c.T * c.k, down_list, max_tiles, 0};
-        items = items_for(slots_down, mt_shift_down, ((narrow ? c.d / 32 : c.d / 64) + 3) / 4, down.y_shift, down.y_chunks);
+        items = items_for(slots_down, mt_shift_down, ((cut.narrow ? c.d / 32 : c.d / 64) + 3) / 4, down.y_shift, down.y_chunks);
         if (items > 0x7fffffffL) return fail(MOE_ERR_UNSUPPORTED, "too many work items for one launch (%ld)", items);
         down.grid = static_cast<unsigned>(items < n_cu ? items : n_cu);
-        if (narrow) launch_ffn_down_narrow(down, s);
+        if (cut.narrow) launch_ffn_down_narrow(down, s);
         else launch_ffn_down(down, s);
         MOE_LAUNCH_CHECK("ffn_mfma_kernel<down>");
         return MOE_OK;

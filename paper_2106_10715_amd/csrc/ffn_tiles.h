@@ -8,7 +8,6 @@ namespace moe {
 
 // Most rows of one expert segment covered by one block of the large FFN kernels.
 constexpr int kTileM = 320;
-constexpr int kEvenTileM = 288;         // most rows of one where the experts have more than two
 // Rows of a tile when the up-projection gathers its rows itself: a thread then holds one source offset per
 // 32-row block, which the registers allow up to seven blocks (eight accumulator blocks leave no room).
 constexpr int kGatherTileM = 224;
@@ -33,60 +32,116 @@ inline bool few_rows(const moe_cfg& c, int n_cu) {
     return rows <= (3 * items < n_cu ? 32L : items <= n_cu ? 8L : 2L) * c.E;
 }
 
-// Highest row tile of the up-projection.  A tile of 17 or 18 blocks of 16 rows costs less than two of 9, which read the weights twice and need 1.5
-// times the bytes per product, and experts that all have as many tiles keep the rounds of the compute units even; so what matters is where the limit lies
-// against the mean and its spread.  Layer us by limit (d 4096, f 10240; tokens / experts):
+// How a launch of the large kernels over e_count experts with max_rows rows in all is cut.
+struct FfnTiles {
+    int up, down;       // most rows of a tile of the two projections (a work list each, unless equal)
+    bool narrow;        // units of 32 columns in the down-projection instead of 64
+};
+
+// Blocks of 16 rows of the experts of a launch, as far as they are known before the loads are: an eighth of the experts each and the largest one, if the loads are
+// less, or more, uneven than those of a random gate, whose columns differ in length by 1 / sqrt(2 d).
+constexpr int kShares = 9;
+struct ExpertBlocks {
+    int blocks[2][kShares];
+    double experts[kShares];
+    ExpertBlocks(double mean, int e_count, int d) {
+        const double log_e = log(static_cast<double>(e_count)), skew = 0.9 * mean * log_e;
+        const double spread = e_count > 1 ? sqrt(mean + skew * skew / d) : 0;          // (the rows of a single expert are known)
+        // of the normal distribution, at the middle of every share and of the last of e_count
+        const double at[kShares] = {-1.534, -0.887, -0.489, -0.157, 0.157, 0.489, 0.887, 1.534, 1.48 * sqrt(log_e) - 0.6};
+        for (int i = 0; i < kShares; ++i) {
+            experts[i] = i < 8 ? (e_count - 1) / 8.0 : 1;
+            for (int s = 0; s < 2; ++s) {
+                const double rows = mean + (s == 0 ? 0.6 : 1.4) * spread * at[i];
+                blocks[s][i] = rows < 1 ? 1 : static_cast<int>((static_cast<long>(rows) + 15) / 16);
+            }
+        }
+    }
+};
+
+// A product's work items are its row tiles by its `columns` groups of four column units.  This is the time of all of them on n_cu compute units, in that of a
+// block of 16 rows: an item takes its blocks and per_item (half a block more above 18, with two steps of loads ahead instead of three), and the
+// whole lies half-way between every round as long as its longest item and all items spread evenly (a round that is not full is faster, and
+// short items make up for long ones).
+inline double ffn_cost(const ExpertBlocks& of, int columns, double per_item, int tile_rows, int n_cu) {
+    const int most = tile_rows / 16;
+    double total = 0;
+    for (int s = 0; s < 2; ++s) {
+        double of_height[kTileM / 16 + 1] = {};
+        for (int i = 0; i < kShares; ++i) {
+            const int n = of.blocks[s][i], tiles = (n + most - 1) / most, each = n / tiles, more = n - each * tiles;
+            auto height = [](int b) { return b < 2 ? 2 : b == 3 ? 4 : b; };            // (those the kernels have code for)
+            if (more > 0) of_height[height(each + 1)] += more * columns * of.experts[i];
+            of_height[height(each)] += (tiles - more) * columns * of.experts[i];
+        }
+        double items = 0;
+        int begun = 0;
+        for (int b = kTileM / 16; b > 0; --b) {
+            if (of_height[b] == 0) continue;
+            items += of_height[b];
+            const int rounds = items > 0.5 ? static_cast<int>((items - 0.5) / n_cu) + 1 : 0;        // (a fraction of an item begins none)
+            total += (rounds - begun + of_height[b] / n_cu) * (per_item + b + (b > 18 ? 0.5 : 0));
+            begun = rounds;
+        }
+    }
+    return total;
+}
+
+// The height of a product's tiles: `before` (256 rows, 224 where the up-projection gathers, lower ones for a down-projection of few items), unless a multiple of 32
+// rows is better by 4 % of a round and 1 % of the whole.  What matters is how the items divide into rounds of the compute units, how often the weights
+// are read and how long the steps of low tiles are: a tile of 17 or 18 blocks costs less than two of 9, and small layers need low tiles to have an item for
+// every unit.  Time against that with `before`, layers of one to three random gates each, d 128 to 4096, f 192 to 10240, 4 to 64 experts, 48 to 1400 rows
+// per expert: 0.939 in the mean of 1200, 44 of them more than 2 % slower (the loads are not known), 0.936 and 48 of 994 others, and 0.961 and 2 of 192 of
+// up to 4100 rows.  (Low tiles wherever items leave units idle, else 320 rows up to two tiles and even ones of 288 beyond: 0.966 and 163, 0.961 and 123,
+// 0.983 and 16, the worst 1.47.)  Layer us by limit, d 4096, f 10240 (tokens / experts):
 //            2048/8  2300/8  4096/8  4500/8  6000/8  4300/16  8192/32  9000/32  16384/32  20000/64  28000/32  65536/32
 //   160         552     591     978    1004    1385     1096     2133     2197      3665      5116      6056     13055
 //   224         549     593     977    1037    1201     1089     2143     2194      3558      4644      5541     12561
 //   256         540     590     952    1035    1270     1156     2086     2268      3441      4643      5347     12486
 //   288         521     604     850    1006    1272      953     1932     2085      3440      4668      5361     12155
 //   320         519     568     844     920    1272      949     1862     1975      3339      4440      5540     12145
-// Hence 320 up to two such tiles per expert, and beyond as many rows as give nearly all experts the same number of tiles of at most 288 rows: tiles of 19
-// and 20 blocks, with two steps of loads ahead instead of three, gain nothing where the matrix pipes are the bound.
-// With fewer items than compute units the tiles are cut as low as leaves no more items than those (1100 tokens on 4 experts, d 1024, f 4096 320 /
-// 160 rows 101.9 / 93.5 us; 4000 on 8, d 512, f 1024 66 / 59; whole experts / cut, 400 on 4, d 512, f 1024 36.2 / 26.4, 820 on 4, d 1024, f 1024 64.5 / 50.4, 700 on
-// 4, d 768, f 3072 72.2 / 59.4, 1500 on 12, d 320, f 640 39.1 / 33.6, 300 on 4, d 1024, f 2048 53.9 / 47.9, but 1200 on 16, d 1024, f 512 49.8 / 53.0); and where the experts have several tiles, one more each if the items then take their rounds
-// in less time, by their blocks and 4 for what an item costs beside them (3000 tokens on 4 experts, d 2048, f 6144 285 -> 257; 6000 on 8 as above).
-inline int ffn_tile_rows(const moe_cfg& c, bool gather, int n_cu, int e_count, long max_rows) {
-    if (few_rows(c, n_cu)) return kFewTileM;
-    const long mean_rows = max_rows / (e_count > 0 ? e_count : 1), columns = static_cast<long>(e_count) * ((c.f / 32 + 3) / 4);
-    const double most = mean_rows + 2.5 * sqrt(static_cast<double>(mean_rows));       // rows of nearly all experts, if the loads are even
-    auto rows_for = [&](long n) { return (static_cast<long>(most / n) + 16) / 16 * 16; };
-    // (the kernel that gathers has code for tiles up to its own limit: nothing below may go over it)
-    const long even = gather ? kGatherTileM : kEvenTileM;
-    long limit = gather ? kGatherTileM : kTileM, tiles = (mean_rows + limit - 1) / limit;
-    if (tiles > 2) {
-        tiles = static_cast<long>(most / even) + 1;
-        limit = rows_for(tiles);
+inline int ffn_tile_rows(const ExpertBlocks& of, double rounds, int columns, int reduction, int before, int most, int n_cu) {
+    const double per_item = 4 + 960.0 / reduction;
+    int best = before;
+    double least = ffn_cost(of, columns, per_item, before, n_cu) * (rounds > 4 ? 0.99 : rounds > 1 ? 1 - 0.04 / rounds : 0.96);
+    for (int rows = most / 32 * 32; rows >= kMinTileM; rows -= 32) {
+        const double cost = ffn_cost(of, columns, per_item, rows, n_cu);
+        if (cost < least) {
+            least = cost;
+            best = rows;
+        }
     }
-    if (columns * tiles < n_cu) {
-        long n = n_cu / columns;
-        // (tiles of fewer than 48 rows, whose steps take as long as theirs, only where the down-projection needs them as well)
-        const bool low = 8L * e_count * ((c.d / 32 + 3) / 4) <= 3L * n_cu;
-        while (n > 1 && (rows_for(n) < kMinTileM || (!low && mean_rows < 48 * n))) --n;
-        const long rows = rows_for(n) < kMinTileM ? kMinTileM : rows_for(n);
-        return static_cast<int>(rows < limit ? rows : limit);
-    }
-    auto cost = [&](long n) { return (columns * n + n_cu - 1) / n_cu * (4 + ((mean_rows + n - 1) / n + 15) / 16); };
-    if (tiles > 1 && cost(tiles + 1) <= cost(tiles)) limit = rows_for(tiles + 1) < limit ? rows_for(tiles + 1) : limit;
-    return static_cast<int>(limit);
+    return best;
 }
 
-// Height of the down-projection's row tiles.  Its work items are (row tile x 256 output columns): with few experts of
-// a tile or so each there are fewer items than compute units (8 experts of about 256 rows: 8 to 16 tiles x 16 column
-// groups for 256 compute units, and a tile takes as long as its 160 reduction steps whether others run or not).  The
-// tiles are then cut lower, so that every expert gives as many tiles as fill the chip (with a quarter of headroom for
-// experts above the mean); measured on that layer: 0.235 -> 0.184 ms.  Lower tiles for the up-projection, which has
-// five times the column groups, only cost (0.327 -> 0.354 ms), so the two kernels have a tile list each.
-inline int ffn_down_tile_rows(const moe_cfg& c, int e_count, long max_rows, int tile_m_up, int n_cu) {
-    const long mean_rows = max_rows / (e_count > 0 ? e_count : 1);
-    const int col_groups = (c.d / 64 + 3) / 4;
-    if (mean_rows <= 224 || static_cast<long>(e_count) * col_groups >= n_cu) return tile_m_up;
-    const long per_expert = (n_cu + static_cast<long>(e_count) * col_groups - 1) / (static_cast<long>(e_count) * col_groups);
-    long tm = ((mean_rows * 5 / 4 + per_expert - 1) / per_expert + 31) / 32 * 32;
-    tm = tm < kMinTileM ? kMinTileM : tm;
-    return tm < tile_m_up ? static_cast<int>(tm) : tile_m_up;
+inline FfnTiles ffn_tiles(const moe_cfg& c, bool gather, int n_cu, int e_count, long max_rows) {
+    if (few_rows(c, n_cu)) return {kFewTileM, kFewTileM, false};
+    const long mean_rows = max_rows / e_count;
+    const double mean = static_cast<double>(max_rows) / e_count, tiles = e_count * (mean > 256 ? mean / 256 : 1);
+    const ExpertBlocks of(mean, e_count, c.d);
+    FfnTiles t;
+    // (nothing may go over what the kernel has code for: the one that gathers has less)
+    const int up_columns = (c.f / 32 + 3) / 4, wide = (c.d / 64 + 3) / 4;
+    t.up = ffn_tile_rows(of, tiles * up_columns / n_cu, up_columns, c.d, gather ? kGatherTileM : 256, gather ? kGatherTileM : kTileM, n_cu);
+    // Narrow units while the experts are likely to have a single tile each, mean rows up to 224, and their items are
+    // bound by the weight stream: on 256-row tiles, and once experts spill into second tiles, the narrow unit's
+    // second LDS read per MFMA costs more than the idle compute units do; measured on 8 experts: 128 rows per
+    // expert 0.148 ms narrow against 0.177 ms wide, 256 rows 0.274 against 0.239.
+    const long tiles_hint = (max_rows + t.up - 1) / t.up > e_count ? (max_rows + t.up - 1) / t.up : e_count;
+    t.narrow = tiles_hint * wide < 2 * 256 && mean_rows <= 224;
+    // Wide units: with few experts of a tile or so each there are fewer items than compute units (8 experts of about 256 rows: 8 to 16 tiles x 16 column
+    // groups for 256 compute units, and a tile takes as long as its 160 reduction steps whether others run or not).  The
+    // tiles are then cut lower, so that every expert gives as many tiles as fill the chip (with a quarter of headroom for
+    // experts above the mean); measured on that layer: 0.235 -> 0.184 ms.
+    long rows = gather ? kGatherTileM : 256;
+    if (mean_rows > 224 && static_cast<long>(e_count) * wide < n_cu) {
+        const long per_expert = (n_cu + static_cast<long>(e_count) * wide - 1) / (static_cast<long>(e_count) * wide);
+        const long fill = ((mean_rows * 5 / 4 + per_expert - 1) / per_expert + 31) / 32 * 32;
+        rows = fill < kMinTileM ? kMinTileM : fill < rows ? fill : rows;
+    }
+    const int columns = t.narrow ? (c.d / 32 + 3) / 4 : wide;
+    t.down = ffn_tile_rows(of, tiles * columns / n_cu, columns, c.f, static_cast<int>(rows), kTileM, n_cu);
+    return t;
 }
 
 }  // namespace moe
