@@ -210,7 +210,7 @@ __device__ __attribute__((always_inline)) inline void rank_f32(const float (&fv)
 // TPW: tokens per wave (they share the W_g loads); NE: experts per lane at most.  The kernel is bound by the latency of
 // its loads: kUnroll terms are requested at a time (one memory latency for all of them), and a batch too short to give
 // every compute unit several waves is handled one token per wave.
-// QUADS (fp32, a multiple of four columns, rows of W_g at 16-byte boundaries): a lane takes four columns and four neighbouring terms at a time, 5 loads of 16 bytes
+// QUADS (fp32, a multiple of four columns; not by the address of W_g, so that equal matrices give equal weights wherever they lie): a lane takes four columns and four neighbouring terms at a time, 5 loads of 16 bytes
 // for 16 products instead of 32 of 4, and at d 1024 and 8 experts everything at once instead of in four batches.  us, single terms / quads: 512 tokens, d 1024, 8
 // experts 19.7 / 11.9, 16 tokens 11.5 / 8.2, 1000 tokens, d 640 16.8 / 11.1, 1024, d 576, 12 experts 19.2 / 11.2, 4096, d 1024, 16 57.2 / 37.6, 8192, d 512, 64
 // 155 / 105, 5000, d 4096, 32 769 / 573; d 128 to 512 and 4 experts equal.
@@ -253,6 +253,7 @@ __global__ __launch_bounds__(kWaves * 64) void route_kernel(const XT* __restrict
     int span, log2ks = 0;
     if constexpr (QUADS) {
         typedef float quad __attribute__((ext_vector_type(4)));
+        typedef float quad_at_4 __attribute__((ext_vector_type(4), aligned(4)));
         constexpr int kAtOnce = TPW == 1 ? 8 : 2;                  // quads of terms requested at a time, of the kBK / 4 of a partial sum
         int EQ = 1;                                // lanes that hold different columns
         while (4 * EQ < E) EQ <<= 1;
@@ -275,7 +276,7 @@ __global__ __launch_bounds__(kWaves * 64) void route_kernel(const XT* __restrict
 #pragma unroll
                     for (int tt = 0; tt < TPW; ++tt) xv[u][tt] = *reinterpret_cast<const quad*>(x + xrow[tt] + at);
 #pragma unroll
-                    for (int r = 0; r < 4; ++r) wv[u][r] = *reinterpret_cast<const quad*>(Wg + static_cast<size_t>(at + r) * E + col);
+                    for (int r = 0; r < 4; ++r) wv[u][r] = *reinterpret_cast<const quad_at_4*>(Wg + static_cast<size_t>(at + r) * E + col);
                 }
 #pragma unroll
                 for (int u = 0; u < kAtOnce; ++u) {
@@ -1378,7 +1379,7 @@ int launch_route(const moe_cfg& c, const void* x, const void* Wg, const float* b
     const int tpw = c.T <= 4096 ? 1 : 4;
     const int per_block = kWaves * tpw;
     dim3 grid((c.T + per_block - 1) / per_block), block(kWaves * 64);
-    const bool quads = cols % 4 == 0 && aligned16(Wg);
+    const bool quads = cols % 4 == 0;
 #define MOE_ROUTE_F32(TPW, NE)                                                                                        \
     hipLaunchKernelGGL((quads ? route_kernel<float, TPW, NE, true> : route_kernel<float, TPW, NE, false>), grid, block, 0, s, static_cast<const float*>(x),               \
                        static_cast<const float*>(Wg), bias, idx, w, c.T, c.d, cols, c.k, c.renorm, hash)

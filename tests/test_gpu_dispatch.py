@@ -632,30 +632,31 @@ def test_expert_ffn_tiles_of_more_than_256_rows(d, f, rest):
 @pytest.mark.parametrize("T,d,E,k,renorm", [(1, 64, 4, 1, 1), (7, 192, 4, 2, 0), (33, 320, 12, 3, 0), (70, 1088, 64, 2, 1), (50, 2112, 68, 1, 0), (20, 448, 256, 8, 0),
                                             (4099, 128, 8, 2, 0), (4100, 192, 100, 2, 1)])
 def test_f32_gate_by_four_columns(T, d, E, k, renorm):
-    """Gate matrices whose rows lie at 16-byte boundaries, read four columns at a time, against the same matrix 4 bytes further on, read one by one: the experts
-    are the same ones, and the weights differ by the order of sums of d products (each side within some d / 64 + 40 roundings of the logits, both doubled)."""
+    """Gate matrices of a multiple of four columns, read four at a time: the experts are those of 64-bit arithmetic and the weights within the order of sums of d
+    products (some d / 64 + 40 roundings of the logits, doubled); and an equal matrix 4, 8 or 12 bytes past a 16-byte boundary gives the same bits."""
     x, W = _normal(T, d, seed=21), _normal(d, E, seed=22) * d ** -0.5
     W[:, 1] = W[:, 0]                                # a tie in every token
     bias = 0.1 * _normal(E, seed=23)
     bias[1] = bias[0]
     cfg = M.MoeCfg.make(T, d, 64, E, k, "f32", renorm)
     ws = torch.empty(M.moe_workspace_bytes(cfg), dtype=torch.uint8, device="cuda")
-    shifted = torch.empty(d * E + 1, device="cuda")[1:].view(d, E)
-    shifted.copy_(W)
-    assert W.data_ptr() % 16 == 0 and shifted.data_ptr() % 16 == 4
     out = []
-    for Wg in (W, shifted):
+    for shift in (0, 1, 2, 3):
+        Wg = torch.empty(d * E + shift, device="cuda")[shift:].view(d, E)
+        Wg.copy_(W)
+        assert Wg.data_ptr() % 16 == 4 * shift
         idx, w = torch.full((T, k), -1, dtype=torch.int32, device="cuda"), torch.empty((T, k), device="cuda")
         M.moe_route(cfg, x, Wg, bias, idx, w, ws)
         torch.cuda.synchronize()
         out.append((idx, w))
     logits = x.double() @ W.double() + bias.double()
     top = logits.sort(dim=1, descending=True, stable=True)
-    assert torch.equal(out[0][0].long(), top.indices[:, :k]) and torch.equal(out[1][0], out[0][0])
+    assert torch.equal(out[0][0].long(), top.indices[:, :k])
+    for idx, w in out[1:]:
+        assert torch.equal(idx, out[0][0]) and torch.equal(w, out[0][1])
     want = top.values[:, :k].softmax(1) if renorm else (top.values[:, :k] - logits.logsumexp(1, keepdim=True)).exp()
     bound = 2 * (d / 64 + 40) * 2.0 ** -24 * float(x.norm(dim=1).max() * W.norm(dim=0).max()) + 1e-6
-    for _, w in out:
-        assert ((w.double() - want).abs() <= bound * want).all()
+    assert ((out[0][1].double() - want).abs() <= bound * want).all()
 
 
 @pytest.mark.parametrize("T,d,E,k,renorm", [(15570, 64, 33, 1, 1), (15571, 192, 64, 2, 0), (16400, 1088, 40, 3, 1), (33000, 576, 50, 2, 0)])
