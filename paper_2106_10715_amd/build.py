@@ -38,6 +38,8 @@ EXTRA = {"ffn.hip": ["-mllvm", "-enable-misched=false", "-mllvm", "-amdgpu-atomi
 # brackets those regions with "; pipeline begin" / "; pipeline end"; the build reads the assembly and
 # refuses any scratch access between the two or inside an inner loop of these kernels.
 NO_SPILL = {"ffn.hip": "ffn_mfma"}
+# The parts of ffn.hip with tiles of more than 16 blocks, whose last sums are in assembly.
+TALL = (1, 3, 4)
 
 
 def check_no_spill(asm: str, kernel_pattern: str, what: str = "assembly") -> None:
@@ -162,28 +164,44 @@ def check_m0_free(asm: str, kernel_pattern: str, what: str = "assembly") -> int:
     return written
 
 
-_SUM = re.compile(r"v_mfma\S+ v\[(\d+):(\d+)\], ([^,]+), ([^,]+),")
+_SUM = re.compile(r"v_mfma\S+ v\[(\d+):(\d+)\], ([^,]+), ([^,]+), (\S+)")
 _SETTLE = 18                             # wait states after which the longest of these instructions has written its sum
 
 
 def check_sums_settle(asm: str, kernel_pattern: str, what: str = "assembly") -> int:
     """The sums that do not fit the accumulation registers come from matrix instructions in inline assembly, whose latency the compiler
     does not know.  Nothing but the same kind of instruction, as its sum, may touch such registers before _SETTLE wait states have passed
-    (an instruction is one, "s_nop N" N + 1), in layout order and at the targets of branches.  Raises on one; returns the number of those instructions."""
+    (an instruction is one, "s_nop N" N + 1), on any way the program can take from there; and no vector instruction may have written one of its operands
+    in the two wait states before it, in layout order.  Raises on either; returns the number of those instructions."""
     lines = asm.splitlines()
     labels = {l.split(":")[0]: i for i, l in enumerate(lines) if l.startswith(".LBB")}
-    kernel, in_asm, found, now, written = None, False, 0, 0, {}
+    kernel, in_asm, found, now, written = None, False, 0, 0, {}      # written: register -> wait state after the last vector instruction that wrote it
 
-    def step(n, text, at, sums):                       # the wait state after this line; sums: register -> when it was written
-        op = text.split()[0]
-        if op == "s_nop":
-            return at + int(text.split()[1], 0) + 1
-        got = _SUM.match(text)
-        used = _vregs(got[3] + "," + got[4]) if got else _vregs(text)
-        for reg in used:
-            if reg in sums and at - sums[reg] < _SETTLE:
-                raise RuntimeError(f"{what}: {kernel}: line {n + 1} ({text}) touches v{reg} {at - sums[reg]} wait states after a matrix instruction in assembly")
-        return at + 1
+    def walk(at, sum_of, passed):                      # from line `at` on, `passed` wait states after the instruction
+        regs = set(range(sum_of[0], sum_of[1] + 1))
+        while at < len(lines) and passed < _SETTLE:
+            text = lines[at].strip().split(";")[0].strip()
+            at += 1
+            if text.startswith(".Lfunc_end"):
+                return
+            if not text or text.startswith(".") or text.endswith(":"):
+                continue
+            got = _SUM.match(text)
+            whole = got is not None and (int(got[1]), int(got[2])) == sum_of and got[5] == f"v[{got[1]}:{got[2]}]"
+            if (_vregs(got[3] + "," + got[4]) if whole else _vregs(text)) & regs:
+                raise RuntimeError(f"{what}: {kernel}: line {at} ({text}) touches v[{sum_of[0]}:{sum_of[1]}] {passed} wait states after a matrix instruction in assembly")
+            if whole or text.startswith("s_endpgm"):
+                return                                 # (the next one of this sum is looked at by itself)
+            op = text.split()[0]
+            passed += int(text.split()[1], 0) + 1 if op == "s_nop" else 1
+            if op.startswith(("s_branch", "s_cbranch")):
+                if text.split()[-1] not in labels:
+                    raise RuntimeError(f"{what}: {kernel}: line {at} ({text}) goes to an unknown place")
+                walk(labels[text.split()[-1]], sum_of, passed)
+                if op == "s_branch":
+                    return
+            elif op.startswith(("s_setpc", "s_swappc", "s_call")):
+                raise RuntimeError(f"{what}: {kernel}: line {at} ({text}) goes to an unknown place")
 
     for n, line in enumerate(lines):
         text = line.strip()
@@ -197,23 +215,16 @@ def check_sums_settle(asm: str, kernel_pattern: str, what: str = "assembly") -> 
         code = text.split(";")[0].strip()
         if kernel is None or not code or code.startswith(".") or code.endswith(":"):
             continue
-        now = step(n, code, now, written)
         got = _SUM.match(code)
-        if got and in_asm:
+        if in_asm and got:
+            early = [reg for reg in _vregs(code) if now - written.get(reg, -2) < 2]
+            if early:
+                raise RuntimeError(f"{what}: {kernel}: line {n + 1} ({code}) reads v{early[0]} within two wait states of its writing")
             found += 1
-            written.update((reg, now) for reg in range(int(got[1]), int(got[2]) + 1))
-        elif code.startswith(("s_branch", "s_cbranch")):
-            fresh = {reg: at for reg, at in written.items() if now - at < _SETTLE}
-            at, m = now, labels.get(code.split()[-1], len(lines)) + 1
-            while fresh and m < len(lines) and at - now < _SETTLE and not lines[m].startswith("_Z"):
-                there = lines[m].strip().split(";")[0].strip()
-                if there and not there.startswith(".") and not there.endswith(":"):
-                    if there.startswith(("s_branch", "s_endpgm")):
-                        break
-                    at = step(m, there, at, fresh)
-                m += 1
-        if code.startswith(("s_branch", "s_endpgm", "s_setpc")):
-            written = {}                               # what follows in the file is not what follows in time
+            walk(n + 1, (int(got[1]), int(got[2])), 0)
+        now += int(code.split()[1], 0) + 1 if code.startswith("s_nop") else 1
+        if code.startswith("v_") and not got:
+            written.update((reg, now) for reg in _vregs(code.split(",")[0]))
     return found
 
 
@@ -289,9 +300,11 @@ def _check(src: str, part: int) -> None:
     check_no_spill(text, NO_SPILL[src], src)
     loops = check_loads_in_flight(text, NO_SPILL[src], src), check_prologue_in_flight(text, NO_SPILL[src], src)
     m0 = check_m0_free(text, NO_SPILL[src], src)
-    check_sums_settle(text, NO_SPILL[src], src)
+    sums = check_sums_settle(text, NO_SPILL[src], src)
     if part > 0 and (0 in loops or m0 == 0):
         raise RuntimeError(f"{src}: no pipelined loop, or no load into LDS, found to verify (markers missing?)")
+    if part in TALL and sums == 0:
+        raise RuntimeError(f"{src}, part {part}: no matrix instruction in assembly found to verify (printed in another way?)")
 
 
 def _compile(src: str, part: int) -> str:

@@ -261,8 +261,29 @@ def test_build_refuses_sums_of_matrix_instructions_in_assembly_touched_early():
         return "_Zk_ffn_mfma: ; @k\n.LBB0_1:\n" + "".join(body) + "\ts_endpgm\n.Lfunc_end0:\n"
     use, wait = "\tv_mov_b32_e32 v1, v6\n", "\ts_nop 15\n\ts_nop 15\n"
     assert B.check_sums_settle(kernel(mfma, mfma, wait, use), "ffn_mfma") == 2          # the same sum again, and the use in time
+    jumps = (mfma, "\ts_cbranch_scc1 .LBB0_2\n", wait, "\ts_endpgm\n.LBB0_2:\n\ts_branch .LBB0_3\n.LBB0_4:\n", wait, "\ts_endpgm\n.LBB0_3:\n")      # two jumps to the use
     for bad in (kernel(mfma, use), kernel(mfma, "\ts_nop 15\n", use), kernel(use, mfma, "\ts_cbranch_scc1 .LBB0_1\n"),
-                kernel(mfma, mfma.replace("v[4:7], v[8:11]", "v[20:23], v[4:7]").replace(", v[4:7]\n", ", v[20:23]\n"))):
+                kernel(mfma, mfma.replace("v[4:7], v[8:11]", "v[20:23], v[4:7]").replace(", v[4:7]\n", ", v[20:23]\n")),
+                kernel(mfma, mfma.replace("v[4:7]", "v[6:9]")), kernel(*jumps, use), kernel("\tv_mov_b32_e32 v9, v1\n", mfma, wait), kernel("\tv_mov_b32_e32 v5, 0\n\ts_nop 0\n", mfma)):
         with pytest.raises(RuntimeError, match="wait states"):
             B.check_sums_settle(bad, "ffn_mfma")
+    assert B.check_sums_settle(kernel(*jumps, wait, use), "ffn_mfma") == 1
+    assert B.check_sums_settle(kernel("\tv_mov_b32_e32 v9, v1\n\ts_nop 1\n", mfma, wait), "ffn_mfma") == 1
+    for lost in ("\ts_cbranch_scc1 .LBB0_9\n", "\ts_setpc_b64 s[2:3]\n"):
+        with pytest.raises(RuntimeError, match="unknown place"):
+            B.check_sums_settle(kernel(mfma, lost, wait), "ffn_mfma")
     assert B.check_sums_settle(kernel(mfma, use).replace("ffn_mfma", "other"), "ffn_mfma") == 0
+
+
+def test_build_wants_matrix_instructions_in_assembly_where_tiles_are_tall(monkeypatch, tmp_path):
+    """An assembly that the check finds none in (printed in another way, say) is no proof that they are used in time."""
+    from paper_2106_10715_amd import build as B
+    monkeypatch.setattr(B, "_built", lambda *a: str(tmp_path / "x.s"))
+    (tmp_path / "x.s").write_text("")
+    monkeypatch.setattr(B.subprocess, "run", lambda *a, **k: type("Done", (), {"returncode": 0, "stderr": ""}))
+    for name in ("check_loads_in_flight", "check_prologue_in_flight", "check_m0_free"):
+        monkeypatch.setattr(B, name, lambda *a: 1)
+    B._check("ffn.hip", 2)
+    for part in B.TALL:
+        with pytest.raises(RuntimeError, match="in assembly found"):
+            B._check("ffn.hip", part)
