@@ -8,6 +8,7 @@ import paper_2106_10715_amd as M
 from oracle import moe_oracle as O
 from paper_2106_10715_amd import harness as H
 from test_gpu_stages import TOL, gpu_route, make_inputs, rel_l2, rounded, run_ffn
+from tile_rows import N_CU, heights
 
 pytestmark = pytest.mark.gpu
 
@@ -300,28 +301,67 @@ def _four_calls(cfg, dx, dW, db, packed, ws):
     return y4, y
 
 
-# chunks of 64 in the two reductions: 1 and 3, 2 and 5, 4 and 6, 7 and 8, 9 and 4 (rounds of four, and what does not fill one)
-@pytest.mark.parametrize("d,f", [(64, 192), (128, 320), (256, 384), (448, 512), (576, 256)])
-def test_expert_ffn_every_tile_height(d, f):
-    """Tiles of 1 to 16 blocks of 16 rows, full and not, and experts split evenly over two and three of them."""
-    counts = [16 * b - b % 3 for b in range(1, 17)] + [257, 513, 700]
-    got, ref, offsets = run_ffn(sum(counts), d, f, len(counts), 1, "bf16", counts, 0, seed=d + f)
-    for e in range(len(counts)):
-        lo, hi = offsets[e], offsets[e + 1]
-        assert rel_l2(got[lo:hi], ref[lo:hi]) <= TOL["bf16"], f"expert {e}"
-
-
-@pytest.mark.parametrize("T,E,d,f", [(2100, 16, 320, 192), (2100, 16, 576, 448)])
-def test_gathered_tiles_equal_batched(T, E, d, f):
-    """Rows looked up in x, tiles of many heights: the layer gives the bytes of the four calls."""
-    rng = np.random.default_rng(T + d)
+def _tall_ffn(counts, d, f, E, T, want):
+    """Experts of `counts` rows, and others without, in a call of at most T rows, whose tiles have up to `want` = (up, down, narrow units) rows: every expert against
+    fp64, and the last 40 rows of every expert with the bits that they have in a call of their own (which the kernels for few rows take)."""
+    assert torch.cuda.get_device_properties(0).multi_processor_count == N_CU and heights(T, d, f, E) == want and sum(counts) <= T
+    x = _normal(T, d, seed=d + f).bfloat16()
+    ex = [[(_normal(*s, seed=100 + 3 * e + i) * 0.05).bfloat16() for i, s in enumerate(((d, f), (d, f), (f, d)))] for e in range(len(counts))]
     cfg = M.MoeCfg.make(T, d, f, E, 1, "bf16")
-    x, Wg, _ = make_inputs(T, T, d, E, "bf16")
-    ex = [tuple(rounded(rng.standard_normal(s) * 0.05, "bf16") for s in ((d, f), (d, f), (f, d))) for _ in range(E)]
-    packed = H.pack_experts(W.Workload("t", T, d, f, E, 1, "bf16", 0), cfg, experts=lambda e: ex[e])[0]
-    bias = torch.linspace(-1.0, 1.0, E, device="cuda")
-    ws = torch.empty(M.moe_workspace_bytes(cfg), dtype=torch.uint8, device="cuda")
-    y4, y = _four_calls(cfg, H.to_device(x, "bf16"), H.to_device(Wg, "bf16"), bias, packed, ws)
+    packed = torch.zeros((E, M.moe_expert_bytes(cfg)), dtype=torch.uint8, device="cuda")
+    for e, matrices in enumerate(ex):
+        M.moe_pack_weights(cfg, *matrices, packed[e])
+
+    def run(rows, counts):
+        n = rows.shape[0]
+        cfg = M.MoeCfg.make(n, d, f, E, 1, "bf16")
+        offsets = torch.tensor([0] + counts + [0] * (E - len(counts)), device="cuda").cumsum(0).int()
+        Y = torch.full((n, d), float("nan"), dtype=torch.bfloat16, device="cuda")
+        M.moe_expert_ffn(cfg, rows, offsets, packed, Y, torch.empty(M.moe_workspace_bytes(cfg), dtype=torch.uint8, device="cuda"))
+        torch.cuda.synchronize()
+        return Y
+    got, lo = run(x, counts), 0
+    for e, n in enumerate(counts):
+        W_in, W_gate, W_out = (m.double() for m in ex[e])
+        rows = x[lo:lo + n]
+        ref = (torch.nn.functional.gelu(rows.double() @ W_gate) * (rows.double() @ W_in)) @ W_out
+        error = (got[lo:lo + n].double() - ref).norm(dim=1) / ref.norm(dim=1)
+        assert (error <= TOL["bf16"]).all(), f"expert {e}: row {error.argmax().item()} of {n}"
+        few = min(n, 40)
+        alone = run(rows[n - few:].clone(), [0] * e + [few])
+        assert torch.equal(alone, got[lo + n - few:lo + n]), f"expert {e}: rows {n - few} to {n}"
+        lo += n
+    assert torch.isnan(got[lo:]).all()
+
+
+# steps of 64 in the two reductions, 1 to 10 each: fewer than are requested ahead, rounds of four (three for 19 and 20 blocks) and what does not fill one
+@pytest.mark.parametrize("up,down,E,T,narrow", [
+    (1, 7, 256, 38400, True), (2, 6, 256, 25600, True), (3, 3, 120, 20400, True), (4, 8, 120, 20400, True), (5, 5, 160, 27200, True), (5, 2, 250, 42500, True),
+    (6, 1, 250, 42500, True), (7, 7, 64, 10880, True), (8, 4, 120, 22800, True), (9, 10, 100, 20000, True), (10, 9, 100, 20000, True),
+    (1, 2, 160, 44800, False), (2, 9, 200, 46000, False), (3, 5, 160, 48000, False), (5, 3, 100, 25000, False), (5, 10, 100, 25000, False), (6, 4, 100, 28000, False),
+    (7, 7, 100, 28000, False), (8, 8, 100, 28000, False), (9, 6, 64, 17920, False), (10, 1, 256, 38400, False)])
+def test_expert_ffn_every_tile_height(up, down, E, T, narrow):
+    """Tiles of 1 to 20 blocks of 16 rows in both kernels, full and not, of experts with one, and of 11 to 20 where an expert has two or three."""
+    _tall_ffn([16 * b - b % 3 for b in range(1, 21)] + [32 * b - 5 for b in range(11, 21)] + [321, 960], 64 * up, 64 * down, E, T, (320, 320, narrow))
+
+
+@pytest.mark.parametrize("d,f", [(64, 576), (128, 832), (192, 960), (256, 960), (320, 832), (384, 960), (448, 960)])
+def test_gathered_tiles_equal_batched(d, f):
+    """Rows looked up in x, tiles of 1 to 14 blocks, and of 8 and 14 where an expert has two: the layer gives the bytes of the four calls, whose tiles are others."""
+    counts = [16 * b - b % 3 for b in range(1, 15)] + [225, 448, 0, 0, 0, 0]
+    T, E = sum(counts), len(counts)
+    assert heights(T, d, f, E, gather=True)[0] == 224 and T // E <= 160
+    expert = torch.tensor([e for e, n in enumerate(counts) for _ in range(n)], device="cuda")
+    g = torch.Generator(device="cuda")
+    g.manual_seed(d)
+    x = _normal(T, d, seed=d)
+    x[:, :E] = 4.0 * torch.nn.functional.one_hot(expert[torch.randperm(T, generator=g, device="cuda")], E)
+    cfg = M.MoeCfg.make(T, d, f, E, 1, "bf16")
+    packed = torch.empty((E, M.moe_expert_bytes(cfg)), dtype=torch.uint8, device="cuda")
+    for e in range(E):
+        M.moe_pack_weights(cfg, *((_normal(*s, seed=70 + 3 * e + i) * 0.05).bfloat16() for i, s in enumerate(((d, f), (d, f), (f, d)))), packed[e])
+    ws = torch.full((M.moe_workspace_bytes(cfg) // 2,), float("nan"), dtype=torch.bfloat16, device="cuda").view(torch.uint8)
+    y4, y = _four_calls(cfg, x.bfloat16(), torch.eye(d, E, device="cuda").bfloat16(), None, packed, ws)
     assert torch.isfinite(y.float()).all()
     assert torch.equal(y, y4)
 
@@ -451,15 +491,11 @@ def test_gate_infinite_logits_keep_the_fp32_order(E, k, renorm, special, dtype):
         assert idx[7].min() >= 0 and idx[7].max() < E and len(set(idx[7].tolist())) == k
 
 
-@pytest.mark.parametrize("counts", [[700, 10, 300, 0, 257, 40, 600, 33, 513, 5, 270, 120], [300] * 7 + [90, 200], [260, 255, 256] * 3, [2000, 1, 1, 1]],
+@pytest.mark.parametrize("counts", [[700, 10, 300, 0, 257, 40, 600, 33, 513, 5, 270, 120], [330] * 7 + [90, 200], [350, 255, 256] * 3, [2000, 1, 1, 1]],
                          ids=lambda c: f"{len(c)}-{sum(c)}")
 def test_expert_ffn_merged_work_list(counts):
     """Experts of several tiles among experts of one: 192 rows per expert and more, where the work list merges the two kinds."""
-    got, ref, offsets = run_ffn(sum(counts), 128, 320, len(counts), 1, "bf16", counts, 0, seed=sum(counts))
-    for e in range(len(counts)):
-        lo, hi = offsets[e], offsets[e + 1]
-        if hi > lo:
-            assert rel_l2(got[lo:hi], ref[lo:hi]) <= TOL["bf16"], f"expert {e}"
+    _tall_ffn(counts, 384, 256, 100, 28000, (320, 320, False))
 
 
 def test_three_million_rows_on_one_expert():
@@ -565,14 +601,20 @@ def _ffn_by_expert(counts, d, f, seed):
 # steps of the down-projection: 3, 4 + 1, 4 + 2, 4 + 3 (rounds of four, and what does not fill one)
 @pytest.mark.parametrize("f", [192, 320, 384, 448])
 def test_expert_ffn_every_tile_height_of_the_wide_down_projection(f):
-    """32 experts x 16 column groups: units of 64 columns and, with fewer than 192 rows per expert, the sorted list."""
-    _ffn_by_expert([16 * b - b % 3 for b in range(1, 17)] * 2, 4096, f, seed=f)
+    """32 experts x 16 column groups: tiles of 1 to 16 blocks in units of 64 columns and, with fewer than 192 rows per expert, the sorted list, where the
+    up-projection has few items and so lower tiles and a list of its own."""
+    counts = [16 * b - b % 3 for b in range(1, 17)] * 2
+    up, down, narrow = heights(sum(counts), 4096, f, 32)
+    assert up <= 96 and down == 256 and not narrow
+    _ffn_by_expert(counts, 4096, f, seed=f)
 
 
 def test_expert_ffn_tall_tiles_in_a_merged_work_list():
-    """More than 224 rows per expert and a column group for every compute unit: the down-projection's tiles have the full height, experts of several
-    among experts of one."""
-    _ffn_by_expert([700, 256, 513, 230, 257, 100, 768, 144, 260, 200, 300, 176, 512, 60, 1000, 0], 4096, 192, seed=7)
+    """More than 224 rows per expert and a column group for every compute unit: the down-projection's tiles have 256 rows, experts of several
+    among experts of one, beside an up-projection of tiles of 64."""
+    counts = [700, 256, 513, 230, 257, 100, 768, 144, 260, 200, 300, 176, 512, 60, 1000, 0]
+    assert heights(sum(counts), 4096, 192, 16) == (64, 256, False)
+    _ffn_by_expert(counts, 4096, 192, seed=7)
 
 
 @pytest.mark.parametrize("d,f", [(192, 640), (704, 320)])
@@ -597,36 +639,9 @@ def test_f32_rows_keep_their_bits_in_every_tile_height(d, f):
         assert torch.equal(run(x[:n].clone()), want[:n]), f"{n} rows"
 
 
-# (narrow units of the down-projection; wide ones, and tiles of the full height in a batch of this many rows, need a column group for every compute unit)
-@pytest.mark.parametrize("d,f,rest", [(192, 320, 12), (320, 448, 12), (4096, 2048, 290), (4096, 2112, 290)])
-def test_expert_ffn_tiles_of_more_than_256_rows(d, f, rest):
-    """17 to 20 blocks of 16 rows, whose last sums lie in other registers than the rest: at their edges, alone and among several tiles of one expert,
-    reductions of 3 steps to 64; and a row has the bits that it has in a short batch."""
-    counts = [257, 272, 273, 288, 289, 304, 305, 320, 321, 576, 560] + [rest] * 5
-    if d < 4096:
-        _ffn_by_expert(counts, d, f, seed=d + f)
-    T, E = sum(counts), len(counts)
-    cfg = M.MoeCfg.make(T, d, f, E, 1, "bf16")
-    x = _normal(T, d, seed=5).bfloat16()
-    packed = torch.empty((E, M.moe_expert_bytes(cfg)), dtype=torch.uint8, device="cuda")
-    for e in range(E):
-        M.moe_pack_weights(cfg, *((_normal(*s, seed=6 + i) * 0.05).bfloat16() for i, s in enumerate(((d, f), (d, f), (f, d)))), packed[e])
-
-    def run(cfg, rows, offsets):
-        Y = torch.full((cfg.T, d), float("nan"), dtype=torch.bfloat16, device="cuda")
-        M.moe_expert_ffn(cfg, rows, torch.tensor(offsets, dtype=torch.int32, device="cuda"), packed, Y,
-                         torch.empty(M.moe_workspace_bytes(cfg), dtype=torch.uint8, device="cuda"))
-        torch.cuda.synchronize()
-        return Y
-    offsets = [0]
-    for c in counts:
-        offsets.append(offsets[-1] + c)
-    want = run(cfg, x, offsets)
-    assert torch.isfinite(want).all()
-    for e in range(11):                              # the last 40 rows of an expert, alone
-        lo, hi = offsets[e + 1] - 40, offsets[e + 1]
-        alone = run(M.MoeCfg.make(40, d, f, E, 1, "bf16"), x[lo:hi].clone(), [0] * (e + 1) + [40] * (E - e))
-        assert torch.equal(alone, want[lo:hi]), f"expert {e}"
+def test_expert_ffn_tiles_of_more_than_256_rows_in_long_reductions():
+    """17 to 20 blocks of 16 rows, whose last sums lie in other registers than the rest, at their edges, alone and among several tiles of one expert, in 64 and 35 steps."""
+    _tall_ffn([257, 272, 273, 288, 289, 304, 305, 320, 321, 576, 560, 960], 4096, 2240, 17, 5250, (320, 320, False))
 
 
 @pytest.mark.parametrize("T,d,E,k,renorm", [(1, 64, 4, 1, 1), (7, 192, 4, 2, 0), (33, 320, 12, 3, 0), (70, 1088, 64, 2, 1), (50, 2112, 68, 1, 0), (20, 448, 256, 8, 0),

@@ -20,6 +20,7 @@ import moe_workloads as W
 import paper_2106_10715_amd as M
 from oracle import moe_oracle as O
 from paper_2106_10715_amd import harness as H
+from tile_rows import heights
 
 pytestmark = pytest.mark.gpu
 
@@ -110,15 +111,15 @@ def check_whole(wl, L):
     return s
 
 
-def seam_rows(n):
-    """Rows of an n-row expert segment at the seams of the kernel's tiling: the segment is cut into
-    ceil(n / 256) tiles of equal height (a multiple of 32); first and last row of every tile, and the start
-    of the last 32-row block."""
-    tiles = (n + 255) // 256
-    per = min(256, ((n + tiles - 1) // tiles + 31) // 32 * 32)
+def seam_rows(n, limits):
+    """Rows of an n-row expert segment at the seams of the kernels' tiling: for each limit, its blocks of 16 rows spread evenly over as few tiles as that many rows
+    allow; first and last row of every tile, and the start of the last 32-row block."""
     out = {0, n - 1, (n - 1) // 32 * 32}
-    for t in range(tiles):
-        out |= {min(t * per, n - 1), min((t + 1) * per, n) - 1}
+    for limit in limits:
+        tiles, blocks = -(-n // limit), -(-n // 16)
+        for t in range(tiles):
+            lo, hi = ((i * (blocks // tiles) + min(i, blocks % tiles)) * 16 for i in (t, t + 1))
+            out |= {lo, min(hi, n) - 1}
     return out
 
 
@@ -151,12 +152,13 @@ def check_sampled(wl, L, n_experts=4, random_rows=6, n_tokens=48):
         for j in range(wl.k):
             need[int(r.idx[t, j])].add(int(inv2[t, j]))
     pool = W.make_pool()
+    limits = set(heights(wl.T, wl.d, wl.f, wl.E, wl.k)[:2])
     Yp_ref = {}                                   # batched row -> oracle output row
     worst_row, n_rows = 0.0, 0
     try:
         for e in pick:
             lo, hi = int(p.offsets[e]), int(p.offsets[e + 1])
-            rows = {lo + v for v in seam_rows(hi - lo)} | {int(v) for v in rng.integers(lo, hi, size=random_rows)} | need[e]
+            rows = {lo + v for v in seam_rows(hi - lo, limits)} | {int(v) for v in rng.integers(lo, hi, size=random_rows)} | need[e]
             rows = np.array(sorted(rows))
             ref = O.expert_ffn_rows(p.Xp[rows], *W.gen_expert(wl, e, pool))
             got = H.to_f64(s["Yp"][torch.from_numpy(rows).cuda()])

@@ -391,8 +391,9 @@ def run_ffn(T, d, f, E, k, dtype, counts, act=0, seed=0):
     (192, 320, 2, [129, 127], "bf16", 1),                    # tanh GELU
     (320, 128, 6, [0, 0, 64, 0, 0, 200], "f32", 1),
     (512, 1024, 3, [257, 128, 31], "bf16", 0),
-    (256, 384, 3, [700, 0, 310], "bf16", 0),                 # few experts of many rows: the down-projection's tiles are cut lower than the up-projection's
-    (1024, 256, 8, [250, 260, 241, 283, 256, 255, 257, 246], "bf16", 0),   # 8 experts of about a tile each: two down tiles per expert
+    (256, 384, 3, [700, 0, 310], "bf16", 0),                 # few experts of many rows: tiles of 64 rows in both projections
+    (256, 1536, 3, [700, 0, 310], "bf16", 0),                # the down-projection's tiles are cut lower than the up-projection's
+    (1024, 1536, 8, [250, 260, 241, 283, 256, 255, 257, 246], "bf16", 0),   # 8 experts of about 256 rows: two or three up and four or five down tiles per expert
 ])
 def test_expert_ffn_matches_oracle(d, f, E, counts, dtype, act):
     A = sum(counts)
@@ -444,8 +445,8 @@ def _random_ffn_case(seed):
 
 @pytest.mark.parametrize("seed", range(56))
 def test_expert_ffn_random_shapes(seed):
-    """Seeded sweep over widths, depths and segment lengths (empty, one row, around the 32-row block and the
-    256-row tile, several tiles, skewed): every segment on its own against the oracle."""
+    """Seeded sweep over widths, depths and segment lengths (empty, one row, around 32 and
+    256 rows, several tiles, skewed): every segment on its own against the oracle."""
     d, f, E, counts = _random_ffn_case(1000 + seed)
     got, ref, offsets = run_ffn(sum(counts), d, f, E, 1, "bf16", counts, seed % 2, seed=seed)
     assert np.isfinite(got).all()

@@ -42,7 +42,7 @@ def check(tiles, offsets, tile_m):
 
 @pytest.mark.parametrize("counts,tile_m", [
     ([2965819], 256), ([2965820], 256), ([3000000], 256), ([2 ** 25 - 1], 256),       # around the first 32-bit overflow of tile x blocks, the largest
-    ([3000000], 64), ([2 ** 25 - 1], 64), ([2595100], 224),                           # the other tile heights
+    ([3000000], 64), ([2 ** 25 - 1], 64), ([2595100], 224), ([2 ** 25 - 1], 320),       # other tile heights
     ([5, 3000000, 0, 100], 256), ([16 * 2 ** 20 - 3, 700, 16 * 2 ** 20 + 1], 192),    # and among small experts
 ])
 def test_large_experts(plan, counts, tile_m):
@@ -50,7 +50,7 @@ def test_large_experts(plan, counts, tile_m):
     check(tiles, offsets, tile_m)
 
 
-@pytest.mark.parametrize("tile_m", [64, 96, 224, 256])
+@pytest.mark.parametrize("tile_m", [64, 96, 224, 256, 288, 320])
 @pytest.mark.parametrize("E,mean,skew", [(1, 40, 0), (1, 5000, 0), (7, 100, 1), (7, 400, 2), (33, 230, 1), (256, 3, 1), (256, 300, 3)])
 def test_rows_once(plan, E, mean, skew, tile_m):
     rng = np.random.default_rng(E + mean + tile_m)
