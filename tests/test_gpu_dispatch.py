@@ -77,6 +77,16 @@ def test_few_rows_expert_ffn(counts, d, f):
             assert rel_l2(got[lo:hi], ref[lo:hi]) <= TOL["bf16"], f"expert {e}"
 
 
+# (a wave of the down-projection per compute unit at most and 64 steps or more: 14 in flight; 64, 65, 70 and 139 steps are rounds of 14 and 8, 9, 0 and 13 more. The last
+# two are past the limit of steps, and of waves)
+@pytest.mark.parametrize("counts,d,f", [([1], 4096, 4096), ([16], 256, 4160), ([3, 0, 13], 1024, 4480), ([1, 1, 1, 1], 1024, 8896), ([16], 256, 4032), ([1, 1, 1, 1, 1], 1024, 4096)],
+                         ids=lambda c: str(c) if isinstance(c, int) else "x".join(map(str, c)))
+def test_few_rows_long_down_projection(counts, d, f):
+    got, ref, offsets = run_ffn(sum(counts), d, f, len(counts), 1, "bf16", counts, 0, seed=d + f)
+    error = np.linalg.norm(got - ref, axis=1) / np.linalg.norm(ref, axis=1)
+    assert (error <= TOL["bf16"]).all(), f"row {error.argmax()}: {error.max():.3e}"
+
+
 @pytest.mark.parametrize("T,k", [(1, 1), (7, 2), (30, 1), (21, 3)])
 def test_few_rows_streamed_equals_resident(T, k):
     wl = W.Workload("few", T=T, d=256, f=384, E=6, k=k, dtype="bf16", seed=50 + T)
