@@ -42,7 +42,7 @@ struct FfnTiles {
 // less, or more, uneven than those of a random gate, whose columns differ in length by 1 / sqrt(2 d).
 constexpr int kShares = 9;
 struct ExpertBlocks {
-    int blocks[2][kShares];
+    int blocks[2][kShares], most = 1;
     double experts[kShares];
     ExpertBlocks(double mean, int e_count, int d) {
         const double log_e = log(static_cast<double>(e_count)), skew = 0.9 * mean * log_e;
@@ -54,16 +54,19 @@ struct ExpertBlocks {
             for (int s = 0; s < 2; ++s) {
                 const double rows = mean + (s == 0 ? 0.6 : 1.4) * spread * at[i];
                 blocks[s][i] = rows < 1 ? 1 : static_cast<int>((static_cast<long>(rows) + 15) / 16);
+                if (blocks[s][i] > most) most = blocks[s][i];
             }
         }
     }
 };
 
 // A product's work items are its row tiles by its `columns` groups of four column units.  This is the time of all of them on n_cu compute units, in that of a
-// block of 16 rows: an item takes its blocks and per_item (half a block more above 18, with two steps of loads ahead instead of three), and the
-// whole lies half-way between every round as long as its longest item and all items spread evenly (a round that is not full is faster, and
-// short items make up for long ones).
-inline double ffn_cost(const ExpertBlocks& of, int columns, double per_item, int tile_rows, int n_cu) {
+// block of 16 rows: an item takes its blocks and per_item of the reduction (above 18, with two steps of loads ahead instead of three, half a block more, and 19 as
+// much as 20, which are staged alike: 65536 tokens on 32 experts of 10240, tiles of 272, 288, 304 and 320 rows 12.39, 12.30, 12.53 and 12.49 ms, but 50000
+// 9.91, 9.90, 9.78 and 9.64), and the whole lies half-way between every round as long as its longest item and all items spread evenly (a round that is not full
+// is faster, and short items make up for long ones).
+inline double per_item(int reduction) { return 4 + 960.0 / reduction; }
+inline double ffn_cost(const ExpertBlocks& of, int columns, double item, int tile_rows, int n_cu) {
     const int most = tile_rows / 16;
     double total = 0;
     for (int s = 0; s < 2; ++s) {
@@ -76,22 +79,22 @@ inline double ffn_cost(const ExpertBlocks& of, int columns, double per_item, int
         }
         double items = 0;
         int begun = 0;
-        for (int b = kTileM / 16; b > 0; --b) {
+        for (int b = most < 4 ? 4 : most; b > 0; --b) {
             if (of_height[b] == 0) continue;
             items += of_height[b];
             const int rounds = items > 0.5 ? static_cast<int>((items - 0.5) / n_cu) + 1 : 0;        // (a fraction of an item begins none)
-            total += (rounds - begun + of_height[b] / n_cu) * (per_item + b + (b > 18 ? 0.5 : 0));
+            total += (rounds - begun + of_height[b] / n_cu) * (item + b + (b == 19 ? 1 : b == 20 ? 0.5 : 0));
             begun = rounds;
         }
     }
     return total;
 }
 
-// The height of a product's tiles: `before` (256 rows, 224 where the up-projection gathers, lower ones for a down-projection of few items), unless a multiple of 32
-// rows is better by 4 % of a round and 1 % of the whole.  What matters is how the items divide into rounds of the compute units, how often the weights
+// The height of a product's tiles: `before` (256 rows, 224 where the up-projection gathers, lower ones for a down-projection of few items; see ffn_tiles), unless a
+// multiple of 32 rows is better by 4 % of a round and 1 % of the whole (2 % beyond 16 rounds).  What matters is how the items divide into rounds of the compute units, how often the weights
 // are read and how long the steps of low tiles are: a tile of 17 or 18 blocks costs less than two of 9, and small layers need low tiles to have an item for
 // every unit.  Time against that with `before`, layers of one to three random gates each, d 128 to 4096, f 192 to 10240, 4 to 64 experts, 48 to 1400 rows
-// per expert: 0.939 in the mean of 1200, 44 of them more than 2 % slower (the loads are not known), 0.936 and 48 of 994 others, and 0.961 and 2 of 192 of
+// per expert: 0.939 in the mean of 1200, 44 of them more than 2 % slower (the loads are not known), 0.936 and 49 of 994 others, and 0.963 and 2 of 192 of
 // up to 4100 rows.  (Low tiles wherever items leave units idle, else 320 rows up to two tiles and even ones of 288 beyond: 0.966 and 163, 0.961 and 123,
 // 0.983 and 16, the worst 1.47.)  Layer us by limit, d 4096, f 10240 (tokens / experts):
 //            2048/8  2300/8  4096/8  4500/8  6000/8  4300/16  8192/32  9000/32  16384/32  20000/64  28000/32  65536/32
@@ -101,11 +104,12 @@ inline double ffn_cost(const ExpertBlocks& of, int columns, double per_item, int
 //   288         521     604     850    1006    1272      953     1932     2085      3440      4668      5361     12155
 //   320         519     568     844     920    1272      949     1862     1975      3339      4440      5540     12145
 inline int ffn_tile_rows(const ExpertBlocks& of, double rounds, int columns, int reduction, int before, int most, int n_cu) {
-    const double per_item = 4 + 960.0 / reduction;
+    const double item = per_item(reduction);
     int best = before;
-    double least = ffn_cost(of, columns, per_item, before, n_cu) * (rounds > 4 ? 0.99 : rounds > 1 ? 1 - 0.04 / rounds : 0.96);
+    double least = ffn_cost(of, columns, item, before, n_cu) * (rounds > 16 ? 0.98 : rounds > 4 ? 0.99 : rounds > 1 ? 1 - 0.04 / rounds : 0.96);
     for (int rows = most / 32 * 32; rows >= kMinTileM; rows -= 32) {
-        const double cost = ffn_cost(of, columns, per_item, rows, n_cu);
+        if (rows - 32 >= 16 * of.most) continue;           // (the next one has the same tiles)
+        const double cost = ffn_cost(of, columns, item, rows, n_cu);
         if (cost < least) {
             least = cost;
             best = rows;
@@ -122,7 +126,16 @@ inline FfnTiles ffn_tiles(const moe_cfg& c, bool gather, int n_cu, int e_count, 
     FfnTiles t;
     // (nothing may go over what the kernel has code for: the one that gathers has less)
     const int up_columns = (c.f / 32 + 3) / 4, wide = (c.d / 64 + 3) / 4;
-    t.up = ffn_tile_rows(of, tiles * up_columns / n_cu, up_columns, c.d, gather ? kGatherTileM : 256, gather ? kGatherTileM : kTileM, n_cu);
+    const double up_rounds = tiles * up_columns / n_cu;
+    // In long launches on experts of many rows it also matters that neighbours in the list belong to one expert (groups of four share its weights): where all of 32
+    // experts have four tiles 28000 tokens take 5391-5406 us, where some have three up to 5678. As many rows, then, as give nearly all experts the same number
+    // of tiles of at most 288 (65536 tokens, eight tiles of up to 272 rows against seven and eight of 288 12.00 / 12.06 ms, of four gates).
+    long before = gather ? kGatherTileM : 256, even = 0;
+    if (!gather && mean > 2 * kTileM && up_rounds > 16) {
+        const double most = mean + 2.5 * sqrt(mean);
+        before = even = static_cast<long>(most / (static_cast<long>(most / 288) + 1) + 16) / 16 * 16;
+    }
+    t.up = ffn_tile_rows(of, up_rounds, up_columns, c.d, static_cast<int>(before), gather ? kGatherTileM : kTileM, n_cu);
     // Narrow units while the experts are likely to have a single tile each, mean rows up to 224, and their items are
     // bound by the weight stream: on 256-row tiles, and once experts spill into second tiles, the narrow unit's
     // second LDS read per MFMA costs more than the idle compute units do; measured on 8 experts: 128 rows per
@@ -133,14 +146,16 @@ inline FfnTiles ffn_tiles(const moe_cfg& c, bool gather, int n_cu, int e_count, 
     // groups for 256 compute units, and a tile takes as long as its 160 reduction steps whether others run or not).  The
     // tiles are then cut lower, so that every expert gives as many tiles as fill the chip (with a quarter of headroom for
     // experts above the mean); measured on that layer: 0.235 -> 0.184 ms.
-    long rows = gather ? kGatherTileM : 256;
     if (mean_rows > 224 && static_cast<long>(e_count) * wide < n_cu) {
         const long per_expert = (n_cu + static_cast<long>(e_count) * wide - 1) / (static_cast<long>(e_count) * wide);
         const long fill = ((mean_rows * 5 / 4 + per_expert - 1) / per_expert + 31) / 32 * 32;
-        rows = fill < kMinTileM ? kMinTileM : fill < rows ? fill : rows;
+        before = fill < kMinTileM ? kMinTileM : fill < before ? fill : before;
     }
     const int columns = t.narrow ? (c.d / 32 + 3) / 4 : wide;
-    t.down = ffn_tile_rows(of, tiles * columns / n_cu, columns, c.f, static_cast<int>(rows), kTileM, n_cu);
+    t.down = ffn_tile_rows(of, tiles * columns / n_cu, columns, c.f, static_cast<int>(before), kTileM, n_cu);
+    // (nor a list of its own for 2 %: writing it takes 0.2 to 0.5 us, and the even tiles of long launches are the better ones for both products)
+    if (t.up == even && tiles * columns / n_cu > 8) t.down = t.up;
+    else if (t.down != t.up && ffn_cost(of, columns, per_item(c.f), t.up, n_cu) <= 1.02 * ffn_cost(of, columns, per_item(c.f), t.down, n_cu)) t.down = t.up;
     return t;
 }
 
