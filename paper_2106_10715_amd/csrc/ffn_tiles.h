@@ -71,19 +71,25 @@ inline double ffn_cost(const ExpertBlocks& of, int columns, double item, int til
     double total = 0;
     for (int s = 0; s < 2; ++s) {
         double of_height[kTileM / 16 + 1] = {};
+        auto add = [&](int b, double n) { of_height[b < 4 ? 4 : b] += n; };             // (the steps of lower tiles take as long)
         for (int i = 0; i < kShares; ++i) {
-            const int n = of.blocks[s][i], tiles = (n + most - 1) / most, each = n / tiles, more = n - each * tiles;
-            auto height = [](int b) { return b < 2 ? 2 : b == 3 ? 4 : b; };            // (those the kernels have code for)
-            if (more > 0) of_height[height(each + 1)] += more * columns * of.experts[i];
-            of_height[height(each)] += (tiles - more) * columns * of.experts[i];
+            const int n = of.blocks[s][i];
+            if (n <= most) {
+                add(n, of.experts[i]);
+                continue;
+            }
+            const int tiles = (n + most - 1) / most, each = n / tiles, more = n - each * tiles;
+            add(each, (tiles - more) * of.experts[i]);
+            if (more > 0) add(each + 1, more * of.experts[i]);
         }
         double items = 0;
         int begun = 0;
-        for (int b = most < 4 ? 4 : most; b > 0; --b) {
+        for (int b = most; b >= 4; --b) {
             if (of_height[b] == 0) continue;
-            items += of_height[b];
+            const double here = of_height[b] * columns;
+            items += here;
             const int rounds = items > 0.5 ? static_cast<int>((items - 0.5) / n_cu) + 1 : 0;        // (a fraction of an item begins none)
-            total += (rounds - begun + of_height[b] / n_cu) * (item + b + (b == 19 ? 1 : b == 20 ? 0.5 : 0));
+            total += (rounds - begun + here / n_cu) * (item + b + (b == 19 ? 1 : b == 20 ? 0.5 : 0));
             begun = rounds;
         }
     }
