@@ -65,7 +65,7 @@ struct ExpertBlocks {
 // much as 20, which are staged alike: 65536 tokens on 32 experts of 10240, tiles of 272, 288, 304 and 320 rows 12.39, 12.30, 12.53 and 12.49 ms, but 50000
 // 9.91, 9.90, 9.78 and 9.64), and the whole lies half-way between every round as long as its longest item and all items spread evenly (a round that is not full
 // is faster, and short items make up for long ones).
-inline double per_item(int reduction) { return 4 + 960.0 / reduction; }
+inline double per_item(int reduction, bool narrow) { return 4 + 960.0 / reduction + (narrow ? 4 : 0); }      // (narrow units: bound by their weights)
 inline double ffn_cost(const ExpertBlocks& of, int columns, double item, int tile_rows, int n_cu) {
     const int most = tile_rows / 16;
     double total = 0;
@@ -100,7 +100,7 @@ inline double ffn_cost(const ExpertBlocks& of, int columns, double item, int til
 // multiple of 32 rows is better by 4 % of a round and 1 % of the whole (2 % beyond 16 rounds).  What matters is how the items divide into rounds of the compute units, how often the weights
 // are read and how long the steps of low tiles are: a tile of 17 or 18 blocks costs less than two of 9, and small layers need low tiles to have an item for
 // every unit.  Time against that with `before`, layers of one to three random gates each, d 128 to 4096, f 192 to 10240, 4 to 64 experts, 48 to 1400 rows
-// per expert: 0.939 in the mean of 1200, 44 of them more than 2 % slower (the loads are not known), 0.936 and 49 of 994 others, and 0.963 and 2 of 192 of
+// per expert: 0.939 in the mean of 1200, 43 of them more than 2 % slower (the loads are not known), 0.936 and 46 of 994 others, and 0.963 and 2 of 192 of
 // up to 4100 rows.  (Low tiles wherever items leave units idle, else 320 rows up to two tiles and even ones of 288 beyond: 0.966 and 163, 0.961 and 123,
 // 0.983 and 16, the worst 1.47.)  Layer us by limit, d 4096, f 10240 (tokens / experts):
 //            2048/8  2300/8  4096/8  4500/8  6000/8  4300/16  8192/32  9000/32  16384/32  20000/64  28000/32  65536/32
@@ -109,8 +109,7 @@ inline double ffn_cost(const ExpertBlocks& of, int columns, double item, int til
 //   256         540     590     952    1035    1270     1156     2086     2268      3441      4643      5347     12486
 //   288         521     604     850    1006    1272      953     1932     2085      3440      4668      5361     12155
 //   320         519     568     844     920    1272      949     1862     1975      3339      4440      5540     12145
-inline int ffn_tile_rows(const ExpertBlocks& of, double rounds, int columns, int reduction, int before, int most, int n_cu) {
-    const double item = per_item(reduction);
+inline int ffn_tile_rows(const ExpertBlocks& of, double rounds, int columns, double item, int before, int most, int n_cu) {
     int best = before;
     double least = ffn_cost(of, columns, item, before, n_cu) * (rounds > 16 ? 0.98 : rounds > 4 ? 0.99 : rounds > 1 ? 1 - 0.04 / rounds : 0.96);
     for (int rows = most / 32 * 32; rows >= kMinTileM; rows -= 32) {
@@ -141,7 +140,7 @@ inline FfnTiles ffn_tiles(const moe_cfg& c, bool gather, int n_cu, int e_count, 
         const double most = mean + 2.5 * sqrt(mean);
         before = even = static_cast<long>(most / (static_cast<long>(most / 288) + 1) + 16) / 16 * 16;
     }
-    t.up = ffn_tile_rows(of, up_rounds, up_columns, c.d, static_cast<int>(before), gather ? kGatherTileM : kTileM, n_cu);
+    t.up = ffn_tile_rows(of, up_rounds, up_columns, per_item(c.d, false), static_cast<int>(before), gather ? kGatherTileM : kTileM, n_cu);
     // Narrow units while the experts are likely to have a single tile each, mean rows up to 224, and their items are
     // bound by the weight stream: on 256-row tiles, and once experts spill into second tiles, the narrow unit's
     // second LDS read per MFMA costs more than the idle compute units do; measured on 8 experts: 128 rows per
@@ -158,10 +157,11 @@ inline FfnTiles ffn_tiles(const moe_cfg& c, bool gather, int n_cu, int e_count, 
         before = fill < kMinTileM ? kMinTileM : fill < before ? fill : before;
     }
     const int columns = t.narrow ? (c.d / 32 + 3) / 4 : wide;
-    t.down = ffn_tile_rows(of, tiles * columns / n_cu, columns, c.f, static_cast<int>(before), kTileM, n_cu);
-    // (nor a list of its own for 2 %: writing it takes 0.2 to 0.5 us, and the even tiles of long launches are the better ones for both products)
+    const double item = per_item(c.f, t.narrow);
+    t.down = ffn_tile_rows(of, tiles * columns / n_cu, columns, item, static_cast<int>(before), kTileM, n_cu);
+    // (nor a list of its own for 2 %: it costs 0.3 to 1.5 us, and the even tiles of long launches are the better ones for both products)
     if (t.up == even && tiles * columns / n_cu > 8) t.down = t.up;
-    else if (t.down != t.up && ffn_cost(of, columns, per_item(c.f), t.up, n_cu) <= 1.02 * ffn_cost(of, columns, per_item(c.f), t.down, n_cu)) t.down = t.up;
+    else if (t.down != t.up && ffn_cost(of, columns, item, t.up, n_cu) <= 1.02 * ffn_cost(of, columns, item, t.down, n_cu)) t.down = t.up;
     return t;
 }
 
