@@ -171,7 +171,7 @@ constexpr int kKC = 64;                 // reduction elements staged per pipelin
 constexpr int kKS = kKC / 32;           // MFMA k-steps per pipeline step
 constexpr uint32_t kStepBytes = (kKC / 16) * 2048;   // bytes of a wave's weight stream one pipeline step spans
 constexpr int kLdsRow = 8;              // uint4 per activation row in LDS: 128 B; piece p of row r lies at place p ^ (r % 8)
-constexpr int kLdsBytes = 4 * 288 * kLdsRow * 16;   // four activation tiles of the full height, in blocks of 32 rows
+constexpr int kLdsBytes = 4 * 288 * kLdsRow * 16;   // four activation tiles of up to 288 rows, or three of up to 320, in blocks of 32
 
 typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 
@@ -220,7 +220,7 @@ __device__ inline void ld_to_lds(uint32_t lds_base, uint32_t voff, const void* s
     asm volatile("s_add_u32 m0, %0, %3\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2" : : "s"(lds_base), "v"(voff), "s"(sbase), "n"(OFFSET) : "memory", "scc");
 }
 
-// The MFMAs of a pipeline step (RB blocks of 16 rows) are issued in units: unit u = (k-step u / H, row group u % H), H = 2 or 4
+// The MFMAs of a pipeline step (RB blocks of 16 rows) are issued in units: unit u = (k-step u / H, row group u % H), H = 2, 4 or 5
 // groups of at most 4 blocks.  The A fragments of unit u+1 are read from LDS while the MFMAs of unit u run; two
 // register buffers of G fragments alternate.
 // Fragment (rb, ks) of lane l = row rb*16 + l%16, 8 elements at k = 32 ks + 8 (l / 16).
@@ -779,7 +779,8 @@ __global__ __launch_bounds__(256) void ffn_mfma_kernel(const uint16_t* __restric
         if (sh_q < 0) return;                      // every queue is empty (uniform for the block)
         // The tile code below is compiled for 12 or 18 tile heights; values that do not change from item to
         // item would be hoisted out of this loop and held in registers across all of them.  The inputs
-        // are made opaque per iteration instead.
+        // are made opaque per iteration instead.  (In the up-projection that does not gather, most heights still keep one or two 8-byte values in
+        // scratch memory over their main loop, outside of which they are stored and loaded: twice per item, of some 100 us.)
         int Kl = K, Nl = N;
         asm volatile("" : "+s"(Kl), "+s"(Nl));
         const int units = Nl / (32 * (GATED ? 1 : NF));

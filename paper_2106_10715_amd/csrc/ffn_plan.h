@@ -35,9 +35,10 @@ __device__ inline void ffn_plan_block(const int32_t* offsets, int e_first, int e
     }
     // The highest tiles first among those of either kind below, so that the last items are the short ones; among equals the expert with more
     // rows, then by index.
-    // (By rows alone: 2048 tokens on 8 experts, whose tiles are 16 blocks high up to 256 rows and 8 or 9 above, ended with the 16;
+    // (By rows alone, with tiles of up to 256 rows: 2048 tokens on 8 experts, whose tiles were 16 blocks high up to 256 rows and 8 or 9 above, ended with the 16;
     // 65536 tokens on 32 experts 12424 -> 12334 us.)
-    constexpr int kRowBits = 26;               // rows < 2^31 / 64, height <= 16
+    constexpr int kRowBits = 26;               // rows < 2^31 / 64
+    static_assert(kTileM / 16 < 1 << (31 - kRowBits), "a height and the rows below it fit the key");
     int key = 0;
     if (cnt > 0) {
         const int tiles = (cnt + tile_m - 1) / tile_m;

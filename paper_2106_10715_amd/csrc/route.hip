@@ -592,7 +592,8 @@ constexpr int gate_rows(int tok) { return tok > 32 ? tok : 32; }     // token ro
 // PAIRS: two blocks per compute unit, of 128 registers a thread, where there are that many: one ranks its tokens and decides the close ones while the other loads.
 // The gate fragments are then requested half a group ahead, the token pieces two groups.  us, one block / two (64 experts): 16384 tokens, d 4096 57.3 / 54.5, 32768
 // 95.7 / 88.2, 16384, d 2048 32.6 / 29.7, 20000, d 1024 34.6 / 25.0; with a block more per compute unit for some only, 10000, d 4096 44.1 / 45.8, 8192 28.6 /
-// 29.9; 32 experts, whose blocks of 64 tokens take less of the gate, 16384 42.4 / 44.5.
+// 29.9; 32 experts, whose blocks of 64 tokens take less of the gate, 16384 42.4 / 44.5.  (On another box 16384, d 4096 49.1 / 43.2, d 1024 26.3 / 18.2.)  The 128
+// registers are not quite enough: 92 bytes per thread go to scratch memory and come back, in the loops over close tokens.
 // RAW: `pack` is W_g itself, for a matrix that is not packed and of at most 512 rows, one group of 64 for each wave: its pieces are put together from single
 // values, all requested at once, and its column norms are added up on the way, in the order of gate_prep_kernel, whose launch that saves. us, packed by the call / RAW: 1025
 // tokens, d 320, 33 experts 11.0 / 8.3, 500, d 512, 64 10.5 / 7.8, 300, d 512, 8 10.7 / 8.0, 4000, d 512, 31 13.1 / 11.1, 2500, d 448, 64 13.2 / 12.2.
