@@ -210,11 +210,15 @@ __device__ __attribute__((always_inline)) inline void rank_f32(const float (&fv)
 // TPW: tokens per wave (they share the W_g loads); NE: experts per lane at most.  The kernel is bound by the latency of
 // its loads: kUnroll terms are requested at a time (one memory latency for all of them), and a batch too short to give
 // every compute unit several waves is handled one token per wave.
-// QUADS (fp32, a multiple of four columns; not by the address of W_g, so that equal matrices give equal weights wherever they lie): a lane takes four columns and four neighbouring terms at a time, 5 loads of 16 bytes
-// for 16 products instead of 32 of 4, and at d 1024 and 8 experts everything at once instead of in four batches.  us, single terms / quads: 512 tokens, d 1024, 8
-// experts 19.7 / 11.9, 16 tokens 11.5 / 8.2, 1000 tokens, d 640 16.8 / 11.1, 1024, d 576, 12 experts 19.2 / 11.2, 4096, d 1024, 16 57.2 / 37.6, 8192, d 512, 64
-// 155 / 105, 5000, d 4096, 32 769 / 573; d 128 to 512 and 4 experts equal.
-template <typename XT, int TPW, int NE, bool QUADS = false>
+// QUADS (fp32; quads of terms in flight, 0: single ones): a lane takes four columns and four neighbouring terms at a time, 5 loads of 16 bytes for 16 products
+// instead of 32 of 4. Chosen by the matrix alone, and not by its address, so that a token's bits are the same in every batch and equal matrices give equal weights:
+// a multiple of four columns, and more terms than the single ones of a lane request at once (where those fit, the quads' lanes stand idle or request what is not there, and
+// there are more steps to add the lanes up: 64 tokens, d 256, 4 experts 5.3 / 5.6 us single / quads, 1100 6.0 / 7.0, 8192, d 128, 8 11.0 / 14.0).
+// us, single terms / quads: 64 tokens, d 1024, 8 experts 11.7 / 5.9, 1100, d 576, 4 8.1 / 7.2, 1100, d 1024, 16 21.8 / 9.7, 4096, d 1024, 16 28.5 / 14.9, 8192, d 512, 64
+// 150 / 102, 5000, d 4096, 32 769 / 573; slower are beyond 4096 tokens 4 experts with d 576 to 1024 (15.3 / 15.9).
+// Eight quads take 207 registers, two waves of a SIMD; four take 116 and are as fast where two blocks per compute unit are not all: 2500 tokens, d 64, 64 experts
+// 9.3 / 6.5, 4096, d 192, 16 10.6 / 7.6 (with eight 11.5); four tokens per wave have registers for two.
+template <typename XT, int TPW, int NE, int QUADS = 0>
 __global__ __launch_bounds__(kWaves * 64) void route_kernel(const XT* __restrict__ x, const XT* __restrict__ Wg,
                                                             const float* __restrict__ bias,
                                                             int32_t* __restrict__ idx, float* __restrict__ w,
@@ -251,10 +255,11 @@ __global__ __launch_bounds__(kWaves * 64) void route_kernel(const XT* __restrict
     // Blocked summation: partial sums of kBK terms are added into the running total, so a logit goes
     // through at most kBK + ceil(d / (KS kBK)) + log2(KS) + 1 roundings instead of d.
     int span, log2ks = 0;
-    if constexpr (QUADS) {
+    if constexpr (QUADS > 0) {
         typedef float quad __attribute__((ext_vector_type(4)));
         typedef float quad_at_4 __attribute__((ext_vector_type(4), aligned(4)));
-        constexpr int kAtOnce = TPW == 1 ? 8 : 2;                  // quads of terms requested at a time, of the kBK / 4 of a partial sum
+        constexpr int kAtOnce = QUADS;                             // quads of terms requested at a time, of the kBK / 4 of a partial sum
+        static_assert(kBK / 4 % kAtOnce == 0, "a partial sum is a whole number of load batches");
         int EQ = 1;                                // lanes that hold different columns
         while (4 * EQ < E) EQ <<= 1;
         const int KQ = 64 / EQ, cq = lane & (EQ - 1), kq = lane / EQ, col = min(4 * cq, E - 4);
@@ -1331,13 +1336,13 @@ int launch_route(const moe_cfg& c, const void* x, const void* Wg, const float* b
     if (c.T == 0) return MOE_OK;
     const int hash = c.gate == MOE_GATE_HASH ? 1 : 0;
     const int cols = gate_columns(c);          // columns of the gate matrix: experts, or sign bits
+    int dev = 0;
+    const DeviceInfo* info = nullptr;
+    if (int rc = device_info(&dev, &info)) return rc;
+    const int n_cu = info->compute_units;
     if (c.dtype == MOE_BF16) {
         const int NB = (cols + 31) / 32;
         const size_t EP = static_cast<size_t>(NB) * 32;
-        int dev = 0;
-        const DeviceInfo* info = nullptr;
-        if (int rc = device_info(&dev, &info)) return rc;
-        const int n_cu = info->compute_units;
         // a gate packed once by the caller (it is frozen: Section 2.3) is read where it lies; else it is packed
         // into the workspace first, by every call
         // (but for short reductions and batches, where the kernel is as well off with the matrix itself: RAW)
@@ -1380,14 +1385,21 @@ int launch_route(const moe_cfg& c, const void* x, const void* Wg, const float* b
     const int tpw = c.T <= 4096 ? 1 : 4;
     const int per_block = kWaves * tpw;
     dim3 grid((c.T + per_block - 1) / per_block), block(kWaves * 64);
-    const bool quads = cols % 4 == 0;
-#define MOE_ROUTE_F32(TPW, NE)                                                                                        \
-    hipLaunchKernelGGL((quads ? route_kernel<float, TPW, NE, true> : route_kernel<float, TPW, NE, false>), grid, block, 0, s, static_cast<const float*>(x),               \
+    int lanes = 1;
+    while (lanes < cols && lanes < 64) lanes <<= 1;
+    const bool quads = cols % 4 == 0 && static_cast<long>(c.d) * lanes > 64 * kBK;
+    const bool rounds = c.T > 2 * kWaves * n_cu;
+#define MOE_ROUTE_F32(TPW, NE, QUADS)                                                                                 \
+    hipLaunchKernelGGL((quads ? route_kernel<float, TPW, NE, QUADS> : route_kernel<float, TPW, NE, 0>), grid, block, 0, s, static_cast<const float*>(x),               \
                        static_cast<const float*>(Wg), bias, idx, w, c.T, c.d, cols, c.k, c.renorm, hash)
     if (tpw == 1) {
-        if (cols <= 64) MOE_ROUTE_F32(1, 1); else MOE_ROUTE_F32(1, kNE);
+        if (cols <= 64) {
+            if (rounds) MOE_ROUTE_F32(1, 1, 4); else MOE_ROUTE_F32(1, 1, 8);
+        } else {
+            if (rounds) MOE_ROUTE_F32(1, kNE, 4); else MOE_ROUTE_F32(1, kNE, 8);
+        }
     } else {
-        if (cols <= 64) MOE_ROUTE_F32(4, 1); else MOE_ROUTE_F32(4, kNE);
+        if (cols <= 64) MOE_ROUTE_F32(4, 1, 2); else MOE_ROUTE_F32(4, kNE, 2);
     }
 #undef MOE_ROUTE_F32
     MOE_LAUNCH_CHECK("route_kernel");
