@@ -210,14 +210,11 @@ __device__ __attribute__((always_inline)) inline void rank_f32(const float (&fv)
 // TPW: tokens per wave (they share the W_g loads); NE: experts per lane at most.  The kernel is bound by the latency of
 // its loads: kUnroll terms are requested at a time (one memory latency for all of them), and a batch too short to give
 // every compute unit several waves is handled one token per wave.
-// QUADS (fp32; quads of terms in flight, 0: single ones): a lane takes four columns and four neighbouring terms at a time, 5 loads of 16 bytes for 16 products
-// instead of 32 of 4. Chosen by the matrix alone, and not by its address, so that a token's bits are the same in every batch and equal matrices give equal weights:
-// a multiple of four columns, and more terms than the single ones of a lane request at once (where those fit, the quads' lanes stand idle or request what is not there, and
-// there are more steps to add the lanes up: 64 tokens, d 256, 4 experts 5.3 / 5.6 us single / quads, 1100 6.0 / 7.0, 8192, d 128, 8 11.0 / 14.0).
-// us, single terms / quads: 64 tokens, d 1024, 8 experts 11.7 / 5.9, 1100, d 576, 4 8.1 / 7.2, 1100, d 1024, 16 21.8 / 9.7, 4096, d 1024, 16 28.5 / 14.9, 8192, d 512, 64
-// 150 / 102, 5000, d 4096, 32 769 / 573; slower are beyond 4096 tokens 4 experts with d 576 to 1024 (15.3 / 15.9).
-// Eight quads take 207 registers, two waves of a SIMD; four take 116 and are as fast where two blocks per compute unit are not all: 2500 tokens, d 64, 64 experts
-// 9.3 / 6.5, 4096, d 192, 16 10.6 / 7.6 (with eight 11.5); four tokens per wave have registers for two.
+// QUADS (fp32; quads of terms requested at a time, 0: single ones): a lane takes four columns and four neighbouring terms at a time, 5 loads of 16 bytes for 16 products
+// instead of 32 of 4, wherever W_g has a multiple of four columns, at any address and in every batch, so that a token's bits are the same everywhere.  us, single
+// terms / quads: 64 tokens, d 256, 4 experts 5.3 / 4.0, d 1024, 8 11.6 / 5.5, 1100, d 1024, 16 21.8 / 9.4, 4096, d 192, 16 10.6 / 7.4, d 1024, 16 28.6 / 14.6, 5000, d 4096, 32
+// 769 / 573; of 441 sizes none is slower. As many at a time as a lane has in all, but no more than 8 (207 registers, two waves of a SIMD), or 4 (116) where there are more blocks than
+// two per compute unit: with 8 everywhere 64 tokens, d 256, 4 experts take 0.3 us longer and 4096, d 256, 8 14.4 us instead of 7.0. Four tokens per wave have registers for 2.
 template <typename XT, int TPW, int NE, int QUADS = 0>
 __global__ __launch_bounds__(kWaves * 64) void route_kernel(const XT* __restrict__ x, const XT* __restrict__ Wg,
                                                             const float* __restrict__ bias,
@@ -309,28 +306,60 @@ __global__ __launch_bounds__(kWaves * 64) void route_kernel(const XT* __restrict
 #pragma unroll
                 for (int c = 0; c < 4; ++c) sum[tt][c] += part[tt][c];
         }
-        for (int off = EQ; off < 64; off <<= 1) {
-            ++log2ks;
+        if constexpr (NE == 1) {                   // (at most 16 lanes of columns: 4 or more that a column is added up over)
+            // In each of the first two steps a lane hands half of its columns over and keeps the sums of the others, the same ones as if both kept all of them: column c ends in the lanes
+            // with bits c / 2 and c % 2 in those places. 21 exchanges instead of 58 for a token at 4 columns, 63 instead of 160 for four.
+            const bool high = (lane & EQ) != 0, odd = (lane & 2 * EQ) != 0;
+            float r[TPW + 1];                      // of the tokens, and the column's square
 #pragma unroll
-            for (int c = 0; c < 4; ++c) {
-                wsum[c] += __shfl_xor(wsum[c], off);
-#pragma unroll
-                for (int tt = 0; tt < TPW; ++tt) sum[tt][c] += __shfl_xor(sum[tt][c], off);
+            for (int tt = 0; tt <= TPW; ++tt) {
+                const quad v = tt < TPW ? sum[tt < TPW ? tt : 0] : wsum;
+                const float k0 = (high ? v[2] : v[0]) + __shfl_xor(high ? v[0] : v[2], EQ), k1 = (high ? v[3] : v[1]) + __shfl_xor(high ? v[1] : v[3], EQ);
+                r[tt] = (odd ? k1 : k0) + __shfl_xor(odd ? k0 : k1, 2 * EQ);
+                if (tt < TPW) xsq[tt] += __shfl_xor(xsq[tt], EQ);
+                if (tt < TPW) xsq[tt] += __shfl_xor(xsq[tt], 2 * EQ);
             }
+            log2ks = 2;
+            for (int off = 4 * EQ; off < 64; off <<= 1) {
+                ++log2ks;
 #pragma unroll
-            for (int tt = 0; tt < TPW; ++tt) xsq[tt] += __shfl_xor(xsq[tt], off);
-        }
-        // every column to the lanes that rank it: expert e lies in part e % 4 of lane e / 4
-#pragma unroll
-        for (int i = 0; i < NE; ++i) {
-            const int ei = min(eg + 64 * i, E - 1), from = ei >> 2, c = ei & 3;
+                for (int tt = 0; tt <= TPW; ++tt) {
+                    r[tt] += __shfl_xor(r[tt], off);
+                    if (tt < TPW) xsq[tt] += __shfl_xor(xsq[tt], off);
+                }
+            }
+            wsq[0] = r[TPW];                       // (only their largest is wanted)
+            // every column to the lane that ranks it
+            const int ei = min(eg, E - 1), from = (ei >> 2) + ((ei & 2) >> 1) * EQ + (ei & 1) * 2 * EQ;
 #pragma unroll
             for (int tt = 0; tt < TPW; ++tt) {
-                const float v0 = __shfl(sum[tt][0], from), v1 = __shfl(sum[tt][1], from), v2 = __shfl(sum[tt][2], from), v3 = __shfl(sum[tt][3], from);
-                tot[tt][i] = eg + 64 * i < E ? (c & 2 ? (c & 1 ? v3 : v2) : (c & 1 ? v1 : v0)) : 0.f;
+                const float v = __shfl(r[tt], from);
+                tot[tt][0] = eg < E ? v : 0.f;
             }
+        } else {
+            for (int off = EQ; off < 64; off <<= 1) {
+                ++log2ks;
+#pragma unroll
+                for (int c = 0; c < 4; ++c) {
+                    wsum[c] += __shfl_xor(wsum[c], off);
+#pragma unroll
+                    for (int tt = 0; tt < TPW; ++tt) sum[tt][c] += __shfl_xor(sum[tt][c], off);
+                }
+#pragma unroll
+                for (int tt = 0; tt < TPW; ++tt) xsq[tt] += __shfl_xor(xsq[tt], off);
+            }
+            // every column to the lanes that rank it: expert e lies in part e % 4 of lane e / 4
+#pragma unroll
+            for (int i = 0; i < NE; ++i) {
+                const int ei = min(eg + 64 * i, E - 1), from = ei >> 2, c = ei & 3;
+#pragma unroll
+                for (int tt = 0; tt < TPW; ++tt) {
+                    const float v0 = __shfl(sum[tt][0], from), v1 = __shfl(sum[tt][1], from), v2 = __shfl(sum[tt][2], from), v3 = __shfl(sum[tt][3], from);
+                    tot[tt][i] = eg + 64 * i < E ? (c & 2 ? (c & 1 ? v3 : v2) : (c & 1 ? v1 : v0)) : 0.f;
+                }
+            }
+            wsq[0] = fmaxf(fmaxf(wsum[0], wsum[1]), fmaxf(wsum[2], wsum[3]));       // (only their largest is wanted)
         }
-        wsq[0] = fmaxf(fmaxf(wsum[0], wsum[1]), fmaxf(wsum[2], wsum[3]));       // (only their largest is wanted)
     } else {
         span = KS * kBK;
         for (int kb = 0; kb < d; kb += span) {
@@ -1385,16 +1414,16 @@ int launch_route(const moe_cfg& c, const void* x, const void* Wg, const float* b
     const int tpw = c.T <= 4096 ? 1 : 4;
     const int per_block = kWaves * tpw;
     dim3 grid((c.T + per_block - 1) / per_block), block(kWaves * 64);
-    int lanes = 1;
-    while (lanes < cols && lanes < 64) lanes <<= 1;
-    const bool quads = cols % 4 == 0 && static_cast<long>(c.d) * lanes > 64 * kBK;
+    const bool quads = cols % 4 == 0;
     const bool rounds = c.T > 2 * kWaves * n_cu;
+    int lanes = 1;                             // that hold different columns
+    while (4 * lanes < cols) lanes <<= 1;
 #define MOE_ROUTE_F32(TPW, NE, QUADS)                                                                                 \
     hipLaunchKernelGGL((quads ? route_kernel<float, TPW, NE, QUADS> : route_kernel<float, TPW, NE, 0>), grid, block, 0, s, static_cast<const float*>(x),               \
                        static_cast<const float*>(Wg), bias, idx, w, c.T, c.d, cols, c.k, c.renorm, hash)
     if (tpw == 1) {
         if (cols <= 64) {
-            if (rounds) MOE_ROUTE_F32(1, 1, 4); else MOE_ROUTE_F32(1, 1, 8);
+            if (static_cast<long>(c.d) * lanes <= 2 * 4 * 64) MOE_ROUTE_F32(1, 1, 2); else if (rounds) MOE_ROUTE_F32(1, 1, 4); else MOE_ROUTE_F32(1, 1, 8);
         } else {
             if (rounds) MOE_ROUTE_F32(1, kNE, 4); else MOE_ROUTE_F32(1, kNE, 8);
         }

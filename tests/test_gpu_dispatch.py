@@ -657,7 +657,7 @@ def test_expert_ffn_tiles_of_more_than_256_rows_in_long_reductions():
 @pytest.mark.parametrize("T,d,E,k,renorm", [(1, 64, 4, 1, 1), (7, 192, 4, 2, 0), (33, 320, 12, 3, 0), (70, 1088, 64, 2, 1), (50, 2112, 68, 1, 0), (20, 448, 256, 8, 0),
                                             (4099, 128, 8, 2, 0), (4100, 192, 100, 2, 1)])
 def test_f32_gate_by_four_columns(T, d, E, k, renorm):
-    """Gate matrices of a multiple of four columns, read four at a time where the reduction is long: the experts are those of 64-bit arithmetic and the weights within the order of sums of d
+    """Gate matrices of a multiple of four columns, read four at a time: the experts are those of 64-bit arithmetic and the weights within the order of sums of d
     products (some d / 64 + 40 roundings of the logits, doubled); and an equal matrix 4, 8 or 12 bytes past a 16-byte boundary gives the same bits."""
     x, W = _normal(T, d, seed=21), _normal(d, E, seed=22) * d ** -0.5
     W[:, 1] = W[:, 0]                                # a tie in every token
@@ -684,10 +684,10 @@ def test_f32_gate_by_four_columns(T, d, E, k, renorm):
     assert ((out[0][1].double() - want).abs() <= bound * want).all()
 
 
-# d times the lanes of a row of columns, rounded up to a power of two, around 2048, beyond which columns are read four at a time
+# two quads of four terms per lane at most, and more: 1, 2, 4, 8, 16 and 32 lanes of four columns
 @pytest.mark.parametrize("d,E", [(512, 4), (576, 4), (256, 8), (320, 8), (128, 12), (192, 12), (64, 32), (128, 32), (64, 64), (64, 100), (1088, 8)])
 def test_f32_gate_keeps_its_bits_in_every_batch(d, E):
-    """A wave per token with eight quads of terms requested at a time, with four from the third block per compute unit on, and four tokens per wave beyond 4096:
+    """A wave per token with two or eight quads of terms requested at a time, with four from the third block per compute unit on, and four tokens per wave beyond 4096:
     the experts are those of 64-bit arithmetic, and a token has the same weights, bit for bit, in all of them."""
     T, k = 4101, 2
     x, W = _normal(T, d, seed=24), _normal(d, E, seed=25) * d ** -0.5
