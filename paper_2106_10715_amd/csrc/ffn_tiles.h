@@ -101,7 +101,7 @@ inline double ffn_cost(const ExpertBlocks& of, int columns, double item, int til
 // are read and how long the steps of low tiles are: a tile of 17 or 18 blocks costs less than two of 9, and small layers need low tiles to have an item for
 // every unit.  Time against that with `before`, layers of one gate each, every height of each product timed, d 64 to 4096, f 192 to 10240, 4 to 64 experts, up to
 // 32768 tokens: 0.959 in the mean of 3083 with random gates, 137 of them more than 2 % slower and 52 more than 5 % (the loads are not known; the best height of each would take 0.940),
-// 0.976, 93 and 31 of 2286 with Zipf loads, exponents of 0.4 to 1.2.  (Low tiles wherever items leave units idle, else 320 rows up to two tiles and even ones of 288 beyond: 0.979, 312 and 134,
+// 0.976, 111 and 36 of 2286 with Zipf loads, exponents of 0.4 to 1.2.  (Low tiles wherever items leave units idle, else 320 rows up to two tiles and even ones of 288 beyond: 0.979, 312 and 134,
 // 0.991, 235 and 101.)  Layer us by limit, d 4096, f 10240 (tokens / experts):
 //            2048/8  2300/8  4096/8  4500/8  6000/8  4300/16  8192/32  9000/32  16384/32  20000/64  28000/32  65536/32
 //   160         552     591     978    1004    1385     1096     2133     2197      3665      5116      6056     13055
@@ -120,10 +120,10 @@ inline int ffn_tile_rows(const ExpertBlocks& of, double rounds, int columns, dou
             best = rows;
         }
     }
-    // With items for less than half of the units an expert of more rows than expected would leave the others idle: as low as leaves the expected tiles whole (466 tokens on 12 experts, d 1024,
+    // With items for less than 0.8 of the units an expert of more rows than expected would leave the others idle: as low as leaves the expected tiles whole (466 tokens on 12 experts, d 1024,
     // f 320, loads by a Zipf law with an exponent of 1.2, the largest 196 rows: tiles of 224 rows 48 us, of 64 40).
     const int whole = (of.most + 1) / 2 * 32;
-    if (rounds <= 0.5 && whole < best) best = whole < kMinTileM ? kMinTileM : whole;
+    if (rounds <= 0.8 && whole < best) best = whole < kMinTileM ? kMinTileM : whole;
     return best;
 }
 

@@ -355,7 +355,7 @@ def test_expert_ffn_every_tile_height(up, down, E, T, narrow):
     _tall_ffn([16 * b - b % 3 for b in range(1, 21)] + [32 * b - 5 for b in range(11, 21)] + [321, 960], 64 * up, 64 * down, E, T, (320, 320, narrow))
 
 
-@pytest.mark.parametrize("d,f", [(64, 576), (128, 832), (192, 960), (256, 960), (320, 832), (384, 960), (448, 960)])
+@pytest.mark.parametrize("d,f", [(64, 576), (128, 832), (192, 1408), (256, 1408), (320, 1408), (384, 1408), (448, 1408)])
 def test_gathered_tiles_equal_batched(d, f):
     """Rows looked up in x, tiles of 1 to 14 blocks, and of 8 and 14 where an expert has two: the layer gives the bytes of the four calls, whose tiles are others."""
     counts = [16 * b - b % 3 for b in range(1, 15)] + [225, 448, 0, 0, 0, 0]

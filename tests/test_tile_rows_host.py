@@ -35,7 +35,7 @@ def test_whole_layers(E, d, f, gather):
 
 
 # The heights on 256 compute units, where another choice has cost (layer us, another one / this): few items in the up-projection and none missing in the
-# down-projection, 248 / 175, 381 / 326, 125 / 98; experts around a limit, 523 / 413, 539 / 463; items for less than half of the units, 48 / 40 with an uneven load;
+# down-projection, 248 / 175, 381 / 326, 125 / 98; experts around a limit, 523 / 413, 539 / 463; items for less than 0.8 of the units, 48 / 40 with an uneven load;
 # calls whose tests count on a list for each product; and calls that have always been cut like this.
 @pytest.mark.parametrize("T,d,f,E,k,want", [
     (6400, 4096, 256, 64, 1, (96, 224, False)), (22400, 4096, 192, 32, 1, (256, 288, False)), (12800, 1024, 256, 64, 1, (160, 320, True)),
